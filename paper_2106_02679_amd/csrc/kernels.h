@@ -16,6 +16,7 @@ namespace lga {
 hipError_t prepare_kernels();
 hipError_t attn_prepare_kernels();      // attention_bf16.hip's part
 hipError_t gemm_prepare_kernels();      // gemm_bf16.hip's part
+hipError_t gemm_f32_prepare_kernels();  // gemm_f32.hip's part
 
 // ---- element-wise / row kernels (rowops.hip) ---------------------------------------------
 // fp32 -> 16-bit copy of a parameter vector ("restore": parameters converted to 16 bits before use); E = bf16 or f16.
@@ -73,8 +74,11 @@ void launch_adam(float *w, float *m, float *v, const float *g, E *w16, size_t n,
 // C[M,N] = sum_k A(m,k) B(k,n), then the epilogue.
 //   a_kmajor: A is stored [M][lda] (k contiguous); otherwise [K][lda] (m contiguous).
 //   b_kmajor: B is stored [N][ldb] (k contiguous); otherwise [K][ldb] (n contiguous).
-// fp32 correctness-mode kernel (plain FMA, LDS tiles):
+// fp32 kernel (fp32 matrix instruction), any shape and alignment:
 void launch_gemm_f32(const GemmParams<float> &p, bool a_kmajor, bool b_kmajor, Epilogue epi, hipStream_t s);
+// Slices of the k range it cuts an accumulating GEMM into when it is given scratch for their partial results, slices * M * N
+// floats (1 = none; K = 0: the most any K would give).
+int gemm_f32_slices(int M, int N, int K);
 // 16-bit MFMA kernel (E = bf16 or f16), fp32 accumulate.  Needs lda, ldb, ldc, N multiples of 8 and 16-byte aligned
 // bases.
 // Returns false, launching nothing, for a layout / epilogue pair that is not built (gemm_mfma_supports) or a leading

@@ -41,6 +41,7 @@ hipError_t prepare_kernels() {
     std::call_once(once, [] {
         result = attn_prepare_kernels();
         if (result == hipSuccess) result = gemm_prepare_kernels();
+        if (result == hipSuccess) result = gemm_f32_prepare_kernels();
     });
     return result;
 }
@@ -147,7 +148,7 @@ struct Plan {
     size_t ldf;                // row pitch (elements) of the d_ff-wide activations u, gl, du
     size_t h, qkv, a, x1, h2, u, gl, du, dh2, dx1, da, dqkv, dh;
     size_t mean1, rstd1, mean2, rstd2, lse, delta, partial;
-    size_t splitk, splitk_floats;   // partial results of weight-gradient GEMMs whose k range is split (narrow layers)
+    size_t splitk, splitk_floats;   // partial results of weight-gradient GEMMs whose k range is split (narrow layers, fp32)
     size_t nonfinite;          // int per layer: the last checked Adam step found a non-finite gradient value
     size_t attn_ws, attn_ws_bytes;  // workspace of the GEMM-built attention (head sizes without a fused kernel)
     size_t total;
@@ -212,11 +213,10 @@ Plan make_plan(const lga_config &c) {
         p.dyT[i] = take(is16 ? (size_t)wg_out[i] * p.ldk * 2 : 0);
     }
     p.splitk_floats = 0;
-    if (is16)
-        for (int i = 0; i < 4; ++i) {
-            const size_t slices = (size_t)gemm_splitk_slices(wg_in[i], wg_out[i], 0);
-            if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * wg_in[i] * wg_out[i]);
-        }
+    for (int i = 0; i < 4; ++i) {
+        const size_t slices = (size_t)(is16 ? gemm_splitk_slices(wg_in[i], wg_out[i], 0) : gemm_f32_slices(wg_in[i], wg_out[i], (int)t));
+        if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * wg_in[i] * wg_out[i]);
+    }
     p.splitk = take(p.splitk_floats * 4);
     p.mean1 = take(t * 4);
     p.rstd1 = take(t * 4);
@@ -530,6 +530,7 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, T *d
         if constexpr (std::is_same<T, float>::value) {
             g.K = t; g.beta = beta;
             g.A = X; g.lda = ldx; g.B = dY; g.ldb = ldy;
+            g.partial = st->at<float>(st->plan.splitk); g.partial_floats = st->plan.splitk_floats;
             gemm<T>(g, false, false, EPI_ACCUM_F32, s);
         } else {
             const int ldk = (int)st->plan.ldk;
