@@ -1,6 +1,8 @@
 // Softmax attention (causal or unmasked), correctness-mode kernels: one wavefront per (sequence, head, position).
-// Scores, softmax and all sums in fp32; T is the storage type.  Used by the fp32 mode; the
-// The 16-bit modes run the MFMA kernels in attention_bf16.hip.
+// Scores, softmax and all sums in fp32; T is the storage type.  Serves what the faster kernels do not: fp32 heads above 128
+// (attention_f32.hip takes the others, 5 to 10 times faster) and 16-bit heads above 160 at lengths that are no multiple of 8.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace lga {
@@ -160,6 +162,8 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_simple_kernel(const T *__rest
 template <class T> void launch_attn_fwd_simple(const T *qkv, T *out, float *lse, AttnShape sh, hipStream_t s) {
     const size_t blocks = (size_t)sh.n_seq * sh.heads * sh.s;
     if (blocks == 0) return;
+    if constexpr (std::is_same<T, float>::value)
+        if (attn_f32_supports(sh)) return launch_attn_fwd_f32(qkv, out, lse, sh, s);
     const size_t smem = (size_t)(sh.dh + sh.s) * sizeof(float);
     ProfScope scope("attn_fwd_simple_kernel", 2.0 * blocks * sh.s * sh.dh, 4.0 * sizeof(T) * blocks * sh.dh, s);
     hipLaunchKernelGGL((attn_fwd_simple_kernel<T>), dim3((unsigned)blocks), dim3(64), smem, s, qkv, out, lse, sh);
@@ -173,6 +177,8 @@ void launch_attn_bwd_simple(const T *qkv, const T *out, const float *lse, const 
                             AttnShape sh, hipStream_t s) {
     const size_t blocks = (size_t)sh.n_seq * sh.heads * sh.s;
     if (blocks == 0) return;
+    if constexpr (std::is_same<T, float>::value)
+        if (attn_f32_supports(sh)) return launch_attn_bwd_f32(qkv, out, lse, dout, dqkv, delta, sh, s);
     const size_t smem_q = (size_t)(2 * sh.dh + sh.s) * sizeof(float);
     const size_t smem_kv = (size_t)(2 * sh.dh + 2 * sh.s) * sizeof(float);
     ProfScope scope("attn_bwd_simple_kernels", 7.0 * blocks * sh.s * sh.dh, 9.0 * sizeof(T) * blocks * sh.dh, s);

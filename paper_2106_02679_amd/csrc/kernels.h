@@ -105,6 +105,11 @@ template <class T> void launch_attn_fwd_simple(const T *qkv, T *out, float *lse,
 template <class T>
 void launch_attn_bwd_simple(const T *qkv, const T *out, const float *lse, const T *dout, T *dqkv, float *delta,
                             AttnShape sh, hipStream_t s);
+// The same on fp32 tensors with the fp32 matrix instruction (attention_f32.hip), head sizes up to 128.
+bool attn_f32_supports(AttnShape sh);
+void launch_attn_fwd_f32(const float *qkv, float *out, float *lse, AttnShape sh, hipStream_t s);
+void launch_attn_bwd_f32(const float *qkv, const float *out, const float *lse, const float *dout, float *dqkv, float *delta,
+                         AttnShape sh, hipStream_t s);
 // MFMA kernels with LDS-resident online softmax (E = bf16 or f16).  Head sizes other than those
 // attn_bf16_supports() accepts are routed to the one-wavefront kernels above.
 bool attn_bf16_supports(int dh);
