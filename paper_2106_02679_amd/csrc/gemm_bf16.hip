@@ -12,8 +12,10 @@
 // is served by gemm_bf16_dma_kernel: 256 threads = 4 wavefronts (2x2) on a 256x256x64 tile,
 // v_mfma_f32_16x16x32_bf16, tiles moved global -> LDS without passing through registers.
 //
+// Problems with fewer than 128 such tiles go to gemm_small.hip.
+//
 // gemm_bf16_kernel is the register-staged predecessor and still serves the other operand layouts of
-// the op-level API and the small (128x128-tile) problems: both operands sit in LDS k-contiguous
+// the op-level API and of the GEMM-built attention: both operands sit in LDS k-contiguous
 // (8 chunks of 16 B per row, XOR-swizzled against bank conflicts), so every MFMA operand is one 16-byte
 // LDS read; an operand that is not k-contiguous in HBM is transposed in registers (8x8 blocks of 16-bit
 // values) on its way from global memory to LDS; two LDS stages; the global loads of tile k+1 are in
@@ -29,13 +31,13 @@
 #include <cstring>
 #include <type_traits>
 
+#include "gemm16.h"
 #include "kernels.h"
 
 namespace lga {
 
 namespace {
 
-constexpr int BK = 64;           // k elements per stage
 
 __device__ __forceinline__ int swz(int row) { return ((row >> 1) ^ (row >> 4)) & 7; }
 
@@ -63,13 +65,6 @@ __device__ __forceinline__ void transpose8x8(const u32x4 (&in)[8], u32x4 (&out)[
 //   KMAJOR: storage [rows][ld], k contiguous.  Thread t: chunk t%8, rows t/8 + 32*i.
 //   else:   storage [k][ld], row index contiguous.  Thread t owns the 8x8 block with rows
 //           8*(t%(ROWS/8)).., k 8*(t/(ROWS/8)).., transposed in registers before the LDS store.
-constexpr int kBufRange = 0x40000000;          // 1 GiB window; valid offsets are far below it
-constexpr int kBufPoison = 0x7FFFFF00;         // always out of range
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, kBufRange, 0x00020000);
-}
-
 template <int ROWS, bool KMAJOR> struct Stager {
     static constexpr int NV = KMAJOR ? ROWS / 32 : 8;
     static constexpr int NOFF = KMAJOR ? NV : 1;
@@ -145,103 +140,6 @@ template <int ROWS, bool KMAJOR> struct Stager {
         }
     }
 };
-
-template <int EPI, class E>
-__device__ __forceinline__ void epilogue4(const GemmParams<E> &p, int m, int n, const float (&a)[4]) {
-    const size_t idx = (size_t)m * p.ldc + n;
-    if constexpr (EPI == EPI_ACCUM_F32) {
-        f32x4 o = {a[0], a[1], a[2], a[3]};
-        if (p.beta != 0.f) {
-            const f32x4 old = *reinterpret_cast<const f32x4 *>(p.outf + idx);
-            o += p.beta * old;
-        }
-        *reinterpret_cast<f32x4 *>(p.outf + idx) = o;
-        return;
-    } else {
-        float r[4] = {a[0], a[1], a[2], a[3]};
-        if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RESID || EPI == EPI_BIAS_GELU) {
-            const f32x4 b = *reinterpret_cast<const f32x4 *>(p.bias + n);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] += b[i];
-        }
-        if constexpr (EPI == EPI_BIAS_RESID) {
-            const x4<E> x = *reinterpret_cast<const x4<E> *>(p.aux + idx);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] += (float)x[i];
-        }
-        if constexpr (EPI == EPI_MUL_DGELU) {
-            const x4<E> u = *reinterpret_cast<const x4<E> *>(p.aux + idx);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] *= gelu_grad_f((float)u[i]);
-        }
-        if constexpr (EPI == EPI_BIAS_GELU) {
-            x4<E> u;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                u[i] = (E)r[i];
-                r[i] = gelu_f(r[i]);
-            }
-            *reinterpret_cast<x4<E> *>(p.out2 + idx) = u;
-        }
-        x4<E> o;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = (E)r[i];
-        *reinterpret_cast<x4<E> *>(p.out + idx) = o;
-    }
-}
-
-// The same for 8 consecutive n of one row, with 16-byte accesses (bf16 outputs only): n, ldc multiples of 8 and
-// 16-byte aligned tensors.
-// aux8: the 8 values of aux at (m, n .. n + 7) for the two epilogues that read it, and b0, b1: the bias of columns
-// n .. n + 7 for the three that add it, both loaded by the caller (ahead of time).
-template <int EPI, class E>
-__device__ __forceinline__ void epilogue8(const GemmParams<E> &p, int m, int n, const f32x4 &lo, const f32x4 &hi,
-                                          const x8<E> &aux8, const f32x4 &b0, const f32x4 &b1) {
-    static_assert(EPI != EPI_ACCUM_F32, "16-bit outputs only");
-    const size_t idx = (size_t)m * p.ldc + n;
-    float r[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RESID || EPI == EPI_BIAS_GELU) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            r[i] += b0[i];
-            r[4 + i] += b1[i];
-        }
-    }
-    if constexpr (EPI == EPI_BIAS_RESID) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) r[i] += (float)aux8[i];
-    }
-    if constexpr (EPI == EPI_MUL_DGELU) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) r[i] *= gelu_grad_f((float)aux8[i]);
-    }
-    if constexpr (EPI == EPI_BIAS_GELU) {
-        x8<E> u;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            u[i] = (E)r[i];
-            r[i] = gelu_f(r[i]);
-        }
-        *reinterpret_cast<x8<E> *>(p.out2 + idx) = u;
-    }
-    x8<E> o;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] = (E)r[i];
-    *reinterpret_cast<x8<E> *>(p.out + idx) = o;
-}
-
-// Batched launch: work item `tile` belongs to problem tile / ntiles; rebase the operands and outputs onto it.
-template <class E> __device__ __forceinline__ void select_problem(GemmParams<E> &p, int &tile, int ntiles) {
-    const int z = tile / ntiles;
-    tile -= z * ntiles;
-    p.A += z * p.strideA;
-    p.B += z * p.strideB;
-    const long long c = z * p.strideC;
-    if (p.out) p.out += c;
-    if (p.out2) p.out2 += c;
-    if (p.outf) p.outf += c;
-    if (p.aux) p.aux += c;
-}
 
 template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams<E> p, int tiles_m, int tiles_n) {
@@ -483,7 +381,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams<E> p, int til
 // this one runs at 1.65 GHz (1.56 PFLOP/s), both with the matrix pipe busy in 0.9 of the cycles.  For the same reason
 // the two products that a block receives per k tile are issued back to back (see `half` in the kernel): the second finds
 // the accumulator still in the pipe.
-__device__ __forceinline__ int swz16(int row) { return (row >> 1) & 7; }      // 16 rows of one chunk column -> 8 chunk places x 2 row parities
 
 template <int BM, int BN, int WGM, int WGN, int EPI, class E>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParams<E> p, int tiles_m, int tiles_n) {
@@ -895,7 +792,8 @@ LGA_INSTANTIATE_DMA(EPI_ACCUM_F32);
 
 // The kernel that serves a (tile size, layout, epilogue) combination and its dynamic LDS in bytes.
 template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E> struct KernelFor {
-    static constexpr bool kDma = A_KM && B_KM && BM == 256;
+    static constexpr bool kDma = A_KM && B_KM;
+    static_assert(!kDma || BM == 256, "smaller k-contiguous problems: gemm_small.hip");
     static constexpr size_t smem = kDma ? (size_t)5 * BM * BK * sizeof(E)            // the DMA kernel's operand ring
                                         : (size_t)2 * (BM + BN) * BK * sizeof(E);    // two stages of both operands
     static auto get() -> void (*)(GemmParams<E>, int, int) {
@@ -915,7 +813,7 @@ void launch_one(const GemmParams<E> &p, hipStream_t s) {
     void (*kern)(GemmParams<E>, int, int) = KernelFor<BM, BN, A_KM, B_KM, EPI, E>::get();
     char name[96];
     const char *et = std::is_same<E, bf16>::value ? "bf16" : "f16";       // profile names: gemm_bf16_... or gemm_f16_...
-    if (A_KM && B_KM && BM == 256)
+    if (A_KM && B_KM)
         snprintf(name, sizeof(name), "gemm_%s_dma_kernel<%d, %d, %d>", et, BM, BN, EPI);
     else
         snprintf(name, sizeof(name), "gemm_%s_kernel<%d, %d, %s, %s, %d>", et, BM, BN, A_KM ? "true" : "false",
@@ -952,54 +850,53 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmPa
     // Large tiles when they fill the 256 CUs at least about once (the direct-to-LDS kernel is so much faster per
     // tile that a partly idle second round still wins); smaller ones otherwise.
     const long big = (long)((p.M + 255) / 256) * ((p.N + 255) / 256);
-    if constexpr (A_KM && B_KM && EPI == EPI_ACCUM_F32) {
-        // A weight-gradient GEMM of a narrow layer: few output tiles, very long k.  The k range is cut into slices
-        // that run as separate work items of the large-tile kernel and are summed afterwards.
-        const int slices = p.batch > 1 ? 1 : gemm_splitk_slices(p.M, p.N, p.K);
-        if (slices > 1 && p.partial && (size_t)slices * p.M * p.N <= p.partial_floats && p.N % 4 == 0 && p.ldc % 4 == 0 &&
-            (reinterpret_cast<uintptr_t>(p.outf) & 15) == 0) {
-            GemmParams<E> q = p;
-            q.kchunk = ((p.K + slices - 1) / slices + BK - 1) / BK * BK;
-            q.ksplit = (p.K + q.kchunk - 1) / q.kchunk;          // rounding the slice length up may have emptied the last ones
-            launch_one<256, 256, A_KM, B_KM, EPI, E>(q, s);
-            ProfScope scope("splitk_reduce_kernel", (double)q.ksplit * p.M * p.N,
-                            4.0 * p.M * p.N * (q.ksplit + (p.beta != 0.f ? 2.0 : 1.0)), s);
-            const size_t quads = (size_t)p.M * (p.N / 4);
-            const unsigned blocks = (unsigned)std::min<size_t>((quads + 255) / 256, 256 * 16);
-            hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, s, p.partial, q.ksplit, (size_t)p.M * p.N,
-                               p.outf, p.M, p.N, p.ldc, p.beta);
-            return;
-        }
-    }
-    if (p.batch > 1) {
-        // many small problems (the products of attention, one per head): enough work items either way, so take the
-        // tile size that pads the output less, the large one on a tie
-        const double pad256 = (double)big * 65536.0, pad128 = (double)((p.M + 127) / 128) * ((p.N + 127) / 128) * 16384.0;
-        const bool short_rows = A_KM && B_KM && (p.lda < BK || p.ldb < BK);      // see below
-        if (big * p.batch >= 128 && pad256 <= 1.15 * pad128 && !short_rows)
-            launch_one<256, 256, A_KM, B_KM, EPI, E>(p, s);
-        else
-            launch_one<128, 128, A_KM, B_KM, EPI, E>(p, s);
-        return;
-    }
-    // (the direct-to-LDS kernel wants rows of at least 128 bytes: see its per-lane load offsets)
-    if (big >= 128 && !(A_KM && B_KM && (p.lda < BK || p.ldb < BK))) {
-        if constexpr (A_KM && B_KM) {
-            const int tm = (p.M + 255) / 256, tn = (p.N + 255) / 256;
-            if (tm % 16 == 0 && tn % 16 == 0) {                  // + 1 % on the weight-gradient shapes of d = 12288
+    if constexpr (A_KM && B_KM) {
+        if constexpr (EPI == EPI_ACCUM_F32) {
+            // A weight-gradient GEMM of a narrow layer: few output tiles, very long k.  The k range is cut into slices
+            // that run as separate work items of the large-tile kernel and are summed afterwards - where that gives at least
+            // 192 work items: with fewer the small tiles are faster (768 x 768 x 8192, 72 items: 36 against 30 us;
+            // 768 x 2304 x 8192, 216 items: 43 against 48; 1280 x 3840 x 2048, 150 items: 41 against 32).
+            const int slices = p.batch > 1 ? 1 : gemm_splitk_slices(p.M, p.N, p.K);
+            if (slices > 1 && big * slices >= 192 && p.partial && (size_t)slices * p.M * p.N <= p.partial_floats && p.N % 4 == 0 &&
+                p.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(p.outf) & 15) == 0) {
                 GemmParams<E> q = p;
-                q.sblock = 1;
+                q.kchunk = ((p.K + slices - 1) / slices + BK - 1) / BK * BK;
+                q.ksplit = (p.K + q.kchunk - 1) / q.kchunk;          // rounding the slice length up may have emptied the last ones
                 launch_one<256, 256, A_KM, B_KM, EPI, E>(q, s);
+                launch_splitk_reduce(p.partial, q.ksplit, p.outf, p.M, p.N, p.ldc, p.beta, s);
                 return;
             }
         }
-        launch_one<256, 256, A_KM, B_KM, EPI, E>(p, s);
+        // (the direct-to-LDS loads of the large-tile kernel want rows of at least 128 bytes: see its per-lane load offsets)
+        const bool short_rows = p.lda < BK || p.ldb < BK;
+        bool large = big >= 128;
+        if (p.batch > 1) {
+            // many small problems (the products of attention, one per head): enough work items either way, so take the
+            // tile size that pads the output less, the large one on a tie
+            const double pad256 = (double)big * 65536.0, pad128 = (double)((p.M + 127) / 128) * ((p.N + 127) / 128) * 16384.0;
+            large = big * p.batch >= 128 && pad256 <= 1.15 * pad128;
+        }
+        if (!large || short_rows) return launch_gemm_small<EPI, E>(p, s);
+        GemmParams<E> q = p;
+        const int tm = (p.M + 255) / 256, tn = (p.N + 255) / 256;
+        q.sblock = p.batch <= 1 && tm % 16 == 0 && tn % 16 == 0;     // + 1 % on the weight-gradient shapes of d = 12288
+        launch_one<256, 256, A_KM, B_KM, EPI, E>(q, s);
     } else {
-        launch_one<128, 128, A_KM, B_KM, EPI, E>(p, s);
+        const double pad256 = (double)big * 65536.0, pad128 = (double)((p.M + 127) / 128) * ((p.N + 127) / 128) * 16384.0;
+        const bool large = p.batch > 1 ? big * p.batch >= 128 && pad256 <= 1.15 * pad128 : big >= 128;
+        if (large) launch_one<256, 256, A_KM, B_KM, EPI, E>(p, s);
+        else launch_one<128, 128, A_KM, B_KM, EPI, E>(p, s);
     }
 }
 
 }  // namespace
+
+void launch_splitk_reduce(const float *partial, int slices, float *out, int M, int N, int ldc, float beta, hipStream_t s) {
+    ProfScope scope("splitk_reduce_kernel", (double)slices * M * N, 4.0 * M * N * (slices + (beta != 0.f ? 2.0 : 1.0)), s);
+    const size_t quads = (size_t)M * (N / 4);
+    const unsigned blocks = (unsigned)std::min<size_t>((quads + 255) / 256, 256 * 16);
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, s, partial, slices, (size_t)M * N, out, M, N, ldc, beta);
+}
 
 int gemm_splitk_slices(int M, int N, int K) {
     const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
@@ -1060,7 +957,8 @@ template bool launch_gemm_mfma<f16>(const GemmParams<f16> &, bool, bool, Epilogu
 namespace {
 template <bool A_KM, bool B_KM, int EPI, class E> hipError_t raise_pair() {
     hipError_t e = KernelFor<256, 256, A_KM, B_KM, EPI, E>::raise_lds_limit();
-    if (e == hipSuccess) e = KernelFor<128, 128, A_KM, B_KM, EPI, E>::raise_lds_limit();
+    if constexpr (!(A_KM && B_KM))
+        if (e == hipSuccess) e = KernelFor<128, 128, A_KM, B_KM, EPI, E>::raise_lds_limit();
     return e;
 }
 template <class E> hipError_t raise_all() {

@@ -17,6 +17,7 @@ hipError_t prepare_kernels();
 hipError_t attn_prepare_kernels();      // attention_bf16.hip's part
 hipError_t gemm_prepare_kernels();      // gemm_bf16.hip's part
 hipError_t gemm_f32_prepare_kernels();  // gemm_f32.hip's part
+hipError_t gemm_small_prepare_kernels();  // gemm_small.hip's part
 
 // ---- element-wise / row kernels (rowops.hip) ---------------------------------------------
 // fp32 -> 16-bit copy of a parameter vector ("restore": parameters converted to 16 bits before use); E = bf16 or f16.
@@ -87,6 +88,11 @@ constexpr int kGemmMaxLd = ((1 << 30) - 256) / (2 * 256);      // 2 097 151 elem
 bool gemm_mfma_supports(bool a_kmajor, bool b_kmajor, Epilogue epi);
 template <class E>
 bool launch_gemm_mfma(const GemmParams<E> &p, bool a_kmajor, bool b_kmajor, Epilogue epi, hipStream_t s);
+// Its share of problems with fewer than 128 tiles of 256 x 256, both operands k-contiguous (gemm_small.hip); p.ldc, p.N multiples of 8
+// and every tensor 16-byte aligned.  Uses p.partial for slices of a long k range where that is large enough.
+template <int EPI, class E> void launch_gemm_small(const GemmParams<E> &p, hipStream_t s);
+// out[m, n] = beta * out[m, n] + sum_z partial[z][m][n], slices in index order; N and ldc multiples of 4, 16-byte aligned
+void launch_splitk_reduce(const float *partial, int slices, float *out, int M, int N, int ldc, float beta, hipStream_t s);
 // Into how many slices of the k range launch_gemm_mfma cuts an fp32-accumulating, k-contiguous GEMM whose output has
 // too few 256 x 256 tiles to occupy the chip (1 = not at all); it then needs slices * M * N floats of scratch.
 // k = 0 asks for the largest count any k would give (for sizing the scratch).

@@ -42,6 +42,7 @@ hipError_t prepare_kernels() {
         result = attn_prepare_kernels();
         if (result == hipSuccess) result = gemm_prepare_kernels();
         if (result == hipSuccess) result = gemm_f32_prepare_kernels();
+        if (result == hipSuccess) result = gemm_small_prepare_kernels();
     });
     return result;
 }
