@@ -63,10 +63,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base) {
 //   pitch_rd<DH>  rows read with ds_read_b128 (lane = row): 16 bytes of padding rotate the banks row by row
 //   pitch_tr<DH>  rows read with the transposing ds_read_b64_tr_b16, one pass of which covers 4 consecutive
 //                 rows x 64 bytes: power-of-two row sizes get 64 bytes of padding, the others already stagger
-//   pitch_both<DH> rows read both ways: an odd number of 16-byte slots (ds_read_b128 conflict-free) that is 5 or 13
-//                 modulo 16, which leaves the transposing read with two-way conflicts on a few lanes only
 template <int DH> constexpr int pitch_rd() { return DH + 8; }
-template <int DH> constexpr int pitch_both() { return DH <= 32 ? 40 : DH <= 96 ? 104 : 168; }
 template <int DH> constexpr int pitch_tr() { return (DH == 64 || DH == 128) ? DH + 32 : DH; }
 
 // Per-lane part of the address of a transposed operand read from a NATURAL tile [position][pitch]:
@@ -136,6 +133,85 @@ template <int ROWS, int DH, int PITCH> struct TileDma {
         for (int i = 0; i < NJ; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(static_cast<char *>(dst) + (i * 4 + wave) * 1024), 16,
                                                      row[i] < nvalid ? off[i] : kBufPoison, 0, 0, 0);
+    }
+};
+
+// Tiles that are read both ways - rows with ds_read_b128 and transposed with ds_read_b64_tr_b16 - keep the
+// unpadded pitch DH and an XOR swizzle of the 16-byte chunk index that is free of bank conflicts for both:
+// 16 consecutive rows put one logical chunk into 16 different bank groups, and 4 consecutive rows (from a
+// multiple of 4) put an aligned group of 4 chunks into 4 different ones.
+template <int DH> __device__ __forceinline__ int sw_both(int row) {
+    if constexpr (DH == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
+    else if constexpr (DH == 64) return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+    else return (row >> 2) & 3;              // 32, 96, 160: the row pitch already staggers groups of 4 chunks
+}
+// DMA of a ROWS x DH tile (global row pitch gp2 bytes) into such a tile: lane L of instruction j fills chunk
+// slot 64 j + L = row * (DH / 8) + physical chunk, with the logical chunk that the swizzle maps there.
+template <int ROWS, int DH> struct TileDmaSw {
+    static constexpr int NCH = DH / 8;
+    static constexpr int NI = ROWS * NCH / 64;              // instructions per tile
+    static constexpr int NJ = (NI + 3) / 4;                 // per wavefront, at most
+    static constexpr int ELEMS = ROWS * DH;
+    static_assert((ROWS * NCH) % 64 == 0, "tile is a whole number of DMA instructions");
+    int row[NJ], off[NJ];
+    // dh <= DH: the head size in memory; logical chunks from dh / 8 on are padding (zeros)
+    __device__ __forceinline__ void init(int wave, int lane, int gp2, int dh) {
+#pragma unroll
+        for (int i = 0; i < NJ; ++i) {
+            const int slot = (i * 4 + wave) * 64 + lane, r = slot / NCH, pc = slot % NCH;
+            row[i] = (pc ^ sw_both<DH>(r)) < dh / 8 ? r : 0x7FFFFFFF;
+            off[i] = r * gp2 + ((pc ^ sw_both<DH>(r)) << 4);
+        }
+    }
+    // src, dst: tiles of 16-bit elements of either format
+    __device__ __forceinline__ void issue(const void *src, void *dst, int nvalid, int wave) const {
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src);
+#pragma unroll
+        for (int i = 0; i < NJ; ++i) {
+            const int j = i * 4 + wave;
+            if (NI % 4 != 0 && j >= NI) continue;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(static_cast<char *>(dst) + j * 1024), 16, row[i] < nvalid ? off[i] : kBufPoison,
+                                                     0, 0, 0);
+        }
+    }
+};
+// Per-lane address parts (elements) of the two kinds of operand read from such a tile.  The swizzle splits
+// into a part that XORs the chunk group (DH = 64, 128 only) and one that XORs within the group, which leaves
+// few distinct lane values; everything else is a compile-time offset.
+template <int DH> struct BothAddr {
+    static constexpr int NG = DH == 128 ? 4 : DH == 64 ? 2 : 1;     // chunk groups the swizzle permutes
+    int nb[NG][2];      // natural read: [chunk group][ks & 1]
+    int tb[NG][2];      // transposed read: [32-column block c (if NG > 1)][second half of the 16 positions]
+    __device__ __forceinline__ void init(int lane) {
+        const int lrow = lane & 31, half = lane >> 5, i = lane & 15, g = (lane >> 4) & 1;
+        const int s = sw_both<DH>(lrow), s_hi = s >> 2, s_lo = s & 3;
+#pragma unroll
+        for (int a = 0; a < NG; ++a)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) nb[a][e] = lrow * DH + 32 * (a ^ s_hi) + (((2 * e + half) ^ s_lo) << 3);
+#pragma unroll
+        for (int sec = 0; sec < 2; ++sec) {
+            const int row = 8 * sec + 4 * half + (i >> 2);           // + 16 kk, which does not change the swizzle
+            const int t = sw_both<DH>(row), t_hi = t >> 2, t_lo = t & 3;
+            const int b = 2 * g + ((i & 3) >> 1);
+#pragma unroll
+            for (int c = 0; c < NG; ++c) tb[c][sec] = row * DH + 32 * (c ^ t_hi) + ((b ^ t_lo) << 3) + 4 * (i & 1);
+        }
+    }
+    // MFMA first operand: row 32 u + lrow of the tile, k = 16 ks + 8 half + (0..7)
+    template <class E> __device__ __forceinline__ x8<E> nat(const E *tile, int u, int ks) const {
+        const int a = ks >> 1;
+        return *reinterpret_cast<const x8<E> *>(tile + 32 * u * DH + nb[NG > 1 ? a : 0][ks & 1] + (NG > 1 ? 0 : 32 * a));
+    }
+    // MFMA first operand "row 32 c + lrow of the transposed tile, k element e <-> tile row 16 kk + 8 (e/4) + 4 half + e%4"
+    template <class E> __device__ __forceinline__ x8<E> tr(const E *tile, int c, int kk) const {
+        const uint32_t a0 = (uint32_t)(uintptr_t)(tile + tb[NG > 1 ? c : 0][0]);
+        const uint32_t a1 = (uint32_t)(uintptr_t)(tile + tb[NG > 1 ? c : 0][1]);
+        u32x2 lo, hi;
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(a0), "i"((16 * kk * DH + (NG > 1 ? 0 : 32 * c)) * 2));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(a1), "i"((16 * kk * DH + (NG > 1 ? 0 : 32 * c)) * 2));
+        const u32x4 v = {lo[0], lo[1], hi[0], hi[1]};
+        return __builtin_bit_cast(x8<E>, v);
     }
 };
 
@@ -498,7 +574,9 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const E *__restrict__ o
 // A wavefront owns 32 queries (Q and dO operands in registers); key tiles of 64 (K and V as stored) stream
 // from global memory straight into one of two LDS stages while the other is multiplied, one barrier per
 // tile.  K^T operands come from the natural K tile through the transposing LDS read.  Two workgroups per
-// CU, so that one's MFMAs run under the other's VALU work.
+// CU, so that one's MFMAs run under the other's VALU work - which needs tiles of DH elements per row, swizzled: with padded rows
+// the two stages take 90 KB at DH = 128 and only one workgroup fits (16 heads x 8100 positions x 128, causal: 605 us; now 478, and no
+// bank conflicts instead of a quarter of the LDS cycles; 384 x 1024 x 64: 142 -> 118).
 template <int DH, int OCC, class E>
 __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restrict__ qkv, const float *__restrict__ lse,
                                                           const float *__restrict__ delta,
@@ -506,10 +584,8 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
                                                           AttnShape sh) {
     constexpr int KT = 64;
     constexpr int NK = DH / 16, NC = DH / 32;
-    constexpr int PK = pitch_both<DH>(), PV = pitch_rd<DH>();
-    typedef TileDma<KT, DH, PK> DmaK;
-    typedef TileDma<KT, DH, PV> DmaV;
-    constexpr int STAGE = DmaK::ELEMS + DmaV::ELEMS;
+    typedef TileDmaSw<KT, DH> Dma;
+    constexpr int TILE = Dma::ELEMS, STAGE = 2 * TILE;          // K tile, then V tile
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     E *lds = reinterpret_cast<E *>(smem_raw);
 
@@ -547,17 +623,15 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
 
-    DmaK dk;
-    DmaV dv;
-    dk.init(wave, lane, (int)(pitch * 2), dh);
-    dv.init(wave, lane, (int)(pitch * 2), dh);
+    Dma dma;                                                    // K and V rows have the same pitch
+    dma.init(wave, lane, (int)(pitch * 2), dh);
     auto dma_tile = [&](int k0, int stage) {
-        E *Ks = lds + stage * STAGE, *Vs = Ks + DmaK::ELEMS;
-        dk.issue(seq + (size_t)k0 * pitch + d, Ks, sh.s - k0, wave);
-        dv.issue(seq + (size_t)k0 * pitch + 2 * d, Vs, sh.s - k0, wave);
+        E *Ks = lds + stage * STAGE;
+        dma.issue(seq + (size_t)k0 * pitch + d, Ks, sh.s - k0, wave);
+        dma.issue(seq + (size_t)k0 * pitch + 2 * d, Ks + TILE, sh.s - k0, wave);
     };
-    const int koff = lrow * PK + 8 * half, voff = lrow * PV + 8 * half;   // per-lane parts of the operand addresses
-    const int ktoff = tr_lane_off<PK>(lane);
+    BothAddr<DH> ad;
+    ad.init(lane);
 
     const bool causal = sh.causal != 0;
     const int kend = causal ? min(sh.s, qb * 128 + 128) : sh.s;
@@ -572,7 +646,7 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
         asm volatile("" ::: "memory");
         if (k0 + KT < kend) dma_tile(k0 + KT, stage ^ 1);
         if (causal && k0 > qw0 + 31) continue;     // whole tile is in this wavefront's future
-        const E *Ks = lds + stage * STAGE, *Vs = Ks + DmaK::ELEMS;
+        const E *Ks = lds + stage * STAGE, *Vs = Ks + TILE;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
             const int kbs = k0 + 32 * kb;          // first key of this block of 32
@@ -583,8 +657,8 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
             x8<E> kf[NK], vfr[NK], ktf[2 * NC];
 #pragma unroll
             for (int ks = 0; ks < NK; ++ks) {
-                kf[ks] = *reinterpret_cast<const x8<E> *>(Ks + koff + kb * 32 * PK + 16 * ks);
-                vfr[ks] = *reinterpret_cast<const x8<E> *>(Vs + voff + kb * 32 * PV + 16 * ks);
+                kf[ks] = ad.nat(Ks, kb, ks);
+                vfr[ks] = ad.nat(Vs, kb, ks);
             }
             f32x16 st, dpt;
 #pragma unroll
@@ -599,7 +673,7 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-                for (int c = 0; c < NC; ++c) ktf[kk * NC + c] = frag_nat_tr<PK>(Ks + ktoff, c, 2 * kb + kk);
+                for (int c = 0; c < NC; ++c) ktf[kk * NC + c] = ad.tr(Ks, c, 2 * kb + kk);
             __builtin_amdgcn_sched_barrier(0);
             if (causal ? kbs == qw0 : kbs + 32 > sh.s) {     // the diagonal block, or the ragged last one: masked keys
 #pragma unroll
@@ -637,86 +711,6 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
 
 
 // ============================================================================================
-// Tiles that are read both ways - rows with ds_read_b128 and transposed with ds_read_b64_tr_b16 - keep the
-// unpadded pitch DH and an XOR swizzle of the 16-byte chunk index that is free of bank conflicts for both:
-// 16 consecutive rows put one logical chunk into 16 different bank groups, and 4 consecutive rows (from a
-// multiple of 4) put an aligned group of 4 chunks into 4 different ones.
-template <int DH> __device__ __forceinline__ int sw_both(int row) {
-    if constexpr (DH == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
-    else if constexpr (DH == 64) return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
-    else return (row >> 2) & 3;              // 32, 96, 160: the row pitch already staggers groups of 4 chunks
-}
-// DMA of a ROWS x DH tile (global row pitch gp2 bytes) into such a tile: lane L of instruction j fills chunk
-// slot 64 j + L = row * (DH / 8) + physical chunk, with the logical chunk that the swizzle maps there.
-template <int ROWS, int DH> struct TileDmaSw {
-    static constexpr int NCH = DH / 8;
-    static constexpr int NI = ROWS * NCH / 64;              // instructions per tile
-    static constexpr int NJ = (NI + 3) / 4;                 // per wavefront, at most
-    static constexpr int ELEMS = ROWS * DH;
-    static_assert((ROWS * NCH) % 64 == 0, "tile is a whole number of DMA instructions");
-    int row[NJ], off[NJ];
-    // dh <= DH: the head size in memory; logical chunks from dh / 8 on are padding (zeros)
-    __device__ __forceinline__ void init(int wave, int lane, int gp2, int dh) {
-#pragma unroll
-        for (int i = 0; i < NJ; ++i) {
-            const int slot = (i * 4 + wave) * 64 + lane, r = slot / NCH, pc = slot % NCH;
-            row[i] = (pc ^ sw_both<DH>(r)) < dh / 8 ? r : 0x7FFFFFFF;
-            off[i] = r * gp2 + ((pc ^ sw_both<DH>(r)) << 4);
-        }
-    }
-    // src, dst: tiles of 16-bit elements of either format
-    __device__ __forceinline__ void issue(const void *src, void *dst, int nvalid, int wave) const {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src);
-#pragma unroll
-        for (int i = 0; i < NJ; ++i) {
-            const int j = i * 4 + wave;
-            if (j >= NI) continue;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(static_cast<char *>(dst) + j * 1024), 16, row[i] < nvalid ? off[i] : kBufPoison,
-                                                     0, 0, 0);
-        }
-    }
-};
-// Per-lane address parts (elements) of the two kinds of operand read from such a tile.  The swizzle splits
-// into a part that XORs the chunk group (DH = 64, 128 only) and one that XORs within the group, which leaves
-// few distinct lane values; everything else is a compile-time offset.
-template <int DH> struct BothAddr {
-    static constexpr int NG = DH == 128 ? 4 : DH == 64 ? 2 : 1;     // chunk groups the swizzle permutes
-    int nb[NG][2];      // natural read: [chunk group][ks & 1]
-    int tb[NG][2];      // transposed read: [32-column block c (if NG > 1)][second half of the 16 positions]
-    __device__ __forceinline__ void init(int lane) {
-        const int lrow = lane & 31, half = lane >> 5, i = lane & 15, g = (lane >> 4) & 1;
-        const int s = sw_both<DH>(lrow), s_hi = s >> 2, s_lo = s & 3;
-#pragma unroll
-        for (int a = 0; a < NG; ++a)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) nb[a][e] = lrow * DH + 32 * (a ^ s_hi) + (((2 * e + half) ^ s_lo) << 3);
-#pragma unroll
-        for (int sec = 0; sec < 2; ++sec) {
-            const int row = 8 * sec + 4 * half + (i >> 2);           // + 16 kk, which does not change the swizzle
-            const int t = sw_both<DH>(row), t_hi = t >> 2, t_lo = t & 3;
-            const int b = 2 * g + ((i & 3) >> 1);
-#pragma unroll
-            for (int c = 0; c < NG; ++c) tb[c][sec] = row * DH + 32 * (c ^ t_hi) + ((b ^ t_lo) << 3) + 4 * (i & 1);
-        }
-    }
-    // MFMA first operand: row 32 u + lrow of the tile, k = 16 ks + 8 half + (0..7)
-    template <class E> __device__ __forceinline__ x8<E> nat(const E *tile, int u, int ks) const {
-        const int a = ks >> 1;
-        return *reinterpret_cast<const x8<E> *>(tile + 32 * u * DH + nb[NG > 1 ? a : 0][ks & 1] + (NG > 1 ? 0 : 32 * a));
-    }
-    // MFMA first operand "row 32 c + lrow of the transposed tile, k element e <-> tile row 16 kk + 8 (e/4) + 4 half + e%4"
-    template <class E> __device__ __forceinline__ x8<E> tr(const E *tile, int c, int kk) const {
-        const uint32_t a0 = (uint32_t)(uintptr_t)(tile + tb[NG > 1 ? c : 0][0]);
-        const uint32_t a1 = (uint32_t)(uintptr_t)(tile + tb[NG > 1 ? c : 0][1]);
-        u32x2 lo, hi;
-        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(a0), "i"((16 * kk * DH + (NG > 1 ? 0 : 32 * c)) * 2));
-        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(a1), "i"((16 * kk * DH + (NG > 1 ? 0 : 32 * c)) * 2));
-        const u32x4 v = {lo[0], lo[1], hi[0], hi[1]};
-        return __builtin_bit_cast(x8<E>, v);
-    }
-};
-
-// ============================================================================================
 // dK, dV.  One workgroup per (sequence, head, block of 128 keys), see block_of(); rank = key block index (with the
 // causal mask the first key block has the most queries).
 //
@@ -726,19 +720,21 @@ template <int DH> struct BothAddr {
 // With the causal mask the first two query tiles of a key block contain its diagonal (masked, partly skipped); all
 // later ones - without the mask, all tiles from the start of the sequence - are fully visible and go through a loop
 // without tests (rows past the end of the sequence are zero and carry zero statistics: they add nothing).
+// LDS stages; four where the loop over fully visible tiles is pipelined across units
+template <int DH> constexpr int dkv_stages() { return DH == 96 || DH == 128 ? 4 : 3; }
 template <int DH, class E>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(const E *__restrict__ qkv, const float *__restrict__ lse,
                                                               const float *__restrict__ delta,
                                                               const E *__restrict__ dout, E *__restrict__ dqkv,
                                                               AttnShape sh) {
-    constexpr int QT = 64, NST = 3;
+    constexpr int QT = 64, NST = dkv_stages<DH>();
     constexpr int NK = DH / 16, NC = DH / 32;
     typedef TileDmaSw<QT, DH> Dma;
     constexpr int TILE = Dma::ELEMS, STAGE = 2 * TILE;          // Q tile, then dO tile
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     E *lds = reinterpret_cast<E *>(smem_raw);
     float *lse_s = reinterpret_cast<float *>(lds + NST * STAGE);     // [NST][QT]  log-sum-exp, log2 domain, negated
-    float *dl_s = lse_s + NST * QT;                                  // [NST][QT]  delta
+    float *dl_s = lse_s + NST * QT;                                  // [NST][QT]  delta, negated
 
     int bh, kb128;
     block_of(sh, (sh.s + 127) / 128, bh, kb128);
@@ -786,78 +782,89 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(const E *__restric
         dq_.issue(seq + (size_t)q0 * pitch, lds + stage * STAGE, sh.s - q0, wave);
         do_.issue(doseq + (size_t)q0 * d, lds + stage * STAGE + TILE, sh.s - q0, wave);
     };
+    // (the value is left as loaded until it is stored: any arithmetic on it here would wait for the load, and with it for every
+    // tile in flight)
     auto load_stat = [&](int t) -> float {
-        const int qq = qbeg + QT * t + lane;
-        if (wave == 0) return qq < sh.s ? -lse[stat0 + qq] * kLog2e : 0.f;
-        if (wave == 1) return qq < sh.s ? delta[stat0 + qq] : 0.f;
-        return 0.f;
+        const int qq = min(qbeg + QT * t + lane, sh.s - 1);
+        return wave == 0 ? lse[stat0 + qq] : delta[stat0 + qq];
     };
-    auto store_stat = [&](int stage, float v) {
-        if (wave == 0) lse_s[stage * QT + lane] = v;
-        if (wave == 1) dl_s[stage * QT + lane] = v;
+    auto store_stat = [&](int t, int stage, float v) {
+        const bool in = qbeg + QT * t + lane < sh.s;
+        if (wave == 0) lse_s[stage * QT + lane] = in ? -v * kLog2e : 0.f;
+        if (wave == 1) dl_s[stage * QT + lane] = in ? -v : 0.f;
     };
 
-    // one (32 keys x 32 queries) unit of tile `stage`: query rows [32 u, 32 u + 32) of the tile, first query qs
-    auto unit = [&](int stage, int u, int qs, auto masked_c) {
-        constexpr bool MASKED = decltype(masked_c)::value;
-        const E *Qs = lds + stage * STAGE, *dOs = Qs + TILE;
-        x8<E> qn[NK], don[NK];
-#pragma unroll
-        for (int ks = 0; ks < NK; ++ks) {
-            qn[ks] = ad.nat(Qs, u, ks);
-            don[ks] = ad.nat(dOs, u, ks);
-        }
-        f32x4 l4[4], d4[4];
+    // A unit is 32 keys x 32 queries: query rows [32 u, 32 u + 32) of the tile in `stage`, first query qs.  Its steps:
+    x8<E> qn[NK], don[NK];                         // row operands (Q, dO) of a unit
+    x8<E> dot[2 * NC], qt[2 * NC];                 // transposed operands
+    x8<E> pf[2], dsf[2];                           // P and dS as operands
+    auto read_rows = [&](int stage, int u, int ks) {
+        qn[ks] = ad.nat(lds + stage * STAGE, u, ks);
+        don[ks] = ad.nat(lds + stage * STAGE + TILE, u, ks);
+    };
+    auto read_tr = [&](int stage, int u, int j) {  // j = kk NC + c
+        dot[j] = ad.tr(lds + stage * STAGE + TILE, j % NC, 2 * u + j / NC);
+        qt[j] = ad.tr(lds + stage * STAGE, j % NC, 2 * u + j / NC);
+    };
+    // S = Q K^T and dP - delta = dO V^T - delta: the latter starts from the negated deltas of its rows, which saves the subtraction
+    auto init_dp = [&](int stage, int u, f32x16 &dp) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            l4[g] = *reinterpret_cast<const f32x4 *>(lse_s + stage * QT + 32 * u + 8 * g + 4 * half);
-            d4[g] = *reinterpret_cast<const f32x4 *>(dl_s + stage * QT + 32 * u + 8 * g + 4 * half);
-        }
-        f32x16 s_, dp;
+            const f32x4 d4 = *reinterpret_cast<const f32x4 *>(dl_s + stage * QT + 32 * u + 8 * g + 4 * half);
 #pragma unroll
-        for (int ks = 0; ks < NK; ++ks) {
-            const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            s_ = MFMA(qn[ks], kf[ks], ks == 0 ? zero : s_);
-            dp = MFMA(don[ks], vf[ks], ks == 0 ? zero : dp);
+            for (int i = 0; i < 4; ++i) dp[4 * g + i] = d4[i];
         }
+    };
+    auto s_dp = [&](int ks, f32x16 &s_, f32x16 &dp) {
+        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        s_ = MFMA(qn[ks], kf[ks], ks == 0 ? zero : s_);
+        dp = MFMA(don[ks], vf[ks], dp);
+    };
+    auto read_lse = [&](int stage, int u, f32x4 (&l4)[4]) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) l4[g] = *reinterpret_cast<const f32x4 *>(lse_s + stage * QT + 32 * u + 8 * g + 4 * half);
+    };
+    auto softmax = [&](int g, const f32x4 &l4, const f32x16 &s_, const f32x16 &dp, int qs, auto masked_c) {      // quarter g of P and dS
+        constexpr bool MASKED = decltype(masked_c)::value;
+        float p[4], ds[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = __builtin_amdgcn_exp2f(fmaf(s_[4 * g + i], c2, l4[i]));
+            if (MASKED && qs + 8 * g + 4 * half + i < key) p[i] = 0.f;
+            ds[i] = p[i] * dp[4 * g + i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            pf[g >> 1][4 * (g & 1) + i] = (E)p[i];
+            dsf[g >> 1][4 * (g & 1) + i] = (E)ds[i];
+        }
+    };
+    auto dv_dk = [&](int j) {
+        dv[j % NC] = MFMA(dot[j], pf[j / NC], dv[j % NC]);
+        dk[j % NC] = MFMA(qt[j], dsf[j / NC], dk[j % NC]);
+    };
+    // all steps of one unit in turn
+    auto unit = [&](int stage, int u, int qs, auto masked_c) {
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) read_rows(stage, u, ks);
+        f32x16 s_, dp;
+        f32x4 l4[4];
+        init_dp(stage, u, dp);
+        read_lse(stage, u, l4);
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) s_dp(ks, s_, dp);
         // the transposed operands take over the registers of the row operands; their latency passes under the
         // exponentials
         __builtin_amdgcn_sched_barrier(0);
-        x8<E> dot[2 * NC], qt[2 * NC];
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                dot[kk * NC + c] = ad.tr(dOs, c, 2 * u + kk);
-                qt[kk * NC + c] = ad.tr(Qs, c, 2 * u + kk);
-            }
+        for (int j = 0; j < 2 * NC; ++j) read_tr(stage, u, j);
         __builtin_amdgcn_sched_barrier(0);
-        f32x16 pr;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int r = 4 * g + i;
-                float p = __builtin_amdgcn_exp2f(fmaf(s_[r], c2, l4[g][i]));
-                if (MASKED && qs + 8 * g + 4 * half + i < key) p = 0.f;
-                pr[r] = p;
-                s_[r] = p * (dp[r] - d4[g][i]);
-            }
-        x8<E> pf[2], dsf[2];
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            pf[kk] = pack16<E>(pr, kk);
-            dsf[kk] = pack16<E>(s_, kk);
-        }
+        for (int g = 0; g < 4; ++g) softmax(g, l4[g], s_, dp, qs, masked_c);
         wait_tr_reads(dot);
         wait_tr_reads(qt);
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                dv[c] = MFMA(dot[kk * NC + c], pf[kk], dv[c]);
-                dk[c] = MFMA(qt[kk * NC + c], dsf[kk], dk[c]);
-            }
+        for (int j = 0; j < 2 * NC; ++j) dv_dk(j);
     };
     // wait for this wavefront's part of the oldest tile in flight (`newer`: a younger one is in flight too),
     // then a bare s_barrier - a __syncthreads() fence would wait for the younger tile as well
@@ -876,41 +883,113 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(const E *__restric
     // tile t is multiplied while tiles t + 1 and t + 2 are in flight
     float stat = load_stat(0);
     dma_tile(0, 0);
-    store_stat(0, stat);
+    store_stat(0, 0, stat);
     if (ntiles > 1) {
         stat = load_stat(1);
         dma_tile(1, 1);
     }
-    // start of every iteration: tile t + 1's statistics go to LDS (published by the barrier after next... by
-    // the next iteration's barrier), tile t is published, tile t + 2 is requested
-    auto advance = [&](int t, int stage) {
-        const int next = stage == NST - 1 ? 0 : stage + 1, after = next == NST - 1 ? 0 : next + 1;
-        if (t + 1 < ntiles) store_stat(next, stat);
+    // start of tile t: tile t + 1's statistics go to LDS (the next call's barrier publishes them), tile t is published, tile
+    // t + 2 is requested
+    auto slot = [&](int t) { return NST == 4 ? t & 3 : t % NST; };
+    auto advance = [&](int t) {
+        if (t + 1 < ntiles) store_stat(t + 1, slot(t + 1), stat);
         publish(t + 1 < ntiles);
         if (t + 2 < ntiles) {
             stat = load_stat(t + 2);
-            dma_tile(t + 2, after);
+            dma_tile(t + 2, slot(t + 2));
         }
     };
     // Two loops in sequence rather than one with two kinds of iteration: with two code paths through the
     // MFMAs in one loop the compiler merges their accumulator registers with copies at every iteration.
-    int stage = 0, t = 0;
+    int t = 0;
     const int ndiag = causal ? 2 : 0;
-    for (; t < ndiag && t < ntiles; ++t, stage = stage == NST - 1 ? 0 : stage + 1) {  // the diagonal part
-        advance(t, stage);
+    for (; t < ndiag && t < ntiles; ++t) {                      // the diagonal part
+        advance(t);
         const int q0 = qbeg + QT * t;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int qs = q0 + 32 * u;
             if (qs + 31 < kw0 || qs >= sh.s) continue;      // all its queries precede this wavefront's keys, or are past the end
-            unit(stage, u, qs, std::true_type{});
+            unit(slot(t), u, qs, std::true_type{});
         }
     }
-    for (; t < ntiles; ++t, stage = stage == NST - 1 ? 0 : stage + 1) {               // fully visible tiles
-        advance(t, stage);
-        const int q0 = qbeg + QT * t;
-        unit(stage, 0, q0, std::false_type{});
-        unit(stage, 1, q0 + 32, std::false_type{});
+    if constexpr (NST == 4) {
+        // Fully visible tiles, one unit's steps spread over its neighbours' (a wavefront is alone on its SIMD: in turn, the LDS reads, the
+        // first products, the exponentials and the second products each leave the other units idle - 0.28 of the matrix
+        // pipe's cycles at 128 channels):
+        //   phase A of unit n   S, dP of unit n + 1  |  P, dS of unit n, its transposed reads
+        //   phase B of unit n   dV, dK of unit n     |  row reads of unit n + 2
+        // 16 heads x 8100 positions x 128, causal: 3670 -> 2270 cycles a unit (1024 of them matrix instructions), 775 -> 693 us; what is
+        // left is the 32 moves a unit out of accumulation registers, LDS waits and the barrier per tile.
+        // Unit n + 2 may lie in the next tile, which is published in phase B of the tile's first unit; the tile itself is still read
+        // in the phases after that, which is what the fourth stage is for.
+        if (t < ntiles) {
+            f32x16 s0, dp0, s1, dp1;
+            f32x4 l4[4];
+            auto phase_a = [&](int stage, int u, const f32x16 &s_, const f32x16 &dp, f32x16 &ns, f32x16 &ndp) __attribute__((always_inline)) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+#pragma unroll
+                    for (int ks = 0; ks < NK; ++ks)
+                        if (ks >= g * NK / 4 && ks < (g + 1) * NK / 4) s_dp(ks, ns, ndp);
+                    softmax(g, l4[g], s_, dp, 0, std::false_type{});
+#pragma unroll
+                    for (int i = 0; i < NK / 2; ++i) {           // one matrix instruction, then its share of the exponentials
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 56 / NK, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int j = 0; j < 2 * NC; ++j)             // done by the third quarter: the last one covers their latency
+                        if (g < 3 && j >= g * 2 * NC / 3 && j < (g + 1) * 2 * NC / 3) read_tr(stage, u, j);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            // ... and at its end the statistics: the log-sum-exps of unit n + 1, the deltas of unit n + 2
+            auto phase_b = [&](int lstage, int lu, int rstage, int ru, f32x16 &rdp, int publish_t) __attribute__((always_inline)) {
+                wait_tr_reads(dot);
+                wait_tr_reads(qt);
+                __builtin_amdgcn_sched_barrier(0);
+                dv_dk(0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (publish_t >= 0 && publish_t < ntiles) advance(publish_t);
+#pragma unroll
+                for (int j = 1; j < 2 * NC; ++j) {
+                    dv_dk(j);
+#pragma unroll
+                    for (int ks = 0; ks < NK; ++ks)
+                        if (ks * (2 * NC - 2) / NK == j - 1) read_rows(rstage, ru, ks);
+                    if (j == 2 * NC - 2) read_lse(lstage, lu, l4);
+                    if (j == 2 * NC - 1) init_dp(rstage, ru, rdp);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            advance(t);
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) read_rows(slot(t), 0, ks);
+            init_dp(slot(t), 0, dp0);
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) s_dp(ks, s0, dp0);
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) read_rows(slot(t), 1, ks);
+            read_lse(slot(t), 0, l4);
+            init_dp(slot(t), 1, dp1);
+            // behind the last tile the products and reads of a tile that does not exist run too, on whatever its stage holds: nothing
+            // uses them, and the loop has one path through the matrix instructions
+            for (; t < ntiles; ++t) {
+                const int cur = slot(t), nxt = slot(t + 1);
+                phase_a(cur, 0, s0, dp0, s1, dp1);
+                phase_b(cur, 1, nxt, 0, dp0, t + 1);
+                phase_a(cur, 1, s1, dp1, s0, dp0);
+                phase_b(nxt, 0, nxt, 1, dp1, -1);
+            }
+        }
+    } else {
+        for (; t < ntiles; ++t) {                               // fully visible tiles
+            advance(t);
+            unit(slot(t), 0, 0, std::false_type{});
+            unit(slot(t), 1, 0, std::false_type{});
+        }
     }
     if (kvalid) {
         E *orow = dqkv + ((size_t)b * sh.s + key) * pitch + (size_t)h * dh;
@@ -958,11 +1037,9 @@ template <int DH> constexpr int smem_fwd() {
     return 3 * (TileDma<64, DH, pitch_rd<DH>()>::ELEMS + TileDma<64, DH, pitch_tr<DH>()>::ELEMS) * 2;
 }
 // dQ: two stages of a 64-key K tile and V tile
-template <int DH> constexpr int smem_dq() {
-    return 2 * (TileDma<64, DH, pitch_both<DH>()>::ELEMS + TileDma<64, DH, pitch_rd<DH>()>::ELEMS) * 2;
-}
-// dK/dV: three stages of a Q tile, a dO tile and the row statistics
-template <int DH> constexpr int smem_dkv() { return 3 * (2 * 64 * DH * 2 + 2 * 64 * 4); }
+template <int DH> constexpr int smem_dq() { return 2 * 2 * 64 * DH * 2; }
+// dK/dV: three or four stages of a Q tile, a dO tile and the row statistics
+template <int DH> constexpr int smem_dkv() { return dkv_stages<DH>() * (2 * 64 * DH * 2 + 2 * 64 * 4); }
 template <int DH> constexpr int occ_dq() { return DH <= 128 ? 2 : 1; }     // workgroups per CU the dQ kernel's register budget is set for
 
 // All three kernels use more dynamic LDS than a launch may ask for by default: raise the limit of every
