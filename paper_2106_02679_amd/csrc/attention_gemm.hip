@@ -1,6 +1,6 @@
-// Softmax attention for head sizes that have no fused MFMA kernel (d_h > 160: the X_[x] family of table B.1 has
-// d_h = 2 x, 216 for X_108 and 320 for X_160), built from the library's own batched 16-bit GEMMs and two row
-// kernels.  The fused kernels keep a query block's operands and accumulators in registers, which ends at d_h = 160;
+// Softmax attention for head sizes that have no fused MFMA kernel (d_h > 320, and the backward pass of few heads above 224; up to
+// 320 attention_wide.hip serves the others), built from the library's own batched 16-bit GEMMs and two row
+// kernels.  The fused kernels keep a query block's operands and accumulators in registers, which ends there;
 // here the score matrix of every head goes through memory instead (fp32, so that the softmax sees unrounded scores):
 //
 //   forward    S = Q K^T                         batched GEMM over the heads, fp32 result
@@ -170,6 +170,7 @@ bool attn_gemm_supports(AttnShape sh, size_t ws_bytes) {
 template <class E>
 void launch_attn_fwd_gemm(const E *qkv, E *out, float *lse, AttnShape sh, void *ws, size_t ws_bytes, hipStream_t st) {
     if (sh.n_seq == 0 || sh.s == 0) return;
+    if (attn_wide_supports(sh.dh)) return launch_attn_fwd_wide<E>(qkv, out, lse, sh, st);
     const int s = sh.s, dh = sh.dh, d = sh.heads * dh, hc_max = heads_per_pass(sh, ws_bytes);
     const float scale = 1.0f / sqrtf((float)dh);
     for (int b = 0; b < sh.n_seq; ++b) {
@@ -206,6 +207,11 @@ template <class E>
 void launch_attn_bwd_gemm(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv, float *delta,
                           AttnShape sh, void *ws, size_t ws_bytes, hipStream_t st) {
     if (sh.n_seq == 0 || sh.s == 0) return;
+    // Above 224 channels the fused dK/dV kernel runs twice, with one workgroup per 128 keys: on a chip half empty its serial walk over the
+    // queries is the longer one (16 heads x 1024 x 256: 157 against 130 us; 16 x 1024 x 176: 100 against 127; 32 x 2048 x 256: 397
+    // against 749).
+    const bool few = sh.dh > 224 && (long)sh.n_seq * sh.heads * ((sh.s + 127) / 128) <= 128;
+    if (attn_wide_supports(sh.dh) && !few) return launch_attn_bwd_wide<E>(qkv, out, lse, dout, dqkv, delta, sh, st);
     const int s = sh.s, dh = sh.dh, d = sh.heads * dh, hc_max = heads_per_pass(sh, ws_bytes);
     const float scale = 1.0f / sqrtf((float)dh);
     const long long ss = (long long)s * s;

@@ -18,6 +18,7 @@ hipError_t attn_prepare_kernels();      // attention_bf16.hip's part
 hipError_t gemm_prepare_kernels();      // gemm_bf16.hip's part
 hipError_t gemm_f32_prepare_kernels();  // gemm_f32.hip's part
 hipError_t gemm_small_prepare_kernels();  // gemm_small.hip's part
+hipError_t attn_wide_prepare_kernels();   // attention_wide.hip's part
 
 // ---- element-wise / row kernels (rowops.hip) ---------------------------------------------
 // fp32 -> 16-bit copy of a parameter vector ("restore": parameters converted to 16 bits before use); E = bf16 or f16.
@@ -122,6 +123,15 @@ bool attn_bf16_supports(int dh);
 template <class E> void launch_attn_fwd_mfma(const E *qkv, E *out, float *lse, AttnShape sh, hipStream_t s);
 template <class E>
 void launch_attn_bwd_mfma(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv, float *delta,
+                          AttnShape sh, hipStream_t s);
+
+// delta[sequence, head, query] = sum_c dO O
+template <class E> void launch_attn_delta(const E *out, const E *dout, float *delta, AttnShape sh, hipStream_t s);
+// Fused kernels for head sizes above 160 and up to 320, multiples of 8 (attention_wide.hip).
+bool attn_wide_supports(int dh);
+template <class E> void launch_attn_fwd_wide(const E *qkv, E *out, float *lse, AttnShape sh, hipStream_t s);
+template <class E>
+void launch_attn_bwd_wide(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv, float *delta,
                           AttnShape sh, hipStream_t s);
 
 // The same attention for head sizes without a fused kernel, built from batched GEMMs and two row kernels

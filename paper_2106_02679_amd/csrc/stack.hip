@@ -43,6 +43,7 @@ hipError_t prepare_kernels() {
         if (result == hipSuccess) result = gemm_prepare_kernels();
         if (result == hipSuccess) result = gemm_f32_prepare_kernels();
         if (result == hipSuccess) result = gemm_small_prepare_kernels();
+        if (result == hipSuccess) result = attn_wide_prepare_kernels();
     });
     return result;
 }

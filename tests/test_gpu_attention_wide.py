@@ -1,0 +1,63 @@
+"""GPU parity of the fused attention for head sizes above 160: every padded size and its neighbours, sequence lengths at the edges of
+the 32-position tiles and 128-position blocks, and scores that keep growing along the keys, so that the softmax reference moves
+in tile after tile.  Gates as for the other 16-bit attention kernels (test_gpu_ops.TOL_ATTN)."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2106_02679_amd import binding as B
+from gpu_helpers import to_dev, empty_dev, to_host, rel_err
+from test_gpu_ops import attention_reference, rnd, ROUND, TOL_ATTN, BF16, F16
+
+
+def run(dt, qkv, dout, n_seq, s, heads, dh, causal):
+    d = heads * dh
+    qd, dod = to_dev(qkv, dt), to_dev(dout, dt)
+    out, dqkv = empty_dev((n_seq * s, d), dt), empty_dev((n_seq * s, 3 * d), dt)
+    lse, delta = torch.empty(n_seq * heads * s, device="cuda"), torch.empty(n_seq * heads * s, device="cuda")
+    ws = torch.empty(int(B.lib.lga_op_attention_gemm_workspace_bytes(s, heads)), device="cuda", dtype=torch.uint8)
+    B.check(B.lib.lga_op_attention_gemm_fwd(dt, qd.data_ptr(), out.data_ptr(), lse.data_ptr(), n_seq, s, heads, dh, int(causal),
+                                            ws.data_ptr(), ws.numel(), None))
+    B.check(B.lib.lga_op_attention_gemm_bwd(dt, qd.data_ptr(), out.data_ptr(), lse.data_ptr(), dod.data_ptr(), dqkv.data_ptr(),
+                                            delta.data_ptr(), n_seq, s, heads, dh, int(causal), ws.data_ptr(), ws.numel(), None))
+    torch.cuda.synchronize()
+    return to_host(out), lse.cpu().numpy().reshape(n_seq, heads, s), to_host(dqkv)
+
+
+def check(dt, got, want, d, loose=1.0):
+    out, lse, dqkv = got
+    assert rel_err(out, want[0]) < TOL_ATTN[dt][0]
+    assert np.abs(lse - want[1]).max() < 1e-3 * max(1.0, np.abs(want[1]).max())
+    for i, name in enumerate(("dq", "dk", "dv")):
+        sl = slice(i * d, (i + 1) * d)
+        assert rel_err(dqkv[:, sl], want[2][:, sl]) < loose * TOL_ATTN[dt][1], name
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dt", [BF16, F16])
+@pytest.mark.parametrize("dh", [168, 192, 200, 224, 232, 256, 264, 320])
+def test_wide_heads_at_the_edges_of_tiles_and_blocks(dh, dt, causal):
+    # the last two have enough blocks that the backward pass above 224 channels is fused too
+    for n_seq, s, heads in ((1, 8, 1), (2, 40, 2), (1, 128, 1), (1, 136, 2), (1, 264, 45), (2, 160, 40)):
+        rng = np.random.default_rng(dh + s)
+        qkv, dout = rnd(rng, (n_seq * s, 3 * heads * dh), dt), rnd(rng, (n_seq * s, heads * dh), dt)
+        check(dt, run(dt, qkv, dout, n_seq, s, heads, dh, causal),
+              attention_reference(qkv, dout, n_seq, s, heads, dh, causal), heads * dh)
+
+
+@pytest.mark.parametrize("dt,dh,causal", [(BF16, 216, True), (F16, 216, False), (BF16, 320, False), (F16, 256, True)])
+def test_wide_heads_with_scores_that_keep_growing_along_the_keys(dt, dh, causal):
+    n_seq, s, heads = 1, 320, 2
+    d = heads * dh
+    rng = np.random.default_rng(77 + dh)
+    qkv = rng.standard_normal((s, 3 * d)).astype(np.float32)
+    for h in range(heads):
+        qkv[:, h * dh] = math.sqrt(dh)                            # q[:, 0] = sqrt(dh)
+        qkv[:, d + h * dh] = 0.25 * np.arange(s)                  # k[j, 0] = j / 4: key j scores about j / 4 nats with every query
+    qkv, dout = ROUND[dt](qkv), rnd(rng, (s, d), dt)
+    # near one-hot probabilities times keys of size ~80: the rounding of dS weighs more than on ordinary inputs
+    check(dt, run(dt, qkv, dout, n_seq, s, heads, dh, causal), attention_reference(qkv, dout, n_seq, s, heads, dh, causal), d, loose=2.0)
