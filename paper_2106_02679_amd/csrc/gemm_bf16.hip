@@ -7,9 +7,9 @@
 //   forward          Y[t,out]  = X[t,in]  W[in,out]
 //   input gradient   dX[t,in]  = dY[t,out] W[in,out]^T
 //   weight gradient  dW[in,out] (+)= X[t,in]^T dY[t,out]      K = tokens of the micro-batch group
-// are all run by the layer stack with BOTH operands k-contiguous (it keeps a transposed 16-bit copy of
-// every weight matrix and transposes the two operands of a weight-gradient GEMM beforehand).  That layout
-// is served by gemm_bf16_dma_kernel: 256 threads = 4 wavefronts (2x2) on a 256x256x64 tile,
+// The layer stack runs the first two with BOTH operands k-contiguous (it keeps a transposed 16-bit copy of every weight
+// matrix), the third with both as stored, [k][in] and [k][out], where it is large enough for 256 x 256 tiles, and on transposed
+// copies otherwise.  All of these are served by gemm_bf16_dma_kernel: 256 threads = 4 wavefronts (2x2) on a 256x256x64 tile,
 // v_mfma_f32_16x16x32_bf16, tiles moved global -> LDS without passing through registers.
 //
 // Problems with fewer than 128 such tiles go to gemm_small.hip.
@@ -382,7 +382,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams<E> p, int til
 // the two products that a block receives per k tile are issued back to back (see `half` in the kernel): the second finds
 // the accumulator still in the pipe.
 
-template <int BM, int BN, int WGM, int WGN, int EPI, class E>
+//
+// TN: the same loop for operands that are m- and n-contiguous ([k][ld], a weight gradient's activations and output
+// gradients as the layer stores them).  An operand tile is then 64 k rows of 256 elements: a DMA instruction fills two of
+// its 512-byte rows, and ds_read_b64_tr_b16 transposes on the way to the registers - twice the LDS read instructions of
+// half the width.  A wavefront's read covers 8 rows x 32 bytes per cycle, so 32-byte segment g of row r is stored at
+// segment g ^ (r & 7): 8 rows, 8 different bank groups.  A lane's 8 k values of a step are rows 4 lq .. + 3 and 16 + 4 lq .. + 3,
+// for both operands alike.  The loop runs no slower for it: the four weight gradients of a d = 768 layer over 32768 tokens take 104 us
+// each on average, 107 in the k-contiguous form - and the transposing passes before those took 330 us more, at the rate of a copy.
+// With the bias gradients' column sums in a pass of their own (99 us; they rode along with the transposes) the layer's backward
+// went from 2.26 to 1.93 ms; a training step of a d = 2048 layer over 65536 tokens from 25.0 to 24.0 ms, of a d = 12288 layer
+// over 16384 from 160.4 to 158.8.
+template <int BM, int BN, int WGM, int WGN, int EPI, class E, bool TN>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParams<E> p, int tiles_m, int tiles_n) {
     constexpr int NW = WGM * WGN;                   // wavefronts per workgroup, WGM x WGN over the tile
     constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -415,8 +426,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
             // this workgroup multiplies slice z of the k range into partial result z ([M][N], dense)
             const int z = tile / ntiles, k0 = z * p.kchunk;
             tile -= z * ntiles;
-            p.A += k0;
-            p.B += k0;
+            p.A += TN ? (size_t)k0 * p.lda : k0;
+            p.B += TN ? (size_t)k0 * p.ldb : k0;
             p.K = min(p.K - k0, p.kchunk);
             p.outf = p.partial + (size_t)z * p.M * p.N;
             p.ldc = p.N;
@@ -464,21 +475,29 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
     // and tell their places apart by the instruction's immediate offset, 1024 (i % 4) - which the hardware adds to the
     // memory address too, so the per-lane offsets have it subtracted.  (A row is at least 128 bytes long here - the
     // launcher sends shorter leading dimensions to the other kernel - so the difference is never negative.)
-    auto dma_row = [&](int i) { return (wave * NIA + i) * 8 + (lane >> 3); };
+    // (TN: an instruction fills two rows of 512 bytes, and the launcher sends leading dimensions below 256 elsewhere.)
+    auto dma_row = [&](int i) { return TN ? (wave * NIA + i) * 2 + (lane >> 5) : (wave * NIA + i) * 8 + (lane >> 3); };
     static_assert(NIA == NIB && NIA % 4 == 0, "row mapping and M0 groups below");
     int offA[NIA], offB[NIB];
 #pragma unroll
     for (int i = 0; i < NIA; ++i) {
         const int r = dma_row(i);
-        offA[i] = (m0 + r < p.M) ? r * lda2 + (((lane & 7) ^ swz16(r)) << 4) - (i & 3) * 1024 : kBufPoison;
+        if constexpr (TN) {
+            const int chunk = (lane & 31) ^ ((r & 7) << 1);
+            offA[i] = (m0 + chunk * 8 < p.M) ? r * lda2 + chunk * 16 - (i & 3) * 1024 : kBufPoison;
+        } else offA[i] = (m0 + r < p.M) ? r * lda2 + (((lane & 7) ^ swz16(r)) << 4) - (i & 3) * 1024 : kBufPoison;
     }
 #pragma unroll
     for (int i = 0; i < NIB; ++i) {
         const int r = dma_row(i);
-        offB[i] = (n0 + r < p.N) ? r * ldb2 + (((lane & 7) ^ swz16(r)) << 4) - (i & 3) * 1024 : kBufPoison;
+        if constexpr (TN) {
+            const int chunk = (lane & 31) ^ ((r & 7) << 1);
+            offB[i] = (n0 + chunk * 8 < p.N) ? r * ldb2 + chunk * 16 - (i & 3) * 1024 : kBufPoison;
+        } else offB[i] = (n0 + r < p.N) ? r * ldb2 + (((lane & 7) ^ swz16(r)) << 4) - (i & 3) * 1024 : kBufPoison;
     }
-    const E *a_ptr = p.A + (size_t)m0 * p.lda;
-    const E *b_ptr = p.B + (size_t)n0 * p.ldb;
+    const E *a_ptr = p.A + (TN ? (size_t)m0 : (size_t)m0 * p.lda);
+    const E *b_ptr = p.B + (TN ? (size_t)n0 : (size_t)n0 * p.ldb);
+    const size_t a_step = TN ? (size_t)BK * p.lda : BK, b_step = TN ? (size_t)BK * p.ldb : BK;      // elements per k tile
     const int nk = (p.K + BK - 1) / BK, nk_full = p.K / BK;
 
     typedef __attribute__((address_space(3))) void *lds_ptr;
@@ -496,9 +515,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
     };
     // krem < 64 (partial last tile): k chunks at or beyond krem read as zero.
     auto dma_one = [&](bool is_a, int q, int kt, int krem, int i) {
-        const __amdgpu_buffer_rsrc_t r = make_rsrc((is_a ? a_ptr : b_ptr) + (size_t)kt * BK);
+        const __amdgpu_buffer_rsrc_t r = make_rsrc((is_a ? a_ptr : b_ptr) + kt * (is_a ? a_step : b_step));
         int off = is_a ? offA[i] : offB[i];
-        if (krem < BK) off |= ((((lane & 7) ^ swz16(dma_row(i))) * 8 < krem) ? 0 : kBufPoison);
+        if constexpr (TN) {
+            if (dma_row(i) >= krem) off = kBufPoison;
+        } else if (krem < BK) off |= ((((lane & 7) ^ swz16(dma_row(i))) * 8 < krem) ? 0 : kBufPoison);
         lds_dma(r, q, i, off, 0);
     };
     // MFMA operands of a whole k tile: block f of k step s (32 k each) of A and of B, 128 registers.  A tile is
@@ -517,8 +538,29 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
     const int lane_sw = lq ^ (l16 >> 1);
     const int lane_a = ((wm * WM + l16) * BK + lane_sw * 8) * 2;
     const int lane_b = ((wn * WN + l16) * BK + lane_sw * 8) * 2;
+    // TN: block f's segment of row r is (8 wm + f) ^ (r & 7), and r & 7 is the lane's whatever the step and half
+    const int tn_row = 4 * lq + (l16 >> 2);
+    auto tn_lane = [&](int w, int f) { return tn_row * (BM * 2) + w * (WM * 2) + ((f ^ (tn_row & 7)) << 5) + (l16 & 3) * 8; };
+    // Rows 4 lq .. + 3 and 16 + 4 lq .. + 3 of column l16 of the block at LDS byte address addr + imm (imm a constant).  In asm: the
+    // builtin makes the compiler wait for all direct-to-LDS loads in flight before it.  The result must not be touched before one
+    // of the waits below, which name it.
+    auto tr_read = [&](int addr, int imm) __attribute__((always_inline)) {
+        u32x2 lo, hi;
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(addr), "i"(imm));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(addr), "i"(imm + 16 * BM * 2));
+        const u32x4 v = {lo[0], lo[1], hi[0], hi[1]};
+        return __builtin_bit_cast(x8<E>, v);
+    };
+    const int lds_base = (int)(uintptr_t)(lds_ptr)smem_raw;
+    static_assert(!TN || (WM == 128 && WN == 128), "8 segments per wavefront");
     // operand f of step s (f < FN: B block f, else A block f - FN) of the tile whose A operand is in slot qa
     auto load_frag = [&](int s, int qa, int f) {
+        if constexpr (TN) {
+            const int step = s * 32 * BM * 2;
+            if (f < FN) bf[s][f] = tr_read(lds_base + tn_lane(wn, f) + wrap(qa + 1) * (kSlotElems * 2), step);
+            else af[s][f - FN] = tr_read(lds_base + tn_lane(wm, f - FN) + qa * (kSlotElems * 2), step);
+            return;
+        }
         if (f < FN) {
             const int vb = (lane_b ^ (s << 6)) + wrap(qa + 1) * (kSlotElems * 2);
             bf[s][f] = *reinterpret_cast<const x8<E> *>(smem_raw + vb + f * 16 * BK * 2);
@@ -536,13 +578,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
     //    address arithmetic per read;
     //  - the direct-to-LDS loads use one buffer resource per operand for the whole tile and take the k position from
     //    a scalar offset that advances once per k tile; the LDS destination is a constant.
-    int pa[2][3], pb[2][3];
+    // (TN: the swizzle makes one lane address per block, 48 registers.)
+    constexpr int kLanes = TN ? FM : 2;
+    int pa[kLanes][3], pb[kLanes][3];
 #pragma unroll
-    for (int v = 0; v < 2; ++v)
+    for (int v = 0; v < kLanes; ++v)
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
-            pa[v][r] = (lane_a ^ (v << 6)) + r * 65536;
-            pb[v][r] = (lane_b ^ (v << 6)) + r * 65536;
+            pa[v][r] = (TN ? lds_base + tn_lane(wm, v) : lane_a ^ (v << 6)) + r * 65536;
+            pb[v][r] = (TN ? lds_base + tn_lane(wn, v) : lane_b ^ (v << 6)) + r * 65536;
             // opaque to the compiler, which would otherwise fold the range into each read's offset and add it back
             // with a VALU instruction per read
             asm volatile("" : "+v"(pa[v][r]), "+v"(pb[v][r]));
@@ -550,16 +594,29 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
     auto load_frag_c = [&](int s, int qa, int f) {           // qa: a constant at every call
         const bool is_b = f < FN;
         const int blk = is_b ? f : f - FN;
+        if constexpr (TN) {
+            const int at = (is_b ? wrap(qa + 1) : qa) * (kSlotElems * 2) + s * 32 * BM * 2;
+            const x8<E> v = tr_read(is_b ? pb[blk][at >> 16] : pa[blk][at >> 16], at & 0xFFFF);
+            if (is_b) bf[s][blk] = v;
+            else af[s][blk] = v;
+            return;
+        }
         const int off = (is_b ? wrap(qa + 1) : qa) * (kSlotElems * 2) + blk * 16 * BK * 2;      // below 160 KB
         const unsigned char *src = smem_raw + (is_b ? pb[s][off >> 16] : pa[s][off >> 16]) + (off & 0xFFFF);
         if (is_b) bf[s][blk] = *reinterpret_cast<const x8<E> *>(src);
         else af[s][blk] = *reinterpret_cast<const x8<E> *>(src);
     };
     const __amdgpu_buffer_rsrc_t rsA = make_rsrc(a_ptr), rsB = make_rsrc(b_ptr);
+    // TN: where k tile kt + 2 of the main loop begins; a tile's rows reach too far for a scalar offset, so each tile has its resource
+    const E *a_run = a_ptr + 2 * a_step, *b_run = b_ptr + 2 * b_step;
     // DMA instruction i of a full k tile of A or B into (constant) ring slot q; koff: byte offset of the k tile in a row
     auto dma_c = [&](bool is_a, int q, int koff, int i) {
         // (two calls: the host pass of the compiler does not take a conditional expression of the resource type)
         const int vo = is_a ? offA[i] : offB[i];
+        if constexpr (TN) {
+            lds_dma(make_rsrc(is_a ? a_run : b_run), q, i, vo, 0);
+            return;
+        }
         if (is_a) lds_dma(rsA, q, i, vo, koff);
         else lds_dma(rsB, q, i, vo, koff);
     };
@@ -587,6 +644,19 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
         load_frag(0, 0, f);
         load_frag(1, 0, f);
     }
+    // TN: names operands that a wait before it has made valid: A blocks g0 .. g0 + 3 of both steps, B block j of both steps
+    auto got_a = [&](int g0) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(af[0][g0]), "+v"(af[1][g0]), "+v"(af[0][g0 + 1]), "+v"(af[1][g0 + 1]), "+v"(af[0][g0 + 2]), "+v"(af[1][g0 + 2]),
+                          "+v"(af[0][g0 + 3]), "+v"(af[1][g0 + 3]));
+    };
+    auto got_b = [&](int j) __attribute__((always_inline)) { asm volatile("" : "+v"(bf[0][j]), "+v"(bf[1][j])); };
+    auto wait_first_half = [&]() __attribute__((always_inline)) {       // what half 0 multiplies, when fewer reads follow it than in the main loop
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        got_a(0);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) got_b(j);
+    };
+    if constexpr (TN) wait_first_half();
 
     // Half h of a k tile: A blocks g = 4 h .. 4 h + 3 against all B blocks, column by column (j outer, g inner), and
     // for each block its two products in a row on the same accumulator.  Measured on register operands, a second
@@ -611,6 +681,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
 #pragma unroll
         for (int pr = 0; pr < 4 * FN; ++pr) {
             const int j = pr >> 2, g = 4 * h + (pr & 3);
+            if constexpr (TN && LEAN) {
+                // at least 20 reads were issued after those of this column's B block and of the A blocks, and they return in order
+                if (h == 0 && (pr & 3) == 0) {
+                    asm volatile("s_waitcnt lgkmcnt(14)" ::: "memory");
+                    if (j == 0) got_a(0);
+                    got_b(j);
+                }
+            }
             mfma_16x16x32_acc<E>(bf[0][j], af[0][g], acc[g][j]);
             mfma_16x16x32_acc<E>(bf[1][j], af[1][g], acc[g][j]);
             if ((pr & 3) == 0 && do_dma) {
@@ -647,6 +725,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
         const int krem2 = STRAIGHT ? BK : p.K - (kt + 2) * BK;
         const int qa1 = wrap(qa + 2), qa2 = wrap(qa + 4);      // A(kt+1), A(kt+2); B(kt+2) goes to qa
 
+        if constexpr (TN) wait_first_half();
         half(std::false_type{}, 0, more2, true, qa2, kt + 2, krem2, true, FM / 2, false, qa);
         // A bare s_barrier: __syncthreads() would add a fence that waits for every load, A(kt+2)'s included.
         // The LDS reads above must have returned before other wavefronts may overwrite those slots.
@@ -657,6 +736,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
+        if constexpr (TN) got_a(FM / 2);
         __builtin_amdgcn_sched_barrier(0);
         half(std::false_type{}, 1, more2, false, qa, kt + 2, krem2, more1, 0, more1, qa1);
     };
@@ -669,8 +749,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
+        if constexpr (TN) got_a(FM / 2);
         __builtin_amdgcn_sched_barrier(0);
         half(std::true_type{}, 1, true, false, qa, koff2, BK, true, 0, true, qa1);
+        if constexpr (TN) {
+            a_run += a_step;
+            b_run += b_step;
+        }
     };
     int kt = 0, qa = 0;
     // Main loop, unrolled over one period of the ring (five k tiles; the slot of A(kt) is 0, 2, 4, 1, 3, 0, ...).
@@ -690,6 +775,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
     // the accumulators' last updates must have left the matrix pipe before anything else reads them (see
     // mfma_16x16x32_acc): twice the longest wait the instruction set asks for after a matrix instruction
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    if constexpr (TN) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // (the last tile left no read behind)
 
     if constexpr (EPI != EPI_ACCUM_F32) {
         // bf16 outputs: a lane holds 4 consecutive n of 64 different (row, column group) places, so storing from
@@ -779,25 +865,27 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
 
 // Explicit instantiations: the host compiler does not always emit the launch stub of a kernel template from its use
 // in the launchers below alone.
-#define LGA_INSTANTIATE_DMA(EPI)                                                                                 \
-    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, bf16>(GemmParams<bf16>, int, int);        \
-    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, f16>(GemmParams<f16>, int, int)
-LGA_INSTANTIATE_DMA(EPI_STORE);
-LGA_INSTANTIATE_DMA(EPI_BIAS);
-LGA_INSTANTIATE_DMA(EPI_BIAS_RESID);
-LGA_INSTANTIATE_DMA(EPI_BIAS_GELU);
-LGA_INSTANTIATE_DMA(EPI_MUL_DGELU);
-LGA_INSTANTIATE_DMA(EPI_ACCUM_F32);
+#define LGA_INSTANTIATE_DMA(EPI, ...)                                                                                       \
+    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, bf16, __VA_ARGS__>(GemmParams<bf16>, int, int);     \
+    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, f16, __VA_ARGS__>(GemmParams<f16>, int, int)
+LGA_INSTANTIATE_DMA(EPI_STORE, false);
+LGA_INSTANTIATE_DMA(EPI_BIAS, false);
+LGA_INSTANTIATE_DMA(EPI_BIAS_RESID, false);
+LGA_INSTANTIATE_DMA(EPI_BIAS_GELU, false);
+LGA_INSTANTIATE_DMA(EPI_MUL_DGELU, false);
+LGA_INSTANTIATE_DMA(EPI_ACCUM_F32, false);
+LGA_INSTANTIATE_DMA(EPI_ACCUM_F32, true);
 #undef LGA_INSTANTIATE_DMA
 
 // The kernel that serves a (tile size, layout, epilogue) combination and its dynamic LDS in bytes.
-template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E> struct KernelFor {
-    static constexpr bool kDma = A_KM && B_KM;
+template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E, bool DMA = A_KM && B_KM> struct KernelFor {
+    static constexpr bool kDma = DMA;
+    static_assert(!kDma || A_KM == B_KM, "both operands k-contiguous, or neither");
     static_assert(!kDma || BM == 256, "smaller k-contiguous problems: gemm_small.hip");
     static constexpr size_t smem = kDma ? (size_t)5 * BM * BK * sizeof(E)            // the DMA kernel's operand ring
                                         : (size_t)2 * (BM + BN) * BK * sizeof(E);    // two stages of both operands
     static auto get() -> void (*)(GemmParams<E>, int, int) {
-        if constexpr (kDma) return gemm_bf16_dma_kernel<BM, BN, 2, 2, EPI, E>;
+        if constexpr (kDma) return gemm_bf16_dma_kernel<BM, BN, 2, 2, EPI, E, !A_KM>;
         else return gemm_bf16_kernel<BM, BN, A_KM, B_KM, EPI, E>;
     }
     // up to 160 KB of dynamic LDS: more than a launch may ask for by default
@@ -806,15 +894,16 @@ template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E> struct KernelF
     }
 };
 
-template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E>
+template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E, bool DMA = A_KM && B_KM>
 void launch_one(const GemmParams<E> &p, hipStream_t s) {
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-    const size_t smem = KernelFor<BM, BN, A_KM, B_KM, EPI, E>::smem;
-    void (*kern)(GemmParams<E>, int, int) = KernelFor<BM, BN, A_KM, B_KM, EPI, E>::get();
+    using Kernel = KernelFor<BM, BN, A_KM, B_KM, EPI, E, DMA>;
+    const size_t smem = Kernel::smem;
+    void (*kern)(GemmParams<E>, int, int) = Kernel::get();
     char name[96];
     const char *et = std::is_same<E, bf16>::value ? "bf16" : "f16";       // profile names: gemm_bf16_... or gemm_f16_...
-    if (A_KM && B_KM)
-        snprintf(name, sizeof(name), "gemm_%s_dma_kernel<%d, %d, %d>", et, BM, BN, EPI);
+    if (DMA)
+        snprintf(name, sizeof(name), "gemm_%s_dma%s_kernel<%d, %d, %d>", et, A_KM ? "" : "_tn", BM, BN, EPI);
     else
         snprintf(name, sizeof(name), "gemm_%s_kernel<%d, %d, %s, %s, %d>", et, BM, BN, A_KM ? "true" : "false",
                  B_KM ? "true" : "false", EPI);
@@ -846,6 +935,25 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
     }
 }
 
+// The slices in which the large-tile kernels run a weight gradient: 1 if its tiles alone are enough work, 0 if even slices are not
+// (see launch_tiles).
+template <class E> int large_tile_slices(const GemmParams<E> &p) {
+    const long big = (long)((p.M + 255) / 256) * ((p.N + 255) / 256);
+    const int slices = p.batch > 1 ? 1 : gemm_splitk_slices(p.M, p.N, p.K);
+    if (slices > 1 && big * slices >= 192 && p.partial && (size_t)slices * p.M * p.N <= p.partial_floats && p.N % 4 == 0 &&
+        p.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(p.outf) & 15) == 0)
+        return slices;
+    return big >= 128 ? 1 : 0;
+}
+
+template <bool A_KM, bool B_KM, int EPI, class E> void launch_slices(const GemmParams<E> &p, int slices, hipStream_t s) {
+    GemmParams<E> q = p;
+    q.kchunk = ((p.K + slices - 1) / slices + BK - 1) / BK * BK;
+    q.ksplit = (p.K + q.kchunk - 1) / q.kchunk;          // rounding the slice length up may have emptied the last ones
+    launch_one<256, 256, A_KM, B_KM, EPI, E, true>(q, s);
+    launch_splitk_reduce(p.partial, q.ksplit, p.outf, p.M, p.N, p.ldc, p.beta, s);
+}
+
 template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmParams<E> &p, hipStream_t s) {
     // Large tiles when they fill the 256 CUs at least about once (the direct-to-LDS kernel is so much faster per
     // tile that a partly idle second round still wins); smaller ones otherwise.
@@ -856,16 +964,8 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmPa
             // that run as separate work items of the large-tile kernel and are summed afterwards - where that gives at least
             // 192 work items: with fewer the small tiles are faster (768 x 768 x 8192, 72 items: 36 against 30 us;
             // 768 x 2304 x 8192, 216 items: 43 against 48; 1280 x 3840 x 2048, 150 items: 41 against 32).
-            const int slices = p.batch > 1 ? 1 : gemm_splitk_slices(p.M, p.N, p.K);
-            if (slices > 1 && big * slices >= 192 && p.partial && (size_t)slices * p.M * p.N <= p.partial_floats && p.N % 4 == 0 &&
-                p.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(p.outf) & 15) == 0) {
-                GemmParams<E> q = p;
-                q.kchunk = ((p.K + slices - 1) / slices + BK - 1) / BK * BK;
-                q.ksplit = (p.K + q.kchunk - 1) / q.kchunk;          // rounding the slice length up may have emptied the last ones
-                launch_one<256, 256, A_KM, B_KM, EPI, E>(q, s);
-                launch_splitk_reduce(p.partial, q.ksplit, p.outf, p.M, p.N, p.ldc, p.beta, s);
-                return;
-            }
+            const int slices = large_tile_slices(p);
+            if (slices > 1) return launch_slices<A_KM, B_KM, EPI, E>(p, slices, s);
         }
         // (the direct-to-LDS loads of the large-tile kernel want rows of at least 128 bytes: see its per-lane load offsets)
         const bool short_rows = p.lda < BK || p.ldb < BK;
@@ -882,6 +982,17 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmPa
         q.sblock = p.batch <= 1 && tm % 16 == 0 && tn % 16 == 0;     // + 1 % on the weight-gradient shapes of d = 12288
         launch_one<256, 256, A_KM, B_KM, EPI, E>(q, s);
     } else {
+        if constexpr (!A_KM && !B_KM && EPI == EPI_ACCUM_F32) {
+            // the direct-to-LDS kernel takes a weight gradient's operands as stored, by the same rule; its loads want rows of at
+            // least 512 bytes
+            const int slices = p.batch > 1 || p.lda < 256 || p.ldb < 256 ? 0 : large_tile_slices(p);
+            if (slices > 1) return launch_slices<A_KM, B_KM, EPI, E>(p, slices, s);
+            if (slices == 1) {
+                GemmParams<E> q = p;
+                q.sblock = (p.M + 255) / 256 % 16 == 0 && (p.N + 255) / 256 % 16 == 0;
+                return launch_one<256, 256, A_KM, B_KM, EPI, E, true>(q, s);
+            }
+        }
         const double pad256 = (double)big * 65536.0, pad128 = (double)((p.M + 127) / 128) * ((p.N + 127) / 128) * 16384.0;
         const bool large = p.batch > 1 ? big * p.batch >= 128 && pad256 <= 1.15 * pad128 : big >= 128;
         if (large) launch_one<256, 256, A_KM, B_KM, EPI, E>(p, s);
@@ -896,6 +1007,16 @@ void launch_splitk_reduce(const float *partial, int slices, float *out, int M, i
     const size_t quads = (size_t)M * (N / 4);
     const unsigned blocks = (unsigned)std::min<size_t>((quads + 255) / 256, 256 * 16);
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, s, partial, slices, (size_t)M * N, out, M, N, ldc, beta);
+}
+
+bool gemm_takes_stored_operands(int M, int N, int K) {
+    if (M < 256 || N < 256) return false;
+    GemmParams<bf16> p{};
+    p.M = M; p.N = N; p.K = K; p.ldc = N;
+    p.partial_floats = SIZE_MAX;                             // the caller provides as much as the slices need
+    float probe;
+    p.partial = &probe;                                      // (only tested against NULL)
+    return large_tile_slices(p) > 0;
 }
 
 int gemm_splitk_slices(int M, int N, int K) {
@@ -976,6 +1097,7 @@ template <class E> hipError_t raise_all() {
     next(raise_pair<true, true, EPI_ACCUM_F32, E>());
     next(raise_pair<false, false, EPI_STORE, E>());
     next(raise_pair<false, false, EPI_ACCUM_F32, E>());
+    next(KernelFor<256, 256, false, false, EPI_ACCUM_F32, E, true>::raise_lds_limit());
     return e;
 }
 }  // namespace

@@ -37,11 +37,25 @@ void launch_layernorm_fwd(const T *x, const float *g, const float *b, T *y, floa
 //   dbeta[c] = beta * dbeta[c] + sum_r dy[r, c],   dgamma[c] = beta * dgamma[c] + sum_r dy[r, c] xhat[r, c],
 // added up inside the same kernel where the width allows, by the column-sum kernels otherwise; partial then holds
 // layernorm_bwd_partial_floats(rows, d) floats.
+// batch != NULL: the second pass of those sums is left to the caller's launch_colsum_batch; partial must then stay untouched until it.
+struct ColsumJob {
+    const float *partial;      // [chunks][2][cols]
+    float *out0, *out1;        // out1 may be NULL
+    int chunks, cols, blocks;
+    float beta;
+};
+constexpr int kColsumBatch = 6;                            // four biases and two LayerNorms of a layer
+struct ColsumBatch {
+    ColsumJob job[kColsumBatch];
+    int n = 0;
+};
+void launch_colsum_batch(const ColsumBatch &batch, hipStream_t s, bool timed = true);
 size_t layernorm_bwd_partial_floats(int rows, int d);
 template <class T>
 void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const float *rstd, const float *g,
                              const T *resid, T *dx, int rows, int d, hipStream_t s, float beta = 0.f,
-                             float *dbeta = nullptr, float *dgamma = nullptr, float *partial = nullptr);
+                             float *dbeta = nullptr, float *dgamma = nullptr, float *partial = nullptr,
+                             ColsumBatch *batch = nullptr);
 
 // Column sums over rows, in two deterministic passes through `partial`:
 //   out0[c] = beta * out0[c] + sum_r a[r, c]
@@ -51,7 +65,16 @@ void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const f
 size_t colsum_partial_floats(int rows, int cols);
 template <class T>
 void launch_colsum(const T *a, const T *x, const float *mean, const float *rstd, int rows, int cols, int ld,
-                   float beta, float *out0, float *out1, float *partial, hipStream_t s, bool timed = true);
+                   float beta, float *out0, float *out1, float *partial, hipStream_t s, bool timed = true, ColsumBatch *batch = nullptr);
+// Up to four matrices in one launch per pass, each with partial sums of its own.
+template <class T> struct ColsumMatrix {
+    const T *a, *x;
+    const float *mean, *rstd;
+    float *out0, *out1, *partial;
+    int rows, cols, ld;
+};
+template <class T>
+void launch_colsums(const ColsumMatrix<T> *m, int n, float beta, hipStream_t s, bool timed = true, ColsumBatch *batch = nullptr);
 
 // out[c][r] = in[r][c] for matrices of 16-bit elements of any format; R, C, ldi, ldo multiples of 8, 16-byte
 // aligned bases.
@@ -61,6 +84,22 @@ void launch_transpose16(const void *in, void *out, int R, int C, long ldi, long 
 template <class E>
 void launch_transpose16_colsum(const E *in, E *out, int R, int C, long ldi, long ldo, float beta, float *out0,
                                float *partial, hipStream_t s);
+
+// Up to four matrices in one launch; those with partial != NULL (colsum_partial_floats(R, C) floats) also leave the first pass of their
+// column sums (values of format E) there, whose second pass add_transposed_colsum adds to a batch.
+struct TransposeMatrix {
+    const void *in;
+    void *out;
+    float *partial;
+    long ldi, ldo;
+    int R, C, blocks;          // blocks: set by the launcher
+};
+struct TransposeBatch {
+    TransposeMatrix m[4];
+    int n;
+};
+template <class E> void launch_transposes(const TransposeMatrix *m, int n, hipStream_t s);
+void add_transposed_colsum(ColsumBatch &batch, const float *partial, int R, int C, float beta, float *out0);
 
 // 1 into *flag if any of the n values is infinite or not a number (*flag is not cleared here).
 void launch_nonfinite_flag(const float *g, size_t n, int *flag, hipStream_t s);
@@ -98,6 +137,9 @@ void launch_splitk_reduce(const float *partial, int slices, float *out, int M, i
 // too few 256 x 256 tiles to occupy the chip (1 = not at all); it then needs slices * M * N floats of scratch.
 // k = 0 asks for the largest count any k would give (for sizing the scratch).
 int gemm_splitk_slices(int M, int N, int K);
+// Whether a weight gradient of this size runs on the large-tile kernel, which takes both operands as stored ([K][ld], ld >= 256);
+// true for every larger K then, too.  The 16-bit kernels for smaller ones want them k-contiguous.
+bool gemm_takes_stored_operands(int M, int N, int K);
 
 // ---- causal attention --------------------------------------------------------------------
 // qkv: [tokens, 3 d] with columns [Q | K | V], head h at columns h*dh inside each third; tokens =

@@ -398,15 +398,32 @@ __global__ __launch_bounds__(TH) void layernorm_bwd_dx_rows_kernel(const T *__re
 // strip of 32*V columns into partial[row_chunk][2][cols].
 constexpr int kColsumRows = 128;
 
+// The matrices of one launch of the first pass (a matrix per bias of a layer: four).
+template <class T> struct ColsumInput {
+    const T *a, *x;
+    const float *mean, *rstd;
+    float *partial;
+    int rows, cols, ld, blocks;
+};
+template <class T> struct ColsumInputs {
+    ColsumInput<T> m[4];
+    int n;
+};
+
 template <class T, int V, bool WITH_XHAT>
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const T *__restrict__ a, const T *__restrict__ x,
-                                                             const float *__restrict__ mean,
-                                                             const float *__restrict__ rstd, int rows, int cols,
-                                                             int ld, float *__restrict__ partial) {
+__global__ __launch_bounds__(256) void colsum_partial_kernel(ColsumInputs<T> in) {
     __shared__ float red[2][8][32 * V + 1];
+    // workgroup -> (matrix, 128-row chunk, 32 V columns), columns fastest
+    int n = 0, block = blockIdx.x;
+    while (n + 1 < in.n && block >= in.m[n].blocks) block -= in.m[n++].blocks;
+    const T *__restrict__ a = in.m[n].a, *__restrict__ x = in.m[n].x;
+    const float *__restrict__ mean = in.m[n].mean, *__restrict__ rstd = in.m[n].rstd;
+    const int rows = in.m[n].rows, cols = in.m[n].cols, ld = in.m[n].ld;
+    float *__restrict__ partial = in.m[n].partial;
+    const int across = (cols + 32 * V - 1) / (32 * V), bx = block % across, by = block / across;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int c0 = (blockIdx.x * 32 + tx) * V;
-    const int r0 = blockIdx.y * kColsumRows;
+    const int c0 = (bx * 32 + tx) * V;
+    const int r0 = by * kColsumRows;
     const int r1 = min(rows, r0 + kColsumRows);
     float s0[V], s1[V];
 #pragma unroll
@@ -433,7 +450,7 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T *__restrict
     }
     __syncthreads();
     for (int j = threadIdx.x; j < 32 * V; j += 256) {
-        const int c = blockIdx.x * 32 * V + j;
+        const int c = bx * 32 * V + j;
         if (c >= cols) continue;
         float t0 = 0.f, t1 = 0.f;
 #pragma unroll
@@ -441,53 +458,76 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T *__restrict
             t0 += red[0][k][j];
             t1 += red[1][k][j];
         }
-        partial[((size_t)blockIdx.y * 2 + 0) * cols + c] = t0;
-        if constexpr (WITH_XHAT) partial[((size_t)blockIdx.y * 2 + 1) * cols + c] = t1;
+        partial[((size_t)by * 2 + 0) * cols + c] = t0;
+        if constexpr (WITH_XHAT) partial[((size_t)by * 2 + 1) * cols + c] = t1;
     }
 }
 
-// Pass 2: block = 32 columns x 32 groups of row chunks (group q adds chunks q, q + 32, ... in that order), combined
-// through LDS in group order, so the result does not depend on scheduling.  Many groups and four loads in flight per
-// thread: with the partial rows of a kernel that writes one per block (up to 4096) a thread's chain of dependent adds
-// is what this pass takes, not its bytes.
-constexpr int kFinalCols = 32, kFinalGroups = 32;
+// Pass 2, for up to kColsumBatch sums in one launch (the four biases and two LayerNorms of a layer).  Block = 32 columns x 32 V
+// groups of row chunks, a thread V columns of them: group q adds chunks q, q + 32 V, ... in that order, combined through LDS in group
+// order, so the result does not depend on scheduling.  With the partial rows of a kernel that writes one per block (up to 4096)
+// a thread's chain of dependent loads and adds is what this pass takes, not its bytes: hence many groups, and eight rows in
+// flight per thread.
+constexpr int kFinalCols = 32, kFinalThreads = 1024;
 
-__global__ __launch_bounds__(kFinalCols * kFinalGroups) void colsum_final_kernel(const float *__restrict__ partial, int chunks,
-                                                                                 int cols, float beta, float *out0,
-                                                                                 float *out1) {
-    __shared__ float red[2][kFinalGroups][kFinalCols + 1];
-    const int tx = threadIdx.x % kFinalCols, q = threadIdx.x / kFinalCols;
-    const int c = blockIdx.x * kFinalCols + tx;
-    float t0 = 0.f, t1 = 0.f;
-    if (c < cols) {
-        int k = q;
-        for (; k + 3 * kFinalGroups < chunks; k += 4 * kFinalGroups) {
-            float a[4], b[4] = {0.f, 0.f, 0.f, 0.f};
+template <int V> __global__ __launch_bounds__(kFinalThreads) void colsum_final_kernel(ColsumBatch batch) {
+    constexpr int LANES = kFinalCols / V, GROUPS = kFinalThreads / LANES;
+    __shared__ float red[2][GROUPS][kFinalCols + 1];
+    int n = 0, block = blockIdx.x;
+    while (n + 1 < batch.n && block >= batch.job[n].blocks) block -= batch.job[n++].blocks;
+    const ColsumJob &job = batch.job[n];
+    const int chunks = job.chunks, cols = job.cols;
+    const bool two = job.out1 != nullptr;
+    typedef float vec __attribute__((ext_vector_type(V)));
+    {
+        const int tx = threadIdx.x % LANES, q = threadIdx.x / LANES;
+        const int c = block * kFinalCols + tx * V;
+        vec t0 = 0.f, t1 = 0.f;
+        if (c < cols) {
+            const float *row = job.partial + (size_t)q * 2 * cols + c;      // chunk q; the next of the group lies `step` further
+            const size_t step = (size_t)GROUPS * 2 * cols;
+            for (int k = q; k < chunks; k += 8 * GROUPS, row += 8 * step) {
+                vec a[8], b[8];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                a[j] = partial[((size_t)(k + j * kFinalGroups) * 2 + 0) * cols + c];
-                if (out1) b[j] = partial[((size_t)(k + j * kFinalGroups) * 2 + 1) * cols + c];
-            }
+                for (int i = 0; i < 8; ++i) {
+                    const bool there = k + i * GROUPS < chunks;
+                    a[i] = there ? *reinterpret_cast<const vec *>(row + i * step) : (vec)0.f;
+                    b[i] = there && two ? *reinterpret_cast<const vec *>(row + i * step + cols) : (vec)0.f;
+                }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                t0 += a[j];
-                t1 += b[j];
+                for (int i = 0; i < 8; ++i) {
+                    t0 += a[i];
+                    t1 += b[i];
+                }
             }
         }
-        for (; k < chunks; k += kFinalGroups) {
-            t0 += partial[((size_t)k * 2 + 0) * cols + c];
-            if (out1) t1 += partial[((size_t)k * 2 + 1) * cols + c];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            red[0][q][tx * V + v] = t0[v];
+            red[1][q][tx * V + v] = t1[v];
         }
     }
-    red[0][q][tx] = t0;
-    red[1][q][tx] = t1;
     __syncthreads();
-    if (q < 2 && c < cols && (q == 0 || out1)) {
+    const int tx = threadIdx.x % kFinalCols, q = threadIdx.x / kFinalCols;
+    if constexpr (V > 1) {                                                  // 32 V groups to 32
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            s0 += red[0][q * V + i][tx];
+            s1 += red[1][q * V + i][tx];
+        }
+        __syncthreads();
+        red[0][q][tx] = s0;
+        red[1][q][tx] = s1;
+        __syncthreads();
+    }
+    const int c = block * kFinalCols + tx;
+    if (q < 2 && c < cols && (q == 0 || two)) {
         float t = 0.f;
 #pragma unroll
-        for (int j = 0; j < kFinalGroups; ++j) t += red[q][j][tx];
-        float *o = q == 0 ? out0 : out1;
-        o[c] = (beta == 0.f ? 0.f : beta * o[c]) + t;
+        for (int i = 0; i < 32; ++i) t += red[q][i][tx];
+        float *o = q == 0 ? job.out0 : job.out1;
+        o[c] = (job.beta == 0.f ? 0.f : job.beta * o[c]) + t;
     }
 }
 
@@ -549,15 +589,22 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ w, float 
 constexpr int kTrTile = 128;
 constexpr int kTrPitch = kTrTile + 8;     // elements; keeps 16-byte alignment and skews the banks
 
-// SUM: the block also adds up its 128 rows of every column it moves (as values of format E, in fp32) and writes them
-// to partial[blockIdx.y][0][c] - the first pass of the column sums (colsum_partial_kernel's layout, same 128-row
-// chunks), so that the bias gradient costs no pass of its own over a matrix that is being transposed anyway.
-template <class E, bool SUM>
-__global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out,
-                                                          int R, int C, long ldi, long ldo, float *__restrict__ partial) {
+// One launch moves up to four matrices (the two operands of a weight gradient; the four weight matrices of a layer): launched one by
+// one, a narrow layer's each take their 4 us.  With partial given the block also adds up its 128 rows of every column it moves
+// (as values of format E, in fp32) and writes them to partial[row chunk][0][c] - the first pass of the column sums
+// (colsum_partial_kernel's layout, same 128-row chunks), so that the bias gradient costs no pass of its own over a matrix that is being transposed anyway.
+template <class E> __global__ __launch_bounds__(256) void transpose16_kernel(TransposeBatch batch) {
     static_assert(kTrTile == kColsumRows, "one transposed tile = one chunk of rows of the column sums");
     __shared__ __attribute__((aligned(16))) uint16_t tile[kTrTile * kTrPitch];     // [c][r]
-    const int r0 = blockIdx.y * kTrTile, c0 = blockIdx.x * kTrTile;
+    int n = 0, block = blockIdx.x;
+    while (n + 1 < batch.n && block >= batch.m[n].blocks) block -= batch.m[n++].blocks;
+    const uint16_t *__restrict__ in = static_cast<const uint16_t *>(batch.m[n].in);
+    uint16_t *__restrict__ out = static_cast<uint16_t *>(batch.m[n].out);
+    const int R = batch.m[n].R, C = batch.m[n].C;
+    const long ldi = batch.m[n].ldi, ldo = batch.m[n].ldo;
+    float *__restrict__ partial = batch.m[n].partial;
+    const int across = (C + kTrTile - 1) / kTrTile, by = block / across;
+    const int r0 = by * kTrTile, c0 = block % across * kTrTile;
     const int tid = threadIdx.x;
     {
         const int cb = tid & 15, rb = tid >> 4;           // 16 x 16 blocks of 8 x 8
@@ -587,7 +634,7 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t *__rest
         const int gc = c0 + c, gr = r0 + rch * 8;
         const u32x4 piece = *reinterpret_cast<const u32x4 *>(tile + c * kTrPitch + rch * 8);
         if (gc < C && gr < R) *reinterpret_cast<u32x4 *>(out + (size_t)gc * ldo + gr) = piece;
-        if constexpr (SUM) {
+        if (partial) {
             // rows beyond R were staged as zeros; the 16 lanes that hold column c's 128 rows are neighbours
             float sum = 0.f;
 #pragma unroll
@@ -598,7 +645,7 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t *__rest
             }
 #pragma unroll
             for (int m = 8; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 16);
-            if (rch == 0 && gc < C) partial[((size_t)blockIdx.y * 2 + 0) * C + gc] = sum;
+            if (rch == 0 && gc < C) partial[((size_t)by * 2 + 0) * C + gc] = sum;
         }
     }
 }
@@ -682,10 +729,39 @@ size_t layernorm_bwd_partial_floats(int rows, int d) {
     return std::max(fused, colsum_partial_floats(rows, d));
 }
 
+void launch_colsum_batch(const ColsumBatch &batch, hipStream_t s, bool timed) {
+    if (batch.n == 0) return;
+    int blocks = 0;
+    double bytes = 0.0;
+    for (int i = 0; i < batch.n; ++i) {
+        blocks += batch.job[i].blocks;
+        bytes += (batch.job[i].out1 ? 8.0 : 4.0) * batch.job[i].chunks * batch.job[i].cols;
+    }
+    ProfScope scope("colsum_final_kernel", 0.25 * bytes, bytes, s, timed);
+    bool vec = true;
+    for (int i = 0; i < batch.n; ++i) vec &= batch.job[i].cols % 4 == 0 && aligned16(batch.job[i].partial);
+    if (vec) hipLaunchKernelGGL(colsum_final_kernel<4>, dim3((unsigned)blocks), dim3(kFinalThreads), 0, s, batch);
+    else hipLaunchKernelGGL(colsum_final_kernel<1>, dim3((unsigned)blocks), dim3(kFinalThreads), 0, s, batch);
+}
+
+// The second pass of one sum: with the caller's others, or at once.
+static void finish_colsum(ColsumBatch *batch, const float *partial, int chunks, int cols, float beta, float *out0, float *out1, hipStream_t s,
+                          bool timed = true) {
+    const ColsumJob job{partial, out0, out1, chunks, cols, (cols + kFinalCols - 1) / kFinalCols, beta};
+    if (batch) {
+        batch->job[batch->n++] = job;
+        return;
+    }
+    ColsumBatch one;
+    one.job[0] = job;
+    one.n = 1;
+    launch_colsum_batch(one, s, timed);
+}
+
 template <class T>
 void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const float *rstd, const float *g,
                              const T *resid, T *dx, int rows, int d, hipStream_t s, float beta, float *dbeta,
-                             float *dgamma, float *partial) {
+                             float *dgamma, float *partial, ColsumBatch *batch) {
     constexpr int V = VecOf<T>::N;
     const bool sums = dbeta != nullptr;
     const bool vec = d % V == 0 && aligned16(dy) && aligned16(x) && aligned16(resid) && aligned16(dx);
@@ -693,7 +769,7 @@ void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const f
     // the sums ride along where a thread holds one piece of a row (d <= 1024 V): with two, their 4 V extra registers
     // per thread do not fit beside the row
     const bool fused = sums && rows_kernel && d <= 1024 * V && rows > 0 && aligned16(partial);
-    if (sums && !fused) launch_colsum<T>(dy, x, mean, rstd, rows, d, d, beta, dbeta, dgamma, partial, s);
+    if (sums && !fused) launch_colsum<T>(dy, x, mean, rstd, rows, d, d, beta, dbeta, dgamma, partial, s, true, batch);
     if (rows == 0) return;
     {
         ProfScope scope(fused ? "layernorm_bwd_dx_kernel(with sums)" : "layernorm_bwd_dx_kernel", (fused ? 18.0 : 14.0) * rows * d,
@@ -714,18 +790,16 @@ void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const f
         else
             hipLaunchKernelGGL((layernorm_bwd_dx_kernel<T, 1>), dim3(rows), dim3(256), 0, s, dy, x, mean, rstd, g, resid,
                                dx, d);
-        if (fused)
-            hipLaunchKernelGGL(colsum_final_kernel, dim3((d + kFinalCols - 1) / kFinalCols), dim3(kFinalCols * kFinalGroups), 0, s, partial, blocks, d, beta, dbeta,
-                               dgamma);
     }
+    if (fused) finish_colsum(batch, partial, lnb_rows_blocks(rows, d, V), d, beta, dbeta, dgamma, s);
 }
 template void launch_layernorm_bwd_dx<float>(const float *, const float *, const float *, const float *,
                                              const float *, const float *, float *, int, int, hipStream_t, float,
-                                             float *, float *, float *);
+                                             float *, float *, float *, ColsumBatch *);
 template void launch_layernorm_bwd_dx<bf16>(const bf16 *, const bf16 *, const float *, const float *, const float *,
-                                            const bf16 *, bf16 *, int, int, hipStream_t, float, float *, float *, float *);
+                                            const bf16 *, bf16 *, int, int, hipStream_t, float, float *, float *, float *, ColsumBatch *);
 template void launch_layernorm_bwd_dx<f16>(const f16 *, const f16 *, const float *, const float *, const float *,
-                                            const f16 *, f16 *, int, int, hipStream_t, float, float *, float *, float *);
+                                            const f16 *, f16 *, int, int, hipStream_t, float, float *, float *, float *, ColsumBatch *);
 
 size_t colsum_partial_floats(int rows, int cols) {
     const size_t chunks = ((size_t)rows + kColsumRows - 1) / kColsumRows;
@@ -734,66 +808,89 @@ size_t colsum_partial_floats(int rows, int cols) {
 
 template <class T>
 void launch_colsum(const T *a, const T *x, const float *mean, const float *rstd, int rows, int cols, int ld,
-                   float beta, float *out0, float *out1, float *partial, hipStream_t s, bool timed) {
+                   float beta, float *out0, float *out1, float *partial, hipStream_t s, bool timed, ColsumBatch *batch) {
     if (cols == 0) return;
-    constexpr int VMAX = VecOf<T>::N;
-    ProfScope scope(out1 ? "colsum_kernels(with xhat)" : "colsum_kernels", (out1 ? 4.0 : 1.0) * rows * cols,
-                    (out1 ? 2.0 : 1.0) * sizeof(T) * rows * (double)cols, s, timed);
-    const int chunks = rows > 0 ? (rows + kColsumRows - 1) / kColsumRows : 0;
-    const bool vec = (cols % VMAX == 0) && (ld % VMAX == 0) && aligned16(a) && (x == nullptr || aligned16(x));
-    if (chunks > 0) {
-        if (vec) {
-            dim3 grid((cols + 32 * VMAX - 1) / (32 * VMAX), chunks);
-            if (out1)
-                hipLaunchKernelGGL((colsum_partial_kernel<T, VMAX, true>), grid, dim3(256), 0, s, a, x, mean, rstd,
-                                   rows, cols, ld, partial);
-            else
-                hipLaunchKernelGGL((colsum_partial_kernel<T, VMAX, false>), grid, dim3(256), 0, s, a, x, mean, rstd,
-                                   rows, cols, ld, partial);
-        } else {
-            dim3 grid((cols + 31) / 32, chunks);
-            if (out1)
-                hipLaunchKernelGGL((colsum_partial_kernel<T, 1, true>), grid, dim3(256), 0, s, a, x, mean, rstd, rows,
-                                   cols, ld, partial);
-            else
-                hipLaunchKernelGGL((colsum_partial_kernel<T, 1, false>), grid, dim3(256), 0, s, a, x, mean, rstd, rows,
-                                   cols, ld, partial);
-        }
-    }
-    hipLaunchKernelGGL(colsum_final_kernel, dim3((cols + kFinalCols - 1) / kFinalCols), dim3(kFinalCols * kFinalGroups), 0, s, partial, chunks, cols, beta,
-                       out0, out1);
+    const ColsumMatrix<T> m{a, x, mean, rstd, out0, out1, partial, rows, cols, ld};
+    launch_colsums<T>(&m, 1, beta, s, timed, batch);
 }
-template void launch_colsum<float>(const float *, const float *, const float *, const float *, int, int, int, float,
-                                   float *, float *, float *, hipStream_t, bool);
-template void launch_colsum<bf16>(const bf16 *, const bf16 *, const float *, const float *, int, int, int, float,
-                                  float *, float *, float *, hipStream_t, bool);
-template void launch_colsum<f16>(const f16 *, const f16 *, const float *, const float *, int, int, int, float,
-                                  float *, float *, float *, hipStream_t, bool);
+
+template <class T> void launch_colsums(const ColsumMatrix<T> *m, int n, float beta, hipStream_t s, bool timed, ColsumBatch *batch) {
+    constexpr int VMAX = VecOf<T>::N;
+    ColsumInputs<T> in{};
+    bool vec = true, xhat = false;
+    double elems = 0.0;
+    for (int i = 0; i < n; ++i) {
+        vec &= m[i].cols % VMAX == 0 && m[i].ld % VMAX == 0 && aligned16(m[i].a) && (m[i].x == nullptr || aligned16(m[i].x));
+        xhat |= m[i].out1 != nullptr;
+        elems += (double)m[i].rows * m[i].cols;
+    }
+    int blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        const int chunks = (m[i].rows + kColsumRows - 1) / kColsumRows, width = 32 * (vec ? VMAX : 1);
+        const int mine = chunks * ((m[i].cols + width - 1) / width);
+        if (mine > 0) in.m[in.n++] = {m[i].a, m[i].x, m[i].mean, m[i].rstd, m[i].partial, m[i].rows, m[i].cols, m[i].ld, mine};
+        blocks += mine;
+    }
+    if (blocks > 0) {
+        ProfScope scope(xhat ? "colsum_partial_kernel(with xhat)" : "colsum_partial_kernel", (xhat ? 4.0 : 1.0) * elems,
+                        (xhat ? 2.0 : 1.0) * sizeof(T) * elems, s, timed);
+        const dim3 grid((unsigned)blocks);
+        if (vec && xhat) hipLaunchKernelGGL((colsum_partial_kernel<T, VMAX, true>), grid, dim3(256), 0, s, in);
+        else if (vec) hipLaunchKernelGGL((colsum_partial_kernel<T, VMAX, false>), grid, dim3(256), 0, s, in);
+        else if (xhat) hipLaunchKernelGGL((colsum_partial_kernel<T, 1, true>), grid, dim3(256), 0, s, in);
+        else hipLaunchKernelGGL((colsum_partial_kernel<T, 1, false>), grid, dim3(256), 0, s, in);
+    }
+    for (int i = 0; i < n; ++i)
+        finish_colsum(batch, m[i].partial, m[i].rows > 0 ? (m[i].rows + kColsumRows - 1) / kColsumRows : 0, m[i].cols, beta, m[i].out0, m[i].out1, s, timed);
+}
+#define LGA_COLSUM(T)                                                                                                               \
+    template void launch_colsum<T>(const T *, const T *, const float *, const float *, int, int, int, float, float *, float *, \
+                                   float *, hipStream_t, bool, ColsumBatch *);                                                   \
+    template void launch_colsums<T>(const ColsumMatrix<T> *, int, float, hipStream_t, bool, ColsumBatch *)
+LGA_COLSUM(float);
+LGA_COLSUM(bf16);
+LGA_COLSUM(f16);
+#undef LGA_COLSUM
+
+template <class E> void launch_transposes(const TransposeMatrix *m, int n, hipStream_t s) {
+    TransposeBatch batch{};
+    int blocks = 0;
+    double elems = 0.0;
+    bool sums = false;
+    for (int i = 0; i < n; ++i) {
+        if (m[i].R == 0 || m[i].C == 0) continue;
+        batch.m[batch.n] = m[i];
+        batch.m[batch.n].blocks = ((m[i].C + kTrTile - 1) / kTrTile) * ((m[i].R + kTrTile - 1) / kTrTile);
+        blocks += batch.m[batch.n++].blocks;
+        elems += (double)m[i].R * m[i].C;
+        sums |= m[i].partial != nullptr;
+    }
+    if (blocks == 0) return;
+    ProfScope scope(sums ? "transpose16_kernel(with column sums)" : "transpose16_kernel", sums ? elems : 0.0, 4.0 * elems, s);
+    hipLaunchKernelGGL(transpose16_kernel<E>, dim3((unsigned)blocks), dim3(256), 0, s, batch);
+}
+template void launch_transposes<bf16>(const TransposeMatrix *, int, hipStream_t);
+template void launch_transposes<f16>(const TransposeMatrix *, int, hipStream_t);
 
 void launch_transpose16(const void *in, void *out, int R, int C, long ldi, long ldo, hipStream_t s) {
-    if (R == 0 || C == 0) return;
-    ProfScope scope("transpose16_kernel", 0.0, 4.0 * R * (double)C, s);
-    dim3 grid((C + kTrTile - 1) / kTrTile, (R + kTrTile - 1) / kTrTile);
-    hipLaunchKernelGGL((transpose16_kernel<bf16, false>), grid, dim3(256), 0, s, static_cast<const uint16_t *>(in),
-                       static_cast<uint16_t *>(out), R, C, ldi, ldo, (float *)nullptr);
+    const TransposeMatrix m{in, out, nullptr, ldi, ldo, R, C, 0};
+    launch_transposes<bf16>(&m, 1, s);
 }
 
 template <class E>
 void launch_transpose16_colsum(const E *in, E *out, int R, int C, long ldi, long ldo, float beta, float *out0,
                                float *partial, hipStream_t s) {
     if (C == 0) return;
-    ProfScope scope("transpose16_kernel(with column sums)", 1.0 * R * C, 4.0 * R * (double)C, s);
-    const int chunks = (R + kTrTile - 1) / kTrTile;
-    if (R > 0) {
-        dim3 grid((C + kTrTile - 1) / kTrTile, chunks);
-        hipLaunchKernelGGL((transpose16_kernel<E, true>), grid, dim3(256), 0, s, reinterpret_cast<const uint16_t *>(in),
-                           reinterpret_cast<uint16_t *>(out), R, C, ldi, ldo, partial);
-    }
-    hipLaunchKernelGGL(colsum_final_kernel, dim3((C + kFinalCols - 1) / kFinalCols), dim3(kFinalCols * kFinalGroups), 0, s, partial, chunks, C, beta, out0,
-                       (float *)nullptr);
+    const TransposeMatrix m{in, out, partial, ldi, ldo, R, C, 0};
+    launch_transposes<E>(&m, 1, s);
+    finish_colsum(nullptr, partial, (R + kTrTile - 1) / kTrTile, C, beta, out0, nullptr, s);
 }
 template void launch_transpose16_colsum<bf16>(const bf16 *, bf16 *, int, int, long, long, float, float *, float *, hipStream_t);
 template void launch_transpose16_colsum<f16>(const f16 *, f16 *, int, int, long, long, float, float *, float *, hipStream_t);
+
+void add_transposed_colsum(ColsumBatch &batch, const float *partial, int R, int C, float beta, float *out0) {
+    finish_colsum(&batch, partial, (R + kTrTile - 1) / kTrTile, C, beta, out0, nullptr, nullptr);
+}
 
 template <class E>
 void launch_adam(float *w, float *m, float *v, const float *g, E *w16, size_t n, float lr, float beta1, float beta2,

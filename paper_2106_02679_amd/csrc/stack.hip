@@ -144,12 +144,17 @@ int validate_config(const lga_config *c) {
 // Arena plan: one allocation, every sub-buffer 256-byte aligned.
 struct Plan {
     size_t w, m, v, grad, w16, w16t, ckpt, dact;
-    size_t xT[4], dyT[4];      // transposed operands of the four weight-gradient GEMMs (16-bit modes)
+    // The four weight-gradient GEMMs (W_2, W_1, W_o, W_qkv) of the 16-bit modes: stored[i] = it reads the activations and output gradients
+    // as the layer stores them, whose buffers then hold wgrad_groups groups; otherwise transposed copies of them, xT and dyT.
+    bool stored[4];
+    size_t xT[4], dyT[4];
     int wgrad_groups;          // groups whose tokens one weight-gradient GEMM contracts over
+    int dact_groups;           // groups in the ring that dact is where stored[0] (see ActivationGradient); 0: dact holds all groups, in place
     size_t ldk;                // row pitch (elements) of the transposed operands
     size_t ldf;                // row pitch (elements) of the d_ff-wide activations u, gl, du
     size_t h, qkv, a, x1, h2, u, gl, du, dh2, dx1, da, dqkv, dh;
-    size_t mean1, rstd1, mean2, rstd2, lse, delta, partial;
+    size_t mean1, rstd1, mean2, rstd2, lse, delta;
+    size_t partial[6];         // column sums' first passes: the biases of the four matrices, LayerNorm 2, LayerNorm 1
     size_t splitk, splitk_floats;   // partial results of weight-gradient GEMMs whose k range is split (narrow layers, fp32)
     size_t nonfinite;          // int per layer: the last checked Adam step found a non-finite gradient value
     size_t attn_ws, attn_ws_bytes;  // workspace of the GEMM-built attention (head sizes without a fused kernel)
@@ -174,45 +179,56 @@ Plan make_plan(const lga_config &c) {
     p.w16 = take(is16 ? nbuf * P * 2 : 0);
     p.w16t = take(is16 ? nbuf * P * 2 : 0);   // each matrix transposed, at its canonical offset
     p.ckpt = take((c.offload_checkpoints ? std::min<size_t>(2, L + 1) : L + 1) * T * d * esz);
-    p.dact = take(T * d * esz);
-    p.h = take(t * d * esz);
-    p.qkv = take(t * 3 * d * esz);
-    p.a = take(t * d * esz);
-    p.x1 = take(t * d * esz);
-    p.h2 = take(t * d * esz);
     // Rows of d_ff elements whose byte length is a multiple of 32 KB (d_ff = 49152: 96 KB) get a pitch 64 elements
     // longer: with the bare pitch the 256 rows of a GEMM operand tile start in few memory channels, and the two GEMMs
     // that contract over d_ff lose 7 % (1.50 against 1.61 PFLOP/s; 1 % of the step).  Measured without effect on rows
     // of 16 KB (d_ff = 8192), 6 KB and 200 KB, and on the d_model- and 3 d_model-wide rows of all configurations.
     p.ldf = (is16 && (f * esz) % 32768 == 0) ? f + 64 : f;
-    p.u = take(t * p.ldf * esz);
-    p.gl = take(t * p.ldf * esz);
-    p.du = take(t * p.ldf * esz);
-    p.dh2 = take(t * d * esz);
-    p.dx1 = take(t * d * esz);
-    p.da = take(t * d * esz);
-    p.dqkv = take(t * 3 * d * esz);
-    p.dh = take(t * d * esz);
-    // Transposed operands of the weight-gradient GEMMs: [in][ldk] copies of their inputs and [out][ldk]
-    // copies of their output gradients, wgrad_groups groups side by side along the token axis.  The pitch
-    // is padded by 64 elements: the unpadded one is a large power of two, which maps every row of an
-    // operand tile to the same memory channel.
     const size_t groups = (size_t)c.n_micro / c.group;
+    const int wg_in[4] = {(int)f, (int)d, (int)d, (int)d};          // W_2, W_1, W_o, W_qkv
+    const int wg_out[4] = {(int)d, (int)f, (int)d, (int)(3 * d)};
+    // Decided by one group's tokens: the merged GEMM of more of them runs on the large-tile kernel all the more.
+    for (int i = 0; i < 4; ++i) p.stored[i] = is16 && gemm_takes_stored_operands(wg_in[i], wg_out[i], (int)t);
+    auto take_activations = [&](size_t wb) {
+        const size_t n_2 = p.stored[0] ? wb : 1, n_1 = p.stored[1] ? wb : 1, n_o = p.stored[2] ? wb : 1, n_qkv = p.stored[3] ? wb : 1;
+        // (the d_ff-wide buffers' padding: as much as all groups need, so that it does not depend on wb)
+        const size_t pad = groups * t * (p.ldf - f) * esz;
+        p.dact_groups = p.stored[0] ? (int)(((groups + wb - 1) / wb + 1) * wb) : 0;
+        p.dact = take(p.dact_groups ? (size_t)p.dact_groups * t * d * esz : T * d * esz);
+        p.h = take(n_qkv * t * d * esz);
+        p.qkv = take(t * 3 * d * esz);
+        p.a = take(n_o * t * d * esz);
+        p.x1 = take(t * d * esz);
+        p.h2 = take(n_1 * t * d * esz);
+        p.u = take(t * p.ldf * esz);
+        p.gl = take(p.stored[0] ? n_2 * t * f * esz + pad : t * p.ldf * esz);
+        p.du = take(p.stored[1] ? n_1 * t * f * esz + pad : t * p.ldf * esz);
+        p.dh2 = take(t * d * esz);
+        p.dx1 = take(n_o * t * d * esz);
+        p.da = take(t * d * esz);
+        p.dqkv = take(n_qkv * t * 3 * d * esz);
+        p.dh = take(t * d * esz);
+    };
+    // Weight-gradient GEMMs over wgrad_groups groups.  Where they want transposed operands: [in][ldk] copies of their inputs and
+    // [out][ldk] copies of their output gradients, the groups side by side along the token axis.  The pitch is padded by
+    // 64 elements: the unpadded one is a large power of two, which maps every row of an operand tile to the same memory channel.
     const size_t rows = 2 * f + 8 * d;                      // in + out over the four matrices
     size_t wb = c.wgrad_groups ? (size_t)c.wgrad_groups : 1;
     if (is16 && c.wgrad_groups == 0) {
-        // automatic: as many groups as keep these buffers within a quarter of everything else
-        // ... and keep their row pitch within what the GEMM's loads can address
+        // automatic: as many groups as keep these operands within a quarter of everything else
+        // ... and keep the row pitch of transposed ones within what the GEMM's loads can address
+        const size_t before = off;
+        take_activations(1);
         wb = groups;
         while (wb > 1 && (rows * (wb * t + 64) * 2 > off / 4 || wb * t + 64 > (size_t)kGemmMaxLd)) --wb;
+        off = before;
     }
+    take_activations(wb);
     p.wgrad_groups = (int)wb;
     p.ldk = wb * t + 64;
-    const int wg_in[4] = {(int)f, (int)d, (int)d, (int)d};          // W_2, W_1, W_o, W_qkv
-    const int wg_out[4] = {(int)d, (int)f, (int)d, (int)(3 * d)};
     for (int i = 0; i < 4; ++i) {
-        p.xT[i] = take(is16 ? (size_t)wg_in[i] * p.ldk * 2 : 0);
-        p.dyT[i] = take(is16 ? (size_t)wg_out[i] * p.ldk * 2 : 0);
+        p.xT[i] = take(is16 && !p.stored[i] ? (size_t)wg_in[i] * p.ldk * 2 : 0);
+        p.dyT[i] = take(is16 && !p.stored[i] ? (size_t)wg_out[i] * p.ldk * 2 : 0);
     }
     p.splitk_floats = 0;
     for (int i = 0; i < 4; ++i) {
@@ -227,8 +243,8 @@ Plan make_plan(const lga_config &c) {
     const size_t stats = (size_t)c.group * c.micro_batch * c.n_heads * c.seq_len;
     p.lse = take(stats * 4);
     p.delta = take(stats * 4);
-    const size_t widest = std::max<size_t>(3 * d, f);
-    p.partial = take(std::max(colsum_partial_floats((int)t, (int)widest), layernorm_bwd_partial_floats((int)t, (int)c.d_model)) * 4);
+    for (int i = 0; i < 4; ++i) p.partial[i] = take(colsum_partial_floats((int)t, wg_out[i]) * 4);
+    for (int i = 4; i < 6; ++i) p.partial[i] = take(layernorm_bwd_partial_floats((int)t, (int)d) * 4);
     p.nonfinite = take(L * 4);          // one flag per layer, see lga_adam.skip_nonfinite
     // head sizes without a fused attention kernel: score matrices of as many heads of one sequence as fit 4 GiB
     p.attn_ws_bytes = 0;
@@ -319,10 +335,11 @@ void refresh_transposed_weights(lga_stack *st, int l, hipStream_t s) {
     const LayerLayout &o = st->lay;
     const uint16_t *w = st->w16(l);
     uint16_t *wt = st->w16t(l);
-    launch_transpose16(w + o.w_qkv, wt + o.w_qkv, d, 3 * d, 3 * d, d, s);
-    launch_transpose16(w + o.w_o, wt + o.w_o, d, d, d, d, s);
-    launch_transpose16(w + o.w_1, wt + o.w_1, d, f, f, d, s);
-    launch_transpose16(w + o.w_2, wt + o.w_2, f, d, d, f, s);
+    const TransposeMatrix m[4] = {{w + o.w_qkv, wt + o.w_qkv, nullptr, 3 * d, d, d, 3 * d, 0},
+                                  {w + o.w_o, wt + o.w_o, nullptr, d, d, d, d, 0},
+                                  {w + o.w_1, wt + o.w_1, nullptr, f, d, d, f, 0},
+                                  {w + o.w_2, wt + o.w_2, nullptr, d, f, f, d, 0}};
+    launch_transposes<bf16>(m, 4, s);
 }
 
 // ---- overlap mode plumbing -----------------------------------------------------------------------
@@ -428,20 +445,64 @@ void prefetch_weights(lga_stack *st, int next, int cur) {
     restore_weights(st, next);
 }
 
+// What the weight gradients of group `slot` of wgrad_groups are made of: with stored operands each group has its own place, one behind
+// the other, until one GEMM per matrix contracts over all of them.
+template <class T> struct WgradOperands {
+    T *h, *a, *h2, *gl, *du, *dx1, *dqkv;
+    WgradOperands(const lga_stack *st, int slot) {
+        const Plan &p = st->plan;
+        const size_t d = st->cfg.d_model, at = (size_t)slot * st->t;
+        auto place = [&](size_t off, size_t pitch, bool stored) { return st->at<T>(off) + (stored ? at * pitch : 0); };
+        gl = place(p.gl, p.ldf, p.stored[0]);
+        h2 = place(p.h2, d, p.stored[1]);
+        du = place(p.du, p.ldf, p.stored[1]);
+        a = place(p.a, d, p.stored[2]);
+        dx1 = place(p.dx1, d, p.stored[2]);
+        h = place(p.h, d, p.stored[3]);
+        dqkv = place(p.dqkv, 3 * d, p.stored[3]);
+    }
+};
+
+// The running activation gradient of all micro-batches during a sweep over the layers.  In place, a layer turns each group's gradient
+// with respect to its output into that with respect to its input - unless the W_2 gradient still wants the former of the groups it
+// merges: then dact is a ring of groups, and a layer writes wgrad_groups places before where it reads, which is
+// where it has finished (blocks of wgrad_groups groups start at multiples of it, so that a block's rows are one range).
+template <class T> struct ActivationGradient {
+    T *base;
+    size_t gstride;
+    int ring, wb, groups, first = 0;
+    explicit ActivationGradient(const lga_stack *st)
+        : base(st->at<T>(st->plan.dact)), gstride(st->t * st->cfg.d_model), ring(st->plan.dact_groups), wb(st->plan.wgrad_groups),
+          groups(st->cfg.n_micro / st->cfg.group) {}
+    T *in(int gi) const { return base + (size_t)(ring ? (first + gi) % ring : gi) * gstride; }
+    T *out(int gi) const { return base + (size_t)(ring ? (first + ring - wb + gi) % ring : gi) * gstride; }
+    void next_layer() { if (ring) first = (first + ring - wb) % ring; }
+    // all groups' gradients, in order, to dst: one copy, or two where the ring ends in between
+    hipError_t copy_to(void *dst, hipStream_t s) const {
+        const int head = ring ? std::min(groups, ring - first) : groups;
+        hipError_t e = hipMemcpyAsync(dst, in(0), (size_t)head * gstride * sizeof(T), hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess && head < groups)
+            e = hipMemcpyAsync(static_cast<T *>(dst) + (size_t)head * gstride, in(head), (size_t)(groups - head) * gstride * sizeof(T),
+                               hipMemcpyDeviceToDevice, s);
+        return e;
+    }
+};
+
 // Forward of layer l on one micro-batch group (paper section 5 "Model"; pre-LN residual form).
 // x_in: [t, d] group slice of the layer's input checkpoint.  y_out: group slice of the next
 // checkpoint, or NULL when this is the backward pass's recompute (the second feed-forward GEMM's
-// output is not needed there, so it is not recomputed).
-template <class T> void layer_forward(lga_stack *st, int l, const T *x_in, T *y_out) {
+// output is not needed there, so it is not recomputed).  slot: which of the wgrad_groups groups this is, in the buffers that hold
+// several for the weight gradients.
+template <class T> void layer_forward(lga_stack *st, int l, const T *x_in, T *y_out, int slot = 0) {
     const lga_config &c = st->cfg;
     const int d = c.d_model, f = c.d_ff, t = (int)st->t;
     const LayerLayout &o = st->lay;
     const float *pf = st->w(l);
     const T *pw = gemm_weights<T>(st, l);
     hipStream_t s = st->stream;
-    T *h = st->at<T>(st->plan.h), *qkv = st->at<T>(st->plan.qkv), *a = st->at<T>(st->plan.a);
-    T *x1 = st->at<T>(st->plan.x1), *h2 = st->at<T>(st->plan.h2), *u = st->at<T>(st->plan.u);
-    T *gl = st->at<T>(st->plan.gl);
+    const WgradOperands<T> op(st, slot);
+    T *h = op.h, *qkv = st->at<T>(st->plan.qkv), *a = op.a;
+    T *x1 = st->at<T>(st->plan.x1), *h2 = op.h2, *u = st->at<T>(st->plan.u), *gl = op.gl;
     float *lse = st->at<float>(st->plan.lse);
     const AttnShape ash{c.group * c.micro_batch, c.seq_len, c.n_heads, d / c.n_heads, c.attention == LGA_ATTN_CAUSAL};
 
@@ -486,69 +547,81 @@ template <class T> void layer_forward(lga_stack *st, int l, const T *x_in, T *y_
 struct GradStep {
     float beta;       // vectors (biases, LayerNorm): 0 for the layer's first group, then 1
     float beta_mat;   // matrices: 0 for the first weight-gradient GEMM of the layer, then 1
-    int slot;         // 16-bit modes: position of this group's tokens in the transposed operand buffers
+    int slot;         // 16-bit modes: position of this group's tokens among those of the merged GEMM
     bool flush;       // 16-bit modes: run the matrix GEMMs now, over slots 0..slot
 };
 
-// Backward of layer l on one group whose intermediates were just recomputed by layer_forward.
-// dy: [t, d] group slice of the running activation gradient, overwritten with dx.
+// Backward of layer l on one group whose intermediates were just recomputed by layer_forward, in the same slot.
+// dy: [t, d] gradient with respect to the layer's output, dx: with respect to its input (they may be the same).
 // gbuf: the layer's fp32 gradient buffer (canonical layout).
 //
 // The 16-bit modes merge the weight-gradient GEMMs of consecutive groups of a layer (possible because the
-// layered order visits all micro-batches of a layer back to back): each group only appends its
-// transposed operands, and one GEMM then contracts over all their tokens.  The accumulation over
-// micro-batches that the fp32 buffer would do by read-modify-write happens inside the GEMM's
-// k loop instead, so the buffer is touched once per merged GEMM rather than once per group.
-template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, T *dy, float *gbuf, GradStep gs) {
+// layered order visits all micro-batches of a layer back to back): each group only leaves its operands, and one GEMM
+// then contracts over all their tokens.  The accumulation over micro-batches that the fp32 buffer would do by
+// read-modify-write happens inside the GEMM's k loop instead, so the buffer is touched once per merged GEMM rather
+// than once per group.
+template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, const T *dy, T *dx, float *gbuf, GradStep gs) {
     const float beta = gs.beta;
     const lga_config &c = st->cfg;
+    const Plan &p = st->plan;
     const int d = c.d_model, f = c.d_ff, t = (int)st->t;
     const LayerLayout &o = st->lay;
     const float *pf = st->w(l);
     const T *pw = gemm_weights<T>(st, l);
     hipStream_t s = st->stream;
-    T *h = st->at<T>(st->plan.h), *qkv = st->at<T>(st->plan.qkv), *a = st->at<T>(st->plan.a);
-    T *x1 = st->at<T>(st->plan.x1), *h2 = st->at<T>(st->plan.h2), *u = st->at<T>(st->plan.u);
-    T *gl = st->at<T>(st->plan.gl), *du = st->at<T>(st->plan.du), *dh2 = st->at<T>(st->plan.dh2);
-    T *dx1 = st->at<T>(st->plan.dx1), *da = st->at<T>(st->plan.da), *dqkv = st->at<T>(st->plan.dqkv);
-    T *dh = st->at<T>(st->plan.dh);
-    float *mean1 = st->at<float>(st->plan.mean1), *rstd1 = st->at<float>(st->plan.rstd1);
-    float *mean2 = st->at<float>(st->plan.mean2), *rstd2 = st->at<float>(st->plan.rstd2);
-    float *lse = st->at<float>(st->plan.lse), *delta = st->at<float>(st->plan.delta);
-    float *partial = st->at<float>(st->plan.partial);
+    const WgradOperands<T> op(st, gs.slot);
+    T *h = op.h, *qkv = st->at<T>(p.qkv), *a = op.a;
+    T *x1 = st->at<T>(p.x1), *h2 = op.h2, *u = st->at<T>(p.u);
+    T *gl = op.gl, *du = op.du, *dh2 = st->at<T>(p.dh2);
+    T *dx1 = op.dx1, *da = st->at<T>(p.da), *dqkv = op.dqkv;
+    T *dh = st->at<T>(p.dh);
+    float *mean1 = st->at<float>(p.mean1), *rstd1 = st->at<float>(p.rstd1);
+    float *mean2 = st->at<float>(p.mean2), *rstd2 = st->at<float>(p.rstd2);
+    float *lse = st->at<float>(p.lse), *delta = st->at<float>(p.delta);
     const AttnShape ash{c.group * c.micro_batch, c.seq_len, c.n_heads, d / c.n_heads, c.attention == LGA_ATTN_CAUSAL};
+    // The layer's column sums - bias gradients and LayerNorm gains and biases - are finished together in one launch at the end, and
+    // the first passes of those bias gradients that come with no transpose together before dx is written.
+    ColsumBatch sums;
+    ColsumMatrix<T> biases[4];
+    int n_biases = 0;
 
-    // gW[in, out] (+)= X[t, in]^T dY[t, out], contracted over tokens.  The 16-bit modes first write X^T [in][.]
-    // and dY^T [out][.] (two HBM-bound passes, ~1 % of the GEMM's time) so that the GEMM reads both
-    // operands k-contiguous; `which` names the matrix's pair of transposed buffers.
-    const int ldf = (int)st->plan.ldf;                       // pitch of u, gl and du
+    // gW[in, out] (+)= X[t, in]^T dY[t, out], contracted over tokens.  The 16-bit modes' large-tile kernel takes both operands as they
+    // are; the kernels for smaller gradients read k-contiguous ones, X^T [in][.] and dY^T [out][.], written first.  `which` names the
+    // matrix in the plan.
+    const int ldf = (int)p.ldf;                              // pitch of u, gl and du
     // ldx, ldy: row pitches of X and dY where they differ from the widths
     auto wgrad = [&](int which, const T *X, int in, const T *dY, int out, size_t w_off, size_t b_off, int ldx = 0, int ldy = 0) {
         if (!ldx) ldx = in;
         if (!ldy) ldy = out;
+        float *partial = st->at<float>(p.partial[which]);
         GemmParams<T> g{};
         g.M = in; g.N = out;
         g.outf = gbuf + w_off; g.ldc = out;
+        g.partial = st->at<float>(p.splitk); g.partial_floats = p.splitk_floats;
         if constexpr (std::is_same<T, float>::value) {
             g.K = t; g.beta = beta;
             g.A = X; g.lda = ldx; g.B = dY; g.ldb = ldy;
-            g.partial = st->at<float>(st->plan.splitk); g.partial_floats = st->plan.splitk_floats;
             gemm<T>(g, false, false, EPI_ACCUM_F32, s);
         } else {
-            const int ldk = (int)st->plan.ldk;
-            T *xT = st->at<T>(st->plan.xT[which]), *dyT = st->at<T>(st->plan.dyT[which]);
-            launch_transpose16(X, xT + (size_t)gs.slot * t, t, in, ldx, ldk, s);
-            // the bias gradient is the column sum of dY: taken from the tiles as they are transposed
-            launch_transpose16_colsum<T>(dY, dyT + (size_t)gs.slot * t, t, out, ldy, ldk, beta, gbuf + b_off, partial, s);
-            if (gs.flush) {
-                g.K = (gs.slot + 1) * t; g.beta = gs.beta_mat;
+            g.K = (gs.slot + 1) * t; g.beta = gs.beta_mat;
+            if (p.stored[which]) {
+                const size_t before = (size_t)gs.slot * t;   // rows of the groups in the slots before this one
+                g.A = X - before * ldx; g.lda = ldx; g.B = dY - before * ldy; g.ldb = ldy;
+                if (gs.flush) gemm<T>(g, false, false, EPI_ACCUM_F32, s);
+            } else {
+                const int ldk = (int)p.ldk;
+                T *xT = st->at<T>(p.xT[which]), *dyT = st->at<T>(p.dyT[which]);
+                // the bias gradient is the column sum of dY: taken from the tiles as they are transposed
+                const TransposeMatrix m[2] = {{X, xT + (size_t)gs.slot * t, nullptr, ldx, ldk, t, in, 0},
+                                              {dY, dyT + (size_t)gs.slot * t, partial, ldy, ldk, t, out, 0}};
+                launch_transposes<T>(m, 2, s);
+                add_transposed_colsum(sums, partial, t, out, beta, gbuf + b_off);
                 g.A = xT; g.lda = ldk; g.B = dyT; g.ldb = ldk;
-                g.partial = st->at<float>(st->plan.splitk); g.partial_floats = st->plan.splitk_floats;
-                gemm<T>(g, true, true, EPI_ACCUM_F32, s);
+                if (gs.flush) gemm<T>(g, true, true, EPI_ACCUM_F32, s);
+                return;
             }
         }
-        if constexpr (std::is_same<T, float>::value)
-            launch_colsum<T>(dY, nullptr, nullptr, nullptr, t, out, ldy, beta, gbuf + b_off, nullptr, partial, s);
+        biases[n_biases++] = {dY, nullptr, nullptr, nullptr, gbuf + b_off, nullptr, partial, t, out, ldy};
     };
     // lda: row pitch of dY, ldc: of dX and aux, where they differ from the widths
     auto dgrad = [&](const T *dY, int out, size_t w_off, int in, T *dX, Epilogue e, const T *aux, int lda = 0, int ldc = 0) {
@@ -565,7 +638,8 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, T *d
     wgrad(1, h2, d, du, f, o.w_1, o.b_1, 0, ldf);
     dgrad(du, f, o.w_1, d, dh2, EPI_STORE, nullptr, ldf, 0);
     // h2 = LN2(x1); dx1 = dy + LN2'(dh2)
-    launch_layernorm_bwd_dx<T>(dh2, x1, mean2, rstd2, pf + o.ln2_g, dy, dx1, t, d, s, beta, gbuf + o.ln2_b, gbuf + o.ln2_g, partial);
+    launch_layernorm_bwd_dx<T>(dh2, x1, mean2, rstd2, pf + o.ln2_g, dy, dx1, t, d, s, beta, gbuf + o.ln2_b, gbuf + o.ln2_g,
+                               st->at<float>(p.partial[4]), &sums);
     // x1 = x + a Wo + bo
     wgrad(2, a, d, dx1, d, o.w_o, o.b_o);
     dgrad(dx1, d, o.w_o, d, da, EPI_STORE, nullptr);
@@ -577,7 +651,10 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, T *d
     wgrad(3, h, d, dqkv, 3 * d, o.w_qkv, o.b_qkv);
     dgrad(dqkv, 3 * d, o.w_qkv, d, dh, EPI_STORE, nullptr);
     // h = LN1(x); dx = dx1 + LN1'(dh)
-    launch_layernorm_bwd_dx<T>(dh, x_in, mean1, rstd1, pf + o.ln1_g, dx1, dy, t, d, s, beta, gbuf + o.ln1_b, gbuf + o.ln1_g, partial);
+    launch_colsums<T>(biases, n_biases, beta, s, true, &sums);
+    launch_layernorm_bwd_dx<T>(dh, x_in, mean1, rstd1, pf + o.ln1_g, dx1, dx, t, d, s, beta, gbuf + o.ln1_b, gbuf + o.ln1_g,
+                               st->at<float>(p.partial[5]), &sums);
+    launch_colsum_batch(sums, s);
 }
 
 // async: on the second stream, after everything enqueued so far (overlap mode, fused Adam of the layered order)
@@ -678,8 +755,8 @@ template <class T> int forward_layered_t(lga_stack *st, const void *x, void *y) 
 template <class T> int backward_layered_t(lga_stack *st, const void *dy, void *dx, const lga_adam *fused) {
     const lga_config &c = st->cfg;
     const size_t act_bytes = st->T * c.d_model * sizeof(T);
-    T *dact = st->at<T>(st->plan.dact);
-    LGA_HIP(hipMemcpyAsync(dact, dy, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+    ActivationGradient<T> dact(st);
+    LGA_HIP(hipMemcpyAsync(dact.in(0), dy, act_bytes, hipMemcpyDeviceToDevice, st->stream));
     const int groups = c.n_micro / c.group;
     const size_t gstride = st->t * c.d_model;
     for (int l = c.n_layers - 1; l >= 0; --l) {
@@ -697,18 +774,19 @@ template <class T> int backward_layered_t(lga_stack *st, const void *dy, void *d
         ensure_weights(st, l);
         prefetch_weights(st, l - 1, l);
         for (int gi = 0; gi < groups; ++gi) {
-            layer_forward<T>(st, l, in + gi * gstride, nullptr);                       // recompute
             const int wb = st->plan.wgrad_groups;
             const GradStep gs{gi == 0 ? 0.f : 1.f, gi < wb ? 0.f : 1.f, gi % wb, gi % wb == wb - 1 || gi == groups - 1};
-            layer_backward<T>(st, l, in + gi * gstride, dact + gi * gstride, gbuf, gs);
+            layer_forward<T>(st, l, in + gi * gstride, nullptr, gs.slot);              // recompute
+            layer_backward<T>(st, l, in + gi * gstride, dact.in(gi), dact.out(gi), gbuf, gs);
         }
+        dact.next_layer();
         st->grad_owner[st->grad_slot(l)] = l;
         // update as soon as the layer's gradient is complete; in overlap mode beside the next layer's sweep
         if (fused) adam_layer(st, l, *fused, (c.overlap & LGA_OVERLAP_ADAM) != 0);
     }
     if (c.overlap) join_aux(st);                            // later work on the main stream sees every update
     if (c.offload_checkpoints) join_offload(st);
-    if (dx) LGA_HIP(hipMemcpyAsync(dx, dact, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+    if (dx) LGA_HIP(dact.copy_to(dx, st->stream));
     if (fused) st->set_forward(false);                      // checkpoints no longer match the weights
     return finish("lga_backward_layered");
 }
@@ -748,8 +826,8 @@ template <class T> int forward_layer_t(lga_stack *st, int l, const void *x_in, v
 template <class T> int backward_layer_t(lga_stack *st, int l, const void *dy, void *dx, const lga_adam *fused) {
     const lga_config &c = st->cfg;
     const size_t act_bytes = st->T * c.d_model * sizeof(T);
-    T *dact = st->at<T>(st->plan.dact);
-    LGA_HIP(hipMemcpyAsync(dact, dy, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+    ActivationGradient<T> dact(st);
+    LGA_HIP(hipMemcpyAsync(dact.in(0), dy, act_bytes, hipMemcpyDeviceToDevice, st->stream));
     const int groups = c.n_micro / c.group;
     const size_t gstride = st->t * c.d_model;
     if (c.offload_checkpoints) {
@@ -761,18 +839,19 @@ template <class T> int backward_layer_t(lga_stack *st, int l, const void *dy, vo
     if (c.overlap) wait_grad(st, st->grad_slot(l));
     ensure_weights(st, l);
     for (int gi = 0; gi < groups; ++gi) {
-        layer_forward<T>(st, l, in + gi * gstride, nullptr);                           // recompute
         const int wb = st->plan.wgrad_groups;
         const GradStep gs{gi == 0 ? 0.f : 1.f, gi < wb ? 0.f : 1.f, gi % wb, gi % wb == wb - 1 || gi == groups - 1};
-        layer_backward<T>(st, l, in + gi * gstride, dact + gi * gstride, st->grad(l), gs);
+        layer_forward<T>(st, l, in + gi * gstride, nullptr, gs.slot);                  // recompute
+        layer_backward<T>(st, l, in + gi * gstride, dact.in(gi), dact.out(gi), st->grad(l), gs);
     }
+    dact.next_layer();
     st->grad_owner[st->grad_slot(l)] = l;
     if (fused) {
         adam_layer(st, l, *fused, (c.overlap & LGA_OVERLAP_ADAM) != 0);
         st->input_valid[l] = 0;
     }
     if (c.overlap) join_aux(st);
-    if (dx) LGA_HIP(hipMemcpyAsync(dx, dact, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+    if (dx) LGA_HIP(dact.copy_to(dx, st->stream));
     return finish("lga_backward_layer");
 }
 
@@ -797,7 +876,7 @@ int step_mbmajor_t(lga_stack *st, const void *x, const void *dy, void *y, void *
             layer_forward<T>(st, l, in, nullptr);
             // layers alternate here, so every weight-gradient GEMM runs at once on its own micro-batch
             const GradStep gs{mu == 0 ? 0.f : 1.f, mu == 0 ? 0.f : 1.f, 0, true};
-            layer_backward<T>(st, l, in, dact + mu * gstride, st->grad(l), gs);
+            layer_backward<T>(st, l, in, dact + mu * gstride, dact + mu * gstride, st->grad(l), gs);
         }
     }
     for (int l = 0; l < c.n_layers; ++l) st->grad_owner[l] = l;

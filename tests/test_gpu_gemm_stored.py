@@ -1,0 +1,54 @@
+"""GPU parity of the weight gradient that takes its operands as stored (both contiguous along the output's dimensions): the large-tile
+kernel at its edges, and a stack whose merged weight gradients keep several groups' activations and gradients for it.  Tolerances as
+for the other 16-bit GEMMs (fp32 results 1e-5) and stacks (2e-2 against exact arithmetic, 1e-5 between ways of merging)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from oracle import lga_oracle as O
+import synth_inputs as S
+from paper_2106_02679_amd import binding as B
+from gpu_helpers import run_gpu_step, oracle_shape, rel_err, compare_with_oracle
+from test_gpu_ops import check_gemm, BF16, F16
+
+SHAPES = [  # at least 128 tiles of 256 x 256, whole and ragged; k of one, two and three steps of 64, and of the unrolled loop's lengths
+          (2056, 4104, 8), (2056, 4104, 64), (2056, 4104, 72), (2840, 2840, 136), (2840, 2840, 200), (264, 33000, 456), (4096, 4096, 520),
+          (2304, 4096, 1031), (2840, 2856, 704),
+          # leading dimensions below 256, and fewer tiles: the kernels for other layouts
+          (96, 66000, 72), (1000, 1000, 333)]
+
+
+@pytest.mark.parametrize("dt", [BF16, F16])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradient_of_operands_as_stored(shape, dt):
+    check_gemm((dt, 0, 0, B.LGA_EPI_ACCUM_F32) + shape)
+
+
+@pytest.mark.parametrize("overlap", [0, B.LGA_OVERLAP_ADAM])
+def test_stack_whose_weight_gradients_take_stored_operands(overlap):
+    """W_1 and W_2 on the large-tile kernel, W_o and W_qkv on transposed copies; five groups in merged GEMMs of 1, 2 (a ragged last
+    one), 3 and 5, over two layers, so that the ring of activation gradients wraps."""
+    w = S.Workload("stored_bf16", 2, 1536, 12, 6144, 40, 1, 5, "bf16")
+    x, G, params = S.make_inputs(w, seed=3)
+    ref = O.step_microbatch_major(x, G, params, oracle_shape(w), None)
+    runs = [run_gpu_step(w, x, G, params, retain=1, wgrad_groups=wb, overlap=overlap) for wb in (1, 2, 3, 5)]
+    compare_with_oracle(w, runs[0], ref, 2e-2, None)
+    runs.append(run_gpu_step(w, x, G, params, retain=1, order="mbmajor", overlap=overlap))
+    for got in runs[1:]:
+        assert np.array_equal(got["dx"], runs[0]["dx"]) and np.array_equal(got["boundaries"], runs[0]["boundaries"])
+        for l in range(w.n_layers):
+            assert rel_err(got["grads"][l], runs[0]["grads"][l]) < 1e-5
+
+
+def test_narrow_stack_whose_weight_gradients_take_stored_operands_in_slices():
+    """12288 tokens per group: the few output tiles of a narrow layer, their k range in slices."""
+    w = S.Workload("stored_slices_bf16", 1, 512, 8, 2048, 512, 24, 2, "bf16")
+    x, G, params = S.make_inputs(w, seed=4)
+    one, both = (run_gpu_step(w, x, G, params, retain=1, wgrad_groups=wb) for wb in (1, 2))
+    exact = run_gpu_step(S.Workload("stored_slices_fp32", 1, 512, 8, 2048, 512, 24, 2, "fp32"), x, G, params, retain=1)
+    assert np.array_equal(one["dx"], both["dx"])
+    assert rel_err(one["grads"][0], both["grads"][0]) < 1e-5
+    for name, sl in S.tensor_slices(w.d_model, w.d_ff).items():
+        assert rel_err(both["grads"][0][sl], exact["grads"][0][sl]) < 2e-2, name
