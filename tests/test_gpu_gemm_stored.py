@@ -52,3 +52,39 @@ def test_narrow_stack_whose_weight_gradients_take_stored_operands_in_slices():
     assert rel_err(one["grads"][0], both["grads"][0]) < 1e-5
     for name, sl in S.tensor_slices(w.d_model, w.d_ff).items():
         assert rel_err(both["grads"][0][sl], exact["grads"][0][sl]) < 2e-2, name
+
+
+@pytest.mark.parametrize("d,heads,ff", [(1536, 12, 6144), (128, 2, 512)], ids=["ring", "in_place"])
+@pytest.mark.parametrize("layers", [1, 2])
+def test_gradient_buffers_that_overlap_or_are_misaligned(d, heads, ff, layers):
+    """The sweep reads dy and writes dx without copies where it can: dx in dy's place, shifted against it, and both at 8 bytes past
+    an aligned address give the same bits as buffers of their own; so does one layer's call."""
+    n_micro, s, shift = 5, 40, 4
+    params = [np.random.default_rng(l).standard_normal(B.params_per_layer(B.make_config(1, d, heads, ff, s, 1, n_micro, BF16))).astype(np.float32)
+              * 0.02 for l in range(layers)]
+    st = B.Stack(B.make_config(layers, d, heads, ff, s, 1, n_micro, BF16, group=1, retain_grads=1, wgrad_groups=2), np.concatenate(params))
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    n, row = n_micro * s * d, s * d
+    x, g = (torch.randn(n, device="cuda", generator=gen).bfloat16() for _ in range(2))
+
+    def run(dy_at, dx_at, per_layer=False):
+        buf = torch.full((3 * n + 64,), float("nan"), device="cuda", dtype=torch.bfloat16)
+        dy, dx = buf[dy_at:dy_at + n], buf[dx_at:dx_at + n]
+        dy.copy_(g)
+        st.forward_layered(x.data_ptr(), None)
+        if per_layer:
+            for l in reversed(range(layers)):
+                st.backward_layer(l, (dy if l == layers - 1 else dx).data_ptr(), dx.data_ptr(), None)
+        else:
+            st.backward_layered(dy.data_ptr(), dx.data_ptr(), None)
+        torch.cuda.synchronize()
+        return [dx.clone()] + [torch.from_numpy(B.read_device(*st.grads(l), "float32")) for l in range(layers)]
+
+    try:
+        ref = run(0, 2 * n)
+        assert torch.isfinite(ref[0].float()).all()
+        for args in ((0, 0), (0, row), (row, 0), (shift, 2 * n), (0, 2 * n + shift), (shift, shift), (0, 2 * n, True), (0, 0, True), (row, 0, True)):
+            for got, want in zip(run(*args), ref):
+                assert torch.equal(got, want), args
+    finally:
+        st.close()
