@@ -479,6 +479,7 @@ template <int V> __global__ __launch_bounds__(kFinalThreads) void colsum_final_k
     const int chunks = job.chunks, cols = job.cols;
     const bool two = job.out1 != nullptr;
     typedef float vec __attribute__((ext_vector_type(V)));
+    typedef vec loose __attribute__((aligned(4)));         // a caller's scratch: the order of the sums must not depend on its alignment
     {
         const int tx = threadIdx.x % LANES, q = threadIdx.x / LANES;
         const int c = block * kFinalCols + tx * V;
@@ -491,8 +492,8 @@ template <int V> __global__ __launch_bounds__(kFinalThreads) void colsum_final_k
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const bool there = k + i * GROUPS < chunks;
-                    a[i] = there ? *reinterpret_cast<const vec *>(row + i * step) : (vec)0.f;
-                    b[i] = there && two ? *reinterpret_cast<const vec *>(row + i * step + cols) : (vec)0.f;
+                    a[i] = there ? *reinterpret_cast<const loose *>(row + i * step) : (vec)0.f;
+                    b[i] = there && two ? *reinterpret_cast<const loose *>(row + i * step + cols) : (vec)0.f;
                 }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
@@ -739,7 +740,7 @@ void launch_colsum_batch(const ColsumBatch &batch, hipStream_t s, bool timed) {
     }
     ProfScope scope("colsum_final_kernel", 0.25 * bytes, bytes, s, timed);
     bool vec = true;
-    for (int i = 0; i < batch.n; ++i) vec &= batch.job[i].cols % 4 == 0 && aligned16(batch.job[i].partial);
+    for (int i = 0; i < batch.n; ++i) vec &= batch.job[i].cols % 4 == 0;
     if (vec) hipLaunchKernelGGL(colsum_final_kernel<4>, dim3((unsigned)blocks), dim3(kFinalThreads), 0, s, batch);
     else hipLaunchKernelGGL(colsum_final_kernel<1>, dim3((unsigned)blocks), dim3(kFinalThreads), 0, s, batch);
 }
