@@ -90,7 +90,7 @@ typedef struct lga_config {
                              negligible by updating a layer's weights at once) */
     int32_t wgrad_groups; /* 16-bit modes, layered order: consecutive groups of a layer whose weight-gradient
                              GEMMs are merged into one that contracts over all their tokens (their
-                             transposed operands are kept side by side until then: 2 (2 d_ff + 8 d_model)
+                             operands are kept side by side until then: 2 (2 d_ff + 8 d_model)
                              bytes per token, counted by lga_arena_bytes).  The sum over micro-batches then happens in
                              the GEMM's k loop instead of by read-modify-write of the fp32 buffer.
                              1 = no merging, 0 = automatic (as many as keep those operand buffers within
@@ -178,10 +178,11 @@ int lga_loss_scaler_update(lga_loss_scaler *scaler, int32_t overflowed);
  * 2 097 151 elements (3 d_model, d_ff, group * micro_batch * seq_len + 64, and with an explicit wgrad_groups that
  * many groups' tokens + 64; the automatic wgrad_groups stays within it).  Head sizes up to 160 have MFMA attention kernels in the 16-bit modes
  * (built for 32, 64, 96, 128, 160; sizes in between run in the next larger one).  Larger head sizes (table B.1's
- * X_[x] family has d_h = 2 x) run an attention built from batched GEMMs over the heads when seq_len is a multiple of 8
- * (at most 32768); the arena then holds one sequence's score matrices, 12 seq_len^2 bytes per head for as many
- * heads as fit 4 GiB.  Otherwise, and in the fp32 mode, a one-wavefront-per-position kernel is used that is meant
- * for checking, not for speed, and limits seq_len (2 seq_len + 2 d_h <= 15000).  LGA_ERR_OOM if the arena does not
+ * X_[x] family has d_h = 2 x) run, when seq_len is a multiple of 8 (at most 32768), in fused kernels up to 320 and otherwise
+ * as an attention built from batched GEMMs over the heads; the arena then holds one sequence's score matrices,
+ * 12 seq_len^2 bytes per head for as many heads as fit 4 GiB.  Otherwise, and in the fp32 mode for head sizes above 128, a
+ * one-wavefront-per-position kernel is used that is meant for checking, not for speed; it limits seq_len
+ * (2 seq_len + 2 d_h <= 15000), as the fp32 mode does for all head sizes.  LGA_ERR_OOM if the arena does not
  * fit. */
 int lga_init_stack(const lga_config *cfg, const float *host_params, lga_stack **out);
 

@@ -71,8 +71,8 @@ int lga_op_layernorm_bwd(int32_t dtype, const void *dy, const void *x, const flo
 uint64_t lga_op_layernorm_bwd_scratch_floats(int32_t rows, int32_t d);
 
 /* out[c][r] = in[r][c] for matrices of 16-bit elements of either format (in: [R][ldi], out: [C][ldo]); R, C, ldi, ldo multiples of 8,
- * 16-byte aligned.  The stack keeps a transposed 16-bit copy of each weight matrix and transposes the
- * two operands of every weight-gradient GEMM so that all GEMM operands are k-contiguous. */
+ * 16-byte aligned.  The stack keeps a transposed 16-bit copy of each weight matrix, and transposes the two operands of those
+ * weight-gradient GEMMs that are too small for the large-tile kernel, which takes them as stored. */
 int lga_op_transpose(const void *in, void *out, int32_t R, int32_t C, int64_t ldi, int64_t ldo, void *stream);
 
 /* lga_op_transpose of a matrix of format `dtype` (LGA_BF16 or LGA_FP16) that also returns its column sums,
@@ -108,7 +108,8 @@ uint64_t lga_op_colsum_static_max_floats(void);
  *  qkv  [n_seq*s, 3*heads*dh]: columns [Q | K | V], head h at columns h*dh inside each third
  *  out  [n_seq*s, heads*dh]
  *  lse  [n_seq, heads, s] float: log sum_j exp(scaled score_ij)
- * kind 0: one-wavefront-per-position kernel (any dtype, any dh); kind 1: MFMA kernel with
+ * kind 0: any dtype, any dh - one wavefront per position, but for fp32 with dh up to 128, which runs on the fp32 matrix
+ * instruction; kind 1: MFMA kernel with
  * LDS-resident online softmax (16-bit, dh a multiple of 8 up to 160; head sizes other than 32, 64, 96, 128, 160
  * run in the next larger of those kernels with the extra columns read as zeros). */
 int lga_op_attention_fwd(int32_t dtype, int32_t kind, const void *qkv, void *out, float *lse, int32_t n_seq,
@@ -118,8 +119,8 @@ int lga_op_attention_bwd(int32_t dtype, int32_t kind, const void *qkv, const voi
                          const void *dout, void *dqkv, float *delta, int32_t n_seq, int32_t s, int32_t heads,
                          int32_t dh, int32_t causal, void *stream);
 
-/* The same attention for head sizes beyond the fused kernels (table B.1's X_[x] family has d_h = 2 x: 216, 320), built
- * from batched GEMMs over the heads with the score matrices in a workspace: S = Q K^T in fp32, a row kernel for the
+/* The same attention for head sizes beyond 160 (table B.1's X_[x] family has d_h = 2 x: 216, 320).  Head sizes of 161 to 320 run in
+ * fused kernels that leave the workspace alone (the backward of few heads above 224 excepted); the others are built from batched GEMMs over the heads with the score matrices in a workspace: S = Q K^T in fp32, a row kernel for the
  * softmax (P rounded to 16 bits) and O = P V; backward S and dP = dO V^T in fp32, a row kernel for P, delta and dS, then
  * dV = P^T dO, dQ = dS K, dK = dS^T Q.  Arguments and results as above (16-bit dtypes only).  s and dh multiples of 8,
  * s <= 32768.  workspace: device, 256-byte aligned, at least lga_op_attention_gemm_workspace_bytes(s, 1) = 12 s^2 bytes;
