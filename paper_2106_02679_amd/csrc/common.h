@@ -35,7 +35,8 @@ template <> __device__ __forceinline__ f16 from_f32<f16>(float v) { return stati
 // accumulation registers taken by accumulators gives some products a destination other than their addend and then
 // moves accumulators around in the loop.  What the compiler no longer knows about this instruction, the caller
 // guarantees: an accumulator is not read by anything but this instruction until at least 32 wait states after its
-// last update, and its operands a, b are registers whose loads the compiler still tracks (s_waitcnt).  Two of these
+// last update, and its operands a, b are ready: registers whose loads the compiler tracks (s_waitcnt), or results of reads that
+// are assembly themselves, behind a wait that names them and with no loop's edge between the read and that wait.  Two of these
 // in a row on one accumulator need one wait state between them (without it the sums come out wrong): the compiler's
 // hazard pass puts an s_nop there when they are two asm statements, as here - it does not look inside one.
 typedef int i32x4 __attribute__((ext_vector_type(4)));

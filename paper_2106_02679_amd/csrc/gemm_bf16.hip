@@ -650,7 +650,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
                           "+v"(af[0][g0 + 3]), "+v"(af[1][g0 + 3]));
     };
     auto got_b = [&](int j) __attribute__((always_inline)) { asm volatile("" : "+v"(bf[0][j]), "+v"(bf[1][j])); };
-    auto wait_first_half = [&]() __attribute__((always_inline)) {       // what half 0 multiplies, when fewer reads follow it than in the main loop
+    // Reads in flight are values the compiler takes for ready: it may copy a register wherever values meet at a loop's edge or leave a loop.
+    // So no read is outstanding there: k_tile ends with this wait, and the main loop turns in the middle of a k tile, where
+    // the barrier's wait is for every read anyway.
+    auto wait_first_half = [&]() __attribute__((always_inline)) {       // what half 0 multiplies
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         got_a(0);
 #pragma unroll
@@ -682,7 +685,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
         for (int pr = 0; pr < 4 * FN; ++pr) {
             const int j = pr >> 2, g = 4 * h + (pr & 3);
             if constexpr (TN && LEAN) {
-                // at least 20 reads were issued after those of this column's B block and of the A blocks, and they return in order
+                // Reads return in order, four a block.  Behind those of column j's B block lie those of the B blocks after it and of
+                // the A blocks that this half has asked for so far, 4 (FN - 1 - j) + 4 min(j, FM / 2): fewest in the last
+                // column, 4 FM / 2 = 16.  (Behind the A blocks of this half: the last five B blocks'.)
+                static_assert(4 * (FM / 2) >= 14 && FN == 8 && FM == 8, "reads behind the ones waited for");
                 if (h == 0 && (pr & 3) == 0) {
                     asm volatile("s_waitcnt lgkmcnt(14)" ::: "memory");
                     if (j == 0) got_a(0);
@@ -725,10 +731,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
         const int krem2 = STRAIGHT ? BK : p.K - (kt + 2) * BK;
         const int qa1 = wrap(qa + 2), qa2 = wrap(qa + 4);      // A(kt+1), A(kt+2); B(kt+2) goes to qa
 
-        if constexpr (TN) wait_first_half();
         half(std::false_type{}, 0, more2, true, qa2, kt + 2, krem2, true, FM / 2, false, qa);
         // A bare s_barrier: __syncthreads() would add a fence that waits for every load, A(kt+2)'s included.
         // The LDS reads above must have returned before other wavefronts may overwrite those slots.
+        if constexpr (TN) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (more2)
             __builtin_amdgcn_s_waitcnt(kWaitVmA);
         else
@@ -739,27 +745,54 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
         if constexpr (TN) got_a(FM / 2);
         __builtin_amdgcn_sched_barrier(0);
         half(std::false_type{}, 1, more2, false, qa, kt + 2, krem2, more1, 0, more1, qa1);
+        if constexpr (TN) wait_first_half();
     };
-    // The same k tile for the unrolled main loop: ring slot qa is a constant, tiles kt+1 and kt+2 exist and are full;
-    // koff2 is the byte offset of k tile kt+2 within a row.
-    auto k_tile_c = [&](int qa, int koff2) __attribute__((always_inline)) {
-        const int qa1 = wrap(qa + 2), qa2 = wrap(qa + 4);
-        half(std::true_type{}, 0, true, true, qa2, koff2, BK, true, FM / 2, false, qa);
+    // The same k tile for the unrolled main loop, in its two halves: ring slot qa is a constant, tiles kt+1 and kt+2 exist and are
+    // full; koff2 is the byte offset of k tile kt+2 within a row.
+    auto first_half_c = [&](int qa, int koff2) __attribute__((always_inline)) {
+        half(std::true_type{}, 0, true, true, wrap(qa + 4), koff2, BK, true, FM / 2, false, qa);
         __builtin_amdgcn_s_waitcnt(kWaitVmA);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         if constexpr (TN) got_a(FM / 2);
         __builtin_amdgcn_sched_barrier(0);
-        half(std::true_type{}, 1, true, false, qa, koff2, BK, true, 0, true, qa1);
+    };
+    auto second_half_c = [&](int qa, int koff2) __attribute__((always_inline)) {
+        half(std::true_type{}, 1, true, false, qa, koff2, BK, true, 0, true, wrap(qa + 2));
         if constexpr (TN) {
             a_run += a_step;
             b_run += b_step;
         }
     };
+    auto k_tile_c = [&](int qa, int koff2) __attribute__((always_inline)) {
+        first_half_c(qa, koff2);
+        second_half_c(qa, koff2);
+    };
     int kt = 0, qa = 0;
     // Main loop, unrolled over one period of the ring (five k tiles; the slot of A(kt) is 0, 2, 4, 1, 3, 0, ...).
-    {
+    if constexpr (TN) {
+        if (kt + 7 < nk_full) {                              // as below, from the middle of one k tile to the middle of another
+            // from here on 64 values in registers of their own, not one zero that the first products' accumulators are copied from
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j]));
+            first_half_c(0, 0);
+            for (; kt + 7 < nk_full; kt += 5) {
+                second_half_c(0, 0);
+                k_tile_c(2, 0);
+                k_tile_c(4, 0);
+                k_tile_c(1, 0);
+                k_tile_c(3, 0);
+                first_half_c(0, 0);
+            }
+            second_half_c(0, 0);
+            wait_first_half();
+            ++kt;
+            qa = 2;
+        }
+    } else {
         int koff2 = 2 * BK * (int)sizeof(E);
         for (; kt + 6 < nk_full; kt += 5) {
             k_tile_c(0, koff2);
@@ -775,7 +808,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
     // the accumulators' last updates must have left the matrix pipe before anything else reads them (see
     // mfma_16x16x32_acc): twice the longest wait the instruction set asks for after a matrix instruction
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-    if constexpr (TN) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // (the last tile left no read behind)
 
     if constexpr (EPI != EPI_ACCUM_F32) {
         // bf16 outputs: a lane holds 4 consecutive n of 64 different (row, column group) places, so storing from
