@@ -299,14 +299,15 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
 // ---- dK, dV: one workgroup per (sequence, head, 128 keys) ----------------------------------------------------------------------------
 enum WideResult : int { kBoth = 0, kOnlyDV = 1, kOnlyDK = 2 };
 
-template <int DH, int WHAT> constexpr int dkv_occ() { return 1; }
+// up to 224 channels one run gives both results
+template <int DH> constexpr bool dkv_in_one_run() { return DH <= 224; }
 
 template <int DH, int WHAT, class E>
-__global__ __launch_bounds__(256, (dkv_occ<DH, WHAT>())) void attn_wide_dkv_kernel(const E *__restrict__ qkv, const float *__restrict__ lse,
+__global__ __launch_bounds__(256, 1) void attn_wide_dkv_kernel(const E *__restrict__ qkv, const float *__restrict__ lse,
                                                                const float *__restrict__ delta, const E *__restrict__ dout,
                                                                E *__restrict__ dqkv, AttnShape sh) {
     constexpr bool DV = WHAT != kOnlyDK, DK = WHAT != kOnlyDV;
-    constexpr int NK = DH / 16, NC = DH / 32, NST = dkv_occ<DH, WHAT>() == 2 ? 2 : 3;
+    constexpr int NK = DH / 16, NC = DH / 32, NST = 3;
     typedef TileDmaSw<kTile, DH> Dma;
     constexpr int TILE = Dma::ELEMS, STAGE = 2 * TILE;          // Q tile, then dO tile
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -359,19 +360,21 @@ __global__ __launch_bounds__(256, (dkv_occ<DH, WHAT>())) void attn_wide_dkv_kern
     auto store_stat = [&](int t, float v) {
         if (wave == 0) stat_s[t % 3 * 64 + lane] = qbeg + kTile * t + lrow >= sh.s ? 0.f : half == 0 ? -v * kLog2e : -v;
     };
-    // the statistics have one stage more than the tiles, so that tile t + 1's can be stored while tile t's are read
+    // tile t + 1's statistics are stored while tile t's are read: the stage they take was read before the last barrier
     float stat = load_stat(0);
     dma_tile(0);
     store_stat(0, stat);
     if (ntiles > 1) {
         stat = load_stat(1);
-        if (NST > 2) dma_tile(1);
+        dma_tile(1);
     }
     auto advance = [&](int t) {
         if (t + 1 < ntiles) store_stat(t + 1, stat);
-        publish_tile<2 * Dma::NJ>(NST > 2 && t + 1 < ntiles);
-        if (t + 2 < ntiles) stat = load_stat(t + 2);
-        if (t + NST - 1 < ntiles) dma_tile(t + NST - 1);
+        publish_tile<2 * Dma::NJ>(t + 1 < ntiles);
+        if (t + 2 < ntiles) {
+            stat = load_stat(t + 2);
+            dma_tile(t + 2);
+        }
     };
     auto unit = [&](int t, auto masked_c) {
         constexpr bool MASKED = decltype(masked_c)::value;
@@ -499,7 +502,7 @@ LGA_WIDE_TYPE(f16);
 
 template <int DH> constexpr int smem_fwd() { return fwd_stages<DH>() * stage_elems<DH>() * 2; }
 template <int DH> constexpr int smem_dq() { return 3 * stage_elems<DH>() * 2; }
-template <int DH, int WHAT> constexpr int smem_dkv() { return (dkv_occ<DH, WHAT>() == 2 ? 2 : 3) * stage_elems<DH>() * 2 + 3 * 64 * 4; }
+template <int DH> constexpr int smem_dkv() { return 3 * stage_elems<DH>() * 2 + 3 * 64 * 4; }
 
 template <class K> hipError_t raise(K kernel, int bytes) {
     return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -508,11 +511,11 @@ template <int DH, class E> hipError_t raise_dh() {
     hipError_t e = raise(attn_wide_fwd_kernel<DH, E>, smem_fwd<DH>());
     auto next = [&](hipError_t r) { if (e == hipSuccess) e = r; };
     next(raise(attn_wide_dq_kernel<DH, E>, smem_dq<DH>()));
-    if constexpr (DH <= 224) {
-        next(raise(attn_wide_dkv_kernel<DH, kBoth, E>, smem_dkv<DH, kBoth>()));
+    if constexpr (dkv_in_one_run<DH>()) {
+        next(raise(attn_wide_dkv_kernel<DH, kBoth, E>, smem_dkv<DH>()));
     } else {
-        next(raise(attn_wide_dkv_kernel<DH, kOnlyDV, E>, smem_dkv<DH, kOnlyDV>()));
-        next(raise(attn_wide_dkv_kernel<DH, kOnlyDK, E>, smem_dkv<DH, kOnlyDK>()));
+        next(raise(attn_wide_dkv_kernel<DH, kOnlyDV, E>, smem_dkv<DH>()));
+        next(raise(attn_wide_dkv_kernel<DH, kOnlyDK, E>, smem_dkv<DH>()));
     }
     return e;
 }
@@ -543,12 +546,12 @@ void bwd_dh(const E *qkv, const float *lse, const float *delta, const E *dout, E
         hipLaunchKernelGGL((attn_wide_dq_kernel<DH, E>), grid, dim3(256), smem_dq<DH>(), s, qkv, lse, delta, dout, dqkv, sh);
     }
     snprintf(name, sizeof(name), "attn_wide_dkv_kernel<%d>", DH);
-    ProfScope scope(name, (DH <= 192 ? 8.0 : 10.0) * pairs * sh.dh, 6.0 * act, s);
-    if constexpr (DH <= 224) {
-        hipLaunchKernelGGL((attn_wide_dkv_kernel<DH, kBoth, E>), grid, dim3(256), (smem_dkv<DH, kBoth>()), s, qkv, lse, delta, dout, dqkv, sh);
+    ProfScope scope(name, (dkv_in_one_run<DH>() ? 8.0 : 10.0) * pairs * sh.dh, 6.0 * act, s);
+    if constexpr (dkv_in_one_run<DH>()) {
+        hipLaunchKernelGGL((attn_wide_dkv_kernel<DH, kBoth, E>), grid, dim3(256), smem_dkv<DH>(), s, qkv, lse, delta, dout, dqkv, sh);
     } else {
-        hipLaunchKernelGGL((attn_wide_dkv_kernel<DH, kOnlyDV, E>), grid, dim3(256), (smem_dkv<DH, kOnlyDV>()), s, qkv, lse, delta, dout, dqkv, sh);
-        hipLaunchKernelGGL((attn_wide_dkv_kernel<DH, kOnlyDK, E>), grid, dim3(256), (smem_dkv<DH, kOnlyDK>()), s, qkv, lse, delta, dout, dqkv, sh);
+        hipLaunchKernelGGL((attn_wide_dkv_kernel<DH, kOnlyDV, E>), grid, dim3(256), smem_dkv<DH>(), s, qkv, lse, delta, dout, dqkv, sh);
+        hipLaunchKernelGGL((attn_wide_dkv_kernel<DH, kOnlyDK, E>), grid, dim3(256), smem_dkv<DH>(), s, qkv, lse, delta, dout, dqkv, sh);
     }
 }
 

@@ -171,3 +171,16 @@ def run_gpu_step(w: S.Workload, x, G, params, *, group=1, retain=0, order="layer
     finally:
         st.close()
     return out
+
+
+def profiled(call) -> dict:
+    """The kernels that `call` launches, by name, with their launches and algorithmic work (the profile counts every launch of the library
+    in the process; a stack of the smallest size stands in for the handle it is asked through)."""
+    st = B.Stack(B.make_config(1, 8, 1, 8, 8, 1, 1, B.LGA_FP32), None)
+    try:
+        st.profile_begin()
+        call()
+        torch.cuda.synchronize()
+        return {k["name"]: k for k in st.profile_end()}
+    finally:
+        st.close()

@@ -10,7 +10,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from paper_2106_02679_amd import binding as B
-from gpu_helpers import to_dev, empty_dev, to_host, rel_err
+from gpu_helpers import to_dev, empty_dev, to_host, rel_err, profiled
 from test_gpu_ops import attention_reference, rnd, ROUND, TOL_ATTN, BF16, F16
 
 
@@ -61,3 +61,14 @@ def test_wide_heads_with_scores_that_keep_growing_along_the_keys(dt, dh, causal)
     qkv, dout = ROUND[dt](qkv), rnd(rng, (s, d), dt)
     # near one-hot probabilities times keys of size ~80: the rounding of dS weighs more than on ordinary inputs
     check(dt, run(dt, qkv, dout, n_seq, s, heads, dh, causal), attention_reference(qkv, dout, n_seq, s, heads, dh, causal), d, loose=2.0)
+
+
+@pytest.mark.parametrize("dh,products", [(168, 4), (192, 4), (200, 4), (224, 4), (232, 5), (320, 5)])
+def test_the_profile_counts_the_products_that_the_key_gradients_take(dh, products):
+    """One run up to 224 channels (S, dP, dV, dK), beyond it two that both compute S; 2 s^2 dh operations each."""
+    n_seq, s, heads = 1, 512, 40
+    qkv = torch.zeros(n_seq * s, 3 * heads * dh, device="cuda", dtype=torch.bfloat16)
+    dout = torch.zeros(n_seq * s, heads * dh, device="cuda", dtype=torch.bfloat16)
+    kernels = profiled(lambda: run(BF16, qkv.float().cpu().numpy(), dout.float().cpu().numpy(), n_seq, s, heads, dh, False))
+    flops = sum(k["flops"] for name, k in kernels.items() if name.startswith("attn_wide_dkv"))
+    assert flops == products * 2.0 * heads * s * s * dh
