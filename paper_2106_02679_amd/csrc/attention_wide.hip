@@ -2,6 +2,9 @@
 // the manner of the kernels for smaller heads: 32 positions per wavefront, score blocks produced transposed so that a lane owns one
 // position, tiles straight into LDS and read both ways.
 //
+// dS = P (dP - delta) / sqrt(d_h) is rounded to 16 bits with the factor in it: without, it leaves half precision's range at gradients
+// sqrt(d_h) times smaller.
+//
 // What differs is what a wavefront's registers hold.  Forward: 32 queries instead of 64 (one accumulator block of 32 x DH); the softmax
 // reference moves only when a score exceeds it by kLazy, so that the accumulators are rescaled in a few tiles of a row.  dQ:
 // one wavefront per SIMD.  dK/dV: operands and both accumulators of 32 keys fit up to 224 channels; beyond, the kernel runs twice,
@@ -216,8 +219,8 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
     }
     const size_t stat = ((size_t)b * sh.heads + h) * sh.s + q;
     const float lse2 = qvalid ? lse[stat] * kLog2e : INFINITY;     // invalid rows: p = exp2(-inf) = 0
-    const float dl = qvalid ? delta[stat] : 0.f;
     const float scale = rsqrtf((float)dh), c2 = scale * kLog2e;
+    const float dl = qvalid ? delta[stat] * scale : 0.f;           // dS carries the factor when it is rounded: see the file's head
     f32x16 acc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c] = zero16();
@@ -256,7 +259,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
         for (int c = 0; c < NC; ++c) k0t[c] = ad.tr(Ks, c, 0);   // K^T operands
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] *= dpt[r] - dl;
+        for (int r = 0; r < 16; ++r) st[r] *= fmaf(dpt[r], scale, -dl);
         const x8<E> ds0 = pack16<E>(st, 0), ds1 = pack16<E>(st, 1);
         wait_tr_reads(k0t);
 #pragma unroll
@@ -291,7 +294,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
         for (int g = 0; g < 4; ++g) {
             x4<E> o;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = (E)(acc[c][4 * g + i] * scale);
+            for (int i = 0; i < 4; ++i) o[i] = (E)acc[c][4 * g + i];
             if (c * 32 + 8 * g + 4 * half < dh) *reinterpret_cast<x4<E> *>(orow + c * 32 + 8 * g + 4 * half) = o;
         }
 }
@@ -414,7 +417,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dkv_kernel(const E *__restri
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             if constexpr (!DK) probability(r);
-            else s_[r] = pr[r] * dp[r];
+            else s_[r] = pr[r] * scale * dp[r];
         }
         const x8<E> p0 = pack16<E>(pr, 0), p1 = pack16<E>(pr, 1);
         x8<E> s0 = p0, s1 = p1;
@@ -466,7 +469,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dkv_kernel(const E *__restri
             x4<E> o;
             if constexpr (DK) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = (E)(dk[c][4 * g + i] * scale);
+                for (int i = 0; i < 4; ++i) o[i] = (E)dk[c][4 * g + i];
                 *reinterpret_cast<x4<E> *>(orow + d + col) = o;
             }
             if constexpr (DV) {

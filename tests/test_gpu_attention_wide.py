@@ -72,3 +72,20 @@ def test_the_profile_counts_the_products_that_the_key_gradients_take(dh, product
     kernels = profiled(lambda: run(BF16, qkv.float().cpu().numpy(), dout.float().cpu().numpy(), n_seq, s, heads, dh, False))
     flops = sum(k["flops"] for name, k in kernels.items() if name.startswith("attn_wide_dkv"))
     assert flops == products * 2.0 * heads * s * s * dh
+
+
+@pytest.mark.parametrize("dh", [168, 216, 256, 320])
+def test_large_gradients_in_half_precision_stay_finite(dh):
+    """dS = P (dP - delta) / sqrt(d_h) is rounded to half precision with the factor in it: gradients whose unscaled dS lies beyond the
+    format's 65504 while everything that is returned lies within it."""
+    n_seq, s, heads = 1, 264, 104
+    d = heads * dh
+    rng = np.random.default_rng(dh)
+    qkv, dout = rnd(rng, (n_seq * s, 3 * d), F16), ROUND[F16](rng.standard_normal((n_seq * s, d)).astype(np.float32) * 6000)
+    want = attention_reference(qkv, dout, n_seq, s, heads, dh, True)
+    assert np.abs(want[2]).max() < 60000
+    got = []
+    kernels = profiled(lambda: got.append(run(F16, qkv, dout, n_seq, s, heads, dh, True)))
+    assert any(k.startswith("attn_wide_dq") for k in kernels)
+    assert np.isfinite(got[0][2]).all()
+    check(F16, got[0], want, d)
