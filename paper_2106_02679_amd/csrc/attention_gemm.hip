@@ -1,5 +1,5 @@
-// Softmax attention for head sizes that have no fused MFMA kernel (d_h > 320, and the backward pass of few heads above 224; up to
-// 320 attention_wide.hip serves the others), built from the library's own batched 16-bit GEMMs and two row
+// Softmax attention for head sizes that have no fused MFMA kernel (d_h > 320), and for few heads of more than 160 channels (the others
+// up to 320 run the kernels of attention_wide.hip), built from the library's own batched 16-bit GEMMs and two row
 // kernels.  The fused kernels keep a query block's operands and accumulators in registers, which ends there;
 // here the score matrix of every head goes through memory instead (fp32, so that the softmax sees unrounded scores):
 //
@@ -147,6 +147,31 @@ template <class E> struct Carve {
     }
 };
 
+// Fused kernels or GEMMs, for heads of 168 ... 320 channels.  A fused workgroup walks serially over the s positions of the other kind, at
+// so many ns a position whatever else runs; the GEMMs take their launches, a shorter walk and 2 ps (forward) or 4 (backward) per
+// (query, key) pair and head.  So the fused kernels win where heads * s exceeds a number of the padded size, short
+// sequences (where the launches weigh more) earlier.  One sequence, causal, us fused [GEMMs]:
+//   heads x s   192                     224                     256                     320
+//   1 x 1024    fwd 31 [30] bwd 96 [79]     33 [30] 105 [79]        48 [31] 148 [78]        63 [32] 175 [80]
+//   8 x 1024    32 [51]     99 [109]        36 [51] 113 [113]       49 [51] 153 [112]       65 [50] 183 [115]
+//   16 x 1024   33 [52]     101 [123]       37 [55] 117 [131]       49 [53] 157 [130]       66 [60] 186 [159]
+//   24 x 1024   34 [75]     105 [203]       38 [79] 121 [214]       51 [78] 164 [214]       66 [86] 194 [242]
+//   1 x 4096    109 [97]    323 [262]       124 [99] 371 [266]      171 [98] 512 [264]      231 [100] 606 [267]
+//   4 x 4096    113 [207]   331 [498]       124 [219] 383 [520]     173 [215] 525 [512]     233 [221] 620 [603]
+//   8 x 4096    115 [353]   351 [804]       129 [371] 408 [849]     178 [372] 545 [833]     236 [349] 648 [862]
+//   1 x 8192    221 [275]   629 [720]       242 [285] 718 [742]     334 [282] 992 [739]     451 [282] 1175 [745]
+// The rule knows one sequence's shape only: a sequence's results must not depend on how many others share its launch.
+// (The GEMMs take the sequences one after the other, so with several of them the fused kernels would win earlier.)
+int wide_size(int dh) { return dh <= 192 ? 0 : dh <= 224 ? 1 : dh <= 256 ? 2 : 3; }
+bool fused_forward(AttnShape sh) {
+    constexpr double kEnough[4] = {6750, 8750, 15000, 23000};
+    return attn_wide_supports(sh.dh) && (double)sh.heads * sh.s + 6.5e6 / sh.s >= kEnough[wide_size(sh.dh)];
+}
+bool fused_backward(AttnShape sh) {
+    constexpr double kEnough[4] = {7900, 10500, 18750, 23750}, kLaunches[4] = {3.25e6, 3.25e6, 0.75e6, -0.5e6};
+    return attn_wide_supports(sh.dh) && (double)sh.heads * sh.s + kLaunches[wide_size(sh.dh)] / sh.s >= kEnough[wide_size(sh.dh)];
+}
+
 int heads_per_pass(AttnShape sh, size_t ws_bytes) {
     const size_t per_head = attn_gemm_workspace_bytes(sh.s, 1);
     return (int)std::min<size_t>((size_t)sh.heads, ws_bytes / per_head);
@@ -170,7 +195,7 @@ bool attn_gemm_supports(AttnShape sh, size_t ws_bytes) {
 template <class E>
 void launch_attn_fwd_gemm(const E *qkv, E *out, float *lse, AttnShape sh, void *ws, size_t ws_bytes, hipStream_t st) {
     if (sh.n_seq == 0 || sh.s == 0) return;
-    if (attn_wide_supports(sh.dh)) return launch_attn_fwd_wide<E>(qkv, out, lse, sh, st);
+    if (fused_forward(sh)) return launch_attn_fwd_wide<E>(qkv, out, lse, sh, st);
     const int s = sh.s, dh = sh.dh, d = sh.heads * dh, hc_max = heads_per_pass(sh, ws_bytes);
     const float scale = 1.0f / sqrtf((float)dh);
     for (int b = 0; b < sh.n_seq; ++b) {
@@ -207,11 +232,7 @@ template <class E>
 void launch_attn_bwd_gemm(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv, float *delta,
                           AttnShape sh, void *ws, size_t ws_bytes, hipStream_t st) {
     if (sh.n_seq == 0 || sh.s == 0) return;
-    // Above 224 channels the fused dK/dV kernel runs twice, with one workgroup per 128 keys: on a chip half empty its serial walk over the
-    // queries is the longer one (16 heads x 1024 x 256: 157 against 130 us; 16 x 1024 x 176: 100 against 127; 32 x 2048 x 256: 397
-    // against 749).
-    const bool few = sh.dh > 224 && (long)sh.n_seq * sh.heads * ((sh.s + 127) / 128) <= 128;
-    if (attn_wide_supports(sh.dh) && !few) return launch_attn_bwd_wide<E>(qkv, out, lse, dout, dqkv, delta, sh, st);
+    if (fused_backward(sh)) return launch_attn_bwd_wide<E>(qkv, out, lse, dout, dqkv, delta, sh, st);
     const int s = sh.s, dh = sh.dh, d = sh.heads * dh, hc_max = heads_per_pass(sh, ws_bytes);
     const float scale = 1.0f / sqrtf((float)dh);
     const long long ss = (long long)s * s;

@@ -10,7 +10,8 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from paper_2106_02679_amd import binding as B
-from gpu_helpers import to_dev, empty_dev, to_host, rel_err, profiled
+import synth_inputs as S
+from gpu_helpers import to_dev, empty_dev, to_host, rel_err, profiled, run_gpu_step
 from test_gpu_ops import attention_reference, rnd, ROUND, TOL_ATTN, BF16, F16
 
 
@@ -66,7 +67,7 @@ def test_wide_heads_with_scores_that_keep_growing_along_the_keys(dt, dh, causal)
 @pytest.mark.parametrize("dh,products", [(168, 4), (192, 4), (200, 4), (224, 4), (232, 5), (320, 5)])
 def test_the_profile_counts_the_products_that_the_key_gradients_take(dh, products):
     """One run up to 224 channels (S, dP, dV, dK), beyond it two that both compute S; 2 s^2 dh operations each."""
-    n_seq, s, heads = 1, 512, 40
+    n_seq, s, heads = 1, 512, 56
     qkv = torch.zeros(n_seq * s, 3 * heads * dh, device="cuda", dtype=torch.bfloat16)
     dout = torch.zeros(n_seq * s, heads * dh, device="cuda", dtype=torch.bfloat16)
     kernels = profiled(lambda: run(BF16, qkv.float().cpu().numpy(), dout.float().cpu().numpy(), n_seq, s, heads, dh, False))
@@ -89,3 +90,28 @@ def test_large_gradients_in_half_precision_stay_finite(dh):
     assert any(k.startswith("attn_wide_dq") for k in kernels)
     assert np.isfinite(got[0][2]).all()
     check(F16, got[0], want, d)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh,fused,n_seq,s,heads", [
+    (232, True, 1, 264, 80), (256, True, 1, 136, 110), (256, True, 2, 48, 70), (264, True, 1, 264, 104), (320, True, 2, 160, 170),
+    (320, True, 1, 136, 210), (168, False, 1, 1000, 1), (224, False, 2, 520, 3), (256, False, 1, 520, 4), (320, False, 2, 520, 4)])
+def test_wide_heads_on_either_side_of_the_rule_between_fused_kernels_and_gemms(dh, fused, n_seq, s, heads, causal):
+    rng = np.random.default_rng(dh + s)
+    d, got = heads * dh, []
+    qkv, dout = rnd(rng, (n_seq * s, 3 * d), BF16), rnd(rng, (n_seq * s, d), BF16)
+    kernels = profiled(lambda: got.append(run(BF16, qkv, dout, n_seq, s, heads, dh, causal)))
+    assert any(k.startswith("attn_wide_dq") for k in kernels) == fused
+    assert any(k.startswith("attn_ds_rows") for k in kernels) != fused
+    check(BF16, got[0], attention_reference(qkv, dout, n_seq, s, heads, dh, causal), d)
+
+
+@pytest.mark.parametrize("dh,heads,groups", [(256, 8, (1, 2)), (320, 4, (1, 2, 4))])
+def test_wide_heads_do_not_depend_on_how_many_sequences_share_a_launch(dh, heads, groups):
+    """128 and 256 workgroups of the fused kernels: the orders and group sizes agree bit for bit."""
+    w = S.Workload("wide_groups", 1, heads * dh, heads, 512, 256, 8, groups[-1], "bf16")
+    x, G, params = S.make_inputs(w, seed=5)
+    runs = [run_gpu_step(w, x, G, params, group=g, retain=1) for g in groups] + [run_gpu_step(w, x, G, params, retain=1, order="mbmajor")]
+    for got in runs[1:]:
+        assert np.array_equal(got["boundaries"], runs[0]["boundaries"])
+        assert np.array_equal(got["dx"], runs[0]["dx"])
