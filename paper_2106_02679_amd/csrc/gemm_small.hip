@@ -7,7 +7,7 @@
 //    in NS stages, so that NS - 1 steps are in flight while one is multiplied;
 //  - a workgroup is four wavefronts (2 x 2 over the BM x BN tile), or KG groups of four, each of which takes its own part of the
 //    k range; their sums meet in LDS at the end and are added in group order (the result does not depend on scheduling);
-//  - the finished tile is already in LDS, and leaves it row by row, 16 bytes per lane, with the epilogue applied on the way.
+//  - the finished tile leaves through LDS row by row, 16 bytes per lane, with the epilogue applied on the way.
 // Groups and slices of k are for the weight gradients only.  With one group an element's products are added in the order of
 // the large-tile kernel, so an activation does not depend on how many rows share its launch, nor on which of the two kernels
 // runs: the orders and groupings of the micro-batches agree bit for bit.  (Four groups would give 160 x 1920 x 7680 another
@@ -150,6 +150,20 @@ __global__ __launch_bounds__(256 * KG) void gemm_small_kernel(GemmParams<E> p, i
 #pragma unroll
                 for (int j = 0; j < FN; ++j) acc[i][j] = mfma_16x16x32<E>(bf[j], af[i], acc[i][j]);
         }
+    }
+    if constexpr (EPI == EPI_ACCUM_F32 && KG == 1 && BM == 128) {
+        // A whole 128 x 128 tile of fp32 results leaves from the registers, 64 bytes of 16 rows per instruction: with one workgroup on a
+        // compute unit nothing runs beside the way through LDS (1024 x 4096 x 512: 12.2 -> 10.9 us, 2048 x 2048 x 64: 8.5 -> 7.0; 64 x 64
+        // tiles, three on a unit, lose 1 to 3 %).
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const int m = m0 + wm * WM + i * 16 + l16, n = n0 + wn * WN + j * 16 + 4 * lq;
+                const float a[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+                if (m < p.M && n < p.N) epilogue4<EPI, E>(p, m, n, a);
+            }
+        return;
     }
     __syncthreads();                                     // nobody reads the ring any more, no load is in flight
 
