@@ -972,9 +972,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 template <class E> int large_tile_slices(const GemmParams<E> &p) {
     const long big = (long)((p.M + 255) / 256) * ((p.N + 255) / 256);
     const int slices = p.batch > 1 ? 1 : gemm_splitk_slices(p.M, p.N, p.K);
-    if (slices > 1 && big * slices >= 192 && p.partial && (size_t)slices * p.M * p.N <= p.partial_floats && p.N % 4 == 0 &&
-        p.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(p.outf) & 15) == 0)
-        return slices;
+    const bool fits = slices > 1 && p.partial && (size_t)slices * p.M * p.N <= p.partial_floats && p.N % 4 == 0 && p.ldc % 4 == 0 &&
+                      (reinterpret_cast<uintptr_t>(p.outf) & 15) == 0;
+    if (fits && (big * slices >= 192 || (p.K >= 10240 && p.K / gemm_small_slices(p.M, p.N, p.K, p.partial_floats) >= 8192))) return slices;
     return big >= 128 ? 1 : 0;
 }
 
@@ -995,7 +995,9 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmPa
             // A weight-gradient GEMM of a narrow layer: few output tiles, very long k.  The k range is cut into slices
             // that run as separate work items of the large-tile kernel and are summed afterwards - where that gives at least
             // 192 work items: with fewer the small tiles are faster (768 x 768 x 8192, 72 items: 36 against 30 us;
-            // 768 x 2304 x 8192, 216 items: 43 against 48; 1280 x 3840 x 2048, 150 items: 41 against 32).
+            // 768 x 2304 x 8192, 216 items: 43 against 48; 1280 x 3840 x 2048, 150 items: 41 against 32).  Unless one of their
+            // workgroups walks over 8192 k and more: 768 x 768 x 16384, 135 items, 40 against 56; 640 x 640 x 16384, 8192 k
+            // each in two slices, 39 against 44; 256 x 1024 x 65536 58 against 83 - but x 16384, 4096 k each, 37 against 26.
             const int slices = large_tile_slices(p);
             if (slices > 1) return launch_slices<A_KM, B_KM, EPI, E>(p, slices, s);
         }

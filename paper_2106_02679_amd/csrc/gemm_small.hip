@@ -255,6 +255,15 @@ template <class E> hipError_t raise_type() {
 
 }  // namespace
 
+// A long k range over few tiles: slices over the grid, up to 256 workgroups, at least 512 k each; the second kernel costs
+// 5 us and more, so not below 4096 k (128 x 512 x 4096: 10.1 in 8 slices, 10.8 in one piece; x 8192: 11.4, 18)
+int gemm_small_slices(int M, int N, int K, size_t partial_floats) {
+    const long t64 = tiles_of(M, N, 64, 64);
+    if (K <= 4096 || t64 < 1 || t64 > 128) return 1;
+    const long fit = (long)std::min<size_t>(partial_floats / ((size_t)M * N), 32);
+    return (int)std::max<long>(1, std::min({256 / t64, (long)K / 512, fit}));
+}
+
 // Which tile, how many stages and k groups: by how many workgroups a tiling gives the 256 compute units, so that the tiles run in one
 // round and each unit has as many loads in flight as its LDS holds.  Measured at K = 512 ... 16384 (us, best of the others in brackets):
 //   32 x 64, 8 stages, one workgroup per unit    up to 256 of them: 160 x 1920 x 7680 28.5 [35.1], 80 x 4096 x 4096 16.1 [19.3]
@@ -271,19 +280,14 @@ template <int EPI, class E> void launch_gemm_small(const GemmParams<E> &p, hipSt
     if (p.batch > 1) return launch_config<128, 128, 1, 2, EPI, E>(p, s);
     const long t32 = tiles_of(p.M, p.N, 32, 64), t64 = tiles_of(p.M, p.N, 64, 64);
     if constexpr (EPI == EPI_ACCUM_F32) {
-        // A long k range over few tiles: slices over the grid, up to 256 workgroups, at least 512 k each; the second kernel costs
-        // 5 us and more, so not below 4096 k (128 x 512 x 4096: 10.1 in 8 slices, 10.8 in one piece; x 8192: 11.4, 18)
-        if (p.K > 4096 && t64 <= 128 && p.partial && p.N % 4 == 0) {
-            const long fit = (long)std::min<size_t>(p.partial_floats / ((size_t)p.M * p.N), 32);
-            const long slices = std::min({256 / t64, (long)p.K / 512, fit});
-            if (slices > 1) {
-                GemmParams<E> q = p;
-                q.kchunk = (int)(((p.K + slices - 1) / slices + BK - 1) / BK * BK);
-                q.ksplit = (p.K + q.kchunk - 1) / q.kchunk;
-                launch_config<64, 64, 2, 2, EPI, E>(q, s);
-                launch_splitk_reduce(p.partial, q.ksplit, p.outf, p.M, p.N, p.ldc, p.beta, s);
-                return;
-            }
+        const int slices = p.partial && p.N % 4 == 0 ? gemm_small_slices(p.M, p.N, p.K, p.partial_floats) : 1;
+        if (slices > 1) {
+            GemmParams<E> q = p;
+            q.kchunk = ((p.K + slices - 1) / slices + BK - 1) / BK * BK;
+            q.ksplit = (p.K + q.kchunk - 1) / q.kchunk;
+            launch_config<64, 64, 2, 2, EPI, E>(q, s);
+            launch_splitk_reduce(p.partial, q.ksplit, p.outf, p.M, p.N, p.ldc, p.beta, s);
+            return;
         }
         if (t32 <= 256) launch_config<32, 64, 4, 3, EPI, E>(p, s);
         else if (t64 <= 256) launch_config<64, 64, 2, 3, EPI, E>(p, s);

@@ -131,6 +131,8 @@ bool launch_gemm_mfma(const GemmParams<E> &p, bool a_kmajor, bool b_kmajor, Epil
 // Its share of problems with fewer than 128 tiles of 256 x 256, both operands k-contiguous (gemm_small.hip); p.ldc, p.N multiples of 8
 // and every tensor 16-byte aligned.  Uses p.partial for slices of a long k range where that is large enough.
 template <int EPI, class E> void launch_gemm_small(const GemmParams<E> &p, hipStream_t s);
+// Slices of the k range that it cuts a weight gradient into, given so many floats of scratch (1 = none).
+int gemm_small_slices(int M, int N, int K, size_t partial_floats);
 // out[m, n] = beta * out[m, n] + sum_z partial[z][m][n], slices in index order; N and ldc multiples of 4, 16-byte aligned
 void launch_splitk_reduce(const float *partial, int slices, float *out, int M, int N, int ldc, float beta, hipStream_t s);
 // Into how many slices of the k range launch_gemm_mfma cuts an fp32-accumulating, k-contiguous GEMM whose output has

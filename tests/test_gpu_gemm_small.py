@@ -8,7 +8,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from paper_2106_02679_amd import binding as B
-from gpu_helpers import to_dev, rel_err
+from gpu_helpers import to_dev, rel_err, profiled
 from test_gpu_ops import check_gemm, fvec, rnd, BF16, F16
 
 EPILOGUES = (B.LGA_EPI_STORE, B.LGA_EPI_BIAS, B.LGA_EPI_BIAS_RESID, B.LGA_EPI_BIAS_GELU, B.LGA_EPI_MUL_DGELU, B.LGA_EPI_ACCUM_F32)
@@ -65,3 +65,19 @@ def test_weight_gradient_of_a_narrow_layer_with_and_without_slices(M, N, K, beta
         assert rel_err(results[0][:, :N], ref) < 1e-5, floats
         assert np.array_equal(results[0][:, N:], old[:, N:]) and np.array_equal(results[0], results[1])
         assert torch.isnan(scratch[floats:]).all()                   # nothing behind the scratch is written
+
+
+@pytest.mark.parametrize("M,N,K,large", [(768, 768, 8192, False), (768, 768, 16384, True), (640, 640, 8192, False), (640, 640, 16392, True),
+                                         (256, 1024, 16384, False), (256, 1024, 40008, True), (128, 512, 40008, False)])
+def test_a_weight_gradient_over_a_long_k_range_leaves_the_small_tiles_in_time(M, N, K, large):
+    """Few tiles: the small kernel up to 8192 k for one of its workgroups, slices of large tiles beyond."""
+    rng = np.random.default_rng(M + K)
+    A, Bm = rnd(rng, (M, K), BF16), rnd(rng, (N, K), BF16)
+    Ad, Bd, out = to_dev(A, BF16), to_dev(Bm, BF16), torch.empty(M, N, device="cuda")
+    floats = B.lib.lga_op_gemm_splitk_slices(M, N, K) * M * N
+    scratch = torch.empty(floats, device="cuda")
+    kernels = profiled(lambda: B.check(B.lib.lga_op_gemm_splitk(BF16, M, N, K, Ad.data_ptr(), K, Bd.data_ptr(), K, out.data_ptr(), N, 0.0,
+                                                                scratch.data_ptr(), floats, None)))
+    assert any(k.startswith("gemm_bf16_dma_kernel") for k in kernels) == large, kernels.keys()
+    assert any(k.startswith("gemm_bf16_small_kernel") for k in kernels) != large
+    assert rel_err(out.cpu().numpy(), (Ad.float() @ Bd.float().T).cpu().numpy()) < 1e-5
