@@ -151,10 +151,10 @@ __global__ __launch_bounds__(256 * KG) void gemm_small_kernel(GemmParams<E> p, i
                 for (int j = 0; j < FN; ++j) acc[i][j] = mfma_16x16x32<E>(bf[j], af[i], acc[i][j]);
         }
     }
-    if constexpr (EPI == EPI_ACCUM_F32 && KG == 1 && BM == 128) {
-        // A whole 128 x 128 tile of fp32 results leaves from the registers, 64 bytes of 16 rows per instruction: with one workgroup on a
-        // compute unit nothing runs beside the way through LDS (1024 x 4096 x 512: 12.2 -> 10.9 us, 2048 x 2048 x 64: 8.5 -> 7.0; 64 x 64
-        // tiles, three on a unit, lose 1 to 3 %).
+    if constexpr (EPI == EPI_ACCUM_F32 && KG == 1 && BM == 128) if (gridDim.x <= 256) {
+        // A whole 128 x 128 tile of fp32 results leaves from the registers, 64 bytes of 16 rows per instruction, where compute units hold
+        // one workgroup: nothing would run beside the way through LDS (1024 x 4096 x 512, 256 tiles: 12.2 -> 10.9 us,
+        // 2048 x 2048 x 64: 8.5 -> 7.0; but 1280 x 3840 x 256, 300 tiles: 10.6 -> 11.4).
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
