@@ -265,6 +265,7 @@ struct lga_stack {
     LayerLayout lay;
     Plan plan;
     hipStream_t stream;
+    int device;              // the GPU that holds the arena
     char *arena;
     size_t P, T, t;          // params per layer, tokens per step, tokens per group
     // input_valid[l]: boundary l holds the input layer l's last forward saw, and the layer's weights have not
@@ -481,11 +482,18 @@ template <class T> struct ActivationGradient {
           groups(st->cfg.n_micro / st->cfg.group) {}
     const T *in(int gi) const { return src ? src + (size_t)gi * gstride : base + (size_t)(ring ? (first + gi) % ring : gi) * gstride; }
     T *out(int gi) const { return dst ? dst + (size_t)gi * gstride : base + (size_t)(ring ? (first + ring - wb + gi) % ring : gi) * gstride; }
-    // A caller's buffer that the kernels' 16-byte accesses can use and that is none of the stack's own (a borrowed checkpoint may be
-    // read or replaced in the middle of the sweep).
+    // A caller's buffer that the kernels' 16-byte accesses can use, that is none of the stack's own (a borrowed checkpoint may be
+    // read or replaced in the middle of the sweep) and that lies in the memory of the stack's GPU: the kernels read dy several times, which
+    // over a bus takes longer than the copy (pinned host memory), or not at all (another GPU without peer access).
     bool usable(const void *p) const {
         const char *c = static_cast<const char *>(p);
-        return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && (c + st->boundary_bytes() <= st->arena || c >= st->arena + st->plan.total);
+        if ((reinterpret_cast<uintptr_t>(p) & 15) != 0 || (c + st->boundary_bytes() > st->arena && c < st->arena + st->plan.total)) return false;
+        hipPointerAttribute_t at{};
+        if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+            (void)hipGetLastError();                         // memory the runtime does not know: the copy decides
+            return false;
+        }
+        return at.type == hipMemoryTypeDevice && at.device == st->device;
     }
     hipError_t begin(const void *dy, hipStream_t s) {
         if (usable(dy)) {
@@ -1063,7 +1071,9 @@ int lga_init_stack(const lga_config *cfg, const float *host_params, lga_stack **
     st->grad_pending.assign(st->ngrad, 0);
     st->restores = 0;
     st->arena = nullptr;
+    st->device = -1;
     hipError_t e = hipMalloc(reinterpret_cast<void **>(&st->arena), st->plan.total);
+    if (e == hipSuccess) e = hipGetDevice(&st->device);
     if (e != hipSuccess) {
         std::string msg = std::string("hipMalloc of ") + std::to_string(st->plan.total) + " bytes: " + hipGetErrorString(e);
         delete st;

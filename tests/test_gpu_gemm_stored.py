@@ -88,3 +88,29 @@ def test_gradient_buffers_that_overlap_or_are_misaligned(d, heads, ff, layers):
                 assert torch.equal(got, want), args
     finally:
         st.close()
+
+
+@pytest.mark.parametrize("d,heads,ff", [(1536, 12, 6144), (128, 2, 512)], ids=["ring", "in_place"])
+def test_gradient_buffers_in_pinned_host_memory_are_copied(d, heads, ff):
+    """A caller may keep dy and dx in pinned host memory: the sweep and the per-layer call give the bits of device buffers (and copy, instead
+    of reading dy over the bus in every kernel that wants it)."""
+    n_micro, s = 4, 80
+    cfg = B.make_config(1, d, heads, ff, s, 1, n_micro, BF16, group=1, retain_grads=1, wgrad_groups=2)
+    st = B.Stack(cfg, np.random.default_rng(1).standard_normal(B.params_per_layer(cfg)).astype(np.float32) * 0.02)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x, g = (torch.randn(n_micro * s * d, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    try:
+        results = []
+        for call in (st.backward_layered, lambda dy, dx, adam: st.backward_layer(0, dy, dx, adam)):
+            for host in (False, True):
+                dy, dx = (torch.zeros(g.numel(), dtype=torch.bfloat16, pin_memory=True) for _ in range(2)) if host else (g, torch.zeros_like(g))
+                if host:
+                    dy.copy_(g)
+                st.forward_layered(x.data_ptr(), None)
+                call(dy.data_ptr(), dx.data_ptr(), None)
+                torch.cuda.synchronize()
+                results.append([dx.cpu(), torch.from_numpy(B.read_device(*st.grads(0), "float32"))])
+        for got in results[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(got, results[0]))
+    finally:
+        st.close()
