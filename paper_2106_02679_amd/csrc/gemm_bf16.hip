@@ -971,7 +971,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 // (see launch_tiles).
 template <class E> int large_tile_slices(const GemmParams<E> &p) {
     const long big = (long)((p.M + 255) / 256) * ((p.N + 255) / 256);
-    const int slices = p.batch > 1 ? 1 : gemm_splitk_slices(p.M, p.N, p.K);
+    const int slices = p.batch > 1 || p.K == 0 ? 1 : gemm_splitk_slices(p.M, p.N, p.K);        // (its K = 0 means: of any length)
     const bool fits = slices > 1 && p.partial && (size_t)slices * p.M * p.N <= p.partial_floats && p.N % 4 == 0 && p.ldc % 4 == 0 &&
                       (reinterpret_cast<uintptr_t>(p.outf) & 15) == 0;
     if (fits && (big * slices >= 192 || (p.K >= 10240 && p.K / gemm_small_slices(p.M, p.N, p.K, p.partial_floats) >= 8192))) return slices;

@@ -265,7 +265,7 @@ template <int EPI> void launch_epi(const GemmParams<float> &p, bool akc, bool bk
                          ((EPI != EPI_BIAS && EPI != EPI_BIAS_RESID && EPI != EPI_BIAS_GELU) || al16(p.bias));
     GemmParams<float> q = p;
     q.ksplit = 1;
-    if (EPI == EPI_ACCUM_F32 && p.partial) {
+    if (EPI == EPI_ACCUM_F32 && p.partial && p.K > 0) {
         const int slices = gemm_f32_slices(p.M, p.N, p.K);
         if (slices > 1 && (size_t)slices * p.M * p.N <= p.partial_floats) {
             q.kchunk = ((p.K + slices - 1) / slices + TK - 1) / TK * TK;

@@ -311,3 +311,21 @@ def test_mfma_calibration_refuses_bad_arguments_before_touching_the_gpu():
     for iters, mode, s, t in ((0, 0, sink, C.byref(tf)), ((1 << 23) + 1, 0, sink, C.byref(tf)), (10, 2, sink, C.byref(tf)),
                               (10, 0, None, C.byref(tf)), (10, 0, sink, None)):
         assert B.lib.lga_op_mfma_rate(iters, mode, s, t, None) == B.LGA_ERR_ARG
+
+
+def test_a_weight_gradient_over_no_tokens_is_not_divided_into_slices():
+    """K = 0 is an empty sum.  Without a GPU the launch fails and says so; it must not take the process with it (the number of
+    slices for an unknown K, taken for K = 0, gave slices of no length: an integer division by zero)."""
+    import subprocess
+    import sys
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("a GPU is present: the launch would run")
+    code = ("import ctypes as C, sys; sys.path.insert(0, %r); from paper_2106_02679_amd import binding as B\n"
+            "b = C.create_string_buffer(1 << 10); p = (C.addressof(b) + 255) // 256 * 256\n"
+            "for m, n in ((768, 768), (2048, 2048), (64, 64), (4096, 4096)):\n"
+            "    print(B.lib.lga_op_gemm_splitk(B.LGA_BF16, m, n, 0, p, 8, p, 8, p, n, 0.5, p, 1 << 40, None))\n"
+            % os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
+    assert res.returncode == 0, res.returncode
+    assert res.stdout.split() == [str(B.LGA_ERR_HIP)] * 4

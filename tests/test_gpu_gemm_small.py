@@ -81,3 +81,12 @@ def test_a_weight_gradient_over_a_long_k_range_leaves_the_small_tiles_in_time(M,
     assert any(k.startswith("gemm_bf16_dma_kernel") for k in kernels) == large, kernels.keys()
     assert any(k.startswith("gemm_bf16_small_kernel") for k in kernels) != large
     assert rel_err(out.cpu().numpy(), (Ad.float() @ Bd.float().T).cpu().numpy()) < 1e-5
+
+
+@pytest.mark.parametrize("M,N", [(64, 64), (768, 768), (2048, 2048), (4096, 4096)])
+def test_a_weight_gradient_over_no_tokens_scales_what_is_there(M, N):
+    A, out = torch.empty(max(M, N), 8, device="cuda", dtype=torch.bfloat16), torch.randn(M, N, device="cuda")
+    want, scratch = 0.5 * out, torch.full((1 << 20,), float("nan"), device="cuda")
+    B.check(B.lib.lga_op_gemm_splitk(BF16, M, N, 0, A.data_ptr(), 8, A.data_ptr(), 8, out.data_ptr(), N, 0.5, scratch.data_ptr(), 1 << 20, None))
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
