@@ -8,7 +8,8 @@
 //    step's operands on their way from memory to registers while this one is multiplied, one barrier per step;
 //  - a workgroup holds KG = 1, 2 or 4 such groups, each of which takes its own part of the k range; their sums meet in
 //    LDS at the end, in group order (the result does not depend on scheduling), and every group then writes its
-//    share of the tile;
+//    share of the tile.  One group alone adds up the same parts in the same order, so that an activation does not depend
+//    on how many rows share its launch: the parts follow from K, only the groups from the number of tiles;
 //  - where even that leaves compute units idle, the k range is cut into slices over the grid and the partial results
 //    are added in slice order by a second kernel (only with scratch, i.e. for the stack's weight gradients).
 // Measured (one MI355X; before: plain FMA on 64 x 64 x 16 tiles, loads waited for at once, no split of k), averages over the
@@ -148,9 +149,9 @@ template <int EPI> __device__ __forceinline__ void epilogue_f32(const GemmParams
 }
 
 // grid: (n tiles, m tiles, k slices); block: 256 KG threads.  vec_out: every tensor the epilogue touches takes 16-byte accesses
-// at columns that are multiples of 4.
+// at columns that are multiples of 4.  log_parts: into 1, 2 or 4 parts the k range is cut for the order of the sums; with KG > 1 KG of them.
 template <int EPI, int KG>
-__global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(GemmParams<float> p, bool a_kc, bool b_kc, bool vec_out) {
+__global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(GemmParams<float> p, bool a_kc, bool b_kc, bool vec_out, int log_parts) {
     extern __shared__ __attribute__((aligned(16))) float smem_f32[];
     const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -166,17 +167,20 @@ __global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(GemmParams<float> p,
             p.beta = 0.f;
         }
     }
-    // the k range of this group: whole steps, the same number for every group (a group whose part is empty reads zeros)
-    const int steps = ((kstop - kbeg + TK - 1) / TK + KG - 1) / KG;
-    const int kg0 = kbeg + group * steps * TK;
+    // a part of the k range: whole steps, the same number for every part; a group has one (and reads zeros if it is empty), or
+    // one group has all
+    const int all = (kstop - kbeg + TK - 1) / TK, part = KG == 1 ? (all + (1 << log_parts) - 1) >> log_parts : (all + KG - 1) / KG;
+    const int steps = KG == 1 ? all : part;
+    const int kg0 = kbeg + group * part * TK;
     float *lds = smem_f32 + group * (4 * kTileFloats);           // two stages of A and B
 
     Loader la, lb;
     la.init(p.A, m0, p.M, p.lda, a_kc, kstop, t);
     lb.init(p.B, n0, p.N, p.ldb, b_kc, kstop, t);
-    f32x16 acc;
+    f32x16 acc, done;                                            // of the part at hand; of the parts before it (KG = 1)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[r] = done[r] = 0.f;
+    int left = part;
 
     if (steps > 0) {
         la.load(kg0);
@@ -206,6 +210,14 @@ __global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(GemmParams<float> p,
             la.store(nxt);
             lb.store(nxt + kTileFloats);
         }
+        if (KG == 1 && --left == 0) {                            // end of a part (behind the stores, which leave the products time to finish)
+            left = part;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                done[r] += acc[r];
+                acc[r] = 0.f;
+            }
+        }
         __syncthreads();
     }
 
@@ -215,8 +227,10 @@ __global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(GemmParams<float> p,
     if constexpr (KG == 1) {
         if (m >= p.M) return;
 #pragma unroll
+        for (int r = 0; r < 16; ++r) done[r] += acc[r];
+#pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (nq + 8 * q < p.N) epilogue_f32<EPI>(p, m, nq + 8 * q, f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]}, vec_out);
+            if (nq + 8 * q < p.N) epilogue_f32<EPI>(p, m, nq + 8 * q, f32x4{done[4 * q], done[4 * q + 1], done[4 * q + 2], done[4 * q + 3]}, vec_out);
     } else {
         // every group leaves its sums in LDS (the loop's last barrier has passed); group g then adds up column quads
         // g, g + KG, ... of all groups, in group order
@@ -277,13 +291,14 @@ template <int EPI> void launch_epi(const GemmParams<float> &p, bool akc, bool bk
     const int k_each = q.ksplit > 1 ? q.kchunk : p.K;
     // Groups per workgroup: as many as have at least one step each, while the grid leaves room for their wavefronts - a
     // compute unit holds 32 of them, so from 512 tiles on single groups already fill the chip twice.
-    const int kg = tiles * q.ksplit >= 512 ? 1 : k_each > 2 * TK ? 4 : k_each > TK ? 2 : 1;
+    const int most = k_each > 2 * TK ? 4 : k_each > TK ? 2 : 1, kg = tiles * q.ksplit >= 512 ? 1 : most;
+    const int log_parts = (EPI == EPI_ACCUM_F32 ? kg : most) >> 1;          // a weight gradient's k range differs with the grouping anyway
     {
         const double mn = (double)p.M * p.N;
         ProfScope scope("gemm_f32_kernel", 2.0 * mn * p.K, 4.0 * ((double)p.M * p.K + (double)p.K * p.N + mn), s);
-        if (kg == 4) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 4>), grid, dim3(1024), smem_bytes(4), s, q, akc, bkc, vo);
-        else if (kg == 2) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2>), grid, dim3(512), smem_bytes(2), s, q, akc, bkc, vo);
-        else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1>), grid, dim3(256), smem_bytes(1), s, q, akc, bkc, vo);
+        if (kg == 4) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 4>), grid, dim3(1024), smem_bytes(4), s, q, akc, bkc, vo, log_parts);
+        else if (kg == 2) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2>), grid, dim3(512), smem_bytes(2), s, q, akc, bkc, vo, log_parts);
+        else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1>), grid, dim3(256), smem_bytes(1), s, q, akc, bkc, vo, log_parts);
     }
     if (q.ksplit > 1) {
         ProfScope scope("gemm_f32_reduce_kernel", (double)q.ksplit * p.M * p.N, 4.0 * p.M * p.N * (q.ksplit + (p.beta != 0.f ? 2.0 : 1.0)), s);

@@ -68,3 +68,33 @@ def test_fp32_stack_with_weight_gradients_over_slices_of_the_tokens(d, heads, ff
     got = [run_gpu_step(w, x, G, params, group=group, retain=1, adam=adam) for _ in range(2)]
     compare_with_oracle(w, got[0], ref, 1e-5, adam, zero_init=False)
     assert np.array_equal(got[0]["grads"][0], got[1]["grads"][0])
+
+
+@pytest.mark.parametrize("K", [1, 32, 33, 64, 65, 96, 100, 129, 160, 1000, 1024])
+def test_a_row_of_the_result_does_not_depend_on_the_number_of_rows(K):
+    """More and more rows, on both sides of the 512 tiles from which on one group of wavefronts has the whole k range: each prefix bit for
+    bit the same."""
+    N, rows = 1030, (1, 64, 500, 1900, 2000)                      # 17 tiles across, 31 and 32 down
+    rng = np.random.default_rng(K)
+    A, Bm = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)).cuda() for s in ((rows[-1], K), (K, N)))
+    bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).cuda()
+    full = None
+    for M in reversed(rows):
+        out, out2 = torch.zeros(M, N, device="cuda"), torch.zeros(M, N, device="cuda")
+        B.check(B.lib.lga_op_gemm(B.LGA_FP32, 1, 0, B.LGA_EPI_BIAS_GELU, M, N, K, A.data_ptr(), K, Bm.data_ptr(), N, out.data_ptr(),
+                                  out2.data_ptr(), None, N, bias.data_ptr(), None, 0.0, None))
+        torch.cuda.synchronize()
+        full = full or (out, out2)
+        assert torch.equal(out, full[0][:M]) and torch.equal(out2, full[1][:M]), M
+
+
+def test_fp32_orders_and_group_sizes_agree_bit_for_bit():
+    """The size of the paper's X_16 as its encoder: the first feed-forward GEMM has 512, 256 and 128 tiles at groups of 4, 2 and 1
+    micro-batches."""
+    w = S.Workload("fp32_groups", 1, 256, 8, 1024, 256, 2, 4, "fp32")
+    x, G, params = S.make_inputs(w, seed=5)
+    runs = [run_gpu_step(w, x, G, params, group=g, retain=1, attention=B.LGA_ATTN_FULL) for g in (1, 2, 4)]
+    runs.append(run_gpu_step(w, x, G, params, retain=1, order="mbmajor", attention=B.LGA_ATTN_FULL))
+    for got in runs[1:]:
+        assert np.array_equal(got["boundaries"], runs[0]["boundaries"]) and np.array_equal(got["dx"], runs[0]["dx"])
+        assert rel_err(got["grads"][0], runs[0]["grads"][0]) < 1e-5
