@@ -1,5 +1,5 @@
 // Softmax attention (causal or unmasked) on fp32 tensors with the fp32 matrix instruction, head sizes up to 128; all scores,
-// probabilities and sums in fp32.  Larger heads keep the one-wavefront-per-position kernels.
+// probabilities and sums in fp32.  Larger heads and sequences of up to 48 positions keep the one-wavefront-per-position kernels.
 //
 // A wavefront works on 32 positions (queries in the forward and the dQ kernel, keys in the dK/dV kernel) against blocks of 32
 // positions of the other kind.  The score block is produced transposed (streamed positions = first operand of the
@@ -310,8 +310,15 @@ bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 }  // namespace
 
 // Up to 128 channels a wavefront's operands and accumulators fit its registers (dK/dV: 4 x dh / 2 of them); 32 rows of [Q | K | V]
-// lie inside the buffer loads' range.
-bool attn_f32_supports(AttnShape sh) { return sh.dh <= 128 && (double)sh.heads * sh.dh * 12 * 32 < kRange; }
+// lie inside the buffer loads' range.  Short sequences stay with one wavefront per position: they give this kernel one or two streamed
+// blocks, most of its wavefronts nothing to do, and its chain of 32-position products is longer than theirs until there are so many
+// heads that theirs fill the chip.  Backward of n heads in all, us here [one wavefront per position], where the two meet:
+//   s    dh 32                                                 dh 128
+//   32   8: 15 [9]     64: 15 [14]    512: 19 [67]             8: 43 [19]    64: 43 [35]    512: 91 [261]
+//   48   8: 16 [10]    64: 16 [19]    512: 35 [94]             8: 44 [24]    64: 44 [53]    512: 166 [395]
+//   64   8: 15 [16]    64: 15 [40]    512: 38 [239]            8: 42 [31]    64: 43 [144]   512: 173 [919]
+// By the length and not by the number of heads in the launch: a sequence's results must not depend on how many share it.
+bool attn_f32_supports(AttnShape sh) { return sh.s > 48 && sh.dh <= 128 && (double)sh.heads * sh.dh * 12 * 32 < kRange; }
 
 #define LGA_ATTN_F32_DH(dh, CALL)           \
     do {                                    \

@@ -1,6 +1,6 @@
 // Softmax attention (causal or unmasked), correctness-mode kernels: one wavefront per (sequence, head, position).
-// Scores, softmax and all sums in fp32; T is the storage type.  Serves what the faster kernels do not: fp32 heads above 128
-// (attention_f32.hip takes the others, 5 to 10 times faster) and 16-bit heads above 160 at lengths that are no multiple of 8.
+// Scores, softmax and all sums in fp32; T is the storage type.  Serves what the faster kernels do not: fp32 heads above 128 and fp32
+// sequences of up to 48 positions (attention_f32.hip takes the others) and 16-bit heads above 160 at lengths that are no multiple of 8.
 #include <type_traits>
 
 #include "kernels.h"

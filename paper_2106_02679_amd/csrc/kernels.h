@@ -156,7 +156,7 @@ template <class T> void launch_attn_fwd_simple(const T *qkv, T *out, float *lse,
 template <class T>
 void launch_attn_bwd_simple(const T *qkv, const T *out, const float *lse, const T *dout, T *dqkv, float *delta,
                             AttnShape sh, hipStream_t s);
-// The same on fp32 tensors with the fp32 matrix instruction (attention_f32.hip), head sizes up to 128.
+// The same on fp32 tensors with the fp32 matrix instruction (attention_f32.hip), head sizes up to 128 and more than 48 positions.
 bool attn_f32_supports(AttnShape sh);
 void launch_attn_fwd_f32(const float *qkv, float *out, float *lse, AttnShape sh, hipStream_t s);
 void launch_attn_bwd_f32(const float *qkv, const float *out, const float *lse, const float *dout, float *dqkv, float *delta,

@@ -8,7 +8,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from paper_2106_02679_amd import binding as B
-from gpu_helpers import rel_err
+from gpu_helpers import rel_err, profiled
 from test_gpu_ops import attention_reference
 
 
@@ -66,3 +66,22 @@ def test_fp32_causal_attention_keeps_the_future_out_even_if_it_is_not_finite(s, 
     want = attention_reference(qkv, np.concatenate([np.zeros_like(dout[:1]), dout[1:]]), 1, s, 1, dh, True)
     _, _, dqkv = run(q2, d2, 1, s, 1, dh, True)
     assert rel_err(dqkv[1:, dh:], want[2][1:, dh:]) < 2e-5
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh", [8, 10, 32, 64, 128])
+def test_fp32_attention_on_either_side_of_the_length_from_which_on_the_matrix_instruction_serves_it(dh, causal):
+    for n_seq, s, heads, matrix in ((1, 16, 2, False), (2, 48, 1, False), (1, 49, 2, True), (2, 63, 1, True), (1, 64, 3, True), (1, 65, 1, True),
+                                    (1, 97, 2, True)):
+        rng = np.random.default_rng(dh * 1000 + s)
+        qkv = rng.standard_normal((n_seq * s, 3 * heads * dh)).astype(np.float32)
+        dout = rng.standard_normal((n_seq * s, heads * dh)).astype(np.float32)
+        want, got = attention_reference(qkv, dout, n_seq, s, heads, dh, causal), []
+        kernels = profiled(lambda: got.append(run(qkv, dout, n_seq, s, heads, dh, causal)))
+        assert any(k.startswith("attn_fwd_f32") for k in kernels) == any(k.startswith("attn_bwd_dq_f32") for k in kernels) == matrix
+        assert any(k.startswith("attn_fwd_simple") for k in kernels) == any(k.startswith("attn_bwd_simple") for k in kernels) != matrix
+        assert rel_err(got[0][0], want[0]) < 1e-5, (s, heads)
+        assert np.abs(got[0][1] - want[1]).max() < 1e-5 * max(1.0, np.abs(want[1]).max()), (s, heads)
+        d = heads * dh
+        for i in range(3):
+            assert rel_err(got[0][2][:, i * d:(i + 1) * d], want[2][:, i * d:(i + 1) * d]) < 2e-5, (s, heads, "dq dk dv".split()[i])
