@@ -134,6 +134,69 @@ template <int DH> struct BothAddr {
     }
 };
 
+// The same addresses as LDS byte addresses of tiles in one of two stages, moved from one stage to the other in place: one register
+// each and nothing else, where the reads above keep the element offset beside the sum of it and the stage.
+template <int DH, int STAGE_BYTES> struct BothStages {
+    static constexpr int NG = BothAddr<DH>::NG;
+    int nb[NG][2], tb[NG][2];
+    __device__ __forceinline__ void init(const void *lds, int lane) {
+        BothAddr<DH> ad;
+        ad.init(lane);
+        const int base = (int)(uintptr_t)(lds_ptr)lds;
+#pragma unroll
+        for (int a = 0; a < NG; ++a)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                nb[a][e] = base + 2 * ad.nb[a][e];
+                tb[a][e] = base + 2 * ad.tb[a][e];
+            }
+    }
+    // to the other stage; opaque, or the compiler goes back to a sum per tile
+    __device__ __forceinline__ void move(bool up) {
+        const int by = up ? STAGE_BYTES : -STAGE_BYTES;
+#pragma unroll
+        for (int a = 0; a < NG; ++a)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                nb[a][e] += by;
+                tb[a][e] += by;
+                asm volatile("" : "+v"(nb[a][e]), "+v"(tb[a][e]));
+            }
+    }
+    // tile: byte offset of the tile in its stage
+    template <class E> __device__ __forceinline__ x8<E> nat(int tile, int u, int ks) const {
+        const int a = ks >> 1;
+        typedef __attribute__((address_space(3))) const x8<E> *ptr;
+        return *(ptr)(uintptr_t)(uint32_t)(nb[a % NG][ks & 1] + tile + (32 * u * DH + 32 * NG * (a / NG)) * 2);
+    }
+    template <class E> __device__ __forceinline__ x8<E> tr(int tile, int c, int kk) const {
+        u32x2 lo, hi;
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(tb[c % NG][0]), "i"(tile + (16 * kk * DH + 32 * NG * (c / NG)) * 2));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(tb[c % NG][1]), "i"(tile + (16 * kk * DH + 32 * NG * (c / NG)) * 2));
+        const u32x4 v = {lo[0], lo[1], hi[0], hi[1]};
+        return __builtin_bit_cast(x8<E>, v);
+    }
+};
+
+// Row operands of a chain of products, read AHEAD k steps before they are multiplied and no further: left alone the compiler reads all
+// of a tile's at once, and their registers push others into scratch memory.  load(ks, slot), multiply(ks, slot): slots
+// 0 ... AHEAD + 1.
+template <int NK, int AHEAD, class L, class M> __device__ __forceinline__ void products_ahead(L load, M multiply) {
+    constexpr int SLOTS = AHEAD + 2;
+#pragma unroll
+    for (int ks = 0; ks < AHEAD && ks < NK; ++ks) load(ks, ks % SLOTS);
+#pragma unroll
+    for (int ks = 0; ks < NK; ks += 2) {
+#pragma unroll
+        for (int i = AHEAD; i < AHEAD + 2; ++i)
+            if (ks + i < NK) load(ks + i, (ks + i) % SLOTS);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(ks, ks % SLOTS);
+        if (ks + 1 < NK) multiply(ks + 1, (ks + 1) % SLOTS);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // Workgroup -> ((sequence, head), block rank) for a 1-D grid of n_seq * heads * nblocks workgroups, which the
 // hardware hands out in index order.  With the causal mask a (sequence, head)'s blocks differ in length by up to
 // the number of blocks: rank is the slow index, so every (sequence, head)'s longest block (rank 0) starts before

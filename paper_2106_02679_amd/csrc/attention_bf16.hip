@@ -434,8 +434,8 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const E *__restrict__ o
 // from global memory straight into one of two LDS stages while the other is multiplied, one barrier per
 // tile.  K^T operands come from the natural K tile through the transposing LDS read.  Two workgroups per
 // CU, so that one's MFMAs run under the other's VALU work - which needs tiles of DH elements per row, swizzled: with padded rows
-// the two stages take 90 KB at DH = 128 and only one workgroup fits (16 heads x 8100 positions x 128, causal: 605 us; now 478, and no
-// bank conflicts instead of a quarter of the LDS cycles; 384 x 1024 x 64: 142 -> 118).
+// the two stages take 90 KB at DH = 128 and only one workgroup fits (16 heads x 8100 positions x 128, causal: 485 us; now 395, and no
+// bank conflicts instead of a quarter of the LDS cycles; 384 x 1024 x 64: 121 -> 108).
 template <int DH, int OCC, class E>
 __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restrict__ qkv, const float *__restrict__ lse,
                                                           const float *__restrict__ delta,
@@ -489,14 +489,24 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
         dma.issue(seq + (size_t)k0 * pitch + d, Ks, sh.s - k0, wave);
         dma.issue(seq + (size_t)k0 * pitch + 2 * d, Ks + TILE, sh.s - k0, wave);
     };
-    BothAddr<DH> ad;
-    ad.init(lane);
+    // From 128 channels on the registers hold neither all row operands of a block nor a second copy of the read addresses.  Left to itself
+    // the compiler spilled 7 of them inside this loop, reloaded them behind the next tile's loads and so waited for those
+    // before the first product: 4 heads x 4096 x 128, one workgroup on a compute unit, 138 us; 104 without (32 heads x 2048, two on each:
+    // 86 and 73).  Below 128 there is room, and the reads in one go are the faster ones (32 channels: 54 us, 57 in this form).
+    constexpr bool TIGHT = DH >= 128;
+    std::conditional_t<TIGHT, BothStages<DH, STAGE * 2>, BothAddr<DH>> ad;
+    if constexpr (TIGHT) ad.init(lds, lane);
+    else ad.init(lane);
 
     const bool causal = sh.causal != 0;
     const int kend = causal ? min(sh.s, qb * 128 + 128) : sh.s;
     dma_tile(0, 0);
     int stage = 0;
-    for (int k0 = 0; k0 < kend; k0 += KT, stage ^= 1) {
+    auto next_stage = [&]() __attribute__((always_inline)) {
+        stage ^= 1;
+        if constexpr (TIGHT) ad.move(stage != 0);
+    };
+    for (int k0 = 0; k0 < kend; k0 += KT, next_stage()) {
         // this wavefront's part of tile k0 has landed and its LDS reads of the previous tile have returned; after
         // the barrier the tile is published and the other stage is free for the next one
         __builtin_amdgcn_s_waitcnt(0x0070);
@@ -513,18 +523,30 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
             if (causal ? kbs > qw0 : kbs >= sh.s) continue;
             // last visible key of this lane's query, relative to the block: the query itself, or the end of the sequence
             const int klast = causal ? qw0 + lrow - kbs : sh.s - 1 - kbs;
-            x8<E> kf[NK], vfr[NK], ktf[2 * NC];
-#pragma unroll
-            for (int ks = 0; ks < NK; ++ks) {
-                kf[ks] = ad.nat(Ks, kb, ks);
-                vfr[ks] = ad.nat(Vs, kb, ks);
-            }
+            constexpr int AHEAD = 4, SLOTS = TIGHT ? AHEAD + 2 : NK;
+            x8<E> kf[SLOTS], vfr[SLOTS], ktf[2 * NC];
             f32x16 st, dpt;
-#pragma unroll
-            for (int ks = 0; ks < NK; ++ks) {
+            auto load = [&](int ks, int i) __attribute__((always_inline)) {
+                if constexpr (TIGHT) {
+                    kf[i] = ad.template nat<E>(0, kb, ks);
+                    vfr[i] = ad.template nat<E>(TILE * 2, kb, ks);
+                } else {
+                    kf[i] = ad.nat(Ks, kb, ks);
+                    vfr[i] = ad.nat(Vs, kb, ks);
+                }
+            };
+            auto multiply = [&](int ks, int i) __attribute__((always_inline)) {
                 const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                st = MFMA(kf[ks], qf[ks], ks == 0 ? zero : st);
-                dpt = MFMA(vfr[ks], dof[ks], ks == 0 ? zero : dpt);
+                st = MFMA(kf[i], qf[ks], ks == 0 ? zero : st);
+                dpt = MFMA(vfr[i], dof[ks], ks == 0 ? zero : dpt);
+            };
+            if constexpr (TIGHT) {
+                products_ahead<NK, AHEAD>(load, multiply);
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < NK; ++ks) load(ks, ks);
+#pragma unroll
+                for (int ks = 0; ks < NK; ++ks) multiply(ks, ks);
             }
             // the K^T operands take over the registers of the K and V operands; their latency passes under the
             // exponentials
@@ -532,7 +554,10 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-                for (int c = 0; c < NC; ++c) ktf[kk * NC + c] = ad.tr(Ks, c, 2 * kb + kk);
+                for (int c = 0; c < NC; ++c) {
+                    if constexpr (TIGHT) ktf[kk * NC + c] = ad.template tr<E>(0, c, 2 * kb + kk);
+                    else ktf[kk * NC + c] = ad.tr(Ks, c, 2 * kb + kk);
+                }
             __builtin_amdgcn_sched_barrier(0);
             if (causal ? kbs == qw0 : kbs + 32 > sh.s) {     // the diagonal block, or the ragged last one: masked keys
 #pragma unroll
@@ -641,8 +666,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(const E *__restric
         dq_.issue(seq + (size_t)q0 * pitch, lds + stage * STAGE, sh.s - q0, wave);
         do_.issue(doseq + (size_t)q0 * d, lds + stage * STAGE + TILE, sh.s - q0, wave);
     };
-    // (the value is left as loaded until it is stored: any arithmetic on it here would wait for the load, and with it for every
-    // tile in flight)
+    // (the value is left as loaded until it is stored a tile later: arithmetic on it here would wait for it, and with it for every tile
+    // in flight, at once.  The store still waits for the tiles that are in flight then.)
     auto load_stat = [&](int t) -> float {
         const int qq = min(qbeg + QT * t + lane, sh.s - 1);
         return wave == 0 ? lse[stat0 + qq] : delta[stat0 + qq];
@@ -778,8 +803,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(const E *__restric
         // pipe's cycles at 128 channels):
         //   phase A of unit n   S, dP of unit n + 1  |  P, dS of unit n, its transposed reads
         //   phase B of unit n   dV, dK of unit n     |  row reads of unit n + 2
-        // 16 heads x 8100 positions x 128, causal: 3670 -> 2270 cycles a unit (1024 of them matrix instructions), 775 -> 693 us; what is
-        // left is the 32 moves a unit out of accumulation registers, LDS waits and the barrier per tile.
+        // 16 heads x 8100 positions x 128, causal: 3670 -> 2270 cycles a unit (1024 of them matrix instructions), 590 -> 550 us; what is
+        // left is the 32 moves a unit out of accumulation registers, LDS waits, the barrier per tile and, in the two wavefronts that
+        // carry the statistics, a wait for every tile in flight where they store them.
         // Unit n + 2 may lie in the next tile, which is published in phase B of the tile's first unit; the tile itself is still read
         // in the phases after that, which is what the fourth stage is for.
         if (t < ntiles) {

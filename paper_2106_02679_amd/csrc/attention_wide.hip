@@ -34,24 +34,9 @@ template <int NEWER> __device__ __forceinline__ void publish_tile(bool newer) {
 }
 __device__ __forceinline__ f32x16 zero16() { return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; }
 
-// Row operands are read kAhead k steps ahead of their products - enough for the LDS latency with four wavefronts reading - and no
-// further: left alone the compiler reads all of a tile's at once, and their registers push the accumulators into scratch memory.
-// load(ks, slot), multiply(ks, slot): slots 0 ... kSlots - 1.
+// far enough ahead for the LDS latency with four wavefronts reading
 constexpr int kAhead = 6, kSlots = kAhead + 2;
-template <int NK, class L, class M> __device__ __forceinline__ void products(L load, M multiply) {
-#pragma unroll
-    for (int ks = 0; ks < kAhead && ks < NK; ++ks) load(ks, ks % kSlots);
-#pragma unroll
-    for (int ks = 0; ks < NK; ks += 2) {
-#pragma unroll
-        for (int i = kAhead; i < kAhead + 2; ++i)
-            if (ks + i < NK) load(ks + i, (ks + i) % kSlots);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(ks, ks % kSlots);
-        if (ks + 1 < NK) multiply(ks + 1, (ks + 1) % kSlots);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
+template <int NK, class L, class M> __device__ __forceinline__ void products(L load, M multiply) { products_ahead<NK, kAhead>(load, multiply); }
 
 constexpr int kTile = 32;
 // two workgroups per compute unit where registers and LDS (two stages) allow it, else one with three stages

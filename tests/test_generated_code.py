@@ -193,3 +193,11 @@ def test_no_instruction_reads_an_accumulator_that_a_matrix_instruction_is_updati
                 assert since >= 32 or not any(kind == "a" for kind, _ in registers(t)), (name, t)
                 since += int(nop.group(1)) + 1 if nop else 1
     assert checked == 14
+
+
+def test_the_attention_kernels_up_to_160_channels_spill_nothing():
+    """A spilled register is reloaded with the counter that the tiles in flight use: a reload inside the loop over the tiles waits for the
+    next tile before the present one is multiplied."""
+    spills = re.findall(r"\.symbol:\s+(\S+)\.kd.*?\.vgpr_spill_count:\s+(\d+)", assembly("attention_bf16.hip"), re.S)
+    assert len(spills) >= 30
+    assert [s for s in spills if int(s[1])] == []
