@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 from oracle import lga_oracle as O
 import synth_inputs as S
 from paper_2106_02679_amd import binding as B
-from gpu_helpers import run_gpu_step, oracle_shape, rel_err, compare_with_oracle
+from gpu_helpers import run_gpu_step, oracle_shape, rel_err, compare_with_oracle, profiled
 from test_gpu_ops import check_gemm, BF16, F16
 
 SHAPES = [  # at least 128 tiles of 256 x 256, whole and ragged; k of one, two and three steps of 64, and of the unrolled loop's lengths
@@ -43,15 +43,28 @@ def test_stack_whose_weight_gradients_take_stored_operands(overlap):
 
 
 def test_narrow_stack_whose_weight_gradients_take_stored_operands_in_slices():
-    """12288 tokens per group: the few output tiles of a narrow layer, their k range in slices."""
-    w = S.Workload("stored_slices_bf16", 1, 512, 8, 2048, 512, 24, 2, "bf16")
+    """The few output tiles of a narrow layer, their k range in slices: W_1 and W_2 of a 768-wide layer over 8200 tokens in 7 of 1216
+    tokens (the last 904, no whole number of steps), W_qkv in 8 of 1088 (584); over 16400 tokens in 7 of 2368 (2192) and others.
+    The slices cut the tokens elsewhere in every grouping, so that a token left out or taken twice would show."""
+    w = S.Workload("stored_slices_bf16", 1, 768, 12, 3072, 1025, 8, 2, "bf16")
     x, G, params = S.make_inputs(w, seed=4)
-    one, both = (run_gpu_step(w, x, G, params, retain=1, wgrad_groups=wb) for wb in (1, 2))
-    exact = run_gpu_step(S.Workload("stored_slices_fp32", 1, 512, 8, 2048, 512, 24, 2, "fp32"), x, G, params, retain=1)
-    assert np.array_equal(one["dx"], both["dx"])
-    assert rel_err(one["grads"][0], both["grads"][0]) < 1e-5
+    runs = []
+
+    def step(**kw):
+        kernels = profiled(lambda: runs.append(run_gpu_step(w, x, G, params, retain=1, **kw)))
+        sliced = [k["launches"] for n, k in kernels.items() if n.startswith("gemm_bf16_dma_tn_kernel")]
+        return sum(sliced), kernels["splitk_reduce_kernel"]["launches"] if "splitk_reduce_kernel" in kernels else 0
+
+    assert step(wgrad_groups=1) == (6, 6)                    # three matrices of either group; W_o on small tiles from transposed copies
+    assert step(wgrad_groups=2) == (3, 4)                    # both groups in one: W_o still transposed, but in slices of large tiles
+    assert step(group=2) == (4, 4)                           # one group of 16400 tokens: all four
+    assert step(order="mbmajor") == (6, 6)
+    exact = run_gpu_step(S.Workload("stored_slices_fp32", 1, 768, 12, 3072, 1025, 8, 2, "fp32"), x, G, params, retain=1)
+    for got in runs[1:]:
+        assert np.array_equal(got["dx"], runs[0]["dx"]) and np.array_equal(got["boundaries"], runs[0]["boundaries"])
+        assert rel_err(got["grads"][0], runs[0]["grads"][0]) < 1e-5
     for name, sl in S.tensor_slices(w.d_model, w.d_ff).items():
-        assert rel_err(both["grads"][0][sl], exact["grads"][0][sl]) < 2e-2, name
+        assert rel_err(runs[0]["grads"][0][sl], exact["grads"][0][sl]) < 2e-2, name
 
 
 @pytest.mark.parametrize("d,heads,ff", [(1536, 12, 6144), (128, 2, 512)], ids=["ring", "in_place"])
