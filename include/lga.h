@@ -178,10 +178,10 @@ int lga_loss_scaler_update(lga_loss_scaler *scaler, int32_t overflowed);
  * 2 097 151 elements (3 d_model, d_ff, group * micro_batch * seq_len + 64, and with an explicit wgrad_groups that
  * many groups' tokens + 64; the automatic wgrad_groups stays within it).  Head sizes up to 160 have MFMA attention kernels in the 16-bit modes
  * (built for 32, 64, 96, 128, 160; sizes in between run in the next larger one).  Larger head sizes (table B.1's
- * X_[x] family has d_h = 2 x) run, when seq_len is a multiple of 8 (at most 32768), in fused kernels up to 320 and otherwise
+ * X_[x] family has d_h = 2 x) run, when seq_len is a multiple of 8 (at most 32768), in fused kernels (up to 320, enough heads) or
  * as an attention built from batched GEMMs over the heads; the arena then holds one sequence's score matrices,
- * 12 seq_len^2 bytes per head for as many heads as fit 4 GiB.  Otherwise, and in the fp32 mode for head sizes above 128, a
- * one-wavefront-per-position kernel is used that is meant for checking, not for speed; it limits seq_len
+ * 12 seq_len^2 bytes per head for as many heads as fit 4 GiB.  Otherwise, and in the fp32 mode for head sizes above 128 and
+ * for up to 48 positions, a one-wavefront-per-position kernel is used; it limits seq_len
  * (2 seq_len + 2 d_h <= 15000), as the fp32 mode does for all head sizes.  LGA_ERR_OOM if the arena does not
  * fit. */
 int lga_init_stack(const lga_config *cfg, const float *host_params, lga_stack **out);

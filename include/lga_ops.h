@@ -108,10 +108,9 @@ uint64_t lga_op_colsum_static_max_floats(void);
  *  qkv  [n_seq*s, 3*heads*dh]: columns [Q | K | V], head h at columns h*dh inside each third
  *  out  [n_seq*s, heads*dh]
  *  lse  [n_seq, heads, s] float: log sum_j exp(scaled score_ij)
- * kind 0: any dtype, any dh - one wavefront per position, but for fp32 with dh up to 128, which runs on the fp32 matrix
- * instruction; kind 1: MFMA kernel with
- * LDS-resident online softmax (16-bit, dh a multiple of 8 up to 160; head sizes other than 32, 64, 96, 128, 160
- * run in the next larger of those kernels with the extra columns read as zeros). */
+ * kind 0: any dtype, any dh - one wavefront per position, but for fp32 with dh up to 128 and s above 48, which runs on the
+ * fp32 matrix instruction; kind 1: MFMA kernel with LDS-resident online softmax (16-bit, dh a multiple of 8 up to 160; head
+ * sizes other than 32, 64, 96, 128, 160 run in the next larger of those kernels with the extra columns read as zeros). */
 int lga_op_attention_fwd(int32_t dtype, int32_t kind, const void *qkv, void *out, float *lse, int32_t n_seq,
                          int32_t s, int32_t heads, int32_t dh, int32_t causal, void *stream);
 /* dqkv [n_seq*s, 3*heads*dh] written; delta [n_seq, heads, s] float scratch (written). */
@@ -120,8 +119,9 @@ int lga_op_attention_bwd(int32_t dtype, int32_t kind, const void *qkv, const voi
                          int32_t dh, int32_t causal, void *stream);
 
 /* The same attention for head sizes beyond 160 (table B.1's X_[x] family has d_h = 2 x: 216, 320).  Head sizes of 161 to 320 run in
- * fused kernels that leave the workspace alone (the backward of few heads above 224 excepted); the others are built from batched GEMMs over the heads with the score matrices in a workspace: S = Q K^T in fp32, a row kernel for the
- * softmax (P rounded to 16 bits) and O = P V; backward S and dP = dO V^T in fp32, a row kernel for P, delta and dS, then
+ * fused kernels that leave the workspace alone where one sequence has heads and positions enough for them; the others are built
+ * from batched GEMMs over the heads with the score matrices in a workspace: S = Q K^T in fp32, a row kernel for the softmax
+ * (P rounded to 16 bits) and O = P V; backward S and dP = dO V^T in fp32, a row kernel for P, delta and dS, then
  * dV = P^T dO, dQ = dS K, dK = dS^T Q.  Arguments and results as above (16-bit dtypes only).  s and dh multiples of 8,
  * s <= 32768.  workspace: device, 256-byte aligned, at least lga_op_attention_gemm_workspace_bytes(s, 1) = 12 s^2 bytes;
  * up to ..._bytes(s, heads) lets that many heads share each launch.  Contents are scratch. */
