@@ -2,8 +2,9 @@
 // the manner of the kernels for smaller heads: 32 positions per wavefront, score blocks produced transposed so that a lane owns one
 // position, tiles straight into LDS and read both ways.
 //
-// dS = P (dP - delta) / sqrt(d_h) is rounded to 16 bits with the factor in it: without, it leaves half precision's range at gradients
-// sqrt(d_h) times smaller.
+// dS = P (dP - delta) / sqrt(d_h) is rounded to half precision with the factor in it: without, it leaves that format's range at
+// gradients sqrt(d_h) times smaller.  bfloat16 has the range, and the factor goes into the finished sums (as a multiplication per score
+// it would cost the joint dK/dV kernel 8 %).
 //
 // What differs is what a wavefront's registers hold.  Forward: 32 queries instead of 64 (one accumulator block of 32 x DH); the softmax
 // reference moves only when a score exceeds it by kLazy, so that the accumulators are rescaled in a few tiles of a row.  dQ:
@@ -11,8 +12,8 @@
 // once per result (the scores are computed in both: 5 products instead of 4).  Tiles are 32 positions long.
 //
 // Against the path through memory that served these heads (batched GEMMs with fp32 score matrices and two row kernels, 12 s^2
-// bytes per head), causal, forward / backward in us: 2 x 54 heads x 1728 x 216: 873 / 1922 -> 225 / 860; 80 x 2560 x 320: 1273 /
-// 3400 -> 560 / 1700; 32 x 2048 x 256 in half precision: 336 / 749 -> 114 / 380.
+// bytes per head), causal, forward / backward in us: 2 x 54 heads x 1728 x 216: 869 / 1922 -> 209 / 749; 80 x 2560 x 320: 1330 /
+// 3575 -> 560 / 1755; 32 x 2048 x 256 in half precision: 332 / 744 -> 110 / 371.
 #include <cstdio>
 #include <type_traits>
 
@@ -37,6 +38,8 @@ __device__ __forceinline__ f32x16 zero16() { return f32x16{0.f, 0.f, 0.f, 0.f, 0
 // far enough ahead for the LDS latency with four wavefronts reading
 constexpr int kAhead = 6, kSlots = kAhead + 2;
 template <int NK, class L, class M> __device__ __forceinline__ void products(L load, M multiply) { products_ahead<NK, kAhead>(load, multiply); }
+
+template <class E> constexpr bool scale_first() { return std::is_same<E, f16>::value; }
 
 constexpr int kTile = 32;
 // two workgroups per compute unit where registers and LDS (two stages) allow it, else one with three stages
@@ -205,7 +208,8 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
     const size_t stat = ((size_t)b * sh.heads + h) * sh.s + q;
     const float lse2 = qvalid ? lse[stat] * kLog2e : INFINITY;     // invalid rows: p = exp2(-inf) = 0
     const float scale = rsqrtf((float)dh), c2 = scale * kLog2e;
-    const float dl = qvalid ? delta[stat] * scale : 0.f;           // dS carries the factor when it is rounded: see the file's head
+    const float dl = qvalid ? delta[stat] * (scale_first<E>() ? scale : 1.f) : 0.f;
+    const float at_end = scale_first<E>() ? 1.f : scale;
     f32x16 acc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c] = zero16();
@@ -244,7 +248,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
         for (int c = 0; c < NC; ++c) k0t[c] = ad.tr(Ks, c, 0);   // K^T operands
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] *= fmaf(dpt[r], scale, -dl);
+        for (int r = 0; r < 16; ++r) st[r] *= scale_first<E>() ? fmaf(dpt[r], scale, -dl) : dpt[r] - dl;
         const x8<E> ds0 = pack16<E>(st, 0), ds1 = pack16<E>(st, 1);
         wait_tr_reads(k0t);
 #pragma unroll
@@ -279,7 +283,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
         for (int g = 0; g < 4; ++g) {
             x4<E> o;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = (E)acc[c][4 * g + i];
+            for (int i = 0; i < 4; ++i) o[i] = (E)(acc[c][4 * g + i] * at_end);
             if (c * 32 + 8 * g + 4 * half < dh) *reinterpret_cast<x4<E> *>(orow + c * 32 + 8 * g + 4 * half) = o;
         }
 }
@@ -402,7 +406,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dkv_kernel(const E *__restri
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             if constexpr (!DK) probability(r);
-            else s_[r] = pr[r] * scale * dp[r];
+            else s_[r] = scale_first<E>() ? pr[r] * scale * dp[r] : pr[r] * dp[r];
         }
         const x8<E> p0 = pack16<E>(pr, 0), p1 = pack16<E>(pr, 1);
         x8<E> s0 = p0, s1 = p1;
@@ -454,7 +458,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dkv_kernel(const E *__restri
             x4<E> o;
             if constexpr (DK) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = (E)dk[c][4 * g + i];
+                for (int i = 0; i < 4; ++i) o[i] = (E)(dk[c][4 * g + i] * (scale_first<E>() ? 1.f : scale));
                 *reinterpret_cast<x4<E> *>(orow + d + col) = o;
             }
             if constexpr (DV) {
