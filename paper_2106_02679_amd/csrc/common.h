@@ -144,4 +144,11 @@ template <class T> struct GemmParams {
     int sblock;
 };
 
+// The weight gradients of a layer in one launch: an EPI_ACCUM_F32 product each, with ksplit >= 1.
+constexpr int kGemmGroup = 4;
+template <class T> struct GemmGroup {
+    GemmParams<T> p[kGemmGroup];
+    int n;
+};
+
 }  // namespace lga

@@ -101,6 +101,26 @@ __device__ __forceinline__ void epilogue8(const GemmParams<E> &p, int m, int n, 
     *reinterpret_cast<x8<E> *>(p.out + idx) = o;
 }
 
+// Workgroup ids are dealt round-robin over the 8 XCDs: the work item of this workgroup such that each XCD has a contiguous range of them.
+__device__ __forceinline__ int xcd_contiguous(int nwork) {
+    const int pid = blockIdx.x, xcd = pid & 7, local = pid >> 3;
+    const int base = nwork >> 3, rem = nwork & 7;
+    return xcd * base + (xcd < rem ? xcd : rem) + local;
+}
+
+// Grouped launch: the problem that work item `tile` belongs to, and the item's place in it.
+template <int BM, int BN, class E> __device__ __forceinline__ GemmParams<E> select_from_group(const GemmGroup<E> &in, int &tile, int &tiles_m, int &tiles_n) {
+    int z = 0;
+    for (;;) {
+        tiles_m = (in.p[z].M + BM - 1) / BM;
+        tiles_n = (in.p[z].N + BN - 1) / BN;
+        const int items = tiles_m * tiles_n * in.p[z].ksplit;
+        if (z + 1 >= in.n || tile < items) return in.p[z];
+        tile -= items;
+        ++z;
+    }
+}
+
 // Batched launch: work item `tile` belongs to problem tile / ntiles; rebase the operands and outputs onto it.
 template <class E> __device__ __forceinline__ void select_problem(GemmParams<E> &p, int &tile, int ntiles) {
     const int z = tile / ntiles;

@@ -153,13 +153,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams<E> p, int til
 
     // ---- workgroup -> tile, XCD-aware ----------------------------------------------------
     const int ntiles = tiles_m * tiles_n;
-    int tile;
-    {
-        const int nwork = p.batch > 1 ? ntiles * p.batch : ntiles;      // a batch is ntiles work items per problem
-        const int pid = blockIdx.x, xcd = pid & 7, local = pid >> 3;
-        const int base = nwork >> 3, rem = nwork & 7;
-        tile = xcd * base + (xcd < rem ? xcd : rem) + local;
-    }
+    int tile = xcd_contiguous(p.batch > 1 ? ntiles * p.batch : ntiles);      // a batch is ntiles work items per problem
     if (p.batch > 1) select_problem(p, tile, ntiles);
     constexpr int GROUP_M = 8;
     const int group_size = GROUP_M * tiles_n;
@@ -393,8 +387,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams<E> p, int til
 // With the bias gradients' column sums in a pass of their own (99 us; they rode along with the transposes) the layer's backward
 // went from 2.26 to 1.93 ms; a training step of a d = 2048 layer over 65536 tokens from 25.0 to 24.0 ms, of a d = 12288 layer
 // over 16384 from 160.4 to 158.8.
-template <int BM, int BN, int WGM, int WGN, int EPI, class E, bool TN>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParams<E> p, int tiles_m, int tiles_n) {
+// In is GemmParams<E>, or GemmGroup<E>: several weight gradients in one launch, for layers whose matrices do not fill the chip one by
+// one.  Workgroups are dealt to the problems in order, each problem's slices as in a launch of its own.
+template <int BM, int BN, int WGM, int WGN, int EPI, class E, bool TN, class In>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(In in, int tiles_m, int tiles_n) {
+    constexpr bool GROUP = std::is_same<In, GemmGroup<E>>::value;
     constexpr int NW = WGM * WGN;                   // wavefronts per workgroup, WGM x WGN over the tile
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int FM = WM / 16, FN = WN / 16;       // 16 x 16 blocks of a wavefront's tile
@@ -411,16 +408,18 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
     auto slot = [&](int q) { return lds + q * kSlotElems; };
     auto wrap = [](int q) { return q >= kSlots ? q - kSlots : q; };
 
-    const int ntiles = tiles_m * tiles_n;
+    GemmParams<E> p;
     int tile;
-    {
+    if constexpr (GROUP) {
+        tile = xcd_contiguous(gridDim.x);
+        p = select_from_group<BM, BN>(in, tile, tiles_m, tiles_n);
+    } else {
+        p = in;
         // with a split k range there are ksplit work items per tile, slice-major
-        const int nwork = (EPI == EPI_ACCUM_F32 && p.ksplit > 1) ? ntiles * p.ksplit : p.batch > 1 ? ntiles * p.batch : ntiles;
-        const int pid = blockIdx.x, xcd = pid & 7, local = pid >> 3;
-        const int base = nwork >> 3, rem = nwork & 7;
-        tile = xcd * base + (xcd < rem ? xcd : rem) + local;
+        tile = xcd_contiguous(tiles_m * tiles_n * ((EPI == EPI_ACCUM_F32 && p.ksplit > 1) ? p.ksplit : p.batch > 1 ? p.batch : 1));
     }
-    if (p.batch > 1) select_problem(p, tile, ntiles);
+    const int ntiles = tiles_m * tiles_n;
+    if (!GROUP && p.batch > 1) select_problem(p, tile, ntiles);
     if constexpr (EPI == EPI_ACCUM_F32) {
         if (p.ksplit > 1) {
             // this workgroup multiplies slice z of the k range into partial result z ([M][N], dense)
@@ -441,7 +440,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
     const int gsz = min(tiles_m - first_m, GROUP_M);
     int tm = first_m + (tile % group_size) % gsz;
     int tn = (tile % group_size) / gsz;
-    if (p.sblock) {
+    if (!GROUP && p.sblock) {
         // Round r of 256 consecutive workgroup ids is one 16 x 16 block of tiles (blocks walk along n first); XCD
         // x = id mod 8 takes rows 8 (x / 4) .. + 7 and columns 4 (x mod 4) .. + 3 of it.  All 8 XCDs then read the
         // same 16 + 16 operand panels at about the same time, so memory sees each of them once per k step instead of
@@ -452,7 +451,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
         tn = ((r % nsn) << 4) + ((x & 3) << 2) + (local >> 3);
     }
     const int m0 = tm * BM, n0 = tn * BN;
-    if (p.tri == 1 && n0 >= m0 + BM) return;             // whole workgroup: the tile lies above the diagonal
+    if (!GROUP && p.tri == 1 && n0 >= m0 + BM) return;   // whole workgroup: the tile lies above the diagonal
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -897,9 +896,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(GemmParam
 
 // Explicit instantiations: the host compiler does not always emit the launch stub of a kernel template from its use
 // in the launchers below alone.
-#define LGA_INSTANTIATE_DMA(EPI, ...)                                                                                       \
-    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, bf16, __VA_ARGS__>(GemmParams<bf16>, int, int);     \
-    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, f16, __VA_ARGS__>(GemmParams<f16>, int, int)
+#define LGA_INSTANTIATE_DMA_IN(EPI, E, TN, IN) \
+    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, E, TN, IN<E>>(IN<E>, int, int)
+#define LGA_INSTANTIATE_DMA(EPI, TN)                       \
+    LGA_INSTANTIATE_DMA_IN(EPI, bf16, TN, GemmParams);     \
+    LGA_INSTANTIATE_DMA_IN(EPI, f16, TN, GemmParams)
 LGA_INSTANTIATE_DMA(EPI_STORE, false);
 LGA_INSTANTIATE_DMA(EPI_BIAS, false);
 LGA_INSTANTIATE_DMA(EPI_BIAS_RESID, false);
@@ -907,7 +908,10 @@ LGA_INSTANTIATE_DMA(EPI_BIAS_GELU, false);
 LGA_INSTANTIATE_DMA(EPI_MUL_DGELU, false);
 LGA_INSTANTIATE_DMA(EPI_ACCUM_F32, false);
 LGA_INSTANTIATE_DMA(EPI_ACCUM_F32, true);
+LGA_INSTANTIATE_DMA_IN(EPI_ACCUM_F32, bf16, true, GemmGroup);
+LGA_INSTANTIATE_DMA_IN(EPI_ACCUM_F32, f16, true, GemmGroup);
 #undef LGA_INSTANTIATE_DMA
+#undef LGA_INSTANTIATE_DMA_IN
 
 // The kernel that serves a (tile size, layout, epilogue) combination and its dynamic LDS in bytes.
 template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E, bool DMA = A_KM && B_KM> struct KernelFor {
@@ -917,7 +921,7 @@ template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E, bool DMA = A_K
     static constexpr size_t smem = kDma ? (size_t)5 * BM * BK * sizeof(E)            // the DMA kernel's operand ring
                                         : (size_t)2 * (BM + BN) * BK * sizeof(E);    // two stages of both operands
     static auto get() -> void (*)(GemmParams<E>, int, int) {
-        if constexpr (kDma) return gemm_bf16_dma_kernel<BM, BN, 2, 2, EPI, E, !A_KM>;
+        if constexpr (kDma) return gemm_bf16_dma_kernel<BM, BN, 2, 2, EPI, E, !A_KM, GemmParams<E>>;
         else return gemm_bf16_kernel<BM, BN, A_KM, B_KM, EPI, E>;
     }
     // up to 160 KB of dynamic LDS: more than a launch may ask for by default
@@ -964,6 +968,28 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
         float *o = out + m * ldc + n;
         if (beta != 0.f) acc += beta * *reinterpret_cast<const f32x4 *>(o);
         *reinterpret_cast<f32x4 *>(o) = acc;
+    }
+}
+
+// The same for a group's products whose k range is split, one after the other: outputs without gaps between their rows.
+struct SplitkGroup {
+    const float *partial[kGemmGroup];
+    float *out[kGemmGroup];
+    size_t quads[kGemmGroup];
+    float beta[kGemmGroup];
+    int slices, n;
+};
+__global__ __launch_bounds__(256) void splitk_reduce_group_kernel(SplitkGroup g, size_t all) {
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < all; i += (size_t)gridDim.x * 256) {
+        int z = 0;
+        size_t at = i;
+        while (z + 1 < g.n && at >= g.quads[z]) at -= g.quads[z++];
+        const f32x4 *partial = reinterpret_cast<const f32x4 *>(g.partial[z]) + at;
+        f32x4 acc = *partial;
+        for (int k = 1; k < g.slices; ++k) acc += partial[k * g.quads[z]];
+        f32x4 *o = reinterpret_cast<f32x4 *>(g.out[z]) + at;
+        if (g.beta[z] != 0.f) acc += g.beta[z] * *o;
+        *o = acc;
     }
 }
 
@@ -1042,6 +1068,117 @@ void launch_splitk_reduce(const float *partial, int slices, float *out, int M, i
     const unsigned blocks = (unsigned)std::min<size_t>((quads + 255) / 256, 256 * 16);
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, s, partial, slices, (size_t)M * N, out, M, N, ldc, beta);
 }
+
+template <class E> void prepare_gemm_group(GemmGroup<E> &group, const GemmParams<E> *p, int slices) {
+    size_t used = 0;
+    for (int i = 0; i < group.n; ++i) {
+        GemmParams<E> &q = group.p[i];
+        q = p[i];
+        q.kchunk = slices > 1 ? ((p[i].K + slices - 1) / slices + BK - 1) / BK * BK : p[i].K;
+        q.ksplit = slices > 1 ? (p[i].K + q.kchunk - 1) / q.kchunk : 1;
+        q.partial = p[i].partial + used;
+        used += (size_t)slices * p[i].M * p[i].N;
+    }
+}
+template <class E> void launch_splitk_reduce_group(const GemmGroup<E> &group, hipStream_t s) {
+    if (group.p[0].ksplit <= 1) return;
+    SplitkGroup g{};
+    g.n = group.n;
+    g.slices = group.p[0].ksplit;
+    size_t all = 0;
+    double bytes = 0.0;
+    for (int i = 0; i < g.n; ++i) {
+        const GemmParams<E> &p = group.p[i];
+        g.partial[i] = p.partial;
+        g.out[i] = p.outf;
+        g.quads[i] = (size_t)p.M * p.N / 4;
+        g.beta[i] = p.beta;
+        all += g.quads[i];
+        bytes += 16.0 * g.quads[i] * (g.slices + (p.beta != 0.f ? 2.0 : 1.0));
+    }
+    ProfScope scope("splitk_reduce_kernel", 4.0 * g.slices * all, bytes, s);
+    hipLaunchKernelGGL(splitk_reduce_group_kernel, dim3((unsigned)std::min<size_t>((all + 255) / 256, 256 * 16)), dim3(256), 0, s, g, all);
+}
+template void prepare_gemm_group<bf16>(GemmGroup<bf16> &, const GemmParams<bf16> *, int);
+template void prepare_gemm_group<f16>(GemmGroup<f16> &, const GemmParams<f16> *, int);
+template void launch_splitk_reduce_group<bf16>(const GemmGroup<bf16> &, hipStream_t);
+template void launch_splitk_reduce_group<f16>(const GemmGroup<f16> &, hipStream_t);
+
+// Slices of the k range for n weight gradients in one launch of the large-tile kernel, by what a round of 256 workgroups takes (1.2 us per
+// k tile and 12 us around them) and the way of the partial results through memory (4.5 TB/s); 0 where that leaves more than a quarter of the
+// chip idle or a workgroup fewer than 16 k tiles.  The four matrices of a d = 768 layer over 4096 tokens, 108 tiles: 121 us in four launches
+// of the small kernel behind 38 us of transposes, now 58 + 20 us in two slices and 11 us for the bias gradients' column sums.
+int gemm_group_slices(const int *M, const int *N, int n, int K) {
+    long tiles = 0;
+    double outputs = 0.0;
+    for (int i = 0; i < n; ++i) {
+        if (M[i] < 256 || N[i] < 256) return 0;
+        tiles += (long)((M[i] + 255) / 256) * ((N[i] + 255) / 256);
+        outputs += (double)M[i] * N[i];
+    }
+    if (K < 1024) return 0;
+    int best = 0;
+    double best_us = 0.0;
+    for (int s = 1; s <= std::min(32, K / 1024); ++s) {
+        if (tiles * s < 192) continue;
+        const double us = (double)((tiles * s + 255) / 256) * ((double)(K / s) / BK * 1.2 + 12.0) + (s > 1 ? (s + 1) * outputs * 4.0 / 4.5e6 : 0.0);
+        if (best == 0 || us < best_us) best = s, best_us = us;
+    }
+    return best;
+}
+
+template <class E> void launch_gemm_stored_group(const GemmParams<E> *p, int n, hipStream_t s) {
+    int M[kGemmGroup], N[kGemmGroup];
+    size_t outputs = 0;
+    for (int i = 0; i < n; ++i) {
+        M[i] = p[i].M;
+        N[i] = p[i].N;
+        outputs += (size_t)M[i] * N[i];
+    }
+    int slices = std::max(1, gemm_group_slices(M, N, n, p[0].K));
+    if (slices > 1 && (!p[0].partial || slices * outputs > p[0].partial_floats)) slices = 1;
+    (void)prepare_kernels();
+    GemmGroup<E> group{};
+    group.n = n;
+    prepare_gemm_group(group, p, slices);
+    long work = 0;
+    double flops = 0.0, bytes = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const GemmParams<E> &q = group.p[i];
+        const double mn = (double)q.M * q.N;
+        work += (long)((q.M + 255) / 256) * ((q.N + 255) / 256) * q.ksplit;
+        flops += 2.0 * mn * q.K;
+        bytes += 2.0 * ((double)q.M * q.K + (double)q.K * q.N) + mn * (q.beta != 0.f ? 8.0 : 4.0);
+    }
+    {
+        char name[96];
+        snprintf(name, sizeof(name), "gemm_%s_dma_tn_kernel<256, 256, %d> (grouped)", std::is_same<E, bf16>::value ? "bf16" : "f16", EPI_ACCUM_F32);
+        ProfScope scope(name, flops, bytes, s);
+        hipLaunchKernelGGL((gemm_bf16_dma_kernel<256, 256, 2, 2, EPI_ACCUM_F32, E, true, GemmGroup<E>>), dim3((unsigned)work), dim3(256),
+                           (size_t)5 * 256 * BK * sizeof(E), s, group, 0, 0);
+    }
+    launch_splitk_reduce_group(group, s);
+}
+template void launch_gemm_stored_group<bf16>(const GemmParams<bf16> *, int, hipStream_t);
+template void launch_gemm_stored_group<f16>(const GemmParams<f16> *, int, hipStream_t);
+
+// Weight gradients on transposed operands: those that have enough work for the large tiles by themselves alone, the others together.
+template <class E> void launch_gemm_transposed_group(const GemmParams<E> *p, int n, hipStream_t s) {
+    GemmParams<E> rest[kGemmGroup];
+    int n_rest = 0;
+    for (int i = 0; i < n; ++i) {
+        const bool whole = p[i].N % 4 == 0 && p[i].ldc == p[i].N;
+        if (large_tile_slices(p[i]) > 0 || !whole) (void)launch_gemm_mfma<E>(p[i], true, true, EPI_ACCUM_F32, s);
+        else rest[n_rest++] = p[i];
+    }
+    if (n_rest == 1) (void)launch_gemm_mfma<E>(rest[0], true, true, EPI_ACCUM_F32, s);
+    else if (n_rest > 1) {
+        (void)prepare_kernels();
+        launch_gemm_small_group<E>(rest, n_rest, s);
+    }
+}
+template void launch_gemm_transposed_group<bf16>(const GemmParams<bf16> *, int, hipStream_t);
+template void launch_gemm_transposed_group<f16>(const GemmParams<f16> *, int, hipStream_t);
 
 bool gemm_takes_stored_operands(int M, int N, int K) {
     if (M < 256 || N < 256) return false;
@@ -1132,6 +1269,8 @@ template <class E> hipError_t raise_all() {
     next(raise_pair<false, false, EPI_STORE, E>());
     next(raise_pair<false, false, EPI_ACCUM_F32, E>());
     next(KernelFor<256, 256, false, false, EPI_ACCUM_F32, E, true>::raise_lds_limit());
+    next(hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_bf16_dma_kernel<256, 256, 2, 2, EPI_ACCUM_F32, E, true, GemmGroup<E>>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, 5 * 256 * BK * (int)sizeof(E)));
     return e;
 }
 }  // namespace

@@ -85,7 +85,7 @@ template <class E>
 void launch_transpose16_colsum(const E *in, E *out, int R, int C, long ldi, long ldo, float beta, float *out0,
                                float *partial, hipStream_t s);
 
-// Up to four matrices in one launch; those with partial != NULL (colsum_partial_floats(R, C) floats) also leave the first pass of their
+// Up to eight matrices in one launch; those with partial != NULL (colsum_partial_floats(R, C) floats) also leave the first pass of their
 // column sums (values of format E) there, whose second pass add_transposed_colsum adds to a batch.
 struct TransposeMatrix {
     const void *in;
@@ -95,7 +95,7 @@ struct TransposeMatrix {
     int R, C, blocks;          // blocks: set by the launcher
 };
 struct TransposeBatch {
-    TransposeMatrix m[4];
+    TransposeMatrix m[8];
     int n;
 };
 template <class E> void launch_transposes(const TransposeMatrix *m, int n, hipStream_t s);
@@ -135,6 +135,15 @@ template <int EPI, class E> void launch_gemm_small(const GemmParams<E> &p, hipSt
 int gemm_small_slices(int M, int N, int K, size_t partial_floats);
 // out[m, n] = beta * out[m, n] + sum_z partial[z][m][n], slices in index order; N and ldc multiples of 4, 16-byte aligned
 void launch_splitk_reduce(const float *partial, int slices, float *out, int M, int N, int ldc, float beta, hipStream_t s);
+// Several weight gradients (EPI_ACCUM_F32, the same K, ldc = N a multiple of 4) in one launch: on the large-tile kernel from operands as
+// stored, where gemm_group_slices() > 0 for them together, or on k-contiguous ones.  p[0].partial / partial_floats is scratch for all.
+template <class E> void launch_gemm_stored_group(const GemmParams<E> *p, int n, hipStream_t s);
+template <class E> void launch_gemm_transposed_group(const GemmParams<E> *p, int n, hipStream_t s);
+template <class E> void launch_gemm_small_group(const GemmParams<E> *p, int n, hipStream_t s);
+int gemm_group_slices(const int *M, const int *N, int n, int K);
+// A group's parameters with the k range in so many slices (1: not cut), and the sum of the slices (nothing to do without)
+template <class E> void prepare_gemm_group(GemmGroup<E> &group, const GemmParams<E> *p, int slices);
+template <class E> void launch_splitk_reduce_group(const GemmGroup<E> &group, hipStream_t s);
 // Into how many slices of the k range launch_gemm_mfma cuts an fp32-accumulating, k-contiguous GEMM whose output has
 // too few 256 x 256 tiles to occupy the chip (1 = not at all); it then needs slices * M * N floats of scratch.
 // k = 0 asks for the largest count any k would give (for sizing the scratch).

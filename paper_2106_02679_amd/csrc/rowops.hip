@@ -603,7 +603,7 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ w, float 
 constexpr int kTrTile = 128;
 constexpr int kTrPitch = kTrTile + 8;     // elements; keeps 16-byte alignment and skews the banks
 
-// One launch moves up to four matrices (the two operands of a weight gradient; the four weight matrices of a layer): launched one by
+// One launch moves up to eight matrices (the operands of a layer's weight gradients; its four weight matrices): launched one by
 // one, a narrow layer's each take their 4 us.  With partial given the block also adds up its 128 rows of every column it moves
 // (as values of format E, in fp32) and writes them to partial[row chunk][0][c] - the first pass of the column sums
 // (colsum_partial_kernel's layout, same 128-row chunks), so that the bias gradient costs no pass of its own over a matrix that is being transposed anyway.

@@ -147,6 +147,7 @@ struct Plan {
     // The four weight-gradient GEMMs (W_2, W_1, W_o, W_qkv) of the 16-bit modes: stored[i] = it reads the activations and output gradients
     // as the layer stores them, whose buffers then hold wgrad_groups groups; otherwise transposed copies of them, xT and dyT.
     bool stored[4];
+    bool grouped[4];           // those among the stored ones that are only enough work together, in one launch
     size_t xT[4], dyT[4];
     int wgrad_groups;          // groups whose tokens one weight-gradient GEMM contracts over
     int dact_groups;           // groups in the ring that dact is where stored[0] (see ActivationGradient); 0: dact holds all groups, in place
@@ -188,7 +189,15 @@ Plan make_plan(const lga_config &c) {
     const int wg_in[4] = {(int)f, (int)d, (int)d, (int)d};          // W_2, W_1, W_o, W_qkv
     const int wg_out[4] = {(int)d, (int)f, (int)d, (int)(3 * d)};
     // Decided by one group's tokens: the merged GEMM of more of them runs on the large-tile kernel all the more.
-    for (int i = 0; i < 4; ++i) p.stored[i] = is16 && gemm_takes_stored_operands(wg_in[i], wg_out[i], (int)t);
+    int alone = 0, M[4], N[4], rest[4];
+    for (int i = 0; i < 4; ++i) {
+        p.stored[i] = is16 && gemm_takes_stored_operands(wg_in[i], wg_out[i], (int)t);
+        p.grouped[i] = false;
+        if (p.stored[i]) ++alone;
+        else rest[i - alone] = i, M[i - alone] = wg_in[i], N[i - alone] = wg_out[i];
+    }
+    if (is16 && alone < 3 && gemm_group_slices(M, N, 4 - alone, (int)t) > 0)
+        for (int i = 0; i < 4 - alone; ++i) p.stored[rest[i]] = p.grouped[rest[i]] = true;
     auto take_activations = [&](size_t wb) {
         const size_t n_2 = p.stored[0] ? wb : 1, n_1 = p.stored[1] ? wb : 1, n_o = p.stored[2] ? wb : 1, n_qkv = p.stored[3] ? wb : 1;
         // (the d_ff-wide buffers' padding: as much as all groups need, so that it does not depend on wb)
@@ -231,9 +240,23 @@ Plan make_plan(const lga_config &c) {
         p.dyT[i] = take(is16 && !p.stored[i] ? (size_t)wg_out[i] * p.ldk * 2 : 0);
     }
     p.splitk_floats = 0;
-    for (int i = 0; i < 4; ++i) {
-        const size_t slices = (size_t)(is16 ? gemm_splitk_slices(wg_in[i], wg_out[i], 0) : gemm_f32_slices(wg_in[i], wg_out[i], (int)t));
-        if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * wg_in[i] * wg_out[i]);
+    if (is16) {
+        size_t outputs = 0;
+        bool any = false;
+        for (int i = 0; i < 4; ++i) {
+            const size_t slices = (size_t)gemm_splitk_slices(wg_in[i], wg_out[i], 0);
+            if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * wg_in[i] * wg_out[i]);
+            if (p.grouped[i]) any = true, outputs += (size_t)wg_in[i] * wg_out[i];
+        }
+        for (size_t k = 1; any && k <= wb; ++k) {
+            const size_t slices = (size_t)gemm_group_slices(M, N, 4 - alone, (int)(k * t));
+            if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * outputs);
+        }
+    } else {
+        for (int i = 0; i < 4; ++i) {
+            const size_t slices = (size_t)gemm_f32_slices(wg_in[i], wg_out[i], (int)t);
+            if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * wg_in[i] * wg_out[i]);
+        }
     }
     p.splitk = take(p.splitk_floats * 4);
     p.mean1 = take(t * 4);
@@ -624,6 +647,10 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
     ColsumBatch sums;
     ColsumMatrix<T> biases[4];
     int n_biases = 0;
+    // The weight gradients that are not enough work alone wait, with their transposes, until all operands are there.
+    GemmParams<T> together[4];
+    TransposeMatrix moves[8];
+    int n_together = 0, n_moves = 0;
 
     // gW[in, out] (+)= X[t, in]^T dY[t, out], contracted over tokens.  The 16-bit modes' large-tile kernel takes both operands as they
     // are; the kernels for smaller gradients read k-contiguous ones, X^T [in][.] and dY^T [out][.], written first.  `which` names the
@@ -647,17 +674,17 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
             if (p.stored[which]) {
                 const size_t before = (size_t)gs.slot * t;   // rows of the groups in the slots before this one
                 g.A = X - before * ldx; g.lda = ldx; g.B = dY - before * ldy; g.ldb = ldy;
-                if (gs.flush) gemm<T>(g, false, false, EPI_ACCUM_F32, s);
+                if (p.grouped[which]) together[n_together++] = g;
+                else if (gs.flush) gemm<T>(g, false, false, EPI_ACCUM_F32, s);
             } else {
                 const int ldk = (int)p.ldk;
                 T *xT = st->at<T>(p.xT[which]), *dyT = st->at<T>(p.dyT[which]);
                 // the bias gradient is the column sum of dY: taken from the tiles as they are transposed
-                const TransposeMatrix m[2] = {{X, xT + (size_t)gs.slot * t, nullptr, ldx, ldk, t, in, 0},
-                                              {dY, dyT + (size_t)gs.slot * t, partial, ldy, ldk, t, out, 0}};
-                launch_transposes<T>(m, 2, s);
+                moves[n_moves++] = {X, xT + (size_t)gs.slot * t, nullptr, ldx, ldk, t, in, 0};
+                moves[n_moves++] = {dY, dyT + (size_t)gs.slot * t, partial, ldy, ldk, t, out, 0};
                 add_transposed_colsum(sums, partial, t, out, beta, gbuf + b_off);
                 g.A = xT; g.lda = ldk; g.B = dyT; g.ldb = ldk;
-                if (gs.flush) gemm<T>(g, true, true, EPI_ACCUM_F32, s);
+                together[n_together++] = g;
                 return;
             }
         }
@@ -692,6 +719,13 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
     dgrad(dqkv, 3 * d, o.w_qkv, d, dh, EPI_STORE, nullptr);
     // h = LN1(x); dx = dx1 + LN1'(dh)
     launch_colsums<T>(biases, n_biases, beta, s, true, &sums);
+    if constexpr (!std::is_same<T, float>::value) {          // (before dx, which may take the place of dy)
+        launch_transposes<T>(moves, n_moves, s);
+        if (gs.flush && n_together > 0) {
+            if (n_moves > 0) launch_gemm_transposed_group<T>(together, n_together, s);
+            else launch_gemm_stored_group<T>(together, n_together, s);
+        }
+    }
     launch_layernorm_bwd_dx<T>(dh, x_in, mean1, rstd1, pf + o.ln1_g, dx1, dx, t, d, s, beta, gbuf + o.ln1_b, gbuf + o.ln1_g,
                                st->at<float>(p.partial[5]), &sums);
     launch_colsum_batch(sums, s);
