@@ -12,13 +12,15 @@
 //    on how many rows share its launch: the parts follow from K, only the groups from the number of tiles;
 //  - where even that leaves compute units idle, the k range is cut into slices over the grid and the partial results
 //    are added in slice order by a second kernel (only with scratch, i.e. for the stack's weight gradients).
-// Measured (one MI355X; before: plain FMA on 64 x 64 x 16 tiles, loads waited for at once, no split of k), averages over the
-// launches of a step: 256-wide stack of 2048 tokens - weight gradients 440 -> 15 us plus 5 us for the sum of the slices,
-// input gradients 116 -> 19, QKV 55 -> 18, first feed-forward with GELU 65 -> 21; 64-wide stack of 256 tokens - 52 -> 9,
-// 29 -> 9, 16 -> 5, 17 -> 6 us.
+// gemm_f32_dma_kernel serves operands of whole 16-byte pieces in the layouts that the stack uses, gemm_f32_kernel the others; the
+// weight gradients of a layer run in one launch.
+// Measured (one MI355X, us; gemm_f32_kernel -> gemm_f32_dma_kernel -> vendor library): 2048 x 768 x 256 with bias 17.5 -> 14.4 -> 18.7,
+// 4096 x 256 x 1024 31 -> 24 -> 22, 8192 x 512 x 2048 174 -> 144 -> 120; input gradient 2048 x 1024 x 256 17.9 -> 14.2; weight gradient
+// 512 x 1536 x 8192 188 -> 135.  The four weight gradients of a 256-wide layer over 2048 tokens: 80 in eight launches, now 41 in one.
 #include <algorithm>
 #include <type_traits>
 
+#include "gemm16.h"
 #include "kernels.h"
 
 namespace lga {
@@ -148,39 +150,138 @@ template <int EPI> __device__ __forceinline__ void epilogue_f32(const GemmParams
     }
 }
 
-// grid: (n tiles, m tiles, k slices); block: 256 KG threads.  vec_out: every tensor the epilogue touches takes 16-byte accesses
-// at columns that are multiples of 4.  log_parts: into 1, 2 or 4 parts the k range is cut for the order of the sums; with KG > 1 KG of them.
-template <int EPI, int KG>
-__global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(GemmParams<float> p, bool a_kc, bool b_kc, bool vec_out, int log_parts) {
-    extern __shared__ __attribute__((aligned(16))) float smem_f32[];
-    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
-    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-    int kbeg = 0, kstop = p.K;
+// Which tile and slice of the k range a workgroup has.  In: GemmParams, grid (n tiles, m tiles, k slices); or GemmGroup, the weight gradients
+// of a layer in one launch, a one-dimensional grid over all their tiles and slices.
+struct Place {
+    int m0, n0, kbeg, kstop;
+};
+template <int EPI, class In> __device__ __forceinline__ Place place_of(const In &in, GemmParams<float> &p, bool &vec_out) {
+    int tm, tn, slice;
+    if constexpr (std::is_same<In, GemmGroup<float>>::value) {
+        int z = 0, item = blockIdx.x;
+        for (;; ++z) {
+            const int items = ((in.p[z].M + TM - 1) / TM) * ((in.p[z].N + TN - 1) / TN) * in.p[z].ksplit;
+            if (z + 1 >= in.n || item < items) break;
+            item -= items;
+        }
+        p = in.p[z];
+        const int tiles_m = (p.M + TM - 1) / TM, tiles_n = (p.N + TN - 1) / TN;
+        slice = item / (tiles_m * tiles_n);
+        item -= slice * (tiles_m * tiles_n);
+        tm = item / tiles_n;
+        tn = item - tm * tiles_n;
+        vec_out = p.ksplit > 1 ? (p.N & 3) == 0 : (p.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(p.outf) & 15) == 0;
+    } else {
+        p = in;
+        tm = blockIdx.y;
+        tn = blockIdx.x;
+        slice = blockIdx.z;
+    }
+    Place at{tm * TM, tn * TN, 0, p.K};
     if constexpr (EPI == EPI_ACCUM_F32) {
-        if (p.ksplit > 1) {                     // slice blockIdx.z of the k range, into partial result z ([M][N], dense)
-            kbeg = blockIdx.z * p.kchunk;
-            kstop = min(p.K, kbeg + p.kchunk);
-            p.outf = p.partial + (size_t)blockIdx.z * p.M * p.N;
+        if (p.ksplit > 1) {                     // this slice of the k range, into a partial result of its own ([M][N], dense)
+            at.kbeg = slice * p.kchunk;
+            at.kstop = min(p.K, at.kbeg + p.kchunk);
+            p.outf = p.partial + (size_t)slice * p.M * p.N;
             p.ldc = p.N;
             p.beta = 0.f;
         }
     }
-    // a part of the k range: whole steps, the same number for every part; a group has one (and reads zeros if it is empty), or
-    // one group has all
-    const int all = (kstop - kbeg + TK - 1) / TK, part = KG == 1 ? (all + (1 << log_parts) - 1) >> log_parts : (all + KG - 1) / KG;
-    const int steps = KG == 1 ? all : part;
-    const int kg0 = kbeg + group * part * TK;
+    return at;
+}
+
+// The order of a quadrant's sums over its wavefront's steps.  An activation's parts follow from K alone: the parts of a pair, then the
+// pairs, whichever group has them.  A weight gradient's sums are folded every four steps, 128 k, however many a group walks over.
+template <int EPI, int KG> struct PartSums {
+    static constexpr bool FOLD = EPI == EPI_ACCUM_F32, PAIRS = !FOLD && KG < 4;
+    f32x16 acc, pair, total;
+    int each, left, odd = 0;
+    __device__ __forceinline__ explicit PartSums(int part) : each(FOLD ? 4 : part), left(FOLD ? 4 : part) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = pair[r] = total[r] = 0.f;
+    }
+    __device__ __forceinline__ void step() {
+        if (!(FOLD || PAIRS) || --left > 0) return;
+        left = each;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            pair[r] += acc[r];
+            acc[r] = 0.f;
+        }
+        if (PAIRS && KG == 1) {
+            if (odd) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    total[r] += pair[r];
+                    pair[r] = 0.f;
+                }
+            }
+            odd ^= 1;
+        }
+    }
+    __device__ __forceinline__ void finish() {
+        if (FOLD || PAIRS) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = total[r] + (pair[r] + acc[r]);
+        }
+    }
+};
+
+// The sums of a wavefront's quadrant leave.  Lane: row m = l32 of it, columns n = 8 q + 4 half + (0 .. 3).
+template <int EPI, int KG>
+__device__ __forceinline__ void finish_tile(const GemmParams<float> &p, const Place &at, const f32x16 &sum, bool vec_out, float *smem) {
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int lane = threadIdx.x & 63, wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
+    const int m = at.m0 + wm * 32 + l32, nq = at.n0 + wn * 32 + 4 * half;
+    if constexpr (KG == 1) {
+        if (m >= p.M) return;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (nq + 8 * q < p.N) epilogue_f32<EPI>(p, m, nq + 8 * q, f32x4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]}, vec_out);
+    } else {
+        // every group leaves its sums in LDS (nobody reads operands there any more); group g then adds up column quads
+        // g, g + KG, ... of all groups, neighbouring groups first
+        f32x4 *red = reinterpret_cast<f32x4 *>(smem);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[((group * 4 + wave) * 4 + q) * 64 + lane] = f32x4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
+        __syncthreads();
+        if (m >= p.M) return;
+#pragma unroll
+        for (int j = 0; j < 4 / KG; ++j) {
+            const int q = group + j * KG;
+            if (nq + 8 * q >= p.N) continue;
+            f32x4 of[KG];
+#pragma unroll
+            for (int g = 0; g < KG; ++g) of[g] = red[((g * 4 + wave) * 4 + q) * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) of[0][i] = KG == 4 ? (of[0][i] + of[1][i]) + (of[2 % KG][i] + of[3 % KG][i]) : of[0][i] + of[1][i];
+            epilogue_f32<EPI>(p, m, nq + 8 * q, of[0], vec_out);
+        }
+    }
+}
+
+// Block: 256 KG threads.  vec_out: every tensor the epilogue touches takes 16-byte accesses at columns that are multiples of 4.
+// log_parts: into 1, 2 or 4 parts the k range is cut for the order of the sums, (0 + 1) + (2 + 3); a group has 1 / KG of them.
+template <int EPI, int KG, class In>
+__global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(In in, bool a_kc, bool b_kc, bool vec_out, int log_parts) {
+    GemmParams<float> p;
+    const Place at = place_of<EPI>(in, p, vec_out);
+    extern __shared__ __attribute__((aligned(16))) float smem_f32[];
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
+    const int m0 = at.m0, n0 = at.n0, kbeg = at.kbeg, kstop = at.kstop;
+    // a part of the k range: whole steps, the same number for every part (a group reads zeros where one is empty)
+    const int all = (kstop - kbeg + TK - 1) / TK, part = (all + (1 << log_parts) - 1) >> log_parts, each = (part << log_parts) / KG;
+    const int steps = KG == 1 ? all : each;
+    const int kg0 = kbeg + group * each * TK;
     float *lds = smem_f32 + group * (4 * kTileFloats);           // two stages of A and B
 
     Loader la, lb;
     la.init(p.A, m0, p.M, p.lda, a_kc, kstop, t);
     lb.init(p.B, n0, p.N, p.ldb, b_kc, kstop, t);
-    f32x16 acc, done;                                            // of the part at hand; of the parts before it (KG = 1)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = done[r] = 0.f;
-    int left = part;
+    PartSums<EPI, KG> sums(part);
+    f32x16 &acc = sums.acc;
 
     if (steps > 0) {
         la.load(kg0);
@@ -210,65 +311,145 @@ __global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(GemmParams<float> p,
             la.store(nxt);
             lb.store(nxt + kTileFloats);
         }
-        if (KG == 1 && --left == 0) {                            // end of a part (behind the stores, which leave the products time to finish)
-            left = part;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                done[r] += acc[r];
-                acc[r] = 0.f;
-            }
-        }
+        sums.step();                                             // (behind the stores, which leave the products time to finish)
         __syncthreads();
     }
 
-    // lane: row m = l32 of the quadrant, columns n = 8 q + 4 half + (0 .. 3)
-    const int m = m0 + wm * 32 + l32;
-    const int nq = n0 + wn * 32 + 4 * half;
-    if constexpr (KG == 1) {
-        if (m >= p.M) return;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) done[r] += acc[r];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (nq + 8 * q < p.N) epilogue_f32<EPI>(p, m, nq + 8 * q, f32x4{done[4 * q], done[4 * q + 1], done[4 * q + 2], done[4 * q + 3]}, vec_out);
-    } else {
-        // every group leaves its sums in LDS (the loop's last barrier has passed); group g then adds up column quads
-        // g, g + KG, ... of all groups, in group order
-        f32x4 *red = reinterpret_cast<f32x4 *>(smem_f32);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) red[((group * 4 + wave) * 4 + q) * 64 + lane] = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-        __syncthreads();
-        if (m >= p.M) return;
-#pragma unroll
-        for (int j = 0; j < 4 / KG; ++j) {
-            const int q = group + j * KG;
-            if (nq + 8 * q >= p.N) continue;
-            f32x4 sum = red[(wave * 4 + q) * 64 + lane];
-#pragma unroll
-            for (int g = 1; g < KG; ++g) {
-                const f32x4 o = red[((g * 4 + wave) * 4 + q) * 64 + lane];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) sum[i] += o[i];
-            }
-            epilogue_f32<EPI>(p, m, nq + 8 * q, sum, vec_out);
-        }
-    }
+    sums.finish();
+    finish_tile<EPI, KG>(p, at, acc, vec_out, smem_f32);
 }
 
-// out[m, n] = beta * out[m, n] + sum_z partial[z][m][n], the slices in index order
-__global__ __launch_bounds__(256) void gemm_f32_reduce_kernel(const float *__restrict__ partial, int slices, float *__restrict__ out,
-                                                              int M, int N, int ldc, float beta) {
-    const size_t n_all = (size_t)M * N;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_all; i += (size_t)gridDim.x * 256) {
-        float acc = partial[i];
-#pragma unroll 4
-        for (int z = 1; z < slices; ++z) acc += partial[(size_t)z * n_all + i];
-        float *o = out + i / N * ldc + i % N;
-        *o = beta == 0.f ? acc : beta * *o + acc;
+// The same for operands whose rows are whole 16-byte pieces, in the layouts that the stack uses: tiles go from memory to LDS without passing
+// through registers, NS stages of 32 k, NS - 1 steps ahead.  A step's chain of latencies - load, LDS store, LDS read - is what bound the
+// kernel above (50 - 60 TFLOP/s): here it is one wait for loads issued NS - 1 steps ago, and a k-contiguous operand takes one 16-byte LDS
+// read for four matrix instructions.
+// In a step of 32 k, instruction j of quad q multiplies k = 8 q + j (lanes 0 - 31) and 8 q + 4 + j (lanes 32 - 63).
+// LDS, k-contiguous: 64 rows of 128 bytes, 16-byte chunk c of row r at c ^ ((r >> 1) & 7); otherwise: 32 k rows of 256 bytes, chunk c of
+// k row r at c ^ (r & 4 ? 8 : 0): the two halves of a wavefront read different banks.
+template <int EPI, int KG, int NS, bool A_KC, bool B_KC, class In>
+__global__ __launch_bounds__(256 * KG) void gemm_f32_dma_kernel(In in, bool vec_out, int log_parts) {
+    GemmParams<float> p;
+    const Place at = place_of<EPI>(in, p, vec_out);
+    extern __shared__ __attribute__((aligned(16))) float smem_f32[];
+    constexpr int kOperand = 64 * TK, NL = 4, kNewer = (NS - 2) * NL;      // floats of an operand's tile; loads of a wavefront per step
+    static_assert(kNewer < 64, "vmcnt has six bits");
+    constexpr int kWaitOlder = 0x0070 | (kNewer & 15) | (kNewer >> 4 << 14);       // s_waitcnt lgkmcnt(0) vmcnt(kNewer)
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int lane = threadIdx.x & 63, wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
+    const int all = (at.kstop - at.kbeg + TK - 1) / TK, part = (all + (1 << log_parts) - 1) >> log_parts, each = (part << log_parts) / KG;
+    const int steps = KG == 1 ? all : each;
+    const int kg0 = at.kbeg + group * each * TK;
+    float *ring = smem_f32 + group * NS * 2 * kOperand;
+
+    // wavefronts 0, 1 load A, 2, 3 load B; load i fills 1 KB: 8 rows of a k-contiguous operand, 4 k rows of the other layout
+    const bool is_a = wave < 2, kc = is_a ? A_KC : B_KC;
+    const int ld = is_a ? p.lda : p.ldb;
+    const float *base = is_a ? (A_KC ? p.A + (size_t)at.m0 * p.lda : p.A + at.m0) : (B_KC ? p.B + (size_t)at.n0 * p.ldb : p.B + at.n0);
+    const int rows = is_a ? p.M - at.m0 : p.N - at.n0;
+    int off[NL], kloc[NL];                                       // byte offset in the tile; first k of the piece
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const int u = (wave & 1) * NL + i;
+        if (kc) {
+            const int r = u * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+            kloc[i] = 4 * c;
+            off[i] = r < rows ? r * ld * 4 + c * 16 : kBufPoison;
+        } else {
+            const int r = u * 4 + (lane >> 4), c = (lane & 15) ^ (r & 4 ? 8 : 0);
+            kloc[i] = r;
+            off[i] = 4 * c < rows ? r * ld * 4 + c * 16 : kBufPoison;
+        }
     }
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    auto load_step = [&](int s) __attribute__((always_inline)) {
+        const int k0 = kg0 + s * TK, left = at.kstop - k0;
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(left > 0 ? base + (kc ? (size_t)k0 : (size_t)k0 * ld) : base);
+        float *stage = ring + (s % NS) * 2 * kOperand + (is_a ? 0 : kOperand) + (wave & 1) * NL * 256;
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(stage + i * 256), 16, kloc[i] < left ? off[i] : kBufPoison, 0, 0, 0);
+    };
+
+    PartSums<EPI, KG> sums(part);
+    f32x16 &acc = sums.acc;
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+        if (s < steps) load_step(s);
+    const int ra = wm * 32 + l32, rb = wn * 32 + l32;
+    for (int s = 0; s < steps; ++s) {
+        // this wavefront's loads of step s have landed and its LDS reads of step s - 1 have returned; after the barrier the step is
+        // published and the stage of step s - 1 is free
+        if (NS > 2 && s + NS - 2 < steps) __builtin_amdgcn_s_waitcnt(kWaitOlder);
+        else __builtin_amdgcn_s_waitcnt(0x0070);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (s + NS - 1 < steps) load_step(s + NS - 1);
+        if (kg0 + s * TK >= at.kstop) continue;                  // (a group whose share ends before the others')
+        const float *as = ring + (s % NS) * 2 * kOperand, *bs = as + kOperand;
+        f32x4 av[4], bv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (A_KC) av[q] = *reinterpret_cast<const f32x4 *>(as + ra * TK + (((2 * q + half) ^ ((ra >> 1) & 7)) << 2));
+            else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) av[q][j] = as[(8 * q + 4 * half + j) * 64 + (ra ^ (half << 5))];
+            }
+            if constexpr (B_KC) bv[q] = *reinterpret_cast<const f32x4 *>(bs + rb * TK + (((2 * q + half) ^ ((rb >> 1) & 7)) << 2));
+            else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bv[q][j] = bs[(8 * q + 4 * half + j) * 64 + (rb ^ (half << 5))];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[q][j], av[q][j], acc, 0, 0, 0);
+        sums.step();
+    }
+    sums.finish();
+    if constexpr (KG > 1) __syncthreads();                       // nobody reads the ring any more
+    finish_tile<EPI, KG>(p, at, acc, vec_out, smem_f32);
 }
 
 constexpr int smem_bytes(int kg) { return kg * 4 * kTileFloats * (int)sizeof(float); }       // 33.8 KB per group; at least the 16 KB per group of the final sum
+
+constexpr int kDmaStages = 2;
+constexpr int dma_smem(int kg) { return kg * kDmaStages * 2 * 64 * TK * (int)sizeof(float); }       // 32 KB per group
+// The layout that the stack uses with an epilogue
+template <int EPI> constexpr bool kDmaA = EPI != EPI_ACCUM_F32;
+template <int EPI> constexpr bool kDmaB = EPI == EPI_STORE || EPI == EPI_MUL_DGELU;
+
+// Whether the kernel without staging registers takes a product: by its layout, widths and addresses, never by the number of rows of an
+// activation (bits).
+template <int EPI> bool dma_takes(const GemmParams<float> &p, bool akc, bool bkc) {
+    auto al16 = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+    if (akc != kDmaA<EPI> || bkc != kDmaB<EPI> || !al16(p.A) || !al16(p.B)) return false;
+    if (((p.lda | p.ldb) & 3) != 0 || p.lda > kGemmMaxLd || p.ldb > kGemmMaxLd) return false;
+    return ((akc ? p.K : p.M) & 3) == 0 && ((bkc ? p.K : p.N) & 3) == 0;
+}
+
+// Groups per workgroup.  With staging registers: as many as have at least one step each, while the grid leaves room for their wavefronts.
+// Without: four where that leaves every workgroup a compute unit of its own, else two, whose 64 KB let two workgroups share one
+// (800 x 480 x 512, 104 tiles: 12.1 with four, 12.9 with two, 16.4 us with one; 3200 x 480 x 256, 400 tiles: 16.3, 14.8, 16.0;
+// 12800 x 1536 x 512, 4800 tiles: 211, 197, 222).
+template <int EPI, class In>
+void launch_tiles_f32(const In &in, dim3 grid, long work, int most, bool akc, bool bkc, bool dma, bool vec_out, hipStream_t s) {
+    if (dma) {
+        const int kg = std::min(most, work > 256 ? 2 : 4);
+        const int log_parts = (EPI == EPI_ACCUM_F32 ? kg : most) >> 1;
+        constexpr bool A = kDmaA<EPI>, B = kDmaB<EPI>;
+        if (kg == 4) hipLaunchKernelGGL((gemm_f32_dma_kernel<EPI, 4, kDmaStages, A, B, In>), grid, dim3(1024), dma_smem(4), s, in, vec_out, log_parts);
+        else if (kg == 2) hipLaunchKernelGGL((gemm_f32_dma_kernel<EPI, 2, kDmaStages, A, B, In>), grid, dim3(512), dma_smem(2), s, in, vec_out, log_parts);
+        else hipLaunchKernelGGL((gemm_f32_dma_kernel<EPI, 1, kDmaStages, A, B, In>), grid, dim3(256), dma_smem(1), s, in, vec_out, log_parts);
+        return;
+    }
+    const int kg = work >= 512 ? 1 : most;
+    const int log_parts = (EPI == EPI_ACCUM_F32 ? kg : most) >> 1;          // a weight gradient's k range differs with the grouping anyway
+    if (kg == 4) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 4, In>), grid, dim3(1024), smem_bytes(4), s, in, akc, bkc, vec_out, log_parts);
+    else if (kg == 2) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, In>), grid, dim3(512), smem_bytes(2), s, in, akc, bkc, vec_out, log_parts);
+    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, In>), grid, dim3(256), smem_bytes(1), s, in, akc, bkc, vec_out, log_parts);
+}
 
 template <int EPI> void launch_epi(const GemmParams<float> &p, bool akc, bool bkc, hipStream_t s) {
     const int tm = (p.M + TM - 1) / TM, tn = (p.N + TN - 1) / TN;
@@ -279,50 +460,118 @@ template <int EPI> void launch_epi(const GemmParams<float> &p, bool akc, bool bk
                          ((EPI != EPI_BIAS && EPI != EPI_BIAS_RESID && EPI != EPI_BIAS_GELU) || al16(p.bias));
     GemmParams<float> q = p;
     q.ksplit = 1;
-    if (EPI == EPI_ACCUM_F32 && p.partial && p.K > 0) {
-        const int slices = gemm_f32_slices(p.M, p.N, p.K);
-        if (slices > 1 && (size_t)slices * p.M * p.N <= p.partial_floats) {
-            q.kchunk = ((p.K + slices - 1) / slices + TK - 1) / TK * TK;
-            q.ksplit = (p.K + q.kchunk - 1) / q.kchunk;
-        }
-    }
-    const dim3 grid(tn, tm, q.ksplit);
-    const bool vo = q.ksplit > 1 ? (p.N & 3) == 0 && al16(p.partial) : vec_out;
-    const int k_each = q.ksplit > 1 ? q.kchunk : p.K;
-    // Groups per workgroup: as many as have at least one step each, while the grid leaves room for their wavefronts - a
-    // compute unit holds 32 of them, so from 512 tiles on single groups already fill the chip twice.
-    const int most = k_each > 2 * TK ? 4 : k_each > TK ? 2 : 1, kg = tiles * q.ksplit >= 512 ? 1 : most;
-    const int log_parts = (EPI == EPI_ACCUM_F32 ? kg : most) >> 1;          // a weight gradient's k range differs with the grouping anyway
-    {
-        const double mn = (double)p.M * p.N;
-        ProfScope scope("gemm_f32_kernel", 2.0 * mn * p.K, 4.0 * ((double)p.M * p.K + (double)p.K * p.N + mn), s);
-        if (kg == 4) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 4>), grid, dim3(1024), smem_bytes(4), s, q, akc, bkc, vo, log_parts);
-        else if (kg == 2) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2>), grid, dim3(512), smem_bytes(2), s, q, akc, bkc, vo, log_parts);
-        else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1>), grid, dim3(256), smem_bytes(1), s, q, akc, bkc, vo, log_parts);
-    }
-    if (q.ksplit > 1) {
-        ProfScope scope("gemm_f32_reduce_kernel", (double)q.ksplit * p.M * p.N, 4.0 * p.M * p.N * (q.ksplit + (p.beta != 0.f ? 2.0 : 1.0)), s);
-        const unsigned blocks = (unsigned)std::min<size_t>(((size_t)p.M * p.N + 255) / 256, 2048);
-        hipLaunchKernelGGL(gemm_f32_reduce_kernel, dim3(blocks), dim3(256), 0, s, p.partial, q.ksplit, p.outf, p.M, p.N, p.ldc, p.beta);
-    }
+    const int most = p.K > 2 * TK ? 4 : p.K > TK ? 2 : 1;
+    const double mn = (double)p.M * p.N;
+    ProfScope scope("gemm_f32_kernel", 2.0 * mn * p.K, 4.0 * ((double)p.M * p.K + (double)p.K * p.N + mn), s);
+    launch_tiles_f32<EPI>(q, dim3(tn, tm), tiles, most, akc, bkc, dma_takes<EPI>(p, akc, bkc), vec_out, s);
 }
 
-template <int EPI> hipError_t raise_epi() {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_f32_kernel<EPI, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, smem_bytes(4));
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_f32_kernel<EPI, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, smem_bytes(2));
+template <int EPI, class In = GemmParams<float>> hipError_t raise_epi() {
+    hipError_t e = hipSuccess;
+    auto raise = [&](const void *kernel, int bytes) {
+        if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    };
+    constexpr bool A = kDmaA<EPI>, B = kDmaB<EPI>;
+    raise(reinterpret_cast<const void *>(gemm_f32_kernel<EPI, 4, In>), smem_bytes(4));
+    raise(reinterpret_cast<const void *>(gemm_f32_kernel<EPI, 2, In>), smem_bytes(2));
+    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 4, kDmaStages, A, B, In>), dma_smem(4));
+    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 2, kDmaStages, A, B, In>), dma_smem(2));
+    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 1, kDmaStages, A, B, In>), dma_smem(1));
     return e;
+}
+
+// The sums of a group's slices, one product after the other; outputs without gaps between their rows.
+struct ReduceGroup {
+    const float *partial[kGemmGroup];
+    float *out[kGemmGroup];
+    size_t n[kGemmGroup];
+    float beta[kGemmGroup];
+    int slices, count;
+};
+__global__ __launch_bounds__(256) void gemm_f32_reduce_group_kernel(ReduceGroup g, size_t all) {
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < all; i += (size_t)gridDim.x * 256) {
+        int z = 0;
+        size_t at = i;
+        while (z + 1 < g.count && at >= g.n[z]) at -= g.n[z++];
+        float acc = g.partial[z][at];
+#pragma unroll 4
+        for (int k = 1; k < g.slices; ++k) acc += g.partial[z][k * g.n[z] + at];
+        float *o = g.out[z] + at;
+        *o = g.beta[z] == 0.f ? acc : g.beta[z] * *o + acc;
+    }
 }
 
 }  // namespace
 
-// Slices of the k range over the grid: enough for 256 workgroups, each with at least 256 k (two steps for each of its four
-// groups - below that the second kernel and the partial results cost more than the shorter chain gives).
-int gemm_f32_slices(int M, int N, int K) {
-    const long tiles = (long)((M + TM - 1) / TM) * ((N + TN - 1) / TN);
-    long cap = 16;
-    if (K > 0) cap = std::min<long>(cap, K / 256);
-    return (int)std::max<long>(1, std::min<long>(cap, 256 / std::max<long>(1, tiles)));
+// Slices for several weight gradients in one launch, by what they take (192 tiles x 2048: 41 us in one piece, 40 + 5 in two slices,
+// 35 + 6 in four): up to 256 workgroups of four groups 2.35 us per 128 k, up to 512 of two groups 2.3 us per 64 k, some us around
+// them, and the second kernel with the way of the partial results through memory.
+int gemm_f32_group_slices(const int *M, const int *N, int n, int K) {
+    long tiles = 0;
+    double outputs = 0.0;
+    for (int i = 0; i < n; ++i) {
+        tiles += (long)((M[i] + TM - 1) / TM) * ((N[i] + TN - 1) / TN);
+        outputs += (double)M[i] * N[i];
+    }
+    int best = 1;
+    double best_us = 0.0;
+    for (int s = 1; s <= std::min(16, std::max(1, K / 256)); ++s) {
+        const long items = tiles * s;
+        const double k = (double)K / s, sum = s > 1 ? 4.0 + (s + 1) * outputs * 4.0 / 4.5e6 : 0.0;
+        const double us = sum + (items <= 256 ? k / 128.0 * 2.35 + 4.0 : (double)((items + 511) / 512) * (k / 64.0 * 2.3 + 3.0));
+        if (s == 1 || us < best_us) best = s, best_us = us;
+    }
+    return best;
+}
+
+void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s) {
+    (void)prepare_kernels();
+    int M[kGemmGroup], N[kGemmGroup];
+    long tiles = 0;
+    size_t outputs = 0;
+    double flops = 0.0, bytes = 0.0;
+    for (int i = 0; i < n; ++i) {
+        M[i] = p[i].M;
+        N[i] = p[i].N;
+        tiles += (long)((M[i] + TM - 1) / TM) * ((N[i] + TN - 1) / TN);
+        outputs += (size_t)M[i] * N[i];
+        flops += 2.0 * M[i] * N[i] * p[i].K;
+        bytes += 4.0 * ((double)M[i] * p[i].K + (double)p[i].K * N[i] + (double)M[i] * N[i]);
+    }
+    const int K = p[0].K;
+    int slices = gemm_f32_group_slices(M, N, n, K);
+    if (!p[0].partial || slices * outputs > p[0].partial_floats) slices = 1;
+    const int kchunk = slices > 1 ? ((K + slices - 1) / slices + TK - 1) / TK * TK : K;
+    GemmGroup<float> group{};
+    ReduceGroup sum{};
+    group.n = sum.count = n;
+    sum.slices = slices > 1 ? (K + kchunk - 1) / kchunk : 1;
+    size_t used = 0, all = 0;
+    for (int i = 0; i < n; ++i) {
+        GemmParams<float> &q = group.p[i];
+        q = p[i];
+        q.kchunk = kchunk;
+        q.ksplit = sum.slices;
+        q.partial = p[i].partial + used;
+        sum.partial[i] = q.partial;
+        sum.out[i] = q.outf;
+        sum.n[i] = (size_t)M[i] * N[i];
+        sum.beta[i] = q.beta;
+        used += (sum.slices * sum.n[i] + 3) / 4 * 4;
+        all += sum.n[i];
+    }
+    const dim3 grid((unsigned)(tiles * sum.slices));
+    const int most = kchunk > 2 * TK ? 4 : kchunk > TK ? 2 : 1;
+    bool dma = true;
+    for (int i = 0; i < n; ++i) dma = dma && dma_takes<EPI_ACCUM_F32>(p[i], false, false);
+    {
+        ProfScope scope("gemm_f32_kernel (grouped)", flops, bytes, s);
+        launch_tiles_f32<EPI_ACCUM_F32>(group, grid, tiles * sum.slices, most, false, false, dma, false, s);
+    }
+    if (sum.slices > 1) {
+        ProfScope scope("gemm_f32_reduce_kernel", (double)sum.slices * all, 4.0 * all * (sum.slices + (p[0].beta != 0.f ? 2.0 : 1.0)), s);
+        hipLaunchKernelGGL(gemm_f32_reduce_group_kernel, dim3((unsigned)std::min<size_t>((all + 255) / 256, 2048)), dim3(256), 0, s, sum, all);
+    }
 }
 
 hipError_t gemm_f32_prepare_kernels() {
@@ -332,6 +581,7 @@ hipError_t gemm_f32_prepare_kernels() {
     if (e == hipSuccess) e = raise_epi<EPI_BIAS_GELU>();
     if (e == hipSuccess) e = raise_epi<EPI_MUL_DGELU>();
     if (e == hipSuccess) e = raise_epi<EPI_ACCUM_F32>();
+    if (e == hipSuccess) e = raise_epi<EPI_ACCUM_F32, GemmGroup<float>>();
     return e;
 }
 

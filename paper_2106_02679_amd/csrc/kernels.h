@@ -117,9 +117,10 @@ void launch_adam(float *w, float *m, float *v, const float *g, E *w16, size_t n,
 //   b_kmajor: B is stored [N][ldb] (k contiguous); otherwise [K][ldb] (n contiguous).
 // fp32 kernel (fp32 matrix instruction), any shape and alignment:
 void launch_gemm_f32(const GemmParams<float> &p, bool a_kmajor, bool b_kmajor, Epilogue epi, hipStream_t s);
-// Slices of the k range it cuts an accumulating GEMM into when it is given scratch for their partial results, slices * M * N
-// floats (1 = none; K = 0: the most any K would give).
-int gemm_f32_slices(int M, int N, int K);
+// Several weight gradients in one launch: EPI_ACCUM_F32, operands [K][M] and [K][N], the same K, ldc = N.  p[0].partial / partial_floats is
+// scratch for all, slices * (M * N + 3) floats for each.
+int gemm_f32_group_slices(const int *M, const int *N, int n, int K);
+void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s);
 // 16-bit MFMA kernel (E = bf16 or f16), fp32 accumulate.  Needs lda, ldb, ldc, N multiples of 8 and 16-byte aligned
 // bases.
 // Returns false, launching nothing, for a layout / epilogue pair that is not built (gemm_mfma_supports) or a leading

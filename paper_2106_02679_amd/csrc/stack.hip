@@ -253,10 +253,8 @@ Plan make_plan(const lga_config &c) {
             if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * outputs);
         }
     } else {
-        for (int i = 0; i < 4; ++i) {
-            const size_t slices = (size_t)gemm_f32_slices(wg_in[i], wg_out[i], (int)t);
-            if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * wg_in[i] * wg_out[i]);
-        }
+        const size_t slices = (size_t)gemm_f32_group_slices(wg_in, wg_out, 4, (int)t);
+        for (int i = 0; i < 4 && slices > 1; ++i) p.splitk_floats += slices * ((size_t)wg_in[i] * wg_out[i] + 3);
     }
     p.splitk = take(p.splitk_floats * 4);
     p.mean1 = take(t * 4);
@@ -668,7 +666,7 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
         if constexpr (std::is_same<T, float>::value) {
             g.K = t; g.beta = beta;
             g.A = X; g.lda = ldx; g.B = dY; g.ldb = ldy;
-            gemm<T>(g, false, false, EPI_ACCUM_F32, s);
+            together[n_together++] = g;
         } else {
             g.K = (gs.slot + 1) * t; g.beta = gs.beta_mat;
             if (p.stored[which]) {
@@ -719,7 +717,9 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
     dgrad(dqkv, 3 * d, o.w_qkv, d, dh, EPI_STORE, nullptr);
     // h = LN1(x); dx = dx1 + LN1'(dh)
     launch_colsums<T>(biases, n_biases, beta, s, true, &sums);
-    if constexpr (!std::is_same<T, float>::value) {          // (before dx, which may take the place of dy)
+    if constexpr (std::is_same<T, float>::value) {           // (before dx, which may take the place of dy)
+        launch_gemm_f32_group(together, n_together, s);
+    } else {
         launch_transposes<T>(moves, n_moves, s);
         if (gs.flush && n_together > 0) {
             if (n_moves > 0) launch_gemm_transposed_group<T>(together, n_together, s);

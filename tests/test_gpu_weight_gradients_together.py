@@ -1,14 +1,17 @@
 """GPU parity of the weight gradients that share a launch because a layer's matrices are not enough work one by one: the large-tile kernel
-on operands as stored, the small tiles on transposed ones; whole and ragged tiles and k ranges, with and
+on operands as stored, the small tiles on transposed ones, the fp32 kernel; whole and ragged tiles and k ranges, with and
 without slices, accumulated over groups and micro-batches.  16-bit results against the fp32 ones of the same weights and inputs (2e-2, the
 gate of 16-bit stacks), groupings against each other 1e-5 (fp32 sums in another order)."""
 import numpy as np
 import pytest
+import torch
 
 pytestmark = pytest.mark.gpu
 
+from oracle import lga_oracle as O
 import synth_inputs as S
-from gpu_helpers import run_gpu_step, rel_err, profiled
+from paper_2106_02679_amd import binding as B
+from gpu_helpers import run_gpu_step, oracle_shape, rel_err, compare_with_oracle, profiled
 
 
 def launches(kernels, start):
@@ -42,3 +45,53 @@ def test_sixteen_bit_weight_gradients_in_one_launch(d, heads, ff, s, kernel, sli
         assert rel_err(got["grads"][0], runs[0]["grads"][0]) < 1e-5
     for name, sl in S.tensor_slices(d, ff).items():
         assert rel_err(runs[0]["grads"][0][sl], exact["grads"][0][sl]) < 2e-2, name
+
+
+@pytest.mark.parametrize("d,heads,ff,s,b", [(64, 4, 256, 33, 2), (60, 3, 140, 90, 8), (30, 3, 71, 90, 8), (132, 3, 68, 300, 8)],
+                         ids=["one_piece", "slices", "widths_of_no_whole_pieces", "slices_of_two_groups"])
+def test_fp32_weight_gradients_in_one_launch(d, heads, ff, s, b):
+    w = S.Workload("together_fp32", 1, d, heads, ff, s, b, 2, "fp32")
+    x, G, params = S.make_inputs(w, seed=3, weight_std=0.1, bias_std=0.1)
+    ref = O.step_microbatch_major(x, G, params, oracle_shape(w), None)
+    for kw in (dict(group=1), dict(group=2), dict(order="mbmajor")):
+        got = []
+        kernels = profiled(lambda: got.append(run_gpu_step(w, x, G, params, retain=1, **kw)))
+        assert launches(kernels, "gemm_f32_kernel") == 2 // kw.get("group", 1)
+        compare_with_oracle(w, got[0], ref, 1e-5, None, zero_init=False)
+
+
+#        M,   N,   K: whole 16-byte pieces; steps of 32 k and tiles of 64 whole and ragged; one, two and four groups; more than 256 tiles
+DIRECT = [(4, 4, 4), (64, 64, 32), (68, 60, 36), (132, 200, 64), (64, 128, 96), (60, 64, 132), (100, 1024, 260), (1090, 1088, 100),
+          (1156, 1024, 288), (64, 64, 1028)]
+
+
+@pytest.mark.parametrize("shape", DIRECT, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("akm,bkm,epi", [(1, 0, B.LGA_EPI_BIAS), (1, 1, B.LGA_EPI_STORE), (0, 0, B.LGA_EPI_ACCUM_F32)])
+def test_fp32_operands_straight_to_lds_agree_with_the_general_kernel(akm, bkm, epi, shape):
+    """The same product from operands whose rows are whole 16-byte pieces and from copies that start 4 bytes further, which the general
+    kernel takes: both within 1e-5 of exact sums (see the tolerance of the other fp32 GEMM tests); nothing outside the operands is
+    used (NaN lies around them)."""
+    M, N, K = shape
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    results = []
+    for shift in (0, 1):
+        gen.manual_seed(M + N + K)
+
+        def operand(rows, width):
+            pitch = (width + 3) // 4 * 4
+            buf = torch.full((rows * pitch + 256,), float("nan"), device="cuda")
+            m = buf[64 + shift:64 + shift + rows * pitch].view(rows, pitch)
+            m[:, :width] = torch.randn(rows, width, device="cuda", generator=gen)
+            return m, pitch, m[:, :width].double()
+
+        a, lda, a64 = operand(*((M, K) if akm else (K, M)))
+        b, ldb, b64 = operand(*((N, K) if bkm else (K, N)))
+        bias = torch.randn(N, device="cuda", generator=gen)
+        out = torch.zeros(M, N, device="cuda")
+        want = (a64 if akm else a64.t()) @ (b64.t() if bkm else b64) + (bias.double() if epi == B.LGA_EPI_BIAS else 0.0)
+        B.check(B.lib.lga_op_gemm(B.LGA_FP32, akm, bkm, epi, M, N, K, a.data_ptr(), lda, b.data_ptr(), ldb, out.data_ptr(), None, out.data_ptr(), N,
+                                  bias.data_ptr(), None, 0.0, None))
+        torch.cuda.synchronize()
+        results.append(out)
+        assert float((out.double() - want).norm() / want.norm()) < 1e-5
+    assert float((results[0] - results[1]).norm() / results[1].norm()) < 1e-5
