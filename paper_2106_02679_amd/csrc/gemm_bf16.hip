@@ -387,11 +387,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams<E> p, int til
 // With the bias gradients' column sums in a pass of their own (99 us; they rode along with the transposes) the layer's backward
 // went from 2.26 to 1.93 ms; a training step of a d = 2048 layer over 65536 tokens from 25.0 to 24.0 ms, of a d = 12288 layer
 // over 16384 from 160.4 to 158.8.
-// In is GemmParams<E>, or GemmGroup<E>: several weight gradients in one launch, for layers whose matrices do not fill the chip one by
-// one.  Workgroups are dealt to the problems in order, each problem's slices as in a launch of its own.
-template <int BM, int BN, int WGM, int WGN, int EPI, class E, bool TN, class In>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(In in, int tiles_m, int tiles_n) {
-    constexpr bool GROUP = std::is_same<In, GemmGroup<E>>::value;
+// It takes a group of weight gradients in one launch, for layers whose matrices do not fill the chip one by one: workgroups are dealt
+// to the problems in order, each problem's slices as in a launch of its own.
+template <class E, bool TN> using DmaInput = std::conditional_t<TN, GemmGroup<E>, GemmParams<E>>;
+template <int BM, int BN, int WGM, int WGN, int EPI, class E, bool TN>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<E, TN> in, int tiles_m, int tiles_n) {
     constexpr int NW = WGM * WGN;                   // wavefronts per workgroup, WGM x WGN over the tile
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int FM = WM / 16, FN = WN / 16;       // 16 x 16 blocks of a wavefront's tile
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(In in, in
 
     GemmParams<E> p;
     int tile;
-    if constexpr (GROUP) {
+    if constexpr (TN) {
         tile = xcd_contiguous(gridDim.x);
         p = select_from_group<BM, BN>(in, tile, tiles_m, tiles_n);
     } else {
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(In in, in
         tile = xcd_contiguous(tiles_m * tiles_n * ((EPI == EPI_ACCUM_F32 && p.ksplit > 1) ? p.ksplit : p.batch > 1 ? p.batch : 1));
     }
     const int ntiles = tiles_m * tiles_n;
-    if (!GROUP && p.batch > 1) select_problem(p, tile, ntiles);
+    if (!TN && p.batch > 1) select_problem(p, tile, ntiles);
     if constexpr (EPI == EPI_ACCUM_F32) {
         if (p.ksplit > 1) {
             // this workgroup multiplies slice z of the k range into partial result z ([M][N], dense)
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(In in, in
     const int gsz = min(tiles_m - first_m, GROUP_M);
     int tm = first_m + (tile % group_size) % gsz;
     int tn = (tile % group_size) / gsz;
-    if (!GROUP && p.sblock) {
+    if (p.sblock) {
         // Round r of 256 consecutive workgroup ids is one 16 x 16 block of tiles (blocks walk along n first); XCD
         // x = id mod 8 takes rows 8 (x / 4) .. + 7 and columns 4 (x mod 4) .. + 3 of it.  All 8 XCDs then read the
         // same 16 + 16 operand panels at about the same time, so memory sees each of them once per k step instead of
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(In in, in
         tn = ((r % nsn) << 4) + ((x & 3) << 2) + (local >> 3);
     }
     const int m0 = tm * BM, n0 = tn * BN;
-    if (!GROUP && p.tri == 1 && n0 >= m0 + BM) return;   // whole workgroup: the tile lies above the diagonal
+    if (!TN && p.tri == 1 && n0 >= m0 + BM) return;      // whole workgroup: the tile lies above the diagonal
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -896,11 +896,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(In in, in
 
 // Explicit instantiations: the host compiler does not always emit the launch stub of a kernel template from its use
 // in the launchers below alone.
-#define LGA_INSTANTIATE_DMA_IN(EPI, E, TN, IN) \
-    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, E, TN, IN<E>>(IN<E>, int, int)
-#define LGA_INSTANTIATE_DMA(EPI, TN)                       \
-    LGA_INSTANTIATE_DMA_IN(EPI, bf16, TN, GemmParams);     \
-    LGA_INSTANTIATE_DMA_IN(EPI, f16, TN, GemmParams)
+#define LGA_INSTANTIATE_DMA(EPI, TN)                                                                                      \
+    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, bf16, TN>(DmaInput<bf16, TN>, int, int);            \
+    template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, f16, TN>(DmaInput<f16, TN>, int, int)
 LGA_INSTANTIATE_DMA(EPI_STORE, false);
 LGA_INSTANTIATE_DMA(EPI_BIAS, false);
 LGA_INSTANTIATE_DMA(EPI_BIAS_RESID, false);
@@ -908,10 +906,7 @@ LGA_INSTANTIATE_DMA(EPI_BIAS_GELU, false);
 LGA_INSTANTIATE_DMA(EPI_MUL_DGELU, false);
 LGA_INSTANTIATE_DMA(EPI_ACCUM_F32, false);
 LGA_INSTANTIATE_DMA(EPI_ACCUM_F32, true);
-LGA_INSTANTIATE_DMA_IN(EPI_ACCUM_F32, bf16, true, GemmGroup);
-LGA_INSTANTIATE_DMA_IN(EPI_ACCUM_F32, f16, true, GemmGroup);
 #undef LGA_INSTANTIATE_DMA
-#undef LGA_INSTANTIATE_DMA_IN
 
 // The kernel that serves a (tile size, layout, epilogue) combination and its dynamic LDS in bytes.
 template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E, bool DMA = A_KM && B_KM> struct KernelFor {
@@ -920,8 +915,9 @@ template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E, bool DMA = A_K
     static_assert(!kDma || BM == 256, "smaller k-contiguous problems: gemm_small.hip");
     static constexpr size_t smem = kDma ? (size_t)5 * BM * BK * sizeof(E)            // the DMA kernel's operand ring
                                         : (size_t)2 * (BM + BN) * BK * sizeof(E);    // two stages of both operands
-    static auto get() -> void (*)(GemmParams<E>, int, int) {
-        if constexpr (kDma) return gemm_bf16_dma_kernel<BM, BN, 2, 2, EPI, E, !A_KM, GemmParams<E>>;
+    static constexpr bool kGroup = kDma && !A_KM;
+    static auto get() -> void (*)(DmaInput<E, kGroup>, int, int) {
+        if constexpr (kDma) return gemm_bf16_dma_kernel<BM, BN, 2, 2, EPI, E, !A_KM>;
         else return gemm_bf16_kernel<BM, BN, A_KM, B_KM, EPI, E>;
     }
     // up to 160 KB of dynamic LDS: more than a launch may ask for by default
@@ -935,7 +931,7 @@ void launch_one(const GemmParams<E> &p, hipStream_t s) {
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
     using Kernel = KernelFor<BM, BN, A_KM, B_KM, EPI, E, DMA>;
     const size_t smem = Kernel::smem;
-    void (*kern)(GemmParams<E>, int, int) = Kernel::get();
+    auto kern = Kernel::get();
     char name[96];
     const char *et = std::is_same<E, bf16>::value ? "bf16" : "f16";       // profile names: gemm_bf16_... or gemm_f16_...
     if (DMA)
@@ -954,7 +950,15 @@ void launch_one(const GemmParams<E> &p, hipStream_t s) {
     ProfScope scope(name, nb * 2.0 * mn * p.K,
                     nb * (2.0 * ((double)p.M * p.K + (double)p.K * p.N) + mn * (out_bytes + aux_bytes)), s);
     const int work = tiles_m * tiles_n * (p.ksplit > 1 ? p.ksplit : p.batch > 1 ? p.batch : 1);
-    hipLaunchKernelGGL(kern, dim3(work), dim3(256), smem, s, p, tiles_m, tiles_n);
+    if constexpr (Kernel::kGroup) {
+        GemmGroup<E> one{};
+        one.n = 1;
+        one.p[0] = p;
+        one.p[0].ksplit = std::max(1, p.ksplit);
+        hipLaunchKernelGGL(kern, dim3(work), dim3(256), smem, s, one, 0, 0);
+    } else {
+        hipLaunchKernelGGL(kern, dim3(work), dim3(256), smem, s, p, tiles_m, tiles_n);
+    }
 }
 
 // out[m, n] = beta * out[m, n] + sum_z partial[z][m][n]; the slices are added in index order (deterministic).
@@ -1154,7 +1158,7 @@ template <class E> void launch_gemm_stored_group(const GemmParams<E> *p, int n, 
         char name[96];
         snprintf(name, sizeof(name), "gemm_%s_dma_tn_kernel<256, 256, %d> (grouped)", std::is_same<E, bf16>::value ? "bf16" : "f16", EPI_ACCUM_F32);
         ProfScope scope(name, flops, bytes, s);
-        hipLaunchKernelGGL((gemm_bf16_dma_kernel<256, 256, 2, 2, EPI_ACCUM_F32, E, true, GemmGroup<E>>), dim3((unsigned)work), dim3(256),
+        hipLaunchKernelGGL((gemm_bf16_dma_kernel<256, 256, 2, 2, EPI_ACCUM_F32, E, true>), dim3((unsigned)work), dim3(256),
                            (size_t)5 * 256 * BK * sizeof(E), s, group, 0, 0);
     }
     launch_splitk_reduce_group(group, s);
@@ -1269,8 +1273,6 @@ template <class E> hipError_t raise_all() {
     next(raise_pair<false, false, EPI_STORE, E>());
     next(raise_pair<false, false, EPI_ACCUM_F32, E>());
     next(KernelFor<256, 256, false, false, EPI_ACCUM_F32, E, true>::raise_lds_limit());
-    next(hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_bf16_dma_kernel<256, 256, 2, 2, EPI_ACCUM_F32, E, true, GemmGroup<E>>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, 5 * 256 * BK * (int)sizeof(E)));
     return e;
 }
 }  // namespace
