@@ -108,7 +108,7 @@ enum Epilogue : int {
     EPI_STORE = 0,       // out = acc
     EPI_BIAS = 1,        // out = acc + bias[n]
     EPI_BIAS_RESID = 2,  // out = acc + bias[n] + aux[m, n]                 (aux: residual stream)
-    EPI_BIAS_GELU = 3,   // out2 = acc + bias[n]; out = gelu(out2)           (out2: pre-activation)
+    EPI_BIAS_GELU = 3,   // out2 = acc + bias[n]; out = gelu(out2)           (out2: pre-activation; NULL: not stored)
     EPI_MUL_DGELU = 4,   // out = acc * gelu'(aux[m, n])                     (aux: pre-activation)
     EPI_ACCUM_F32 = 5    // outf = beta * outf + acc (fp32 gradient buffer)
 };

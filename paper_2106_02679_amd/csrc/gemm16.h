@@ -52,7 +52,7 @@ __device__ __forceinline__ void epilogue4(const GemmParams<E> &p, int m, int n, 
                 u[i] = (E)r[i];
                 r[i] = gelu_f(r[i]);
             }
-            *reinterpret_cast<x4<E> *>(p.out2 + idx) = u;
+            if (p.out2) *reinterpret_cast<x4<E> *>(p.out2 + idx) = u;
         }
         x4<E> o;
 #pragma unroll
@@ -93,7 +93,7 @@ __device__ __forceinline__ void epilogue8(const GemmParams<E> &p, int m, int n, 
             u[i] = (E)r[i];
             r[i] = gelu_f(r[i]);
         }
-        *reinterpret_cast<x8<E> *>(p.out2 + idx) = u;
+        if (p.out2) *reinterpret_cast<x8<E> *>(p.out2 + idx) = u;
     }
     x8<E> o;
 #pragma unroll

@@ -944,7 +944,7 @@ void launch_one(const GemmParams<E> &p, hipStream_t s) {
         snprintf(name + len, sizeof(name) - len, " (batched)");
     }
     const double mn = (double)p.M * p.N;
-    const double out_bytes = EPI == EPI_ACCUM_F32 ? (p.beta != 0.f ? 8.0 : 4.0) : (EPI == EPI_BIAS_GELU ? 4.0 : 2.0);
+    const double out_bytes = EPI == EPI_ACCUM_F32 ? (p.beta != 0.f ? 8.0 : 4.0) : (EPI == EPI_BIAS_GELU && p.out2 ? 4.0 : 2.0);
     const double aux_bytes = (EPI == EPI_BIAS_RESID || EPI == EPI_MUL_DGELU) ? 2.0 : 0.0;
     const double nb = p.batch > 1 ? p.batch : 1;
     ProfScope scope(name, nb * 2.0 * mn * p.K,

@@ -108,7 +108,7 @@ template <int EPI> __device__ __forceinline__ void epilogue_f32(const GemmParams
             p.out[at] = acc + p.bias[col] + p.aux[at];
         } else if constexpr (EPI == EPI_BIAS_GELU) {
             const float u = acc + p.bias[col];
-            p.out2[at] = u;
+            if (p.out2) p.out2[at] = u;
             p.out[at] = gelu_f(u);
         } else if constexpr (EPI == EPI_MUL_DGELU) {
             p.out[at] = acc * gelu_grad_f(p.aux[at]);
@@ -129,7 +129,7 @@ template <int EPI> __device__ __forceinline__ void epilogue_f32(const GemmParams
             for (int i = 0; i < 4; ++i) o[i] = EPI == EPI_MUL_DGELU ? o[i] * gelu_grad_f(x[i]) : o[i] + x[i];
         }
         if constexpr (EPI == EPI_BIAS_GELU) {
-            *reinterpret_cast<f32x4 *>(p.out2 + idx) = o;
+            if (p.out2) *reinterpret_cast<f32x4 *>(p.out2 + idx) = o;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[i] = gelu_f(o[i]);
         }

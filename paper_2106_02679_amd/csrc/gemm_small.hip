@@ -220,7 +220,7 @@ template <int BM, int BN, int KG, int NS, int EPI, class E> void launch_config(c
     char name[96];
     snprintf(name, sizeof(name), "gemm_%s_small_kernel<%d, %d, %d, %d>%s", et, BM, BN, KG, EPI, batched);
     const double mn = (double)p.M * p.N, nb = p.batch > 1 ? p.batch : 1;
-    const double out_bytes = EPI == EPI_ACCUM_F32 ? (p.beta != 0.f ? 8.0 : 4.0) : EPI == EPI_BIAS_GELU ? 4.0 : 2.0;
+    const double out_bytes = EPI == EPI_ACCUM_F32 ? (p.beta != 0.f ? 8.0 : 4.0) : EPI == EPI_BIAS_GELU && p.out2 ? 4.0 : 2.0;
     const double aux_bytes = (EPI == EPI_BIAS_RESID || EPI == EPI_MUL_DGELU) ? 2.0 : 0.0;
     ProfScope scope(name, nb * 2.0 * mn * p.K, nb * (2.0 * ((double)p.M * p.K + (double)p.K * p.N) + mn * (out_bytes + aux_bytes)), s);
     hipLaunchKernelGGL((gemm_small_kernel<BM, BN, KG, NS, EPI, E, GemmParams<E>>), dim3((unsigned)work), dim3(256 * KG), T::smem, s, p, tiles_m, tiles_n);
