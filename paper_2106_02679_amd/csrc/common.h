@@ -56,10 +56,22 @@ template <> __device__ __forceinline__ f32x16 mfma_32x32x16<f16>(x8<f16> a, x8<f
 }
 
 // ---- wave / block reductions -------------------------------------------------------------
+// Every lane's total of the 64 lanes, in registers: pairs, quads, eights and rows of 16 by data-parallel moves, then rows and halves
+// swapped against each other.  (Six shuffles through LDS, some 100 cycles each, were most of a short LayerNorm.)
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v += dpp_move<0xB1>(v);                 // quad_perm 1 0 3 2
+    v += dpp_move<0x4E>(v);                 // quad_perm 2 3 0 1
+    v += dpp_move<0x141>(v);                // row_half_mirror: the other quad of eight lanes
+    v += dpp_move<0x140>(v);                // row_mirror: the other eight of a row
+    const uint32_t a = __builtin_bit_cast(uint32_t, v);
+    const auto rows = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    v = __builtin_bit_cast(float, (uint32_t)rows[0]) + __builtin_bit_cast(float, (uint32_t)rows[1]);
+    const uint32_t b = __builtin_bit_cast(uint32_t, v);
+    const auto halves = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return __builtin_bit_cast(float, (uint32_t)halves[0]) + __builtin_bit_cast(float, (uint32_t)halves[1]);
 }
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
