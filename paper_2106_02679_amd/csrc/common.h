@@ -61,17 +61,21 @@ template <> __device__ __forceinline__ f32x16 mfma_32x32x16<f16>(x8<f16> a, x8<f
 template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
-__device__ __forceinline__ float wave_sum(float v) {
-    v += dpp_move<0xB1>(v);                 // quad_perm 1 0 3 2
-    v += dpp_move<0x4E>(v);                 // quad_perm 2 3 0 1
-    v += dpp_move<0x141>(v);                // row_half_mirror: the other quad of eight lanes
-    v += dpp_move<0x140>(v);                // row_mirror: the other eight of a row
+// the sum of lanes l, l + 16, l + 32, l + 48, in each of them
+__device__ __forceinline__ float sum_over_rows_of_16(float v) {
     const uint32_t a = __builtin_bit_cast(uint32_t, v);
     const auto rows = __builtin_amdgcn_permlane16_swap(a, a, false, false);
     v = __builtin_bit_cast(float, (uint32_t)rows[0]) + __builtin_bit_cast(float, (uint32_t)rows[1]);
     const uint32_t b = __builtin_bit_cast(uint32_t, v);
     const auto halves = __builtin_amdgcn_permlane32_swap(b, b, false, false);
     return __builtin_bit_cast(float, (uint32_t)halves[0]) + __builtin_bit_cast(float, (uint32_t)halves[1]);
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    v += dpp_move<0xB1>(v);                 // quad_perm 1 0 3 2
+    v += dpp_move<0x4E>(v);                 // quad_perm 2 3 0 1
+    v += dpp_move<0x141>(v);                // row_half_mirror: the other quad of eight lanes
+    v += dpp_move<0x140>(v);                // row_mirror: the other eight of a row
+    return sum_over_rows_of_16(v);
 }
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
@@ -103,7 +107,7 @@ constexpr float kGeluA = 0.044715f;
 // very negative z, whose reciprocal is the correct limit 0.
 __device__ __forceinline__ float gelu_logistic(float u, float u2) {
     constexpr float k = -2.0f * kGeluC * 1.4426950408889634f;            // exp(-2 z) = 2^(k u (1 + a u^2))
-    const float e = __builtin_amdgcn_exp2f((k * u) * fmaf(kGeluA, u2, 1.0f));
+    const float e = __builtin_amdgcn_exp2f(u * fmaf(k * kGeluA, u2, k));
     return __builtin_amdgcn_rcpf(e + 1.0f);
 }
 __device__ __forceinline__ float gelu_f(float u) { return u * gelu_logistic(u, u * u); }
@@ -135,6 +139,7 @@ template <class T> struct GemmParams {
     float *outf;     // fp32 output (EPI_ACCUM_F32)
     const float *bias;
     const T *aux;    // leading dimension ldc
+    float *colsum;   // EPI_MUL_DGELU: [chunks of 128 rows][2][N], sums of the result's columns over a chunk go to [chunk][0] (NULL: no sums)
     float beta;
     // EPI_ACCUM_F32 with few output tiles: scratch for partial results of slices of the k range (see
     // gemm_splitk_slices); NULL or too small = never split.

@@ -64,10 +64,10 @@ __device__ __forceinline__ void epilogue4(const GemmParams<E> &p, int m, int n, 
 // The same for 8 consecutive n of one row, with 16-byte accesses (bf16 outputs only): n, ldc multiples of 8 and
 // 16-byte aligned tensors.
 // aux8: the 8 values of aux at (m, n .. n + 7) for the two epilogues that read it, and b0, b1: the bias of columns
-// n .. n + 7 for the three that add it, both loaded by the caller (ahead of time).
+// n .. n + 7 for the three that add it, both loaded by the caller (ahead of time).  o: the results, too.
 template <int EPI, class E>
 __device__ __forceinline__ void epilogue8(const GemmParams<E> &p, int m, int n, const f32x4 &lo, const f32x4 &hi,
-                                          const x8<E> &aux8, const f32x4 &b0, const f32x4 &b1) {
+                                          const x8<E> &aux8, const f32x4 &b0, const f32x4 &b1, x8<E> &o) {
     static_assert(EPI != EPI_ACCUM_F32, "16-bit outputs only");
     const size_t idx = (size_t)m * p.ldc + n;
     float r[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
@@ -95,7 +95,6 @@ __device__ __forceinline__ void epilogue8(const GemmParams<E> &p, int m, int n, 
         }
         if (p.out2) *reinterpret_cast<x8<E> *>(p.out2 + idx) = u;
     }
-    x8<E> o;
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = (E)r[i];
     *reinterpret_cast<x8<E> *>(p.out + idx) = o;

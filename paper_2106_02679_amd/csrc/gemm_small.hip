@@ -207,7 +207,8 @@ __global__ __launch_bounds__(256 * KG) void gemm_small_kernel(In in, int tiles_m
             o[0] = lo;
             o[1] = hi;
         } else {
-            epilogue8<EPI, E>(p, m, n, lo, hi, aux8, b0, b1);
+            x8<E> o8;
+            epilogue8<EPI, E>(p, m, n, lo, hi, aux8, b0, b1, o8);
         }
     }
 }

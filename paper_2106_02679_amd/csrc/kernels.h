@@ -50,12 +50,19 @@ struct ColsumBatch {
     int n = 0;
 };
 void launch_colsum_batch(const ColsumBatch &batch, hipStream_t s, bool timed = true);
+// biases != NULL (with dbeta): also of_resid[c] = beta * of_resid[c] + sum_r resid[r, c] and the same of dx; partial holds
+// layernorm_bwd_partial_floats(rows, d) floats.
+struct BiasSums {
+    float *of_resid, *of_dx, *partial;
+};
 size_t layernorm_bwd_partial_floats(int rows, int d);
 template <class T>
 void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const float *rstd, const float *g,
                              const T *resid, T *dx, int rows, int d, hipStream_t s, float beta = 0.f,
                              float *dbeta = nullptr, float *dgamma = nullptr, float *partial = nullptr,
-                             ColsumBatch *batch = nullptr);
+                             ColsumBatch *batch = nullptr, const BiasSums *biases = nullptr);
+// Whether biases come at no pass of their own over rows of d elements (of esz bytes, 16-byte aligned).
+bool layernorm_bwd_adds_biases(int d, int esz);
 
 // Column sums over rows, in two deterministic passes through `partial`:
 //   out0[c] = beta * out0[c] + sum_r a[r, c]
@@ -86,7 +93,7 @@ void launch_transpose16_colsum(const E *in, E *out, int R, int C, long ldi, long
                                float *partial, hipStream_t s);
 
 // Up to eight matrices in one launch; those with partial != NULL (colsum_partial_floats(R, C) floats) also leave the first pass of their
-// column sums (values of format E) there, whose second pass add_transposed_colsum adds to a batch.
+// column sums (values of format E) there, whose second pass add_colsum adds to a batch.
 struct TransposeMatrix {
     const void *in;
     void *out;
@@ -99,7 +106,9 @@ struct TransposeBatch {
     int n;
 };
 template <class E> void launch_transposes(const TransposeMatrix *m, int n, hipStream_t s);
-void add_transposed_colsum(ColsumBatch &batch, const float *partial, int R, int C, float beta, float *out0);
+// The second pass of first passes in chunks of 128 rows, left by a kernel that had the matrix in hand
+void add_colsum(ColsumBatch &batch, const float *partial, int rows, int cols, float beta, float *out0);
+constexpr int kGemmSumRows = 128;
 
 // 1 into *flag if any of the n values is infinite or not a number (*flag is not cleared here).
 void launch_nonfinite_flag(const float *g, size_t n, int *flag, hipStream_t s);
@@ -121,6 +130,8 @@ void launch_gemm_f32(const GemmParams<float> &p, bool a_kmajor, bool b_kmajor, E
 // scratch for all, slices * (M * N + 3) floats for each.
 int gemm_f32_group_slices(const int *M, const int *N, int n, int K);
 void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s);
+// Whether an EPI_MUL_DGELU product of this size leaves the first pass of its column sums at p.colsum, in chunks of kGemmSumRows rows.
+bool gemm_dgelu_adds_columns(int M, int N, int lda, int ldb);
 // 16-bit MFMA kernel (E = bf16 or f16), fp32 accumulate.  Needs lda, ldb, ldc, N multiples of 8 and 16-byte aligned
 // bases.
 // Returns false, launching nothing, for a layout / epilogue pair that is not built (gemm_mfma_supports) or a leading

@@ -350,15 +350,17 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_kernel(const T *__restri
 // The same with a block walking over many rows: dy, x and the residual of a row are read once and kept in
 // registers, the gains too, the next row is requested before this row's block-wide sums, and the two sums share one
 // barrier (two scratch rows used in turn).  d <= TH * V * NP.
-// SUMS: every thread also adds up dy and dy * xhat of its columns over the rows its block walks, and the block writes
+// SUMS = 2: every thread also adds up dy and dy * xhat of its columns over the rows its block walks, and the block writes
 // them to partial[blockIdx.x][0 / 1][c] - the first pass of the column sums that give the gradients of the LayerNorm
 // bias and gain (colsum_final_kernel adds the blocks' rows up in a fixed order), from operands that are in registers anyway.
-template <class T, int V, int TH, int NP, bool SUMS>
+// SUMS = 4: the same for resid and dx, to more[blockIdx.x][0 / 1][c]: the gradients of the biases behind and in front of the layer's second
+// LayerNorm, for which a pass over both cost 0.06 us per MB.
+template <class T, int V, int TH, int NP, int SUMS>
 __global__ __launch_bounds__(TH) void layernorm_bwd_dx_rows_kernel(const T *__restrict__ dy, const T *__restrict__ x,
                                                                    const float *__restrict__ mean,
                                                                    const float *__restrict__ rstd,
                                                                    const float *__restrict__ g, const T *resid, T *dx,
-                                                                   int rows, int d, float *__restrict__ partial) {
+                                                                   int rows, int d, float *__restrict__ partial, float *__restrict__ more) {
     __shared__ float red[2][2][16];
     float gv[NP][V];
 #pragma unroll
@@ -389,11 +391,13 @@ __global__ __launch_bounds__(TH) void layernorm_bwd_dx_rows_kernel(const T *__re
         nmu = mean[row];
         nrs = rstd[row];
     };
-    float sb[SUMS ? NP : 1][V], sg[SUMS ? NP : 1][V];
+    float sums[SUMS ? SUMS : 1][NP][V];
 #pragma unroll
-    for (int p = 0; p < (SUMS ? NP : 1); ++p)
+    for (int k = 0; k < SUMS; ++k)
 #pragma unroll
-        for (int i = 0; i < V; ++i) sb[p][i] = sg[p][i] = 0.f;
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int i = 0; i < V; ++i) sums[k][p][i] = 0.f;
     if (blockIdx.x < (unsigned)rows) request(blockIdx.x);
     int turn = 0;
     for (size_t row = blockIdx.x; row < (size_t)rows; row += gridDim.x, turn ^= 1) {
@@ -412,10 +416,11 @@ __global__ __launch_bounds__(TH) void layernorm_bwd_dx_rows_kernel(const T *__re
                     r[p][i] = to_f32(nr[p].v[i]);
                     s1 += gd[p][i];
                     s2 += gd[p][i] * xh[p][i];
-                    if constexpr (SUMS) {
-                        sb[p][i] += a;
-                        sg[p][i] += a * xh[p][i];
+                    if constexpr (SUMS > 0) {
+                        sums[0][p][i] += a;
+                        sums[1][p][i] += a * xh[p][i];
                     }
+                    if constexpr (SUMS > 2) sums[2][p][i] += r[p][i];
                 }
             }
         }
@@ -442,23 +447,24 @@ __global__ __launch_bounds__(TH) void layernorm_bwd_dx_rows_kernel(const T *__re
             if (c < d) {
                 float o[V];
 #pragma unroll
-                for (int i = 0; i < V; ++i) o[i] = r[p][i] + rs * (gd[p][i] - t1 - xh[p][i] * t2);
+                for (int i = 0; i < V; ++i) {
+                    o[i] = r[p][i] + rs * (gd[p][i] - t1 - xh[p][i] * t2);
+                    if constexpr (SUMS > 2) sums[3][p][i] += to_f32(from_f32<T>(o[i]));        // (the values that are stored)
+                }
                 store_pack<T, V>(dxr + c, o);
             }
         }
     }
-    if constexpr (SUMS) {
+#pragma unroll
+    for (int k = 0; k < SUMS; ++k) {
+        float *to = (k < 2 ? partial : more) + ((size_t)blockIdx.x * 2 + (k & 1)) * d;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const int c = (p * TH + threadIdx.x) * V;
             if (c < d) {
 #pragma unroll
-                for (int q = 0; q < V / 4; ++q) {       // 16-byte pieces: partial is 16-byte aligned, c a multiple of 4
-                    const float b4[4] = {sb[p][4 * q], sb[p][4 * q + 1], sb[p][4 * q + 2], sb[p][4 * q + 3]};
-                    const float g4[4] = {sg[p][4 * q], sg[p][4 * q + 1], sg[p][4 * q + 2], sg[p][4 * q + 3]};
-                    store_pack<float, 4>(partial + ((size_t)blockIdx.x * 2 + 0) * d + c + 4 * q, b4);
-                    store_pack<float, 4>(partial + ((size_t)blockIdx.x * 2 + 1) * d + c + 4 * q, g4);
-                }
+                for (int q = 0; q < V; q += 4)          // 16-byte pieces: partial and more are 16-byte aligned, c a multiple of 4
+                    *reinterpret_cast<f32x4 *>(to + c + q) = f32x4{sums[k][p][q], sums[k][p][q + 1], sums[k][p][q + 2], sums[k][p][q + 3]};
             }
         }
     }
@@ -466,11 +472,11 @@ __global__ __launch_bounds__(TH) void layernorm_bwd_dx_rows_kernel(const T *__re
 
 // The same with a row per wavefront (d <= 64 V NP), for the same reason; the four wavefronts' sums meet in LDS at the end.  With the second
 // pass of the sums, 16-bit: 32768 x 768 48 us before, 39 now; 65536 x 256 68 and 30.  (Four packs a lane do not leave room for the sums.)
-template <class T, int V, int NP, bool SUMS>
+template <class T, int V, int NP, int SUMS>
 __global__ __launch_bounds__(256) void layernorm_bwd_dx_wave_kernel(const T *__restrict__ dy, const T *__restrict__ x, const float *__restrict__ mean,
                                                                     const float *__restrict__ rstd, const float *__restrict__ g, const T *resid,
-                                                                    T *dx, int rows, int d, float *__restrict__ partial) {
-    __shared__ float red[SUMS ? 4 : 1][SUMS ? 64 * V * NP : 1];
+                                                                    T *dx, int rows, int d, float *__restrict__ partial, float *__restrict__ more) {
+    __shared__ __attribute__((aligned(16))) float red[4][SUMS ? 64 * V * NP : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = gridDim.x * 4;
     int row = blockIdx.x * 4 + wave;
     Pack<T, V> na[NP], nx[NP], nr[NP];
@@ -489,7 +495,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_wave_kernel(const T *__r
         nrs = rstd[r];
     };
     if (row < rows) request(row);
-    float gv[NP][V], sb[SUMS ? NP : 1][V], sg[SUMS ? NP : 1][V];
+    float gv[NP][V], sums[SUMS ? SUMS : 1][NP][V];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const int c = (p * 64 + lane) * V;
@@ -500,9 +506,10 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_wave_kernel(const T *__r
 #pragma unroll
             for (int i = 0; i < 4; ++i) gv[p][q + i] = t4[i];
         }
-        if constexpr (SUMS)
 #pragma unroll
-            for (int i = 0; i < V; ++i) sb[p][i] = sg[p][i] = 0.f;
+        for (int k = 0; k < SUMS; ++k)
+#pragma unroll
+            for (int i = 0; i < V; ++i) sums[k][p][i] = 0.f;
     }
     for (; row < rows; row += step) {
         float gd[NP][V], xh[NP][V], r[NP][V], s1 = 0.f, s2 = 0.f;
@@ -518,10 +525,11 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_wave_kernel(const T *__r
                     r[p][i] = to_f32(nr[p].v[i]);
                     s1 += gd[p][i];
                     s2 += gd[p][i] * xh[p][i];
-                    if constexpr (SUMS) {
-                        sb[p][i] += a;
-                        sg[p][i] += a * xh[p][i];
+                    if constexpr (SUMS > 0) {
+                        sums[0][p][i] += a;
+                        sums[1][p][i] += a * xh[p][i];
                     }
+                    if constexpr (SUMS > 2) sums[2][p][i] += r[p][i];
                 }
             }
         }
@@ -533,26 +541,25 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_wave_kernel(const T *__r
             if (c < d) {
                 float o[V];
 #pragma unroll
-                for (int i = 0; i < V; ++i) o[i] = r[p][i] + rs * (gd[p][i] - t1 - xh[p][i] * t2);
+                for (int i = 0; i < V; ++i) {
+                    o[i] = r[p][i] + rs * (gd[p][i] - t1 - xh[p][i] * t2);
+                    if constexpr (SUMS > 2) sums[3][p][i] += to_f32(from_f32<T>(o[i]));        // (the values that are stored)
+                }
                 store_pack<T, V>(dx + (size_t)row * d + c, o);
             }
         }
     }
-    if constexpr (SUMS) {
 #pragma unroll
-        for (int which = 0; which < 2; ++which) {
-            if (which) __syncthreads();
+    for (int k = 0; k < SUMS; ++k) {
+        if (k) __syncthreads();
 #pragma unroll
-            for (int p = 0; p < NP; ++p)
+        for (int p = 0; p < NP; ++p)
 #pragma unroll
-                for (int i = 0; i < V; i += 4) {
-                    const float(&v)[V] = which ? sg[p] : sb[p];
-                    *reinterpret_cast<f32x4 *>(&red[wave][(p * 64 + lane) * V + i]) = f32x4{v[i], v[i + 1], v[i + 2], v[i + 3]};
-                }
-            __syncthreads();
-            for (int c = threadIdx.x; c < d; c += 256)
-                partial[((size_t)blockIdx.x * 2 + which) * d + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
-        }
+            for (int i = 0; i < V; i += 4)
+                *reinterpret_cast<f32x4 *>(&red[wave][(p * 64 + lane) * V + i]) = f32x4{sums[k][p][i], sums[k][p][i + 1], sums[k][p][i + 2], sums[k][p][i + 3]};
+        __syncthreads();
+        float *to = (k < 2 ? partial : more) + ((size_t)blockIdx.x * 2 + (k & 1)) * d;
+        for (int c = threadIdx.x; c < d; c += 256) to[c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
     }
 }
 
@@ -960,7 +967,7 @@ static void finish_colsum(ColsumBatch *batch, const float *partial, int chunks, 
 template <class T>
 void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const float *rstd, const float *g,
                              const T *resid, T *dx, int rows, int d, hipStream_t s, float beta, float *dbeta,
-                             float *dgamma, float *partial, ColsumBatch *batch) {
+                             float *dgamma, float *partial, ColsumBatch *batch, const BiasSums *biases) {
     constexpr int V = VecOf<T>::N;
     const bool sums = dbeta != nullptr;
     const bool vec = d % V == 0 && aligned16(dy) && aligned16(x) && aligned16(resid) && aligned16(dx);
@@ -969,24 +976,32 @@ void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const f
     // per thread do not fit beside the row
     const bool fused = sums && rows_kernel && d <= 1024 * V && rows > 0 && aligned16(partial);
     if (sums && !fused) launch_colsum<T>(dy, x, mean, rstd, rows, d, d, beta, dbeta, dgamma, partial, s, true, batch);
-    if (rows == 0) return;
+    const bool all = fused && biases && aligned16(biases->partial);
+    if (biases && !all) launch_colsum<T>(resid, nullptr, nullptr, nullptr, rows, d, d, beta, biases->of_resid, nullptr, biases->partial, s, true, nullptr);
+    if (rows == 0) {
+        if (biases) launch_colsum<T>(dx, nullptr, nullptr, nullptr, rows, d, d, beta, biases->of_dx, nullptr, biases->partial, s, true, nullptr);
+        return;
+    }
     {
-        ProfScope scope(fused ? "layernorm_bwd_dx_kernel(with sums)" : "layernorm_bwd_dx_kernel", (fused ? 18.0 : 14.0) * rows * d,
+        ProfScope scope(fused ? "layernorm_bwd_dx_kernel(with sums)" : "layernorm_bwd_dx_kernel", (all ? 20.0 : fused ? 18.0 : 14.0) * rows * d,
                         4.0 * sizeof(T) * rows * (double)d, s);
         const int blocks = lnb_rows_blocks(rows, d, V);
         if (rows_kernel) {
 #define LGA_LNB_ROWS(TH, NP, SUMS) \
             hipLaunchKernelGGL((layernorm_bwd_dx_rows_kernel<T, V, TH, NP, SUMS>), dim3((unsigned)blocks), dim3(TH), 0, s, dy, x, \
-                               mean, rstd, g, resid, dx, rows, d, partial)
+                               mean, rstd, g, resid, dx, rows, d, partial, all ? biases->partial : nullptr)
 #define LGA_LNB_WAVE(NP, SUMS) \
             hipLaunchKernelGGL((layernorm_bwd_dx_wave_kernel<T, V, NP, SUMS>), dim3((unsigned)blocks), dim3(256), 0, s, dy, x, mean, rstd, g, \
-                               resid, dx, rows, d, partial)
-            if (d <= 64 * V) { if (fused) LGA_LNB_WAVE(1, true); else LGA_LNB_WAVE(1, false); }
-            else if (d <= kLnbWave * 64 * V) { if (fused) LGA_LNB_WAVE(2, true); else LGA_LNB_WAVE(2, false); }
-            else if (d <= 256 * V) { if (fused) LGA_LNB_ROWS(256, 1, true); else LGA_LNB_ROWS(256, 1, false); }
-            else if (d <= 512 * V) { if (fused) LGA_LNB_ROWS(512, 1, true); else LGA_LNB_ROWS(512, 1, false); }
-            else if (d <= 1024 * V) { if (fused) LGA_LNB_ROWS(1024, 1, true); else LGA_LNB_ROWS(1024, 1, false); }
-            else LGA_LNB_ROWS(1024, 2, false);
+                               resid, dx, rows, d, partial, all ? biases->partial : nullptr)
+#define LGA_LNB_SUMS(LAUNCH, ...) \
+            do { if (all) LAUNCH(__VA_ARGS__, 4); else if (fused) LAUNCH(__VA_ARGS__, 2); else LAUNCH(__VA_ARGS__, 0); } while (0)
+            if (d <= 64 * V) LGA_LNB_SUMS(LGA_LNB_WAVE, 1);
+            else if (d <= kLnbWave * 64 * V) LGA_LNB_SUMS(LGA_LNB_WAVE, 2);
+            else if (d <= 256 * V) LGA_LNB_SUMS(LGA_LNB_ROWS, 256, 1);
+            else if (d <= 512 * V) LGA_LNB_SUMS(LGA_LNB_ROWS, 512, 1);
+            else if (d <= 1024 * V) LGA_LNB_SUMS(LGA_LNB_ROWS, 1024, 1);
+            else LGA_LNB_ROWS(1024, 2, 0);
+#undef LGA_LNB_SUMS
 #undef LGA_LNB_ROWS
 #undef LGA_LNB_WAVE
         } else if (vec)
@@ -997,14 +1012,17 @@ void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const f
                                dx, d);
     }
     if (fused) finish_colsum(batch, partial, lnb_rows_blocks(rows, d, V), d, beta, dbeta, dgamma, s);
+    if (all) finish_colsum(batch, biases->partial, lnb_rows_blocks(rows, d, V), d, beta, biases->of_resid, biases->of_dx, s);
+    else if (biases) launch_colsum<T>(dx, nullptr, nullptr, nullptr, rows, d, d, beta, biases->of_dx, nullptr, biases->partial, s, true, nullptr);
 }
+bool layernorm_bwd_adds_biases(int d, int esz) { return d % (16 / esz) == 0 && d <= 1024 * (16 / esz); }
 template void launch_layernorm_bwd_dx<float>(const float *, const float *, const float *, const float *,
                                              const float *, const float *, float *, int, int, hipStream_t, float,
-                                             float *, float *, float *, ColsumBatch *);
+                                             float *, float *, float *, ColsumBatch *, const BiasSums *);
 template void launch_layernorm_bwd_dx<bf16>(const bf16 *, const bf16 *, const float *, const float *, const float *,
-                                            const bf16 *, bf16 *, int, int, hipStream_t, float, float *, float *, float *, ColsumBatch *);
+                                            const bf16 *, bf16 *, int, int, hipStream_t, float, float *, float *, float *, ColsumBatch *, const BiasSums *);
 template void launch_layernorm_bwd_dx<f16>(const f16 *, const f16 *, const float *, const float *, const float *,
-                                            const f16 *, f16 *, int, int, hipStream_t, float, float *, float *, float *, ColsumBatch *);
+                                            const f16 *, f16 *, int, int, hipStream_t, float, float *, float *, float *, ColsumBatch *, const BiasSums *);
 
 size_t colsum_partial_floats(int rows, int cols) {
     const size_t chunks = ((size_t)rows + kColsumRows - 1) / kColsumRows;
@@ -1111,8 +1129,9 @@ void launch_transpose16_colsum(const E *in, E *out, int R, int C, long ldi, long
 template void launch_transpose16_colsum<bf16>(const bf16 *, bf16 *, int, int, long, long, float, float *, float *, hipStream_t);
 template void launch_transpose16_colsum<f16>(const f16 *, f16 *, int, int, long, long, float, float *, float *, hipStream_t);
 
-void add_transposed_colsum(ColsumBatch &batch, const float *partial, int R, int C, float beta, float *out0) {
-    finish_colsum(&batch, partial, (R + kTrTile - 1) / kTrTile, C, beta, out0, nullptr, nullptr);
+void add_colsum(ColsumBatch &batch, const float *partial, int rows, int cols, float beta, float *out0) {
+    static_assert(kTrTile == kColsumRows && kGemmSumRows == kColsumRows, "chunks of 128 rows, whichever kernel leaves them");
+    finish_colsum(&batch, partial, (rows + kColsumRows - 1) / kColsumRows, cols, beta, out0, nullptr, nullptr);
 }
 
 template <class E>

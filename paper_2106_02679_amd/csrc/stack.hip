@@ -264,7 +264,8 @@ Plan make_plan(const lga_config &c) {
     const size_t stats = (size_t)c.group * c.micro_batch * c.n_heads * c.seq_len;
     p.lse = take(stats * 4);
     p.delta = take(stats * 4);
-    for (int i = 0; i < 4; ++i) p.partial[i] = take(colsum_partial_floats((int)t, wg_out[i]) * 4);
+    for (int i = 0; i < 4; ++i)
+        p.partial[i] = take(std::max(colsum_partial_floats((int)t, wg_out[i]), i == 0 ? layernorm_bwd_partial_floats((int)t, (int)d) : 0) * 4);
     for (int i = 4; i < 6; ++i) p.partial[i] = take(layernorm_bwd_partial_floats((int)t, (int)d) * 4);
     p.nonfinite = take(L * 4);          // one flag per layer, see lga_adam.skip_nonfinite
     // head sizes without a fused attention kernel: score matrices of as many heads of one sequence as fit 4 GiB
@@ -647,6 +648,14 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
     ColsumBatch sums;
     ColsumMatrix<T> biases[4];
     int n_biases = 0;
+    // Three of the four bias gradients are sums over matrices that a kernel has in hand anyway, where they do not come with a transpose:
+    // dy and dx1 (b_2, b_o) in the second LayerNorm's backward, du (b_1) in the product that makes it.  From 64 MB on: what is smaller is still in
+    // the caches when one launch adds up all four (d = 768, 32768 tokens: that pass 100 -> 29 us, the product + 10, the LayerNorm + 3; 4096
+    // tokens: 11 -> 8, + 4, + 2).
+    constexpr size_t kCached = (size_t)64 << 20;
+    const bool moved_2 = !std::is_same<T, float>::value && !p.stored[0], moved_o = !std::is_same<T, float>::value && !p.stored[2];
+    const bool rows_add = !moved_2 && !moved_o && 2 * sizeof(T) * t * d >= kCached && layernorm_bwd_adds_biases(d, (int)sizeof(T));
+    const bool dgelu_adds = !std::is_same<T, float>::value && p.stored[1] && sizeof(T) * t * f >= kCached && gemm_dgelu_adds_columns(t, f, d, d);
     // The weight gradients that are not enough work alone wait, with their transposes, until all operands are there.
     GemmParams<T> together[4];
     TransposeMatrix moves[8];
@@ -682,17 +691,20 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
                 // the bias gradient is the column sum of dY: taken from the tiles as they are transposed
                 moves[n_moves++] = {X, xT + (size_t)gs.slot * t, nullptr, ldx, ldk, t, in, 0};
                 moves[n_moves++] = {dY, dyT + (size_t)gs.slot * t, partial, ldy, ldk, t, out, 0};
-                add_transposed_colsum(sums, partial, t, out, beta, gbuf + b_off);
+                add_colsum(sums, partial, t, out, beta, gbuf + b_off);
                 g.A = xT; g.lda = ldk; g.B = dyT; g.ldb = ldk;
                 together[n_together++] = g;
                 return;
             }
         }
-        biases[n_biases++] = {dY, nullptr, nullptr, nullptr, gbuf + b_off, nullptr, partial, t, out, ldy};
+        if (which == 1 && dgelu_adds) add_colsum(sums, partial, t, out, beta, gbuf + b_off);
+        else if (!(rows_add && (which == 0 || which == 2)))
+            biases[n_biases++] = {dY, nullptr, nullptr, nullptr, gbuf + b_off, nullptr, partial, t, out, ldy};
     };
     // lda: row pitch of dY, ldc: of dX and aux, where they differ from the widths
     auto dgrad = [&](const T *dY, int out, size_t w_off, int in, T *dX, Epilogue e, const T *aux, int lda = 0, int ldc = 0) {
         GemmParams<T> g{};
+        if (e == EPI_MUL_DGELU && dgelu_adds) g.colsum = st->at<float>(p.partial[1]);
         g.A = dY; g.lda = lda ? lda : out; g.B = pw + w_off; g.ldb = out; g.M = t; g.N = in; g.K = out;
         g.out = dX; g.ldc = ldc ? ldc : in; g.aux = aux;
         gemm<T>(g, true, true, e, s);
@@ -705,8 +717,9 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
     wgrad(1, h2, d, du, f, o.w_1, o.b_1, 0, ldf);
     dgrad(du, f, o.w_1, d, dh2, EPI_STORE, nullptr, ldf, 0);
     // h2 = LN2(x1); dx1 = dy + LN2'(dh2)
+    const BiasSums of_rows{gbuf + o.b_2, gbuf + o.b_o, st->at<float>(p.partial[0])};
     launch_layernorm_bwd_dx<T>(dh2, x1, mean2, rstd2, pf + o.ln2_g, dy, dx1, t, d, s, beta, gbuf + o.ln2_b, gbuf + o.ln2_g,
-                               st->at<float>(p.partial[4]), &sums);
+                               st->at<float>(p.partial[4]), &sums, rows_add ? &of_rows : nullptr);
     // x1 = x + a Wo + bo
     wgrad(2, a, d, dx1, d, o.w_o, o.b_o);
     dgrad(dx1, d, o.w_o, d, da, EPI_STORE, nullptr);

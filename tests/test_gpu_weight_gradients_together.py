@@ -95,3 +95,29 @@ def test_fp32_operands_straight_to_lds_agree_with_the_general_kernel(akm, bkm, e
         results.append(out)
         assert float((out.double() - want).norm() / want.norm()) < 1e-5
     assert float((results[0] - results[1]).norm() / results[1].norm()) < 1e-5
+
+
+@pytest.mark.parametrize("dtype,s,widths", [("bf16", 1030, (4, 3)), ("fp32", 1000, (9, 7))], ids=["bf16", "fp32"])
+def test_bias_gradients_summed_where_their_matrices_are_made(dtype, s, widths):
+    """From 64 MB on (here two micro-batches per launch; one has it for W_1 only, in bf16, where b_o comes with a transpose) the second LayerNorm's backward and the GELU' product
+    leave the bias gradients' first passes: the same values in other chunks, so 1e-5 between the two, over a ragged last chunk; b_2
+    against the column sum of the output gradient itself."""
+    w = S.Workload("sums", 1, 1024, 16, 4096, s, 8, 4, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    params = np.random.default_rng(2).standard_normal(w.params_per_layer).astype(np.float32) * 0.02
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x, g = (torch.randn(4, 8, s, 1024, device="cuda", generator=gen).to(tdt) for _ in range(2))
+    dx, sl, got = torch.empty_like(x), S.tensor_slices(1024, 4096), []
+    for group in (1, 2):
+        st = B.Stack(B.make_config(1, 1024, 16, 4096, s, 8, 4, B.LGA_BF16 if dtype == "bf16" else B.LGA_FP32, group=group, retain_grads=1), params)
+        st.forward_layered(x.data_ptr(), None)
+        kernels = profiled(lambda: st.backward_layered(g.data_ptr(), dx.data_ptr(), None))
+        grads = B.read_device(*st.grads(0), "float32").astype(np.float64)
+        st.close()
+        got.append({n: grads[sl[n]] for n in ("b_qkv", "b_o", "b_1", "b_2", "ln2_g", "ln2_b")})
+        sums = [k for n, k in kernels.items() if n.startswith("colsum_partial")]
+        assert sum(k["bytes"] for k in sums) == tdt.itemsize * 4 * 8 * s * 1024 * widths[group - 1]        # what is left of 9 widths
+    for name, ref in got[0].items():
+        assert rel_err(got[1][name], ref) < 1e-5, name
+    for run in got:
+        assert rel_err(run["b_2"], g.double().sum((0, 1, 2)).cpu().numpy()) < 1e-6
