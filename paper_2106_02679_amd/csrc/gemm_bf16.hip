@@ -1040,6 +1040,21 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_slices(const GemmP
     launch_splitk_reduce(p.partial, q.ksplit, p.outf, p.M, p.N, p.ldc, p.beta, s);
 }
 
+// Columns that the large-tile kernel leaves to the small one (0: none).  Its tiles run in rounds of 256, and a last round of a few takes as
+// long as a full one; the columns beyond the whole rounds are better off on small tiles where they are few - by what a round takes
+// (1.2 us per k tile and 12 us) against what the small tiles do (550 TFLOP/s, at least 0.42 us per 64 k, 6 us): 2000 x 17024 x 4256,
+// 536 tiles, with GELU 322 -> 219 + 42 us.  Either kernel adds up an element's products in the same order.
+int peeled_columns(int M, int N, int K) {
+    const long tm = (M + 255) / 256, tn = (N + 255) / 256, rounds = tm * tn / 256;
+    if (rounds < 1 || rounds > 4 || tm * tn % 256 == 0 || tm > 256) return 0;
+    const long keep = rounds * 256 / tm;                     // whole columns of tiles that the full rounds hold
+    const int rest = N - (int)keep * 256;
+    if (keep < 1 || rest <= 0) return 0;
+    const double ksteps = (double)K / BK, round = ksteps * 1.2 + 12.0;
+    const double small = std::max(2e-6 * M * rest * K / 550.0, ksteps * 0.42) + 6.0;
+    return small < 0.8 * round ? rest : 0;
+}
+
 template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmParams<E> &p, hipStream_t s) {
     // Large tiles when they fill the 256 CUs at least about once (the direct-to-LDS kernel is so much faster per
     // tile that a partly idle second round still wins); smaller ones otherwise.
@@ -1066,6 +1081,21 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmPa
         }
         if (!large || short_rows) return launch_gemm_small<EPI, E>(p, s);
         GemmParams<E> q = p;
+        const int rest = EPI == EPI_ACCUM_F32 || p.batch > 1 || p.tri || p.colsum ? 0 : peeled_columns(p.M, p.N, p.K);
+        if (rest > 0) {
+            const int n = p.N - rest;
+            q.N = rest;
+            q.B += (size_t)n * p.ldb;
+            q.out += n;
+            if (q.out2) q.out2 += n;
+            if (q.bias) q.bias += n;
+            if (q.aux) q.aux += n;
+            launch_gemm_small<EPI, E>(q, s);
+            q = p;
+            q.N = n;
+            launch_one<256, 256, A_KM, B_KM, EPI, E>(q, s);
+            return;
+        }
         const int tm = (p.M + 255) / 256, tn = (p.N + 255) / 256;
         q.sblock = p.batch <= 1 && tm % 16 == 0 && tn % 16 == 0;     // + 1 % on the weight-gradient shapes of d = 12288
         launch_one<256, 256, A_KM, B_KM, EPI, E>(q, s);
@@ -1155,6 +1185,23 @@ int gemm_group_slices(const int *M, const int *N, int n, int K) {
     return best;
 }
 
+// Matrices that are enough work alone still share a launch where their last rounds then fill each other up, by the same times: T-NLG's four
+// (289 to 1139 tiles over 4000 tokens, 14 rounds together, 16 apart) 1505 -> 1425 us; d = 2048 over 65536, W_o and W_qkv with 64 and 192
+// tiles in slices apart, all 768 whole together, 2226 -> 2073.
+bool gemm_stored_group_wins(const int *M, const int *N, int n, int K) {
+    long tiles = 0;
+    double apart = 0.0;
+    const double round = (double)K / BK * 1.2 + 12.0;
+    for (int i = 0; i < n; ++i) {
+        const long mine = (long)((M[i] + 255) / 256) * ((N[i] + 255) / 256);
+        const int slices = gemm_splitk_slices(M[i], N[i], K);
+        tiles += mine;
+        apart += (double)((mine * slices + 255) / 256) * ((double)K / slices / BK * 1.2 + 12.0) +
+                 (slices > 1 ? (slices + 1) * (double)M[i] * N[i] * 4.0 / 4.5e6 : 0.0);
+    }
+    return n > 1 && tiles >= 224 && (double)((tiles + 255) / 256) * round < 0.99 * apart;
+}
+
 template <class E> void launch_gemm_stored_group(const GemmParams<E> *p, int n, hipStream_t s) {
     int M[kGemmGroup], N[kGemmGroup];
     size_t outputs = 0;
@@ -1234,8 +1281,10 @@ int gemm_splitk_slices(int M, int N, int K) {
     return 1;
 }
 
-bool gemm_dgelu_adds_columns(int M, int N, int lda, int ldb) {
-    return (long)((M + 255) / 256) * ((N + 255) / 256) >= 128 && lda >= BK && ldb >= BK;        // the large-tile kernel, see launch_tiles
+// (The large-tile kernel alone, see launch_tiles.  Columns left to the small one are worth more than the pass over the result: 2000 x 17024 x
+// 4256 with GELU' 341 -> 233 + 41 us, the pass 15.)
+bool gemm_dgelu_adds_columns(int M, int N, int K) {
+    return (long)((M + 255) / 256) * ((N + 255) / 256) >= 128 && K >= BK && peeled_columns(M, N, K) == 0;
 }
 
 bool gemm_mfma_supports(bool a_kmajor, bool b_kmajor, Epilogue epi) {

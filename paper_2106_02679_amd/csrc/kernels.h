@@ -130,8 +130,9 @@ void launch_gemm_f32(const GemmParams<float> &p, bool a_kmajor, bool b_kmajor, E
 // scratch for all, slices * (M * N + 3) floats for each.
 int gemm_f32_group_slices(const int *M, const int *N, int n, int K);
 void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s);
-// Whether an EPI_MUL_DGELU product of this size leaves the first pass of its column sums at p.colsum, in chunks of kGemmSumRows rows.
-bool gemm_dgelu_adds_columns(int M, int N, int lda, int ldb);
+// Whether an EPI_MUL_DGELU product of this size (lda = ldb = K) leaves the first pass of its column sums at p.colsum, in chunks of
+// kGemmSumRows rows.
+bool gemm_dgelu_adds_columns(int M, int N, int K);
 // 16-bit MFMA kernel (E = bf16 or f16), fp32 accumulate.  Needs lda, ldb, ldc, N multiples of 8 and 16-byte aligned
 // bases.
 // Returns false, launching nothing, for a layout / epilogue pair that is not built (gemm_mfma_supports) or a leading
@@ -153,6 +154,7 @@ template <class E> void launch_gemm_stored_group(const GemmParams<E> *p, int n, 
 template <class E> void launch_gemm_transposed_group(const GemmParams<E> *p, int n, hipStream_t s);
 template <class E> void launch_gemm_small_group(const GemmParams<E> *p, int n, hipStream_t s);
 int gemm_group_slices(const int *M, const int *N, int n, int K);
+bool gemm_stored_group_wins(const int *M, const int *N, int n, int K);         // over a launch each, for matrices that are enough work alone
 // A group's parameters with the k range in so many slices (1: not cut), and the sum of the slices (nothing to do without)
 template <class E> void prepare_gemm_group(GemmGroup<E> &group, const GemmParams<E> *p, int slices);
 template <class E> void launch_splitk_reduce_group(const GemmGroup<E> &group, hipStream_t s);

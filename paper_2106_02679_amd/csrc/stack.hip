@@ -147,7 +147,7 @@ struct Plan {
     // The four weight-gradient GEMMs (W_2, W_1, W_o, W_qkv) of the 16-bit modes: stored[i] = it reads the activations and output gradients
     // as the layer stores them, whose buffers then hold wgrad_groups groups; otherwise transposed copies of them, xT and dyT.
     bool stored[4];
-    bool grouped[4];           // those among the stored ones that are only enough work together, in one launch
+    bool grouped[4];           // those among the stored ones that share a launch
     size_t xT[4], dyT[4];
     int wgrad_groups;          // groups whose tokens one weight-gradient GEMM contracts over
     int dact_groups;           // groups in the ring that dact is where stored[0] (see ActivationGradient); 0: dact holds all groups, in place
@@ -196,8 +196,15 @@ Plan make_plan(const lga_config &c) {
         if (p.stored[i]) ++alone;
         else rest[i - alone] = i, M[i - alone] = wg_in[i], N[i - alone] = wg_out[i];
     }
-    if (is16 && alone < 3 && gemm_group_slices(M, N, 4 - alone, (int)t) > 0)
+    if (is16 && alone < 3 && gemm_group_slices(M, N, 4 - alone, (int)t) > 0) {
         for (int i = 0; i < 4 - alone; ++i) p.stored[rest[i]] = p.grouped[rest[i]] = true;
+    } else if (is16) {
+        int n = 0, m_all[4], n_all[4];
+        for (int i = 0; i < 4; ++i)
+            if (p.stored[i]) m_all[n] = wg_in[i], n_all[n++] = wg_out[i];
+        if (gemm_stored_group_wins(m_all, n_all, n, (int)t))
+            for (int i = 0; i < 4; ++i) p.grouped[i] = p.stored[i];
+    }
     auto take_activations = [&](size_t wb) {
         const size_t n_2 = p.stored[0] ? wb : 1, n_1 = p.stored[1] ? wb : 1, n_o = p.stored[2] ? wb : 1, n_qkv = p.stored[3] ? wb : 1;
         // (the d_ff-wide buffers' padding: as much as all groups need, so that it does not depend on wb)
@@ -248,8 +255,11 @@ Plan make_plan(const lga_config &c) {
             if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * wg_in[i] * wg_out[i]);
             if (p.grouped[i]) any = true, outputs += (size_t)wg_in[i] * wg_out[i];
         }
+        int n = 0, m_all[4], n_all[4];
+        for (int i = 0; i < 4; ++i)
+            if (p.grouped[i]) m_all[n] = wg_in[i], n_all[n++] = wg_out[i];
         for (size_t k = 1; any && k <= wb; ++k) {
-            const size_t slices = (size_t)gemm_group_slices(M, N, 4 - alone, (int)(k * t));
+            const size_t slices = (size_t)gemm_group_slices(m_all, n_all, n, (int)(k * t));
             if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * outputs);
         }
     } else {
@@ -655,11 +665,11 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
     constexpr size_t kCached = (size_t)64 << 20;
     const bool moved_2 = !std::is_same<T, float>::value && !p.stored[0], moved_o = !std::is_same<T, float>::value && !p.stored[2];
     const bool rows_add = !moved_2 && !moved_o && 2 * sizeof(T) * t * d >= kCached && layernorm_bwd_adds_biases(d, (int)sizeof(T));
-    const bool dgelu_adds = !std::is_same<T, float>::value && p.stored[1] && sizeof(T) * t * f >= kCached && gemm_dgelu_adds_columns(t, f, d, d);
+    const bool dgelu_adds = !std::is_same<T, float>::value && p.stored[1] && sizeof(T) * t * f >= kCached && gemm_dgelu_adds_columns(t, f, d);
     // The weight gradients that are not enough work alone wait, with their transposes, until all operands are there.
-    GemmParams<T> together[4];
+    GemmParams<T> together[4], moved[4];                     // on operands as stored, on transposed copies
     TransposeMatrix moves[8];
-    int n_together = 0, n_moves = 0;
+    int n_together = 0, n_moved = 0, n_moves = 0;
 
     // gW[in, out] (+)= X[t, in]^T dY[t, out], contracted over tokens.  The 16-bit modes' large-tile kernel takes both operands as they
     // are; the kernels for smaller gradients read k-contiguous ones, X^T [in][.] and dY^T [out][.], written first.  `which` names the
@@ -693,7 +703,7 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
                 moves[n_moves++] = {dY, dyT + (size_t)gs.slot * t, partial, ldy, ldk, t, out, 0};
                 add_colsum(sums, partial, t, out, beta, gbuf + b_off);
                 g.A = xT; g.lda = ldk; g.B = dyT; g.ldb = ldk;
-                together[n_together++] = g;
+                moved[n_moved++] = g;
                 return;
             }
         }
@@ -736,10 +746,8 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
         launch_gemm_f32_group(together, n_together, s);
     } else {
         launch_transposes<T>(moves, n_moves, s);
-        if (gs.flush && n_together > 0) {
-            if (n_moves > 0) launch_gemm_transposed_group<T>(together, n_together, s);
-            else launch_gemm_stored_group<T>(together, n_together, s);
-        }
+        if (gs.flush && n_together > 0) launch_gemm_stored_group<T>(together, n_together, s);
+        if (gs.flush && n_moved > 0) launch_gemm_transposed_group<T>(moved, n_moved, s);
     }
     launch_layernorm_bwd_dx<T>(dh, x_in, mean1, rstd1, pf + o.ln1_g, dx1, dx, t, d, s, beta, gbuf + o.ln1_b, gbuf + o.ln1_g,
                                st->at<float>(p.partial[5]), &sums);

@@ -1,4 +1,4 @@
-"""GPU parity of the weight gradients that share a launch because a layer's matrices are not enough work one by one: the large-tile kernel
+"""GPU parity of the weight gradients that share a launch because a layer's matrices are not enough work one by one, or fill its rounds better: the large-tile kernel
 on operands as stored, the small tiles on transposed ones, the fp32 kernel; whole and ragged tiles and k ranges, with and
 without slices, accumulated over groups and micro-batches.  16-bit results against the fp32 ones of the same weights and inputs (2e-2, the
 gate of 16-bit stacks), groupings against each other 1e-5 (fp32 sums in another order)."""
@@ -22,6 +22,7 @@ def launches(kernels, start):
     (768, 12, 3072, 1024, "gemm_bf16_dma_tn_kernel", True),        # 108 tiles, 2 x 2048 tokens
     (520, 13, 2088, 1032, "gemm_bf16_dma_tn_kernel", True),        # ragged tiles and k steps: 90 tiles, 3 slices, the last of 1344
     (1304, 163, 1304, 300, "gemm_bf16_dma_tn_kernel", False),      # ragged tiles, 1200 tokens in one piece
+    (2048, 16, 4104, 258, "gemm_bf16_dma_tn_kernel", False),       # 136, 136 and 192 tiles, two rounds instead of three; W_o apart
     (128, 2, 512, 64, "gemm_bf16_small_kernel", False),            # tiles of 32 x 64, four groups
     (136, 17, 264, 1250, "gemm_bf16_small_kernel", True),          # 34 tiles of 64 x 64, 5000 tokens in slices, ragged everywhere
     (256, 4, 1024, 40, "gemm_bf16_small_kernel", False),           # 192 tiles of 64 x 64, two groups
@@ -97,26 +98,26 @@ def test_fp32_operands_straight_to_lds_agree_with_the_general_kernel(akm, bkm, e
     assert float((results[0] - results[1]).norm() / results[1].norm()) < 1e-5
 
 
-@pytest.mark.parametrize("dtype,s,widths", [("bf16", 1030, (4, 3)), ("fp32", 1000, (9, 7))], ids=["bf16", "fp32"])
-def test_bias_gradients_summed_where_their_matrices_are_made(dtype, s, widths):
-    """From 64 MB on (here two micro-batches per launch; one has it for W_1 only, in bf16, where b_o comes with a transpose) the second LayerNorm's backward and the GELU' product
+@pytest.mark.parametrize("dtype,d,s,widths", [("bf16", 2048, 763, (5, 3)), ("fp32", 1024, 1000, (9, 7))], ids=["bf16", "fp32"])
+def test_bias_gradients_summed_where_their_matrices_are_made(dtype, d, s, widths):
+    """From 64 MB on (here two micro-batches per launch; one has it for du only, in bf16) the second LayerNorm's backward and the GELU' product
     leave the bias gradients' first passes: the same values in other chunks, so 1e-5 between the two, over a ragged last chunk; b_2
     against the column sum of the output gradient itself."""
-    w = S.Workload("sums", 1, 1024, 16, 4096, s, 8, 4, dtype)
+    w = S.Workload("sums", 1, d, 16, 4 * d, s, 8, 4, dtype)
     gen = torch.Generator(device="cuda").manual_seed(2)
     params = np.random.default_rng(2).standard_normal(w.params_per_layer).astype(np.float32) * 0.02
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
-    x, g = (torch.randn(4, 8, s, 1024, device="cuda", generator=gen).to(tdt) for _ in range(2))
-    dx, sl, got = torch.empty_like(x), S.tensor_slices(1024, 4096), []
+    x, g = (torch.randn(4, 8, s, d, device="cuda", generator=gen).to(tdt) for _ in range(2))
+    dx, sl, got = torch.empty_like(x), S.tensor_slices(d, 4 * d), []
     for group in (1, 2):
-        st = B.Stack(B.make_config(1, 1024, 16, 4096, s, 8, 4, B.LGA_BF16 if dtype == "bf16" else B.LGA_FP32, group=group, retain_grads=1), params)
+        st = B.Stack(B.make_config(1, d, 16, 4 * d, s, 8, 4, B.LGA_BF16 if dtype == "bf16" else B.LGA_FP32, group=group, retain_grads=1), params)
         st.forward_layered(x.data_ptr(), None)
         kernels = profiled(lambda: st.backward_layered(g.data_ptr(), dx.data_ptr(), None))
         grads = B.read_device(*st.grads(0), "float32").astype(np.float64)
         st.close()
         got.append({n: grads[sl[n]] for n in ("b_qkv", "b_o", "b_1", "b_2", "ln2_g", "ln2_b")})
         sums = [k for n, k in kernels.items() if n.startswith("colsum_partial")]
-        assert sum(k["bytes"] for k in sums) == tdt.itemsize * 4 * 8 * s * 1024 * widths[group - 1]        # what is left of 9 widths
+        assert sum(k["bytes"] for k in sums) == tdt.itemsize * 4 * 8 * s * d * widths[group - 1]        # what is left of 9 widths
     for name, ref in got[0].items():
         assert rel_err(got[1][name], ref) < 1e-5, name
     for run in got:
