@@ -65,7 +65,8 @@ __device__ __forceinline__ void epilogue4(const GemmParams<E> &p, int m, int n, 
 // 16-byte aligned tensors.
 // aux8: the 8 values of aux at (m, n .. n + 7) for the two epilogues that read it, and b0, b1: the bias of columns
 // n .. n + 7 for the three that add it, both loaded by the caller (ahead of time).  o: the results, too.
-template <int EPI, class E>
+// PRE: of EPI_BIAS_GELU, whether the pre-activation is stored (a test per store would keep the stores of a strip apart).
+template <int EPI, bool PRE, class E>
 __device__ __forceinline__ void epilogue8(const GemmParams<E> &p, int m, int n, const f32x4 &lo, const f32x4 &hi,
                                           const x8<E> &aux8, const f32x4 &b0, const f32x4 &b1, x8<E> &o) {
     static_assert(EPI != EPI_ACCUM_F32, "16-bit outputs only");
@@ -93,7 +94,7 @@ __device__ __forceinline__ void epilogue8(const GemmParams<E> &p, int m, int n, 
             u[i] = (E)r[i];
             r[i] = gelu_f(r[i]);
         }
-        if (p.out2) *reinterpret_cast<x8<E> *>(p.out2 + idx) = u;
+        if constexpr (PRE) *reinterpret_cast<x8<E> *>(p.out2 + idx) = u;
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = (E)r[i];

@@ -208,7 +208,8 @@ __global__ __launch_bounds__(256 * KG) void gemm_small_kernel(In in, int tiles_m
             o[1] = hi;
         } else {
             x8<E> o8;
-            epilogue8<EPI, E>(p, m, n, lo, hi, aux8, b0, b1, o8);
+            if (EPI != EPI_BIAS_GELU || p.out2) epilogue8<EPI, true, E>(p, m, n, lo, hi, aux8, b0, b1, o8);
+            else epilogue8<EPI, false, E>(p, m, n, lo, hi, aux8, b0, b1, o8);
         }
     }
 }
