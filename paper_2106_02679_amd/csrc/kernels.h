@@ -27,10 +27,10 @@ template <class E> void launch_cast_f32_to_16(const float *src, E *dst, size_t n
 void launch_fill_normal(float *dst, size_t n, float std, uint64_t seed, hipStream_t s);
 void launch_fill_const(float *dst, size_t n, float value, hipStream_t s);
 
-// LayerNorm forward over rows of length d.  Writes y = xhat * g + b and the row statistics.
+// LayerNorm forward over rows of length d.  Writes y = xhat * g + b and the row statistics; keep != NULL: also a copy of x there.
 template <class T>
 void launch_layernorm_fwd(const T *x, const float *g, const float *b, T *y, float *mean, float *rstd,
-                          int rows, int d, float eps, hipStream_t s);
+                          int rows, int d, float eps, hipStream_t s, T *keep = nullptr);
 // LayerNorm backward w.r.t. the input, fused with the residual add:
 //   dx = resid + rstd * (g dy - mean_row(g dy) - xhat * mean_row(g dy xhat))
 // dbeta != NULL: also the gradients of the LayerNorm bias and gain,

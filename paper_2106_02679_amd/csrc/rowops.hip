@@ -142,7 +142,7 @@ template <class T, int V, int TH, int NP, bool CACHE_GB>
 __global__ __launch_bounds__(TH) void layernorm_fwd_rows_kernel(const T *__restrict__ x, const float *__restrict__ g,
                                                                  const float *__restrict__ b, T *__restrict__ y,
                                                                  float *__restrict__ mean_out, float *__restrict__ rstd_out,
-                                                                 int rows, int d, float eps) {
+                                                                 int rows, int d, float eps, T *__restrict__ keep) {
     // Two scratch rows used in turn: a sum's barrier also separates the other row's readers from its next writers,
     // so each block-wide sum costs one barrier.
     __shared__ float red[2][16];
@@ -201,6 +201,7 @@ __global__ __launch_bounds__(TH) void layernorm_fwd_rows_kernel(const T *__restr
                     xv[p][i] = to_f32(nxt[p].v[i]);
                     s += xv[p][i];
                 }
+                if (keep) *reinterpret_cast<Pack<T, V> *>(keep + row * (size_t)d + c) = nxt[p];
             }
         }
         if (row + gridDim.x < (size_t)rows) request(row + gridDim.x);
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(TH) void layernorm_fwd_rows_kernel(const T *__restr
 template <class T, int V, int NP>
 __global__ __launch_bounds__(256) void layernorm_fwd_wave_kernel(const T *__restrict__ x, const float *__restrict__ g, const float *__restrict__ b,
                                                                  T *__restrict__ y, float *__restrict__ mean_out, float *__restrict__ rstd_out,
-                                                                 int rows, int d, float eps) {
+                                                                 int rows, int d, float eps, T *__restrict__ keep) {
     const int lane = threadIdx.x & 63, step = gridDim.x * 4;
     int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     Pack<T, V> nxt[NP];
@@ -278,6 +279,10 @@ __global__ __launch_bounds__(256) void layernorm_fwd_wave_kernel(const T *__rest
                 xv[p][i] = (p * 64 + lane) * V < d ? to_f32(nxt[p].v[i]) : 0.f;
                 s += xv[p][i];
             }
+        if (keep)
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                if ((p * 64 + lane) * V < d) *reinterpret_cast<Pack<T, V> *>(keep + (size_t)row * d + (p * 64 + lane) * V) = nxt[p];
         if (row + step < rows) request(row + step);
         const float mean = wave_sum(s) / (float)d;
         float q = 0.f;
@@ -876,20 +881,22 @@ void launch_fill_const(float *dst, size_t n, float value, hipStream_t s) {
 
 template <class T>
 void launch_layernorm_fwd(const T *x, const float *g, const float *b, T *y, float *mean, float *rstd, int rows,
-                          int d, float eps, hipStream_t s) {
+                          int d, float eps, hipStream_t s, T *keep) {
     if (rows == 0) return;
     constexpr int V = VecOf<T>::N;
-    ProfScope scope("layernorm_fwd_kernel", 8.0 * rows * d, 2.0 * sizeof(T) * rows * (double)d, s);
+    const bool registers = d % V == 0 && aligned16(x) && aligned16(y) && aligned16(g) && aligned16(b) && aligned16(keep) && d <= 1024 * V * 2;
+    if (keep && !registers) (void)hipMemcpyAsync(keep, x, (size_t)rows * d * sizeof(T), hipMemcpyDeviceToDevice, s);
+    ProfScope scope("layernorm_fwd_kernel", 8.0 * rows * d, (keep && registers ? 3.0 : 2.0) * sizeof(T) * rows * (double)d, s);
     // (rows wider than two packs per thread of a 1024-thread block would leave one block per CU: the one-row-per-block
     // kernel, with its many small blocks, is faster there)
-    if (d % V == 0 && aligned16(x) && aligned16(y) && aligned16(g) && aligned16(b) && d <= 1024 * V * 2) {
+    if (registers) {
         // rows are dealt to a fixed number of blocks (enough to fill every CU), which keep what they reuse in registers
 #define LGA_LN_ROWS(TH, NP) \
         hipLaunchKernelGGL((layernorm_fwd_rows_kernel<T, V, TH, NP, true>), dim3((unsigned)std::min(rows, 256 * (2048 / TH))), \
-                           dim3(TH), 0, s, x, g, b, y, mean, rstd, rows, d, eps)
+                           dim3(TH), 0, s, x, g, b, y, mean, rstd, rows, d, eps, keep)
 #define LGA_LN_WAVE(NP) \
         hipLaunchKernelGGL((layernorm_fwd_wave_kernel<T, V, NP>), dim3((unsigned)std::min((rows + 3) / 4, 256 * 8)), dim3(256), 0, s, x, g, b, y, \
-                           mean, rstd, rows, d, eps)
+                           mean, rstd, rows, d, eps, keep)
         if (d <= 64 * V) LGA_LN_WAVE(1);
         else if (d <= 128 * V) LGA_LN_WAVE(2);
         else if (d <= kLnWave * 64 * V) LGA_LN_WAVE(4);
@@ -905,11 +912,11 @@ void launch_layernorm_fwd(const T *x, const float *g, const float *b, T *y, floa
         hipLaunchKernelGGL((layernorm_fwd_kernel<T, 1>), dim3(rows), dim3(256), 0, s, x, g, b, y, mean, rstd, d, eps);
 }
 template void launch_layernorm_fwd<float>(const float *, const float *, const float *, float *, float *, float *, int,
-                                          int, float, hipStream_t);
+                                          int, float, hipStream_t, float *);
 template void launch_layernorm_fwd<bf16>(const bf16 *, const float *, const float *, bf16 *, float *, float *, int,
-                                         int, float, hipStream_t);
+                                         int, float, hipStream_t, bf16 *);
 template void launch_layernorm_fwd<f16>(const f16 *, const float *, const float *, f16 *, float *, float *, int,
-                                         int, float, hipStream_t);
+                                         int, float, hipStream_t, f16 *);
 
 // blocks of the row-walking kernel for `rows` rows of length d (0: that kernel does not serve d)
 static int lnb_rows_blocks(int rows, int d, int V) {

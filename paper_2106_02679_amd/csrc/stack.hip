@@ -496,6 +496,25 @@ template <class T> struct WgradOperands {
     }
 };
 
+// A caller's buffer that the kernels' 16-byte accesses can use, that is none of the stack's own (a borrowed checkpoint may be
+// read or replaced in the middle of the sweep) and that lies in the memory of the stack's GPU: the kernels read dy several times, which
+// over a bus takes longer than the copy (pinned host memory), or not at all (another GPU without peer access).
+bool usable(const lga_stack *st, const void *p) {
+    const char *c = static_cast<const char *>(p);
+    if ((reinterpret_cast<uintptr_t>(p) & 15) != 0 || (c + st->boundary_bytes() > st->arena && c < st->arena + st->plan.total)) return false;
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();                         // memory the runtime does not know: the copy decides
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == st->device;
+}
+// Two boundaries without a byte in common.
+bool apart(const lga_stack *st, const void *a, const void *b) {
+    const char *p = static_cast<const char *>(a), *q = static_cast<const char *>(b);
+    return p + st->boundary_bytes() <= q || q + st->boundary_bytes() <= p;
+}
+
 // The running activation gradient of all micro-batches during a sweep over the layers.  In place, a layer turns each group's gradient
 // with respect to its output into that with respect to its input - unless the W_2 gradient still wants the former of the groups it
 // merges: then dact is a ring of groups, and a layer writes wgrad_groups places before where it reads, which is
@@ -514,21 +533,8 @@ template <class T> struct ActivationGradient {
           groups(st->cfg.n_micro / st->cfg.group) {}
     const T *in(int gi) const { return src ? src + (size_t)gi * gstride : base + (size_t)(ring ? (first + gi) % ring : gi) * gstride; }
     T *out(int gi) const { return dst ? dst + (size_t)gi * gstride : base + (size_t)(ring ? (first + ring - wb + gi) % ring : gi) * gstride; }
-    // A caller's buffer that the kernels' 16-byte accesses can use, that is none of the stack's own (a borrowed checkpoint may be
-    // read or replaced in the middle of the sweep) and that lies in the memory of the stack's GPU: the kernels read dy several times, which
-    // over a bus takes longer than the copy (pinned host memory), or not at all (another GPU without peer access).
-    bool usable(const void *p) const {
-        const char *c = static_cast<const char *>(p);
-        if ((reinterpret_cast<uintptr_t>(p) & 15) != 0 || (c + st->boundary_bytes() > st->arena && c < st->arena + st->plan.total)) return false;
-        hipPointerAttribute_t at{};
-        if (hipPointerGetAttributes(&at, p) != hipSuccess) {
-            (void)hipGetLastError();                         // memory the runtime does not know: the copy decides
-            return false;
-        }
-        return at.type == hipMemoryTypeDevice && at.device == st->device;
-    }
     hipError_t begin(const void *dy, hipStream_t s) {
-        if (usable(dy)) {
+        if (usable(st, dy)) {
             src = static_cast<const T *>(dy);
             return hipSuccess;
         }
@@ -537,11 +543,8 @@ template <class T> struct ActivationGradient {
     // Before the last layer.  If it is the first one, too, dx must not take the place of what the layer still reads of dy: the W_2
     // gradient of merged groups, or other groups where the two overlap without being the same.
     void end_in(void *dx) {
-        if (!dx || !usable(dx)) return;
-        const char *a = reinterpret_cast<const char *>(src), *b = static_cast<const char *>(dx);
-        const size_t n = st->boundary_bytes();
-        const bool apart = !src || a + n <= b || b + n <= a;
-        if (apart || (a == b && !ring)) dst = static_cast<T *>(dx);
+        if (!dx || !usable(st, dx)) return;
+        if (!src || apart(st, src, dx) || (src == dx && !ring)) dst = static_cast<T *>(dx);
     }
     void next_layer() {
         src = nullptr;
@@ -564,8 +567,9 @@ template <class T> struct ActivationGradient {
 // x_in: [t, d] group slice of the layer's input checkpoint.  y_out: group slice of the next
 // checkpoint, or NULL when this is the backward pass's recompute (the second feed-forward GEMM's
 // output is not needed there, so it is not recomputed).  slot: which of the wgrad_groups groups this is, in the buffers that hold
-// several for the weight gradients.
-template <class T> void layer_forward(lga_stack *st, int l, const T *x_in, T *y_out, int slot = 0) {
+// several for the weight gradients.  keep: where the layer's input goes on the way if x_in is not the checkpoint but the caller's.  (A
+// copy of 50 MB of its own takes 20 us, 3 % of a d = 768 layer's forward over 32768 tokens, and a launch.)
+template <class T> void layer_forward(lga_stack *st, int l, const T *x_in, T *y_out, int slot = 0, T *keep = nullptr) {
     const lga_config &c = st->cfg;
     const int d = c.d_model, f = c.d_ff, t = (int)st->t;
     const LayerLayout &o = st->lay;
@@ -592,7 +596,8 @@ template <class T> void layer_forward(lga_stack *st, int l, const T *x_in, T *y_
     };
 
     launch_layernorm_fwd<T>(x_in, pf + o.ln1_g, pf + o.ln1_b, h, st->at<float>(st->plan.mean1),
-                            st->at<float>(st->plan.rstd1), t, d, c.ln_eps, s);
+                            st->at<float>(st->plan.rstd1), t, d, c.ln_eps, s, keep);
+    if (keep) x_in = keep;
     GemmParams<T> g{};
     g.A = h; g.out = qkv; g.bias = pf + o.b_qkv;
     fwd_gemm(g, o.w_qkv, d, 3 * d, EPI_BIAS);
@@ -828,7 +833,8 @@ template <class T> int forward_layered_t(lga_stack *st, const void *x, void *y) 
     const size_t act_bytes = st->T * c.d_model * sizeof(T);
     const bool offload = c.offload_checkpoints != 0;
     if (offload) claim_slot(st, 0);
-    LGA_HIP(hipMemcpyAsync(st->ckpt(0), x, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+    const bool own_x = !offload && usable(st, x);           // the first layer takes x as it is and leaves its checkpoint on the way
+    if (!own_x) LGA_HIP(hipMemcpyAsync(st->ckpt(0), x, act_bytes, hipMemcpyDeviceToDevice, st->stream));
     if (offload) save_boundary(st, 0);
     const int groups = c.n_micro / c.group;
     const size_t gstride = st->t * c.d_model;
@@ -840,8 +846,11 @@ template <class T> int forward_layered_t(lga_stack *st, const void *x, void *y) 
         T *out = reinterpret_cast<T *>(st->ckpt(l + 1));
         ensure_weights(st, l);
         prefetch_weights(st, l + 1, l);
-        for (int gi = 0; gi < groups; ++gi)                 // ... micro-batches inside
-            layer_forward<T>(st, l, in + gi * gstride, out + gi * gstride);
+        const bool from_x = l == 0 && own_x;
+        for (int gi = 0; gi < groups; ++gi) {               // ... micro-batches inside
+            const size_t at = gi * gstride;
+            layer_forward<T>(st, l, (from_x ? static_cast<const T *>(x) : in) + at, out + at, 0, from_x ? reinterpret_cast<T *>(st->ckpt(0)) + at : nullptr);
+        }
         if (offload) save_boundary(st, l + 1);
     }
     if (y) LGA_HIP(hipMemcpyAsync(y, st->ckpt(c.n_layers), act_bytes, hipMemcpyDeviceToDevice, st->stream));
@@ -894,6 +903,7 @@ template <class T> int forward_layer_t(lga_stack *st, int l, const void *x_in, v
     const lga_config &c = st->cfg;
     const size_t act_bytes = st->T * c.d_model * sizeof(T);
     const bool offload = c.offload_checkpoints != 0;
+    bool own_x = false;                                     // the layer takes x_in as it is and leaves the checkpoint on the way
     if (offload) {
         if (x_in == st->host_boundary(l)) {                 // the borrowed checkpoint itself: bring it back if it is away
             fetch_boundary(st, l);
@@ -905,14 +915,16 @@ template <class T> int forward_layer_t(lga_stack *st, int l, const void *x_in, v
         }
         if (!x_out) claim_slot(st, l + 1);
     } else if (x_in != st->ckpt(l)) {
-        LGA_HIP(hipMemcpyAsync(st->ckpt(l), x_in, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+        own_x = usable(st, x_in) && (!x_out || x_in == x_out || apart(st, x_in, x_out));
+        if (!own_x) LGA_HIP(hipMemcpyAsync(st->ckpt(l), x_in, act_bytes, hipMemcpyDeviceToDevice, st->stream));
     }
-    const T *in = reinterpret_cast<const T *>(st->ckpt(l));
+    T *kept = reinterpret_cast<T *>(st->ckpt(l));
+    const T *in = own_x ? static_cast<const T *>(x_in) : kept;
     T *out = reinterpret_cast<T *>(x_out ? x_out : st->ckpt(l + 1));
     const int groups = c.n_micro / c.group;
     const size_t gstride = st->t * c.d_model;
     ensure_weights(st, l);
-    for (int gi = 0; gi < groups; ++gi) layer_forward<T>(st, l, in + gi * gstride, out + gi * gstride);
+    for (int gi = 0; gi < groups; ++gi) layer_forward<T>(st, l, in + gi * gstride, out + gi * gstride, 0, own_x ? kept + gi * gstride : nullptr);
     if (offload) {
         if (!x_out) save_boundary(st, l + 1);
         join_offload(st);
@@ -957,15 +969,28 @@ int step_mbmajor_t(lga_stack *st, const void *x, const void *dy, void *y, void *
     const lga_config &c = st->cfg;
     const size_t act_bytes = st->T * c.d_model * sizeof(T);
     T *dact = st->at<T>(st->plan.dact);
-    LGA_HIP(hipMemcpyAsync(st->ckpt(0), x, act_bytes, hipMemcpyDeviceToDevice, st->stream));
-    LGA_HIP(hipMemcpyAsync(dact, dy, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+    // x, dy and dx are read and written in place where each is usable and no two overlap - a micro-batch writes its dx before the next
+    // one's x and dy are read
+    const void *users[3] = {x, dy, dx};
+    bool in_place = c.offload_checkpoints == 0;
+    for (int i = 0; i < 3 && in_place; ++i) {
+        if (!users[i]) continue;
+        in_place = usable(st, users[i]);
+        for (int j = 0; j < i && in_place; ++j) in_place = !users[j] || apart(st, users[i], users[j]);
+    }
+    if (!in_place) {
+        LGA_HIP(hipMemcpyAsync(st->ckpt(0), x, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+        LGA_HIP(hipMemcpyAsync(dact, dy, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+    }
     const size_t gstride = st->t * c.d_model;               // group == 1: one micro-batch
     for (int l = 0; l < c.n_layers; ++l) st->grad_owner[l] = -1;
     for (int mu = 0; mu < c.n_micro; ++mu) {                // micro-batches outside ...
         for (int l = 0; l < c.n_layers; ++l) {              // ... layers inside
             ensure_weights(st, l);
-            layer_forward<T>(st, l, reinterpret_cast<const T *>(st->ckpt(l)) + mu * gstride,
-                             reinterpret_cast<T *>(st->ckpt(l + 1)) + mu * gstride);
+            T *in = reinterpret_cast<T *>(st->ckpt(l)) + mu * gstride;
+            const bool from_x = in_place && l == 0;
+            layer_forward<T>(st, l, from_x ? static_cast<const T *>(x) + mu * gstride : in, reinterpret_cast<T *>(st->ckpt(l + 1)) + mu * gstride, 0,
+                             from_x ? in : nullptr);
         }
         for (int l = c.n_layers - 1; l >= 0; --l) {
             const T *in = reinterpret_cast<const T *>(st->ckpt(l)) + mu * gstride;
@@ -973,12 +998,14 @@ int step_mbmajor_t(lga_stack *st, const void *x, const void *dy, void *y, void *
             layer_forward<T>(st, l, in, nullptr);
             // layers alternate here, so every weight-gradient GEMM runs at once on its own micro-batch
             const GradStep gs{mu == 0 ? 0.f : 1.f, mu == 0 ? 0.f : 1.f, 0, true};
-            layer_backward<T>(st, l, in, dact + mu * gstride, dact + mu * gstride, st->grad(l), gs);
+            const T *from = (in_place && l == c.n_layers - 1 ? static_cast<const T *>(dy) : dact) + mu * gstride;
+            T *to = (in_place && dx && l == 0 ? static_cast<T *>(dx) : dact) + mu * gstride;
+            layer_backward<T>(st, l, in, from, to, st->grad(l), gs);
         }
     }
     for (int l = 0; l < c.n_layers; ++l) st->grad_owner[l] = l;
     if (y) LGA_HIP(hipMemcpyAsync(y, st->ckpt(c.n_layers), act_bytes, hipMemcpyDeviceToDevice, st->stream));
-    if (dx) LGA_HIP(hipMemcpyAsync(dx, dact, act_bytes, hipMemcpyDeviceToDevice, st->stream));
+    if (dx && !in_place) LGA_HIP(hipMemcpyAsync(dx, dact, act_bytes, hipMemcpyDeviceToDevice, st->stream));
     if (adam)
         for (int l = 0; l < c.n_layers; ++l) adam_layer(st, l, *adam);
     if (c.overlap) join_aux(st);

@@ -1,0 +1,84 @@
+"""The sweeps read x and dy and write dx where the caller has them, without copies, unless that is not the same as copying first:
+buffers that overlap, that are not 16-byte aligned or lie in host memory give the same bits as buffers of their own, and the
+checkpoints hold x and y."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2106_02679_amd import binding as B
+from gpu_helpers import TORCH_DTYPE
+
+SIZES = [(B.LGA_BF16, 128, 2, 512), (B.LGA_BF16, 1536, 12, 6144), (B.LGA_FP32, 64, 4, 256), (B.LGA_FP32, 30, 3, 70)]      # fp32 rows of 30: no 16-byte pieces
+
+
+def make(dt, d, heads, ff, layers, group):
+    cfg = B.make_config(layers, d, heads, ff, 40, 1, 4, dt, group=group, retain_grads=1)
+    params = np.random.default_rng(1).standard_normal(layers * B.params_per_layer(cfg)).astype(np.float32) * 0.02
+    return B.Stack(cfg, params), 4 * 40 * d
+
+
+@pytest.mark.parametrize("dt,d,heads,ff", SIZES, ids=["bf16_128", "bf16_1536", "fp32_64", "fp32_30"])
+@pytest.mark.parametrize("layers,group", [(1, 1), (2, 2)])
+def test_forward_buffers_that_overlap_or_are_misaligned(dt, d, heads, ff, layers, group):
+    st, n = make(dt, d, heads, ff, layers, group)
+    row, shift = 40 * d, 4
+    x0 = torch.randn(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3)).to(TORCH_DTYPE[dt])
+
+    def run(x_at, y_at, per_layer=False):
+        buf = torch.full((3 * n + 64,), float("nan"), device="cuda", dtype=x0.dtype)
+        x, y = buf[x_at:x_at + n], buf[y_at:y_at + n]
+        x.copy_(x0)
+        if per_layer:
+            for l in range(layers):
+                st.forward_layer(l, (x if l == 0 else y).data_ptr(), y.data_ptr())
+        else:
+            st.forward_layered(x.data_ptr(), y.data_ptr())
+        torch.cuda.synchronize()
+        kept = [B.read_device(st.checkpoint(b)[0], n, "float32" if dt == B.LGA_FP32 else "uint16") for b in ([0] if per_layer else [0, layers])]
+        return y.clone(), kept
+
+    try:
+        ref, kept = run(0, 2 * n)
+        view = lambda t: (t if dt == B.LGA_FP32 else t.view(torch.int16)).cpu().numpy().view("float32" if dt == B.LGA_FP32 else "uint16")
+        assert torch.isfinite(ref.float()).all()
+        assert np.array_equal(kept[0], view(x0)) and np.array_equal(kept[1], view(ref))
+        for args in ((0, 0), (0, row), (row, 0), (shift // 2, 2 * n), (0, 2 * n + shift // 2), (0, 2 * n, True), (0, 0, True), (row, 0, True), (0, row, True)):
+            y, k = run(*args)
+            assert torch.equal(y, ref) and np.array_equal(k[0], kept[0]), args
+            assert len(k) == 1 or np.array_equal(k[1], kept[1]), args
+        pinned = torch.empty(2, n, dtype=x0.dtype, pin_memory=True)
+        pinned[0].copy_(x0)
+        st.forward_layered(pinned[0].data_ptr(), pinned[1].data_ptr())
+        torch.cuda.synchronize()
+        assert torch.equal(pinned[1], ref.cpu())
+    finally:
+        st.close()
+
+
+@pytest.mark.parametrize("dt,d,heads,ff", SIZES, ids=["bf16_128", "bf16_1536", "fp32_64", "fp32_30"])
+@pytest.mark.parametrize("layers", [1, 2])
+def test_micro_batch_major_buffers_that_overlap(dt, d, heads, ff, layers):
+    st, n = make(dt, d, heads, ff, layers, 1)
+    row = 40 * d
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    x0, g0 = (torch.randn(n, device="cuda", generator=gen).to(TORCH_DTYPE[dt]) for _ in range(2))
+
+    def run(x_at, g_at, y_at, dx_at):
+        buf = torch.full((8 * n,), float("nan"), device="cuda", dtype=x0.dtype)
+        x, g, y, dx = (buf[a:a + n] for a in (x_at, g_at, y_at, dx_at))
+        x.copy_(x0)
+        g.copy_(g0)
+        st.step_mbmajor(x.data_ptr(), g.data_ptr(), y.data_ptr(), dx.data_ptr(), None)
+        torch.cuda.synchronize()
+        return [y.clone(), dx.clone()] + [torch.from_numpy(B.read_device(*st.grads(l), "float32")) for l in range(layers)]
+
+    try:
+        ref = run(0, 2 * n, 4 * n, 6 * n)
+        assert torch.isfinite(ref[1].float()).all()
+        for args in ((0, 2 * n, 0, 2 * n), (0, 2 * n, 0, 6 * n), (0, 2 * n, 4 * n, 2 * n + row), (0, 2 * n, row, 6 * n), (row, 3 * n, 6 * n, 0), (0, 2 * n, 4 * n + 2, 6 * n)):
+            for got, want in zip(run(*args), ref):
+                assert torch.equal(got, want), args
+    finally:
+        st.close()
