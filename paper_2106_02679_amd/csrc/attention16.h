@@ -16,6 +16,19 @@ template <class E> __device__ __forceinline__ x8<E> frag_global(const E *row_ptr
     if (!valid || 16 * ks + 8 * half >= dh) return x8<E>{0, 0, 0, 0, 0, 0, 0, 0};
     return *reinterpret_cast<const x8<E> *>(row_ptr + 16 * ks + 8 * half);
 }
+// delta of this lane's row: sum_c dO O, of which each half of the wavefront has every other 8 columns.  The dQ kernels take it from the dO
+// operands that they hold anyway, one more read of O, and leave it for the dK/dV kernels: a kernel of its own read both (2 x 1728
+// positions, 54 heads of 216: 27 us, both kernels together 989 -> 980; 32768 x 768: 18, the layer backward 1887 -> 1875).
+template <int NK, class E> __device__ __forceinline__ float row_delta(const x8<E> (&dof)[NK], const x8<E> (&of)[NK]) {
+    float t = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < NK; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t += (float)of[ks][e] * (float)dof[ks][e];
+    const uint32_t bits = __builtin_bit_cast(uint32_t, t);
+    const auto halves = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+    return __builtin_bit_cast(float, (uint32_t)halves[0]) + __builtin_bit_cast(float, (uint32_t)halves[1]);
+}
 // 32x32 fp32 result registers 8*kk .. 8*kk+7 -> 16-bit second operand.
 template <class E> __device__ __forceinline__ x8<E> pack16(const f32x16 &v, int kk) {
     x8<E> o;

@@ -391,42 +391,6 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
     }
 }
 
-// Explicit instantiations: the host compiler does not always emit the launch stub of a kernel template from its
-// use in the launcher below alone.
-
-// ============================================================================================
-// delta[b, h, q] = sum_c dO[q, h*dh + c] * O[q, h*dh + c].  out and dout are [tokens][heads * dh]: consecutive
-// (token, head) items are consecutive runs of dh elements.  A thread multiplies one 16-byte chunk of each tensor
-// (fully coalesced), the chunk sums go through LDS, and one thread per item adds its dh / 8 of them in order.
-template <class E>
-__global__ __launch_bounds__(256) void attn_delta_kernel(const E *__restrict__ out, const E *__restrict__ dout,
-                                                         float *__restrict__ delta, AttnShape sh, int items_per_block) {
-    __shared__ float part[256];
-    const int cpi = sh.dh / 8;                                            // chunks per item
-    const size_t items = (size_t)sh.n_seq * sh.s * sh.heads;
-    const size_t item0 = (size_t)blockIdx.x * items_per_block;
-    const int tid = threadIdx.x;
-    const size_t chunk = item0 * cpi + tid;                               // index into the tensors as arrays of 16-byte chunks
-    float acc = 0.f;
-    if (tid < items_per_block * cpi && chunk < items * cpi) {
-        const x8<E> o = *reinterpret_cast<const x8<E> *>(out + chunk * 8);
-        const x8<E> g = *reinterpret_cast<const x8<E> *>(dout + chunk * 8);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc += (float)o[i] * (float)g[i];
-    }
-    part[tid] = acc;
-    __syncthreads();
-    if (tid < items_per_block && item0 + tid < items) {
-        float t = 0.f;
-        for (int c = 0; c < cpi; ++c) t += part[tid * cpi + c];
-        const size_t item = item0 + tid;                                  // token * heads + head
-        const int h = item % sh.heads;
-        const size_t tok = item / sh.heads;
-        const size_t bb = tok / sh.s, qq = tok % sh.s;
-        delta[(bb * sh.heads + h) * sh.s + qq] = t;
-    }
-}
-
 // ============================================================================================
 // dQ.  One workgroup per (sequence, head, block of 128 queries), see block_of(); rank 0 = the last block.
 //
@@ -437,8 +401,8 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const E *__restrict__ o
 // the two stages take 90 KB at DH = 128 and only one workgroup fits (16 heads x 8100 positions x 128, causal: 485 us; now 395, and no
 // bank conflicts instead of a quarter of the LDS cycles; 384 x 1024 x 64: 121 -> 108).
 template <int DH, int OCC, class E>
-__global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restrict__ qkv, const float *__restrict__ lse,
-                                                          const float *__restrict__ delta,
+__global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restrict__ qkv, const E *__restrict__ out,
+                                                          const float *__restrict__ lse, float *__restrict__ delta,
                                                           const E *__restrict__ dout, E *__restrict__ dqkv,
                                                           AttnShape sh) {
     constexpr int KT = 64;
@@ -463,16 +427,33 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
     const int q = qw0 + lrow;
     const bool qvalid = q < sh.s;
 
+    Dma dma;                                                    // K and V rows have the same pitch
+    dma.init(wave, lane, (int)(pitch * 2), dh);
+    auto dma_tile = [&](int k0, int stage) {
+        E *Ks = lds + stage * STAGE;
+        dma.issue(seq + (size_t)k0 * pitch + d, Ks, sh.s - k0, wave);
+        dma.issue(seq + (size_t)k0 * pitch + 2 * d, Ks + TILE, sh.s - k0, wave);
+    };
     x8<E> qf[NK], dof[NK];
-    const E *dorow = dout + ((size_t)b * sh.s + q) * d + (size_t)h * dh;
+    float lse2, dl;
+    {
+        // (A uniform base and a row each: an index over b and q together is kept up to the store of dQ, which at 128 channels spilled.)
+        const size_t seq0 = (size_t)b * sh.s * d + (size_t)h * dh, row = (size_t)q * d;
+        const size_t stat = ((size_t)b * sh.heads + h) * sh.s;
+        x8<E> of[NK];
 #pragma unroll
-    for (int ks = 0; ks < NK; ++ks) {
-        qf[ks] = frag_global(seq + (size_t)q * pitch, ks, half, qvalid, dh);
-        dof[ks] = frag_global(dorow, ks, half, qvalid, dh);
+        for (int ks = 0; ks < NK; ++ks) {
+            of[ks] = frag_global(out + seq0 + row, ks, half, qvalid, dh);
+            dof[ks] = frag_global(dout + seq0 + row, ks, half, qvalid, dh);
+        }
+        lse2 = qvalid ? (lse + stat)[q] : 0.f;
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) qf[ks] = frag_global(seq + (size_t)q * pitch, ks, half, qvalid, dh);
+        dma_tile(0, 0);                                         // (on its way before anything is waited for)
+        dl = row_delta<NK, E>(dof, of);
+        if (qvalid && half == 0) (delta + stat)[q] = dl;
+        lse2 = qvalid ? lse2 * kLog2e : INFINITY;               // invalid rows: p = exp2(-inf) = 0
     }
-    const size_t stat = ((size_t)b * sh.heads + h) * sh.s + q;
-    const float lse2 = qvalid ? lse[stat] * kLog2e : INFINITY;     // invalid rows: p = exp2(-inf) = 0
-    const float dl = qvalid ? delta[stat] : 0.f;
     const float scale = rsqrtf((float)dh);
     const float c2 = scale * kLog2e;
 
@@ -481,14 +462,6 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
     for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
-
-    Dma dma;                                                    // K and V rows have the same pitch
-    dma.init(wave, lane, (int)(pitch * 2), dh);
-    auto dma_tile = [&](int k0, int stage) {
-        E *Ks = lds + stage * STAGE;
-        dma.issue(seq + (size_t)k0 * pitch + d, Ks, sh.s - k0, wave);
-        dma.issue(seq + (size_t)k0 * pitch + 2 * d, Ks + TILE, sh.s - k0, wave);
-    };
     // From 128 channels on the registers hold neither all row operands of a block nor a second copy of the read addresses.  Left to itself
     // the compiler spilled 7 of them inside this loop, reloaded them behind the next tile's loads and so waited for those
     // before the first product: 4 heads x 4096 x 128, one workgroup on a compute unit, 138 us; 104 without (32 heads x 2048, two on each:
@@ -500,7 +473,6 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
 
     const bool causal = sh.causal != 0;
     const int kend = causal ? min(sh.s, qb * 128 + 128) : sh.s;
-    dma_tile(0, 0);
     int stage = 0;
     auto next_stage = [&]() __attribute__((always_inline)) {
         stage ^= 1;
@@ -900,12 +872,11 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(const E *__restric
 // use in the launchers below alone.
 #define LGA_INSTANTIATE_KERNELS(DH, OCC, E)                                                                          \
     template __global__ void attn_fwd_kernel<DH, E>(const E *, E *, float *, AttnShape);                             \
-    template __global__ void attn_bwd_dq_kernel<DH, OCC, E>(const E *, const float *, const float *, const E *, E *, \
+    template __global__ void attn_bwd_dq_kernel<DH, OCC, E>(const E *, const E *, const float *, float *, const E *, E *, \
                                                             AttnShape);                                              \
     template __global__ void attn_bwd_dkv_kernel<DH, E>(const E *, const float *, const float *, const E *, E *,     \
                                                         AttnShape)
 #define LGA_INSTANTIATE_TYPE(E)                                                                            \
-    template __global__ void attn_delta_kernel<E>(const E *, const E *, float *, AttnShape, int);          \
     LGA_INSTANTIATE_KERNELS(32, 2, E);                                                                     \
     LGA_INSTANTIATE_KERNELS(64, 2, E);                                                                     \
     LGA_INSTANTIATE_KERNELS(96, 2, E);                                                                     \
@@ -959,7 +930,7 @@ template <int DH, class E> void fwd_dh(const E *qkv, E *out, float *lse, AttnSha
     hipLaunchKernelGGL((attn_fwd_kernel<DH, E>), grid, dim3(256), smem_fwd<DH>(), s, qkv, out, lse, sh);
 }
 template <int DH, class E>
-void bwd_dh(const E *qkv, const float *lse, const float *delta, const E *dout, E *dqkv, AttnShape sh,
+void bwd_dh(const E *qkv, const E *out, const float *lse, float *delta, const E *dout, E *dqkv, AttnShape sh,
             hipStream_t s) {
     dim3 grid((unsigned)(sh.n_seq * sh.heads) * ((sh.s + 127) / 128));
     char name[64];
@@ -967,8 +938,8 @@ void bwd_dh(const E *qkv, const float *lse, const float *delta, const E *dout, E
     const double act = (double)sh.n_seq * sh.s * sh.heads * sh.dh * 2.0;
     {
         snprintf(name, sizeof(name), "attn_bwd_dq_kernel<%d>", DH);
-        ProfScope scope(name, 6.0 * pairs * sh.dh, 5.0 * act, s);
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, occ_dq<DH>(), E>), grid, dim3(256), smem_dq<DH>(), s, qkv, lse, delta, dout,
+        ProfScope scope(name, 6.0 * pairs * sh.dh, 6.0 * act, s);
+        hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, occ_dq<DH>(), E>), grid, dim3(256), smem_dq<DH>(), s, qkv, out, lse, delta, dout,
                            dqkv, sh);
     }
     {
@@ -1007,14 +978,6 @@ template <class E> void launch_attn_fwd_mfma(const E *qkv, E *out, float *lse, A
     }
 }
 
-template <class E> void launch_attn_delta(const E *out, const E *dout, float *delta, AttnShape sh, hipStream_t s) {
-    const size_t items = (size_t)sh.n_seq * sh.s * sh.heads;
-    ProfScope scope("attn_delta_kernel", 2.0 * items * sh.dh, 4.0 * items * sh.dh, s);
-    const int items_per_block = 256 / (sh.dh / 8);                  // dh is a multiple of 8, at most 320
-    hipLaunchKernelGGL(attn_delta_kernel<E>, dim3((unsigned)((items + items_per_block - 1) / items_per_block)), dim3(256), 0, s, out,
-                       dout, delta, sh, items_per_block);
-}
-
 template <class E>
 void launch_attn_bwd_mfma(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv,
                           float *delta, AttnShape sh, hipStream_t s) {
@@ -1024,18 +987,16 @@ void launch_attn_bwd_mfma(const E *qkv, const E *out, const float *lse, const E 
         return;
     }
     (void)prepare_kernels();
-    launch_attn_delta<E>(out, dout, delta, sh, s);
     switch (padded_dh(sh.dh)) {
-        case 32: bwd_dh<32, E>(qkv, lse, delta, dout, dqkv, sh, s); break;
-        case 64: bwd_dh<64, E>(qkv, lse, delta, dout, dqkv, sh, s); break;
-        case 96: bwd_dh<96, E>(qkv, lse, delta, dout, dqkv, sh, s); break;
-        case 128: bwd_dh<128, E>(qkv, lse, delta, dout, dqkv, sh, s); break;
-        case 160: bwd_dh<160, E>(qkv, lse, delta, dout, dqkv, sh, s); break;
+        case 32: bwd_dh<32, E>(qkv, out, lse, delta, dout, dqkv, sh, s); break;
+        case 64: bwd_dh<64, E>(qkv, out, lse, delta, dout, dqkv, sh, s); break;
+        case 96: bwd_dh<96, E>(qkv, out, lse, delta, dout, dqkv, sh, s); break;
+        case 128: bwd_dh<128, E>(qkv, out, lse, delta, dout, dqkv, sh, s); break;
+        case 160: bwd_dh<160, E>(qkv, out, lse, delta, dout, dqkv, sh, s); break;
     }
 }
 
 #define LGA_INSTANTIATE_ATTN(E)                                                                          \
-    template void launch_attn_delta<E>(const E *, const E *, float *, AttnShape, hipStream_t);           \
     template void launch_attn_fwd_mfma<E>(const E *, E *, float *, AttnShape, hipStream_t);               \
     template void launch_attn_bwd_mfma<E>(const E *, const E *, const float *, const E *, E *, float *, \
                                           AttnShape, hipStream_t)

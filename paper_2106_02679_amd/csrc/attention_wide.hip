@@ -179,9 +179,9 @@ __global__ __launch_bounds__(256, fwd_occ<DH>()) void attn_wide_fwd_kernel(const
 
 // ---- dQ: one workgroup per (sequence, head, 128 queries) -------------------------------------------------------------------------
 template <int DH, class E>
-__global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restrict__ qkv, const float *__restrict__ lse,
-                                                              const float *__restrict__ delta, const E *__restrict__ dout,
-                                                              E *__restrict__ dqkv, AttnShape sh) {
+__global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restrict__ qkv, const E *__restrict__ out,
+                                                              const float *__restrict__ lse, float *__restrict__ delta,
+                                                              const E *__restrict__ dout, E *__restrict__ dqkv, AttnShape sh) {
     constexpr int NK = DH / 16, NC = DH / 32, NST = 3;
     typedef TileDmaSw<kTile, DH> Dma;
     constexpr int TILE = Dma::ELEMS, STAGE = 2 * TILE;          // K tile, then V tile
@@ -198,22 +198,6 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
     const int qw0 = qb * 128 + wave * 32, q = qw0 + lrow;
     const bool qvalid = q < sh.s, causal = sh.causal != 0;
 
-    x8<E> qf[NK], dof[NK];
-    const E *dorow = dout + ((size_t)b * sh.s + q) * d + (size_t)h * dh;
-#pragma unroll
-    for (int ks = 0; ks < NK; ++ks) {
-        qf[ks] = frag_global(seq + (size_t)q * pitch, ks, half, qvalid, dh);
-        dof[ks] = frag_global(dorow, ks, half, qvalid, dh);
-    }
-    const size_t stat = ((size_t)b * sh.heads + h) * sh.s + q;
-    const float lse2 = qvalid ? lse[stat] * kLog2e : INFINITY;     // invalid rows: p = exp2(-inf) = 0
-    const float scale = rsqrtf((float)dh), c2 = scale * kLog2e;
-    const float dl = qvalid ? delta[stat] * (scale_first<E>() ? scale : 1.f) : 0.f;
-    const float at_end = scale_first<E>() ? 1.f : scale;
-    f32x16 acc[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) acc[c] = zero16();
-
     Dma dma;
     dma.init(wave, lane, (int)(pitch * 2), dh);
     auto dma_tile = [&](int k0, int stage) {
@@ -221,11 +205,35 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
         dma.issue(seq + (size_t)k0 * pitch + d, Ks, sh.s - k0, wave);
         dma.issue(seq + (size_t)k0 * pitch + 2 * d, Ks + TILE, sh.s - k0, wave);
     };
+    const int kend = causal ? min(sh.s, qb * 128 + 128) : sh.s;
+    const float scale = rsqrtf((float)dh), c2 = scale * kLog2e;
+    const float at_end = scale_first<E>() ? 1.f : scale;
+    x8<E> qf[NK], dof[NK];
+    const size_t row = ((size_t)b * sh.s + q) * d + (size_t)h * dh, stat = ((size_t)b * sh.heads + h) * sh.s + q;
+    float lse2, dl;
+    {
+        x8<E> of[NK];
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) {
+            of[ks] = frag_global(out + row, ks, half, qvalid, dh);
+            dof[ks] = frag_global(dout + row, ks, half, qvalid, dh);
+        }
+        lse2 = qvalid ? lse[stat] : 0.f;
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) qf[ks] = frag_global(seq + (size_t)q * pitch, ks, half, qvalid, dh);
+        dma_tile(0, 0);                                         // (on their way before anything is waited for)
+        if (kTile < kend) dma_tile(kTile, 1);
+        dl = row_delta<NK, E>(dof, of);
+        if (qvalid && half == 0) delta[stat] = dl;
+        if constexpr (scale_first<E>()) dl *= scale;
+        lse2 = qvalid ? lse2 * kLog2e : INFINITY;               // invalid rows: p = exp2(-inf) = 0
+    }
+    f32x16 acc[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = zero16();
+
     BothAddr<DH> ad;
     ad.init(lane);
-    const int kend = causal ? min(sh.s, qb * 128 + 128) : sh.s;
-    dma_tile(0, 0);
-    if (kTile < kend) dma_tile(kTile, 1);
     auto tile = [&](int k0, int stage, auto masked_c) {
         const E *Ks = lds + stage * STAGE, *Vs = Ks + TILE;
         f32x16 st = zero16(), dpt = zero16();
@@ -472,7 +480,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dkv_kernel(const E *__restri
 // Explicit instantiations: the host compiler does not always find a kernel template from its use in the launchers below alone.
 #define LGA_WIDE_KERNELS(DH, E)                                                                                  \
     template __global__ void attn_wide_fwd_kernel<DH, E>(const E *, E *, float *, AttnShape);                   \
-    template __global__ void attn_wide_dq_kernel<DH, E>(const E *, const float *, const float *, const E *, E *, AttnShape)
+    template __global__ void attn_wide_dq_kernel<DH, E>(const E *, const E *, const float *, float *, const E *, E *, AttnShape)
 #define LGA_WIDE_DKV(DH, WHAT, E) \
     template __global__ void attn_wide_dkv_kernel<DH, WHAT, E>(const E *, const float *, const float *, const E *, E *, AttnShape)
 #define LGA_WIDE_TYPE(E)          \
@@ -528,14 +536,14 @@ template <int DH, class E> void fwd_dh(const E *qkv, E *out, float *lse, AttnSha
     hipLaunchKernelGGL((attn_wide_fwd_kernel<DH, E>), grid, dim3(256), smem_fwd<DH>(), s, qkv, out, lse, sh);
 }
 template <int DH, class E>
-void bwd_dh(const E *qkv, const float *lse, const float *delta, const E *dout, E *dqkv, AttnShape sh, hipStream_t s) {
+void bwd_dh(const E *qkv, const E *out, const float *lse, float *delta, const E *dout, E *dqkv, AttnShape sh, hipStream_t s) {
     const dim3 grid((unsigned)(sh.n_seq * sh.heads) * ((sh.s + 127) / 128));
     char name[64];
     const double pairs = (double)sh.n_seq * sh.heads * sh.s * sh.s * (sh.causal ? 0.5 : 1.0), act = (double)sh.n_seq * sh.s * sh.heads * sh.dh * 2.0;
     {
         snprintf(name, sizeof(name), "attn_wide_dq_kernel<%d>", DH);
-        ProfScope scope(name, 6.0 * pairs * sh.dh, 5.0 * act, s);
-        hipLaunchKernelGGL((attn_wide_dq_kernel<DH, E>), grid, dim3(256), smem_dq<DH>(), s, qkv, lse, delta, dout, dqkv, sh);
+        ProfScope scope(name, 6.0 * pairs * sh.dh, 6.0 * act, s);
+        hipLaunchKernelGGL((attn_wide_dq_kernel<DH, E>), grid, dim3(256), smem_dq<DH>(), s, qkv, out, lse, delta, dout, dqkv, sh);
     }
     snprintf(name, sizeof(name), "attn_wide_dkv_kernel<%d>", DH);
     ProfScope scope(name, (dkv_in_one_run<DH>() ? 8.0 : 10.0) * pairs * sh.dh, 6.0 * act, s);
@@ -569,11 +577,10 @@ template <class E>
 void launch_attn_bwd_wide(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv, float *delta, AttnShape sh, hipStream_t s) {
     if (sh.n_seq == 0 || sh.s == 0) return;
     (void)prepare_kernels();
-    launch_attn_delta<E>(out, dout, delta, sh, s);
-    if (sh.dh <= 192) bwd_dh<192, E>(qkv, lse, delta, dout, dqkv, sh, s);
-    else if (sh.dh <= 224) bwd_dh<224, E>(qkv, lse, delta, dout, dqkv, sh, s);
-    else if (sh.dh <= 256) bwd_dh<256, E>(qkv, lse, delta, dout, dqkv, sh, s);
-    else bwd_dh<320, E>(qkv, lse, delta, dout, dqkv, sh, s);
+    if (sh.dh <= 192) bwd_dh<192, E>(qkv, out, lse, delta, dout, dqkv, sh, s);
+    else if (sh.dh <= 224) bwd_dh<224, E>(qkv, out, lse, delta, dout, dqkv, sh, s);
+    else if (sh.dh <= 256) bwd_dh<256, E>(qkv, out, lse, delta, dout, dqkv, sh, s);
+    else bwd_dh<320, E>(qkv, out, lse, delta, dout, dqkv, sh, s);
 }
 #define LGA_INSTANTIATE_WIDE(E)                                                                        \
     template void launch_attn_fwd_wide<E>(const E *, E *, float *, AttnShape, hipStream_t);             \

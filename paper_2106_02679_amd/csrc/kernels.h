@@ -192,8 +192,6 @@ template <class E>
 void launch_attn_bwd_mfma(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv, float *delta,
                           AttnShape sh, hipStream_t s);
 
-// delta[sequence, head, query] = sum_c dO O
-template <class E> void launch_attn_delta(const E *out, const E *dout, float *delta, AttnShape sh, hipStream_t s);
 // Fused kernels for head sizes above 160 and up to 320, multiples of 8 (attention_wide.hip).
 bool attn_wide_supports(int dh);
 template <class E> void launch_attn_fwd_wide(const E *qkv, E *out, float *lse, AttnShape sh, hipStream_t s);
