@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "row_walk.h"
 
 namespace lga {
 
@@ -245,15 +246,15 @@ template <class T, int V, int NP>
 __global__ __launch_bounds__(256) void layernorm_fwd_wave_kernel(const T *__restrict__ x, const float *__restrict__ g, const float *__restrict__ b,
                                                                  T *__restrict__ y, float *__restrict__ mean_out, float *__restrict__ rstd_out,
                                                                  int rows, int d, float eps, T *__restrict__ keep) {
-    const int lane = threadIdx.x & 63, step = gridDim.x * 4;
-    int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    RowWalk walk(blockIdx.x, gridDim.x, threadIdx.x >> 6, rows);
     Pack<T, V> nxt[NP];
     auto request = [&](int r) {
 #pragma unroll
         for (int p = 0; p < NP; ++p)
             if ((p * 64 + lane) * V < d) nxt[p] = *reinterpret_cast<const Pack<T, V> *>(x + (size_t)r * d + (p * 64 + lane) * V);
     };
-    if (row < rows) request(row);
+    if (walk.valid()) request(walk.row);
     float gv[NP][V], bv[NP][V];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -270,7 +271,8 @@ __global__ __launch_bounds__(256) void layernorm_fwd_wave_kernel(const T *__rest
             }
         }
     }
-    for (; row < rows; row += step) {
+    for (; walk.valid(); walk.advance()) {
+        const int row = walk.row;
         float xv[NP][V], s = 0.f;
 #pragma unroll
         for (int p = 0; p < NP; ++p)
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(256) void layernorm_fwd_wave_kernel(const T *__rest
 #pragma unroll
             for (int p = 0; p < NP; ++p)
                 if ((p * 64 + lane) * V < d) *reinterpret_cast<Pack<T, V> *>(keep + (size_t)row * d + (p * 64 + lane) * V) = nxt[p];
-        if (row + step < rows) request(row + step);
+        if (walk.has_next()) request(walk.next());
         const float mean = wave_sum(s) / (float)d;
         float q = 0.f;
 #pragma unroll
@@ -482,8 +484,8 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_wave_kernel(const T *__r
                                                                     const float *__restrict__ rstd, const float *__restrict__ g, const T *resid,
                                                                     T *dx, int rows, int d, float *__restrict__ partial, float *__restrict__ more) {
     __shared__ __attribute__((aligned(16))) float red[4][SUMS ? 64 * V * NP : 1];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = gridDim.x * 4;
-    int row = blockIdx.x * 4 + wave;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    RowWalk walk(blockIdx.x, gridDim.x, wave, rows);
     Pack<T, V> na[NP], nx[NP], nr[NP];
     float nmu = 0.f, nrs = 0.f;
     auto request = [&](int r) {
@@ -499,7 +501,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_wave_kernel(const T *__r
         nmu = mean[r];
         nrs = rstd[r];
     };
-    if (row < rows) request(row);
+    if (walk.valid()) request(walk.row);
     float gv[NP][V], sums[SUMS ? SUMS : 1][NP][V];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -516,7 +518,8 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_wave_kernel(const T *__r
 #pragma unroll
             for (int i = 0; i < V; ++i) sums[k][p][i] = 0.f;
     }
-    for (; row < rows; row += step) {
+    for (; walk.valid(); walk.advance()) {
+        const int row = walk.row;
         float gd[NP][V], xh[NP][V], r[NP][V], s1 = 0.f, s2 = 0.f;
         const float mu = nmu, rs = nrs;
 #pragma unroll
@@ -538,7 +541,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_wave_kernel(const T *__r
                 }
             }
         }
-        if (row + step < rows) request(row + step);
+        if (walk.has_next()) request(walk.next());
         const float t1 = wave_sum(s1) / (float)d, t2 = wave_sum(s2) / (float)d;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
@@ -895,11 +898,12 @@ void launch_layernorm_fwd(const T *x, const float *g, const float *b, T *y, floa
         hipLaunchKernelGGL((layernorm_fwd_rows_kernel<T, V, TH, NP, true>), dim3((unsigned)std::min(rows, 256 * (2048 / TH))), \
                            dim3(TH), 0, s, x, g, b, y, mean, rstd, rows, d, eps, keep)
 #define LGA_LN_WAVE(NP) \
-        hipLaunchKernelGGL((layernorm_fwd_wave_kernel<T, V, NP>), dim3((unsigned)std::min((rows + 3) / 4, 256 * 8)), dim3(256), 0, s, x, g, b, y, \
+        hipLaunchKernelGGL((layernorm_fwd_wave_kernel<T, V, NP>), dim3((unsigned)row_walk_blocks(rows, 256 * 8)), dim3(256), 0, s, x, g, b, y, \
                            mean, rstd, rows, d, eps, keep)
-        if (d <= 64 * V) LGA_LN_WAVE(1);
-        else if (d <= 128 * V) LGA_LN_WAVE(2);
-        else if (d <= kLnWave * 64 * V) LGA_LN_WAVE(4);
+        const bool wave = d <= kLnWave * 64 * V && row_walk_takes(rows);
+        if (wave && d <= 64 * V) LGA_LN_WAVE(1);
+        else if (wave && d <= 128 * V) LGA_LN_WAVE(2);
+        else if (wave) LGA_LN_WAVE(4);
         else if (d <= 256 * V) LGA_LN_ROWS(256, 1);
         else if (d <= 512 * V) LGA_LN_ROWS(512, 1);
         else if (d <= 1024 * V) LGA_LN_ROWS(1024, 1);
@@ -918,10 +922,12 @@ template void launch_layernorm_fwd<bf16>(const bf16 *, const float *, const floa
 template void launch_layernorm_fwd<f16>(const f16 *, const float *, const float *, f16 *, float *, float *, int,
                                          int, float, hipStream_t, f16 *);
 
+// whether a row per wavefront
+static bool lnb_wave(int rows, int d, int V) { return d <= kLnbWave * 64 * V && row_walk_takes(rows); }
 // blocks of the row-walking kernel for `rows` rows of length d (0: that kernel does not serve d)
 static int lnb_rows_blocks(int rows, int d, int V) {
     if (d > 1024 * V * 2) return 0;
-    if (d <= kLnbWave * 64 * V) return std::min((rows + 3) / 4, 256 * 4);        // a row per wavefront
+    if (lnb_wave(rows, d, V)) return row_walk_blocks(rows, 256 * 4);
     const int th = d <= 256 * V ? 256 : d <= 512 * V ? 512 : 1024;
     return std::min(rows, 256 * (2048 / th));
 }
@@ -1002,8 +1008,9 @@ void launch_layernorm_bwd_dx(const T *dy, const T *x, const float *mean, const f
                                resid, dx, rows, d, partial, all ? biases->partial : nullptr)
 #define LGA_LNB_SUMS(LAUNCH, ...) \
             do { if (all) LAUNCH(__VA_ARGS__, 4); else if (fused) LAUNCH(__VA_ARGS__, 2); else LAUNCH(__VA_ARGS__, 0); } while (0)
-            if (d <= 64 * V) LGA_LNB_SUMS(LGA_LNB_WAVE, 1);
-            else if (d <= kLnbWave * 64 * V) LGA_LNB_SUMS(LGA_LNB_WAVE, 2);
+            const bool wave = lnb_wave(rows, d, V);
+            if (wave && d <= 64 * V) LGA_LNB_SUMS(LGA_LNB_WAVE, 1);
+            else if (wave) LGA_LNB_SUMS(LGA_LNB_WAVE, 2);
             else if (d <= 256 * V) LGA_LNB_SUMS(LGA_LNB_ROWS, 256, 1);
             else if (d <= 512 * V) LGA_LNB_SUMS(LGA_LNB_ROWS, 512, 1);
             else if (d <= 1024 * V) LGA_LNB_SUMS(LGA_LNB_ROWS, 1024, 1);
