@@ -113,7 +113,9 @@ uint64_t lga_op_colsum_static_max_floats(void);
  * sizes other than 32, 64, 96, 128, 160 run in the next larger of those kernels with the extra columns read as zeros). */
 int lga_op_attention_fwd(int32_t dtype, int32_t kind, const void *qkv, void *out, float *lse, int32_t n_seq,
                          int32_t s, int32_t heads, int32_t dh, int32_t causal, void *stream);
-/* dqkv [n_seq*s, 3*heads*dh] written; delta [n_seq, heads, s] float scratch (written). */
+/* dqkv [n_seq*s, 3*heads*dh] written; delta [n_seq, heads, s] float scratch (written): sum_c dout out of every row.
+ * dqkv must not share memory with qkv or dout; nor with out, except that with kind 1 it may (delta then takes a pass of its own, before
+ * anything is written). */
 int lga_op_attention_bwd(int32_t dtype, int32_t kind, const void *qkv, const void *out, const float *lse,
                          const void *dout, void *dqkv, float *delta, int32_t n_seq, int32_t s, int32_t heads,
                          int32_t dh, int32_t causal, void *stream);

@@ -392,6 +392,32 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
 }
 
 // ============================================================================================
+// delta of every row, from whole 16-byte pieces: a thread multiplies one piece of out and dout (both [tokens][heads * dh], so that
+// consecutive (token, head) items are consecutive runs of dh elements), one thread per item adds its dh / 8 products in order.  Only where the
+// dQ kernel cannot take delta itself because it would read O from memory that it writes dQ to (see delta_apart).
+template <class E>
+__global__ __launch_bounds__(256) void attn_delta_kernel(const E *out, const E *dout, float *delta, AttnShape sh, int items_per_block) {
+    __shared__ float part[256];
+    const int pieces = sh.dh / 8, tid = threadIdx.x;
+    const size_t items = (size_t)sh.n_seq * sh.s * sh.heads, item0 = (size_t)blockIdx.x * items_per_block;
+    float sum = 0.f;
+    if (tid < items_per_block * pieces && item0 + tid / pieces < items) {
+        const x8<E> o = *reinterpret_cast<const x8<E> *>(out + (item0 * pieces + tid) * 8);
+        const x8<E> g = *reinterpret_cast<const x8<E> *>(dout + (item0 * pieces + tid) * 8);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sum += (float)o[i] * (float)g[i];
+    }
+    part[tid] = sum;
+    __syncthreads();
+    if (tid < items_per_block && item0 + tid < items) {
+        float all = 0.f;
+        for (int c = 0; c < pieces; ++c) all += part[tid * pieces + c];
+        const size_t item = item0 + tid, token = item / sh.heads;
+        delta[((token / sh.s) * sh.heads + item % sh.heads) * sh.s + token % sh.s] = all;
+    }
+}
+
+// ============================================================================================
 // dQ.  One workgroup per (sequence, head, block of 128 queries), see block_of(); rank 0 = the last block.
 //
 // A wavefront owns 32 queries (Q and dO operands in registers); key tiles of 64 (K and V as stored) stream
@@ -400,7 +426,8 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
 // CU, so that one's MFMAs run under the other's VALU work - which needs tiles of DH elements per row, swizzled: with padded rows
 // the two stages take 90 KB at DH = 128 and only one workgroup fits (16 heads x 8100 positions x 128, causal: 485 us; now 395, and no
 // bank conflicts instead of a quarter of the LDS cycles; 384 x 1024 x 64: 121 -> 108).
-template <int DH, int OCC, class E>
+// OWN: delta is this kernel's to make, from out; otherwise it is there already (a test of out in the kernel instead: 1 - 2 % at 64 channels).
+template <int DH, int OCC, bool OWN, class E>
 __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restrict__ qkv, const E *__restrict__ out,
                                                           const float *__restrict__ lse, float *__restrict__ delta,
                                                           const E *__restrict__ dout, E *__restrict__ dqkv,
@@ -443,15 +470,17 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
         x8<E> of[NK];
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) {
-            of[ks] = frag_global(out + seq0 + row, ks, half, qvalid, dh);
+            if constexpr (OWN) of[ks] = frag_global(out + seq0 + row, ks, half, qvalid, dh);
             dof[ks] = frag_global(dout + seq0 + row, ks, half, qvalid, dh);
         }
         lse2 = qvalid ? (lse + stat)[q] : 0.f;
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) qf[ks] = frag_global(seq + (size_t)q * pitch, ks, half, qvalid, dh);
         dma_tile(0, 0);                                         // (on its way before anything is waited for)
-        dl = row_delta<NK, E>(dof, of);
-        if (qvalid && half == 0) (delta + stat)[q] = dl;
+        if constexpr (OWN) {
+            dl = row_delta<NK, E>(dof, of);
+            if (qvalid && half == 0) (delta + stat)[q] = dl;
+        } else dl = qvalid ? (delta + stat)[q] : 0.f;
         lse2 = qvalid ? lse2 * kLog2e : INFINITY;               // invalid rows: p = exp2(-inf) = 0
     }
     const float scale = rsqrtf((float)dh);
@@ -872,11 +901,14 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(const E *__restric
 // use in the launchers below alone.
 #define LGA_INSTANTIATE_KERNELS(DH, OCC, E)                                                                          \
     template __global__ void attn_fwd_kernel<DH, E>(const E *, E *, float *, AttnShape);                             \
-    template __global__ void attn_bwd_dq_kernel<DH, OCC, E>(const E *, const E *, const float *, float *, const E *, E *, \
-                                                            AttnShape);                                              \
+    template __global__ void attn_bwd_dq_kernel<DH, OCC, true, E>(const E *, const E *, const float *, float *, const E *, E *,  \
+                                                                  AttnShape);                                        \
+    template __global__ void attn_bwd_dq_kernel<DH, OCC, false, E>(const E *, const E *, const float *, float *, const E *, E *, \
+                                                                   AttnShape);                                       \
     template __global__ void attn_bwd_dkv_kernel<DH, E>(const E *, const float *, const float *, const E *, E *,     \
                                                         AttnShape)
 #define LGA_INSTANTIATE_TYPE(E)                                                                            \
+    template __global__ void attn_delta_kernel<E>(const E *, const E *, float *, AttnShape, int);          \
     LGA_INSTANTIATE_KERNELS(32, 2, E);                                                                     \
     LGA_INSTANTIATE_KERNELS(64, 2, E);                                                                     \
     LGA_INSTANTIATE_KERNELS(96, 2, E);                                                                     \
@@ -904,7 +936,10 @@ template <int DH, class E> hipError_t raise_lds_limits() {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_fwd_kernel<DH, E>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem_fwd<DH>());
     if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_bwd_dq_kernel<DH, occ_dq<DH>(), E>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_bwd_dq_kernel<DH, occ_dq<DH>(), true, E>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, smem_dq<DH>());
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_bwd_dq_kernel<DH, occ_dq<DH>(), false, E>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, smem_dq<DH>());
     if (e == hipSuccess)
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_bwd_dkv_kernel<DH, E>),
@@ -939,8 +974,8 @@ void bwd_dh(const E *qkv, const E *out, const float *lse, float *delta, const E 
     {
         snprintf(name, sizeof(name), "attn_bwd_dq_kernel<%d>", DH);
         ProfScope scope(name, 6.0 * pairs * sh.dh, 6.0 * act, s);
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, occ_dq<DH>(), E>), grid, dim3(256), smem_dq<DH>(), s, qkv, out, lse, delta, dout,
-                           dqkv, sh);
+        const auto kernel = out ? attn_bwd_dq_kernel<DH, occ_dq<DH>(), true, E> : attn_bwd_dq_kernel<DH, occ_dq<DH>(), false, E>;
+        hipLaunchKernelGGL(kernel, grid, dim3(256), smem_dq<DH>(), s, qkv, out, lse, delta, dout, dqkv, sh);
     }
     {
         snprintf(name, sizeof(name), "attn_bwd_dkv_kernel<%d>", DH);
@@ -978,6 +1013,17 @@ template <class E> void launch_attn_fwd_mfma(const E *qkv, E *out, float *lse, A
     }
 }
 
+template <class E> const E *delta_apart(const E *out, const E *dout, const E *dqkv, float *delta, AttnShape sh, hipStream_t s) {
+    const size_t n = (size_t)sh.n_seq * sh.s * sh.heads * sh.dh;
+    if (out + n <= dqkv || dqkv + 3 * n <= out) return out;
+    const size_t items = n / sh.dh;
+    const int items_per_block = 256 / (sh.dh / 8);                  // dh is a multiple of 8, at most 320
+    ProfScope scope("attn_delta_kernel", 2.0 * n, 4.0 * n, s);
+    hipLaunchKernelGGL(attn_delta_kernel<E>, dim3((unsigned)((items + items_per_block - 1) / items_per_block)), dim3(256), 0, s, out, dout, delta, sh,
+                       items_per_block);
+    return nullptr;
+}
+
 template <class E>
 void launch_attn_bwd_mfma(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv,
                           float *delta, AttnShape sh, hipStream_t s) {
@@ -987,6 +1033,7 @@ void launch_attn_bwd_mfma(const E *qkv, const E *out, const float *lse, const E 
         return;
     }
     (void)prepare_kernels();
+    out = delta_apart<E>(out, dout, dqkv, delta, sh, s);
     switch (padded_dh(sh.dh)) {
         case 32: bwd_dh<32, E>(qkv, out, lse, delta, dout, dqkv, sh, s); break;
         case 64: bwd_dh<64, E>(qkv, out, lse, delta, dout, dqkv, sh, s); break;
@@ -997,6 +1044,7 @@ void launch_attn_bwd_mfma(const E *qkv, const E *out, const float *lse, const E 
 }
 
 #define LGA_INSTANTIATE_ATTN(E)                                                                          \
+    template const E *delta_apart<E>(const E *, const E *, const E *, float *, AttnShape, hipStream_t);    \
     template void launch_attn_fwd_mfma<E>(const E *, E *, float *, AttnShape, hipStream_t);               \
     template void launch_attn_bwd_mfma<E>(const E *, const E *, const float *, const E *, E *, float *, \
                                           AttnShape, hipStream_t)

@@ -177,8 +177,8 @@ __global__ __launch_bounds__(256, fwd_occ<DH>()) void attn_wide_fwd_kernel(const
     if (half == 0) lse[((size_t)b * sh.heads + h) * sh.s + q] = m_ref * kLn2 + logf(l_tot);
 }
 
-// ---- dQ: one workgroup per (sequence, head, 128 queries) -------------------------------------------------------------------------
-template <int DH, class E>
+// ---- dQ: one workgroup per (sequence, head, 128 queries); OWN: it makes delta, too, from out; otherwise delta is there ----------
+template <int DH, bool OWN, class E>
 __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restrict__ qkv, const E *__restrict__ out,
                                                               const float *__restrict__ lse, float *__restrict__ delta,
                                                               const E *__restrict__ dout, E *__restrict__ dqkv, AttnShape sh) {
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
         x8<E> of[NK];
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) {
-            of[ks] = frag_global(out + row, ks, half, qvalid, dh);
+            if constexpr (OWN) of[ks] = frag_global(out + row, ks, half, qvalid, dh);
             dof[ks] = frag_global(dout + row, ks, half, qvalid, dh);
         }
         lse2 = qvalid ? lse[stat] : 0.f;
@@ -223,8 +223,10 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dq_kernel(const E *__restric
         for (int ks = 0; ks < NK; ++ks) qf[ks] = frag_global(seq + (size_t)q * pitch, ks, half, qvalid, dh);
         dma_tile(0, 0);                                         // (on their way before anything is waited for)
         if (kTile < kend) dma_tile(kTile, 1);
-        dl = row_delta<NK, E>(dof, of);
-        if (qvalid && half == 0) delta[stat] = dl;
+        if constexpr (OWN) {
+            dl = row_delta<NK, E>(dof, of);
+            if (qvalid && half == 0) delta[stat] = dl;
+        } else dl = qvalid ? delta[stat] : 0.f;
         if constexpr (scale_first<E>()) dl *= scale;
         lse2 = qvalid ? lse2 * kLog2e : INFINITY;               // invalid rows: p = exp2(-inf) = 0
     }
@@ -480,7 +482,8 @@ __global__ __launch_bounds__(256, 1) void attn_wide_dkv_kernel(const E *__restri
 // Explicit instantiations: the host compiler does not always find a kernel template from its use in the launchers below alone.
 #define LGA_WIDE_KERNELS(DH, E)                                                                                  \
     template __global__ void attn_wide_fwd_kernel<DH, E>(const E *, E *, float *, AttnShape);                   \
-    template __global__ void attn_wide_dq_kernel<DH, E>(const E *, const E *, const float *, float *, const E *, E *, AttnShape)
+    template __global__ void attn_wide_dq_kernel<DH, true, E>(const E *, const E *, const float *, float *, const E *, E *, AttnShape); \
+    template __global__ void attn_wide_dq_kernel<DH, false, E>(const E *, const E *, const float *, float *, const E *, E *, AttnShape)
 #define LGA_WIDE_DKV(DH, WHAT, E) \
     template __global__ void attn_wide_dkv_kernel<DH, WHAT, E>(const E *, const float *, const float *, const E *, E *, AttnShape)
 #define LGA_WIDE_TYPE(E)          \
@@ -510,7 +513,8 @@ template <class K> hipError_t raise(K kernel, int bytes) {
 template <int DH, class E> hipError_t raise_dh() {
     hipError_t e = raise(attn_wide_fwd_kernel<DH, E>, smem_fwd<DH>());
     auto next = [&](hipError_t r) { if (e == hipSuccess) e = r; };
-    next(raise(attn_wide_dq_kernel<DH, E>, smem_dq<DH>()));
+    next(raise(attn_wide_dq_kernel<DH, true, E>, smem_dq<DH>()));
+    next(raise(attn_wide_dq_kernel<DH, false, E>, smem_dq<DH>()));
     if constexpr (dkv_in_one_run<DH>()) {
         next(raise(attn_wide_dkv_kernel<DH, kBoth, E>, smem_dkv<DH>()));
     } else {
@@ -543,7 +547,8 @@ void bwd_dh(const E *qkv, const E *out, const float *lse, float *delta, const E 
     {
         snprintf(name, sizeof(name), "attn_wide_dq_kernel<%d>", DH);
         ProfScope scope(name, 6.0 * pairs * sh.dh, 6.0 * act, s);
-        hipLaunchKernelGGL((attn_wide_dq_kernel<DH, E>), grid, dim3(256), smem_dq<DH>(), s, qkv, out, lse, delta, dout, dqkv, sh);
+        const auto kernel = out ? attn_wide_dq_kernel<DH, true, E> : attn_wide_dq_kernel<DH, false, E>;
+        hipLaunchKernelGGL(kernel, grid, dim3(256), smem_dq<DH>(), s, qkv, out, lse, delta, dout, dqkv, sh);
     }
     snprintf(name, sizeof(name), "attn_wide_dkv_kernel<%d>", DH);
     ProfScope scope(name, (dkv_in_one_run<DH>() ? 8.0 : 10.0) * pairs * sh.dh, 6.0 * act, s);
@@ -577,6 +582,7 @@ template <class E>
 void launch_attn_bwd_wide(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv, float *delta, AttnShape sh, hipStream_t s) {
     if (sh.n_seq == 0 || sh.s == 0) return;
     (void)prepare_kernels();
+    out = delta_apart<E>(out, dout, dqkv, delta, sh, s);
     if (sh.dh <= 192) bwd_dh<192, E>(qkv, out, lse, delta, dout, dqkv, sh, s);
     else if (sh.dh <= 224) bwd_dh<224, E>(qkv, out, lse, delta, dout, dqkv, sh, s);
     else if (sh.dh <= 256) bwd_dh<256, E>(qkv, out, lse, delta, dout, dqkv, sh, s);

@@ -192,6 +192,8 @@ template <class E>
 void launch_attn_bwd_mfma(const E *qkv, const E *out, const float *lse, const E *dout, E *dqkv, float *delta,
                           AttnShape sh, hipStream_t s);
 
+// The O that the fused dQ kernels take delta = sum_c dO O from - or, where its memory is also dQKV's, delta from a pass before them, and NULL.
+template <class E> const E *delta_apart(const E *out, const E *dout, const E *dqkv, float *delta, AttnShape sh, hipStream_t s);
 // Fused kernels for head sizes above 160 and up to 320, multiples of 8 (attention_wide.hip).
 bool attn_wide_supports(int dh);
 template <class E> void launch_attn_fwd_wide(const E *qkv, E *out, float *lse, AttnShape sh, hipStream_t s);
