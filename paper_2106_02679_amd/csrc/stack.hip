@@ -54,9 +54,11 @@ namespace {
 #define LGA_HIP(expr)                                                                                   \
     do {                                                                                                \
         hipError_t e_ = (expr);                                                                         \
-        if (e_ != hipSuccess)                                                                           \
+        if (e_ != hipSuccess) {                                                                         \
+            (void)hipGetLastError();       /* reported here, not once more by the next call */           \
             return fail(e_ == hipErrorOutOfMemory ? LGA_ERR_OOM : LGA_ERR_HIP,                          \
                         std::string(#expr) + ": " + hipGetErrorString(e_));                             \
+        }                                                                                               \
     } while (0)
 
 constexpr size_t kAlign = 256;
@@ -507,7 +509,15 @@ bool usable(const lga_stack *st, const void *p) {
         (void)hipGetLastError();                         // memory the runtime does not know: the copy decides
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == st->device;
+    if (at.type != hipMemoryTypeDevice || at.device != st->device) return false;
+    // a boundary that does not fit its allocation is left to the copy, which refuses it
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return c + st->boundary_bytes() <= static_cast<const char *>(base) + size;
 }
 // Two boundaries without a byte in common.
 bool apart(const lga_stack *st, const void *a, const void *b) {

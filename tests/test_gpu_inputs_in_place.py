@@ -82,3 +82,40 @@ def test_micro_batch_major_buffers_that_overlap(dt, d, heads, ff, layers):
                 assert torch.equal(got, want), args
     finally:
         st.close()
+
+
+@pytest.mark.parametrize("which", ["x", "x_in", "dy", "layer_dy", "dx", "mb_x", "mb_dy", "mb_dx"])
+def test_a_buffer_shorter_than_the_activations_is_refused(which):
+    """16 bytes short, in an allocation of its own whose last page holds those 16 bytes all the same: the call reports an error, as the copy
+    that the sweeps once made of it did, and the stack goes on working."""
+    import ctypes as C
+    hip = C.CDLL("libamdhip64.so.7")
+    st, n = make(B.LGA_BF16, 128, 2, 512, 1, 1)
+    short, p = 2 * n - 16, C.c_void_p()
+    assert 0 < short % 4096 <= 4096 - 16                             # (16 more bytes do not reach another page)
+    assert hip.hipMalloc(C.byref(p), C.c_size_t(short)) == 0
+    x, g, y, dx = (torch.randn(n, device="cuda").bfloat16() for _ in range(4))
+    own = {k: t.data_ptr() for k, t in (("x", x), ("g", g), ("y", y), ("dx", dx))}
+    calls = {"x": lambda a, _: st.forward_layered(a, own["y"]),
+             "x_in": lambda a, _: st.forward_layer(0, a, own["y"]),
+             "dy": lambda a, _: st.backward_layered(a, own["dx"], None),
+             "layer_dy": lambda a, _: st.backward_layer(0, a, own["dx"], None),
+             "dx": lambda _, b: st.backward_layered(own["g"], b, None),
+             "mb_x": lambda a, _: st.step_mbmajor(a, own["g"], own["y"], own["dx"], None),
+             "mb_dy": lambda a, _: st.step_mbmajor(own["x"], a, own["y"], own["dx"], None),
+             "mb_dx": lambda _, b: st.step_mbmajor(own["x"], own["g"], own["y"], b, None)}
+    try:
+        st.forward_layered(own["x"], own["y"])
+        torch.cuda.synchronize()
+        with pytest.raises(B.LgaError) as e:
+            calls[which](p.value, p.value)
+        assert e.value.code == B.LGA_ERR_HIP
+        torch.cuda.synchronize()
+        st.forward_layered(own["x"], own["y"])
+        st.backward_layered(own["g"], own["dx"], None)
+        torch.cuda.synchronize()
+        assert torch.isfinite(dx.float()).all()
+    finally:
+        torch.cuda.synchronize()
+        st.close()
+        assert hip.hipFree(p) == 0
