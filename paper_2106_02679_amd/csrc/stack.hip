@@ -980,9 +980,9 @@ int step_mbmajor_t(lga_stack *st, const void *x, const void *dy, void *y, void *
     const size_t act_bytes = st->T * c.d_model * sizeof(T);
     T *dact = st->at<T>(st->plan.dact);
     // x, dy and dx are read and written in place where each is usable and no two overlap - a micro-batch writes its dx before the next
-    // one's x and dy are read
+    // one's x and dy are read - and where dx does not overlap y either, of which dx is the later one
     const void *users[3] = {x, dy, dx};
-    bool in_place = c.offload_checkpoints == 0;
+    bool in_place = c.offload_checkpoints == 0 && (!dx || !y || apart(st, dx, y));
     for (int i = 0; i < 3 && in_place; ++i) {
         if (!users[i]) continue;
         in_place = usable(st, users[i]);

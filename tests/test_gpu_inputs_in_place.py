@@ -84,6 +84,26 @@ def test_micro_batch_major_buffers_that_overlap(dt, d, heads, ff, layers):
         st.close()
 
 
+@pytest.mark.parametrize("layers", [1, 2])
+@pytest.mark.parametrize("before", [0, 1, 3])
+def test_where_y_and_dx_overlap_dx_is_what_stays(layers, before):
+    """Micro-batch order: y is complete before dx is, so that a program with no use for y may give both one buffer.  before: rows that y begins
+    ahead of dx, which keep y's values."""
+    st, n = make(B.LGA_BF16, 128, 2, 512, layers, 1)
+    row = 40 * 128
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x, g = (torch.randn(n, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    try:
+        y, dx = torch.empty_like(x), torch.empty_like(x)
+        st.step_mbmajor(x.data_ptr(), g.data_ptr(), y.data_ptr(), dx.data_ptr(), None)
+        buf = torch.full((2 * n,), float("nan"), device="cuda", dtype=x.dtype)
+        st.step_mbmajor(x.data_ptr(), g.data_ptr(), buf.data_ptr(), buf[before * row:].data_ptr(), None)
+        torch.cuda.synchronize()
+        assert torch.equal(buf[before * row:before * row + n], dx) and torch.equal(buf[:before * row], y[:before * row])
+    finally:
+        st.close()
+
+
 @pytest.mark.parametrize("which", ["x", "x_in", "dy", "layer_dy", "dx", "mb_x", "mb_dy", "mb_dx"])
 def test_a_buffer_shorter_than_the_activations_is_refused(which):
     """16 bytes short, in an allocation of its own whose last page holds those 16 bytes all the same: the call reports an error, as the copy
