@@ -1154,7 +1154,7 @@ template <class E> void prepare_gemm_group(GemmGroup<E> &group, const GemmParams
         q = p[i];
         q.kchunk = slices > 1 ? ((p[i].K + slices - 1) / slices + BK - 1) / BK * BK : p[i].K;
         q.ksplit = slices > 1 ? (p[i].K + q.kchunk - 1) / q.kchunk : 1;
-        q.partial = p[i].partial + used;
+        if (slices > 1) q.partial = p[0].partial + used;
         used += (size_t)slices * p[i].M * p[i].N;
     }
 }

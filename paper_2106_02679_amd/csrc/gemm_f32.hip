@@ -524,23 +524,29 @@ int gemm_f32_group_slices(const int *M, const int *N, int n, int K) {
     return best;
 }
 
+// floats of a product's partial results: the next one's begin on a 16-byte boundary
+static size_t slices_of_one(int M, int N, int slices) { return ((size_t)slices * M * N + 3) / 4 * 4; }
+size_t gemm_f32_group_floats(const int *M, const int *N, int n, int slices) {
+    size_t floats = 0;
+    for (int i = 0; i < n && slices > 1; ++i) floats += slices_of_one(M[i], N[i], slices);
+    return floats;
+}
+
 void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s) {
     (void)prepare_kernels();
     int M[kGemmGroup], N[kGemmGroup];
     long tiles = 0;
-    size_t outputs = 0;
     double flops = 0.0, bytes = 0.0;
     for (int i = 0; i < n; ++i) {
         M[i] = p[i].M;
         N[i] = p[i].N;
         tiles += (long)((M[i] + TM - 1) / TM) * ((N[i] + TN - 1) / TN);
-        outputs += (size_t)M[i] * N[i];
         flops += 2.0 * M[i] * N[i] * p[i].K;
         bytes += 4.0 * ((double)M[i] * p[i].K + (double)p[i].K * N[i] + (double)M[i] * N[i]);
     }
     const int K = p[0].K;
     int slices = gemm_f32_group_slices(M, N, n, K);
-    if (!p[0].partial || slices * outputs > p[0].partial_floats) slices = 1;
+    if (!p[0].partial || gemm_f32_group_floats(M, N, n, slices) > p[0].partial_floats) slices = 1;
     const int kchunk = slices > 1 ? ((K + slices - 1) / slices + TK - 1) / TK * TK : K;
     GemmGroup<float> group{};
     ReduceGroup sum{};
@@ -552,12 +558,12 @@ void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s) {
         q = p[i];
         q.kchunk = kchunk;
         q.ksplit = sum.slices;
-        q.partial = p[i].partial + used;
+        if (sum.slices > 1) q.partial = p[0].partial + used;
         sum.partial[i] = q.partial;
         sum.out[i] = q.outf;
         sum.n[i] = (size_t)M[i] * N[i];
         sum.beta[i] = q.beta;
-        used += (sum.slices * sum.n[i] + 3) / 4 * 4;
+        used += slices_of_one(M[i], N[i], sum.slices);
         all += sum.n[i];
     }
     const dim3 grid((unsigned)(tiles * sum.slices));

@@ -127,8 +127,9 @@ void launch_adam(float *w, float *m, float *v, const float *g, E *w16, size_t n,
 // fp32 kernel (fp32 matrix instruction), any shape and alignment:
 void launch_gemm_f32(const GemmParams<float> &p, bool a_kmajor, bool b_kmajor, Epilogue epi, hipStream_t s);
 // Several weight gradients in one launch: EPI_ACCUM_F32, operands [K][M] and [K][N], the same K, ldc = N.  p[0].partial / partial_floats is
-// scratch for all, slices * (M * N + 3) floats for each.
+// scratch for all, gemm_f32_group_floats() for as many slices as gemm_f32_group_slices(); with less the k range stays whole.
 int gemm_f32_group_slices(const int *M, const int *N, int n, int K);
+size_t gemm_f32_group_floats(const int *M, const int *N, int n, int slices);
 void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s);
 // Whether an EPI_MUL_DGELU product of this size (lda = ldb = K) leaves the first pass of its column sums at p.colsum, in chunks of
 // kGemmSumRows rows.

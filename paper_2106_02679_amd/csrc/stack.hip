@@ -265,8 +265,7 @@ Plan make_plan(const lga_config &c) {
             if (slices > 1) p.splitk_floats = std::max(p.splitk_floats, slices * outputs);
         }
     } else {
-        const size_t slices = (size_t)gemm_f32_group_slices(wg_in, wg_out, 4, (int)t);
-        for (int i = 0; i < 4 && slices > 1; ++i) p.splitk_floats += slices * ((size_t)wg_in[i] * wg_out[i] + 3);
+        p.splitk_floats = gemm_f32_group_floats(wg_in, wg_out, 4, gemm_f32_group_slices(wg_in, wg_out, 4, (int)t));
     }
     p.splitk = take(p.splitk_floats * 4);
     p.mean1 = take(t * 4);

@@ -2,6 +2,8 @@
 on operands as stored, the small tiles on transposed ones, the fp32 kernel; whole and ragged tiles and k ranges, with and
 without slices, accumulated over groups and micro-batches.  16-bit results against the fp32 ones of the same weights and inputs (2e-2, the
 gate of 16-bit stacks), groupings against each other 1e-5 (fp32 sums in another order)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -122,3 +124,44 @@ def test_bias_gradients_summed_where_their_matrices_are_made(dtype, d, s, widths
         assert rel_err(got[1][name], ref) < 1e-5, name
     for run in got:
         assert rel_err(run["b_2"], g.double().sum((0, 1, 2)).cpu().numpy()) < 1e-6
+
+
+class GemmParams(C.Structure):
+    """The launcher's own argument (csrc/common.h), which no entry point passes through."""
+    _fields_ = ([(n, C.c_void_p) for n in ("A", "B")] + [(n, C.c_int) for n in ("M", "N", "K", "lda", "ldb", "ldc")] +
+                [(n, C.c_void_p) for n in ("out", "out2", "outf", "bias", "aux", "colsum")] +
+                [("beta", C.c_float), ("partial", C.c_void_p), ("partial_floats", C.c_size_t), ("ksplit", C.c_int), ("kchunk", C.c_int),
+                 ("batch", C.c_int), ("strideA", C.c_longlong), ("strideB", C.c_longlong), ("strideC", C.c_longlong), ("tri", C.c_int),
+                 ("sblock", C.c_int)])
+
+
+def test_fp32_group_keeps_to_its_scratch():
+    """Outputs of odd sizes, whose partial results begin on 16-byte boundaries: with as many floats as the results alone the k range stays whole, with
+    what the library asks for it is cut, and either way nothing behind the scratch is written.  Only the first product names the scratch."""
+    sizes, K = [(61, 63), (63, 61), (5, 7), (65, 67)], 4000
+    ints = lambda v: (C.c_int * len(v))(*v)
+    M, N = ints([m for m, _ in sizes]), ints([n for _, n in sizes])
+    slices = B.lib._ZN3lga21gemm_f32_group_slicesEPKiS1_ii(M, N, 4, K)
+    floats_of = B.lib._ZN3lga21gemm_f32_group_floatsEPKiS1_ii
+    floats_of.restype = C.c_size_t
+    asked, bare = floats_of(M, N, 4, slices), slices * sum(m * n for m, n in sizes)
+    assert slices > 1 and bare < asked < bare + 16
+    launch = B.lib._ZN3lga21launch_gemm_f32_groupEPKNS_10GemmParamsIfEEiP12ihipStream_t
+    launch.restype, launch.argtypes = None, [C.c_void_p, C.c_int, C.c_void_p]
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    a, b = ([torch.randn(K, mn[i], device="cuda", generator=gen) for mn in sizes] for i in (0, 1))
+    for floats, cut in ((asked, True), (bare, False), (asked - 1, False), (0, False)):
+        scratch = torch.full((asked + 64,), float("nan"), device="cuda")
+        out = [torch.zeros(m, n, device="cuda") for m, n in sizes]
+        p = (GemmParams * 4)()
+        for i, (m, n) in enumerate(sizes):
+            p[i].A, p[i].B, p[i].outf = a[i].data_ptr(), b[i].data_ptr(), out[i].data_ptr()
+            p[i].M, p[i].N, p[i].K, p[i].lda, p[i].ldb, p[i].ldc = m, n, K, m, n, n
+        p[0].partial, p[0].partial_floats = scratch.data_ptr(), floats
+        launch(C.addressof(p), 4, None)
+        torch.cuda.synchronize()
+        written = ~torch.isnan(scratch)
+        assert bool(written.any()) == cut and not bool(written[floats:].any())
+        for i in range(4):
+            want = a[i].double().t() @ b[i].double()
+            assert float((out[i].double() - want).norm() / want.norm()) < 1e-5
