@@ -11,7 +11,7 @@
 //    share of the tile.  One group alone adds up the same parts in the same order, so that an activation does not depend
 //    on how many rows share its launch: the parts follow from K, only the groups from the number of tiles;
 //  - where even that leaves compute units idle, the k range is cut into slices over the grid and the partial results
-//    are added in slice order by a second kernel (only with scratch, i.e. for the stack's weight gradients).
+//    are added in slice order by a second kernel (weight gradients of a layer, which come with scratch).
 // gemm_f32_dma_kernel serves operands of whole 16-byte pieces in the layouts that the stack uses, gemm_f32_kernel the others; the
 // weight gradients of a layer run in one launch.
 // Measured (one MI355X, us; gemm_f32_kernel -> gemm_f32_dma_kernel -> vendor library): 2048 x 768 x 256 with bias 17.5 -> 14.4 -> 18.7,
@@ -150,14 +150,16 @@ template <int EPI> __device__ __forceinline__ void epilogue_f32(const GemmParams
     }
 }
 
-// Which tile and slice of the k range a workgroup has.  In: GemmParams, grid (n tiles, m tiles, k slices); or GemmGroup, the weight gradients
-// of a layer in one launch, a one-dimensional grid over all their tiles and slices.
+// Which tile and part of the k range a workgroup has.  In: GemmParams, grid (n tiles, m tiles); or GemmGroup, the weight gradients of a layer in
+// one launch, a one-dimensional grid over all their tiles and slices of the k range.
 struct Place {
     int m0, n0, kbeg, kstop;
 };
 template <int EPI, class In> __device__ __forceinline__ Place place_of(const In &in, GemmParams<float> &p, bool &vec_out) {
-    int tm, tn, slice;
-    if constexpr (std::is_same<In, GemmGroup<float>>::value) {
+    if constexpr (std::is_same<In, GemmParams<float>>::value) {
+        p = in;
+        return Place{(int)blockIdx.y * TM, (int)blockIdx.x * TN, 0, p.K};
+    } else {
         int z = 0, item = blockIdx.x;
         for (;; ++z) {
             const int items = ((in.p[z].M + TM - 1) / TM) * ((in.p[z].N + TN - 1) / TN) * in.p[z].ksplit;
@@ -166,19 +168,11 @@ template <int EPI, class In> __device__ __forceinline__ Place place_of(const In 
         }
         p = in.p[z];
         const int tiles_m = (p.M + TM - 1) / TM, tiles_n = (p.N + TN - 1) / TN;
-        slice = item / (tiles_m * tiles_n);
+        const int slice = item / (tiles_m * tiles_n);
         item -= slice * (tiles_m * tiles_n);
-        tm = item / tiles_n;
-        tn = item - tm * tiles_n;
+        const int tm = item / tiles_n, tn = item - tm * tiles_n;
+        Place at{tm * TM, tn * TN, 0, p.K};
         vec_out = p.ksplit > 1 ? (p.N & 3) == 0 : (p.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(p.outf) & 15) == 0;
-    } else {
-        p = in;
-        tm = blockIdx.y;
-        tn = blockIdx.x;
-        slice = blockIdx.z;
-    }
-    Place at{tm * TM, tn * TN, 0, p.K};
-    if constexpr (EPI == EPI_ACCUM_F32) {
         if (p.ksplit > 1) {                     // this slice of the k range, into a partial result of its own ([M][N], dense)
             at.kbeg = slice * p.kchunk;
             at.kstop = min(p.K, at.kbeg + p.kchunk);
@@ -186,8 +180,8 @@ template <int EPI, class In> __device__ __forceinline__ Place place_of(const In 
             p.ldc = p.N;
             p.beta = 0.f;
         }
+        return at;
     }
-    return at;
 }
 
 // The order of a quadrant's sums over its wavefront's steps.  An activation's parts follow from K alone: the parts of a pair, then the
@@ -458,12 +452,10 @@ template <int EPI> void launch_epi(const GemmParams<float> &p, bool akc, bool bk
     const bool vec_out = (p.ldc & 3) == 0 && (EPI == EPI_ACCUM_F32 ? al16(p.outf) : al16(p.out)) && (EPI != EPI_BIAS_GELU || al16(p.out2)) &&
                          ((EPI != EPI_BIAS_RESID && EPI != EPI_MUL_DGELU) || al16(p.aux)) &&
                          ((EPI != EPI_BIAS && EPI != EPI_BIAS_RESID && EPI != EPI_BIAS_GELU) || al16(p.bias));
-    GemmParams<float> q = p;
-    q.ksplit = 1;
     const int most = p.K > 2 * TK ? 4 : p.K > TK ? 2 : 1;
     const double mn = (double)p.M * p.N;
     ProfScope scope("gemm_f32_kernel", 2.0 * mn * p.K, 4.0 * ((double)p.M * p.K + (double)p.K * p.N + mn), s);
-    launch_tiles_f32<EPI>(q, dim3(tn, tm), tiles, most, akc, bkc, dma_takes<EPI>(p, akc, bkc), vec_out, s);
+    launch_tiles_f32<EPI>(p, dim3(tn, tm), tiles, most, akc, bkc, dma_takes<EPI>(p, akc, bkc), vec_out, s);
 }
 
 template <int EPI, class In = GemmParams<float>> hipError_t raise_epi() {

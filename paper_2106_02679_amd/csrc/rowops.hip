@@ -904,8 +904,7 @@ void launch_layernorm_fwd(const T *x, const float *g, const float *b, T *y, floa
         if (wave && d <= 64 * V) LGA_LN_WAVE(1);
         else if (wave && d <= 128 * V) LGA_LN_WAVE(2);
         else if (wave) LGA_LN_WAVE(4);
-        else if (d <= 256 * V) LGA_LN_ROWS(256, 1);
-        else if (d <= 512 * V) LGA_LN_ROWS(512, 1);
+        else if (d <= 512 * V) LGA_LN_ROWS(512, 1);              // (and narrower rows, more of them than the wavefronts' walk takes)
         else if (d <= 1024 * V) LGA_LN_ROWS(1024, 1);
         else LGA_LN_ROWS(1024, 2);
 #undef LGA_LN_ROWS
