@@ -1060,19 +1060,32 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_slices(const GemmP
     launch_splitk_reduce(p.partial, q.ksplit, p.outf, p.M, p.N, p.ldc, p.beta, s);
 }
 
+// What a round of 256 large tiles takes, for the rules that weigh rounds against something else.  Measured between 1.19 us per k tile
+// (4096 x 4096 x 1024 .. 4096) and 1.41 (one round of 16384, where the board's power binds; four rounds 1.30), and from 8 (plain store) to 20 us
+// (GELU') around them.
+constexpr double kRoundStep = 1.3, kRound16 = 12.0;
+
 // Columns that the large-tile kernel leaves to the small one (0: none).  Its tiles run in rounds of 256, and a last round of a few takes as
-// long as a full one; the columns beyond the whole rounds are better off on small tiles where they are few - by what a round takes
-// (1.2 us per k tile and 12 us) against what the small tiles do (550 TFLOP/s, at least 0.42 us per 64 k, 6 us): 2000 x 17024 x 4256,
-// 536 tiles, with GELU 322 -> 219 + 42 us.  Either kernel adds up an element's products in the same order.
-int peeled_columns(int M, int N, int K) {
+// long as a full one; the columns beyond the whole rounds are better off on small tiles where they are few - by what a round takes against
+// what the small tiles do: 550 TFLOP/s, at least 0.42 us per 64 k, the way through memory of the rows, which are read a second time, and of
+// what the epilogue reads and writes (tensors: 1 to 3 of the output's size) at 3.5 TB/s, and 6 us.  2000 x 17024 x 4256, 536 tiles, with GELU
+// 285 -> 243 us; 16384 x 1032 x 4096 159 -> 114.  Not 65280 x 264 x 4096, whose rows are 535 MB: 179, with the columns apart 310.
+// Up to four rounds and 65536 rows; of 40 products beyond, columns apart were between 3 % slower and 10 % faster, 2 % on average.
+// Either kernel adds up an element's products in the same order.
+int peeled_columns(int M, int N, int K, int tensors) {
     const long tm = (M + 255) / 256, tn = (N + 255) / 256, rounds = tm * tn / 256;
     if (rounds < 1 || rounds > 4 || tm * tn % 256 == 0 || tm > 256) return 0;
     const long keep = rounds * 256 / tm;                     // whole columns of tiles that the full rounds hold
     const int rest = N - (int)keep * 256;
     if (keep < 1 || rest <= 0) return 0;
-    const double ksteps = (double)K / BK, round = ksteps * 1.2 + 12.0;
-    const double small = std::max(2e-6 * M * rest * K / 550.0, ksteps * 0.42) + 6.0;
+    const double ksteps = (double)K / BK, round = ksteps * kRoundStep + kRound16;
+    const double memory = 2e-6 * ((double)M * K + (double)rest * K + (double)tensors * M * rest) / 3.5;
+    const double small = std::max({2e-6 * M * rest * K / 550.0, ksteps * 0.42, memory}) + 6.0;
     return small < 0.8 * round ? rest : 0;
+}
+// Tensors of the output's size that an epilogue reads and writes
+template <int EPI, class E> int epilogue_tensors(const GemmParams<E> &p) {
+    return 1 + (EPI == EPI_BIAS_RESID || EPI == EPI_MUL_DGELU) + (EPI == EPI_BIAS_GELU && p.out2);
 }
 
 template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmParams<E> &p, hipStream_t s) {
@@ -1101,7 +1114,7 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmPa
         }
         if (!large || short_rows) return launch_gemm_small<EPI, E>(p, s);
         GemmParams<E> q = p;
-        const int rest = EPI == EPI_ACCUM_F32 || p.batch > 1 || p.tri || p.colsum ? 0 : peeled_columns(p.M, p.N, p.K);
+        const int rest = EPI == EPI_ACCUM_F32 || p.batch > 1 || p.tri || p.colsum ? 0 : peeled_columns(p.M, p.N, p.K, epilogue_tensors<EPI>(p));
         if (rest > 0) {
             const int n = p.N - rest;
             q.N = rest;
@@ -1304,7 +1317,7 @@ int gemm_splitk_slices(int M, int N, int K) {
 // (The large-tile kernel alone, see launch_tiles.  Columns left to the small one are worth more than the pass over the result: 2000 x 17024 x
 // 4256 with GELU' 341 -> 233 + 41 us, the pass 15.)
 bool gemm_dgelu_adds_columns(int M, int N, int K) {
-    return (long)((M + 255) / 256) * ((N + 255) / 256) >= 128 && K >= BK && peeled_columns(M, N, K) == 0;
+    return (long)((M + 255) / 256) * ((N + 255) / 256) >= 128 && K >= BK && peeled_columns(M, N, K, 2) == 0;
 }
 
 bool gemm_mfma_supports(bool a_kmajor, bool b_kmajor, Epilogue epi) {

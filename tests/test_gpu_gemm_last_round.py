@@ -41,3 +41,20 @@ def test_columns_behind_the_last_whole_round(shape, dt):
     call(B.LGA_EPI_STORE, got, got, 0, N)
     torch.cuda.synchronize()
     assert float((got[::97, :N].double() - want).norm() / want.norm()) < (4e-3 if dt == B.LGA_BF16 else 5e-4)      # one rounding of the result
+
+
+#        M,     N,    K,  epilogue, whether the columns behind the whole rounds go to the small tiles
+ROUTES = [(4096, 4224, 1024, B.LGA_EPI_MUL_DGELU, True), (11320, 1312, 2048, B.LGA_EPI_BIAS_GELU, True),
+          (65280, 264, 1024, B.LGA_EPI_STORE, False),        # the rows' way through memory: 134 MB for 8 columns
+          (57336, 1032, 640, B.LGA_EPI_STORE, False), (25600, 2536, 64, B.LGA_EPI_MUL_DGELU, False),      # ... the results'
+          (45880, 1688, 64, B.LGA_EPI_BIAS_GELU, False)]
+
+
+@pytest.mark.parametrize("M,N,K,epi,apart", ROUTES)
+def test_columns_apart_only_where_they_cost_less_than_a_round(M, N, K, epi, apart):
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    A, W, aux = (torch.randn(r, c, device="cuda", generator=gen).bfloat16() for r, c in ((M, K), (N, K), (M, N)))
+    out, out2, bias = torch.empty_like(aux), torch.empty_like(aux), torch.randn(N, device="cuda", generator=gen)
+    kernels = profiled(lambda: B.check(B.lib.lga_op_gemm(B.LGA_BF16, 1, 1, epi, M, N, K, A.data_ptr(), K, W.data_ptr(), K, out.data_ptr(), out2.data_ptr(),
+                                                         None, N, bias.data_ptr(), aux.data_ptr(), 0.0, None)))
+    assert any("small" in n for n in kernels) == apart, kernels.keys()
