@@ -1062,8 +1062,8 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_slices(const GemmP
 
 // What a round of 256 large tiles takes, for the rules that weigh rounds against something else.  Measured between 1.19 us per k tile
 // (4096 x 4096 x 1024 .. 4096) and 1.41 (one round of 16384, where the board's power binds; four rounds 1.30), and from 8 (plain store) to 20 us
-// (GELU') around them.
-constexpr double kRoundStep = 1.3, kRound16 = 12.0;
+// (GELU') around them; for weight gradients 1.22 to 1.30 and 16 to 20 us.
+constexpr double kRoundStep = 1.25, kRound16 = 12.0, kRoundF32 = 16.5;
 
 // Columns that the large-tile kernel leaves to the small one (0: none).  Its tiles run in rounds of 256, and a last round of a few takes as
 // long as a full one; the columns beyond the whole rounds are better off on small tiles where they are few - by what a round takes against
@@ -1195,10 +1195,11 @@ template void prepare_gemm_group<f16>(GemmGroup<f16> &, const GemmParams<f16> *,
 template void launch_splitk_reduce_group<bf16>(const GemmGroup<bf16> &, hipStream_t);
 template void launch_splitk_reduce_group<f16>(const GemmGroup<f16> &, hipStream_t);
 
-// Slices of the k range for n weight gradients in one launch of the large-tile kernel, by what a round of 256 workgroups takes (1.2 us per
-// k tile and 12 us around them) and the way of the partial results through memory (4.5 TB/s); 0 where that leaves more than a quarter of the
-// chip idle or a workgroup fewer than 16 k tiles.  The four matrices of a d = 768 layer over 4096 tokens, 108 tiles: 121 us in four launches
-// of the small kernel behind 38 us of transposes, now 58 + 20 us in two slices and 11 us for the bias gradients' column sums.
+// Slices of the k range for n weight gradients in one launch of the large-tile kernel, by what a round of 256 workgroups takes (above) and the way
+// of the partial results through memory (4.5 TB/s); 0 where that leaves more than a quarter of the chip idle or a workgroup fewer than 16 k
+// tiles.  The four matrices of a d = 768 layer over 4096 tokens, 108 tiles: 121 us in four launches of the small kernel behind 38 us of
+// transposes, now 58 + 20 us in two slices and 11 us for the bias gradients' column sums.  (With 1.2 and 12 us for a round: 1072 x 2448 over
+// 6424 tokens in four slices instead of two 183 us, now 161; 1320 x 1416 over 26240 in five instead of one 550, now 517.)
 int gemm_group_slices(const int *M, const int *N, int n, int K) {
     long tiles = 0;
     double outputs = 0.0;
@@ -1212,24 +1213,24 @@ int gemm_group_slices(const int *M, const int *N, int n, int K) {
     double best_us = 0.0;
     for (int s = 1; s <= std::min(32, K / 1024); ++s) {
         if (tiles * s < 192) continue;
-        const double us = (double)((tiles * s + 255) / 256) * ((double)(K / s) / BK * 1.2 + 12.0) + (s > 1 ? (s + 1) * outputs * 4.0 / 4.5e6 : 0.0);
+        const double us = (double)((tiles * s + 255) / 256) * ((double)(K / s) / BK * kRoundStep + kRoundF32) + (s > 1 ? (s + 1) * outputs * 4.0 / 4.5e6 : 0.0);
         if (best == 0 || us < best_us) best = s, best_us = us;
     }
     return best;
 }
 
 // Matrices that are enough work alone still share a launch where their last rounds then fill each other up, by the same times: T-NLG's four
-// (289 to 1139 tiles over 4000 tokens, 14 rounds together, 16 apart) 1505 -> 1425 us; d = 2048 over 65536, W_o and W_qkv with 64 and 192
-// tiles in slices apart, all 768 whole together, 2226 -> 2073.
+// (289 to 1139 tiles over 4000 tokens, 14 rounds together, 16 apart) 1477 -> 1415 us; d = 2048 over 32768 tokens, W_o and W_qkv with 64 and 192
+// tiles in slices apart, all 768 whole together, 2207 -> 2144.
 bool gemm_stored_group_wins(const int *M, const int *N, int n, int K) {
     long tiles = 0;
     double apart = 0.0;
-    const double round = (double)K / BK * 1.2 + 12.0;
+    const double round = (double)K / BK * kRoundStep + kRoundF32;
     for (int i = 0; i < n; ++i) {
         const long mine = (long)((M[i] + 255) / 256) * ((N[i] + 255) / 256);
         const int slices = gemm_splitk_slices(M[i], N[i], K);
         tiles += mine;
-        apart += (double)((mine * slices + 255) / 256) * ((double)K / slices / BK * 1.2 + 12.0) +
+        apart += (double)((mine * slices + 255) / 256) * ((double)K / slices / BK * kRoundStep + kRoundF32) +
                  (slices > 1 ? (slices + 1) * (double)M[i] * N[i] * 4.0 / 4.5e6 : 0.0);
     }
     return n > 1 && tiles >= 224 && (double)((tiles + 255) / 256) * round < 0.99 * apart;
