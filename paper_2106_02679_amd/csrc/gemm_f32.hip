@@ -454,8 +454,9 @@ template <int EPI> void launch_epi(const GemmParams<float> &p, bool akc, bool bk
                          ((EPI != EPI_BIAS && EPI != EPI_BIAS_RESID && EPI != EPI_BIAS_GELU) || al16(p.bias));
     const int most = p.K > 2 * TK ? 4 : p.K > TK ? 2 : 1;
     const double mn = (double)p.M * p.N;
-    ProfScope scope("gemm_f32_kernel", 2.0 * mn * p.K, 4.0 * ((double)p.M * p.K + (double)p.K * p.N + mn), s);
-    launch_tiles_f32<EPI>(p, dim3(tn, tm), tiles, most, akc, bkc, dma_takes<EPI>(p, akc, bkc), vec_out, s);
+    const bool dma = dma_takes<EPI>(p, akc, bkc);
+    ProfScope scope(dma ? "gemm_f32_kernel<dma>" : "gemm_f32_kernel", 2.0 * mn * p.K, 4.0 * ((double)p.M * p.K + (double)p.K * p.N + mn), s);
+    launch_tiles_f32<EPI>(p, dim3(tn, tm), tiles, most, akc, bkc, dma, vec_out, s);
 }
 
 template <int EPI, class In = GemmParams<float>> hipError_t raise_epi() {
@@ -563,7 +564,7 @@ void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s) {
     bool dma = true;
     for (int i = 0; i < n; ++i) dma = dma && dma_takes<EPI_ACCUM_F32>(p[i], false, false);
     {
-        ProfScope scope("gemm_f32_kernel (grouped)", flops, bytes, s);
+        ProfScope scope(dma ? "gemm_f32_kernel<dma> (grouped)" : "gemm_f32_kernel (grouped)", flops, bytes, s);
         launch_tiles_f32<EPI_ACCUM_F32>(group, grid, tiles * sum.slices, most, false, false, dma, false, s);
     }
     if (sum.slices > 1) {

@@ -361,7 +361,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_dx_kernel(const T *__restri
 // them to partial[blockIdx.x][0 / 1][c] - the first pass of the column sums that give the gradients of the LayerNorm
 // bias and gain (colsum_final_kernel adds the blocks' rows up in a fixed order), from operands that are in registers anyway.
 // SUMS = 4: the same for resid and dx, to more[blockIdx.x][0 / 1][c]: the gradients of the biases behind and in front of the layer's second
-// LayerNorm, for which a pass over both cost 0.06 us per MB.
+// LayerNorm, for which a pass over both cost 0.22 us per MB (450 MB, 100 us).
 template <class T, int V, int TH, int NP, int SUMS>
 __global__ __launch_bounds__(TH) void layernorm_bwd_dx_rows_kernel(const T *__restrict__ dy, const T *__restrict__ x,
                                                                    const float *__restrict__ mean,

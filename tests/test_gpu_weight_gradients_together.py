@@ -60,6 +60,7 @@ def test_fp32_weight_gradients_in_one_launch(d, heads, ff, s, b):
         got = []
         kernels = profiled(lambda: got.append(run_gpu_step(w, x, G, params, retain=1, **kw)))
         assert launches(kernels, "gemm_f32_kernel") == 2 // kw.get("group", 1)
+        assert launches(kernels, "gemm_f32_kernel<dma>") == (2 // kw.get("group", 1) if d % 4 == 0 and ff % 4 == 0 else 0)
         compare_with_oracle(w, got[0], ref, 1e-5, None, zero_init=False)
 
 
@@ -72,7 +73,7 @@ DIRECT = [(4, 4, 4), (64, 64, 32), (68, 60, 36), (132, 200, 64), (64, 128, 96), 
 @pytest.mark.parametrize("akm,bkm,epi", [(1, 0, B.LGA_EPI_BIAS), (1, 1, B.LGA_EPI_STORE), (0, 0, B.LGA_EPI_ACCUM_F32)])
 def test_fp32_operands_straight_to_lds_agree_with_the_general_kernel(akm, bkm, epi, shape):
     """The same product from operands whose rows are whole 16-byte pieces and from copies that start 4 bytes further, which the general
-    kernel takes: both within 1e-5 of exact sums (see the tolerance of the other fp32 GEMM tests); nothing outside the operands is
+    kernel takes (as it does rows of 1090 weight-gradient columns either way): both within 1e-5 of exact sums (see the tolerance of the other fp32 GEMM tests); nothing outside the operands is
     used (NaN lies around them)."""
     M, N, K = shape
     gen = torch.Generator(device="cuda").manual_seed(M + N + K)
@@ -92,17 +93,21 @@ def test_fp32_operands_straight_to_lds_agree_with_the_general_kernel(akm, bkm, e
         bias = torch.randn(N, device="cuda", generator=gen)
         out = torch.zeros(M, N, device="cuda")
         want = (a64 if akm else a64.t()) @ (b64.t() if bkm else b64) + (bias.double() if epi == B.LGA_EPI_BIAS else 0.0)
-        B.check(B.lib.lga_op_gemm(B.LGA_FP32, akm, bkm, epi, M, N, K, a.data_ptr(), lda, b.data_ptr(), ldb, out.data_ptr(), None, out.data_ptr(), N,
-                                  bias.data_ptr(), None, 0.0, None))
-        torch.cuda.synchronize()
+        kernels = profiled(lambda: B.check(B.lib.lga_op_gemm(B.LGA_FP32, akm, bkm, epi, M, N, K, a.data_ptr(), lda, b.data_ptr(), ldb, out.data_ptr(),
+                                                             None, out.data_ptr(), N, bias.data_ptr(), None, 0.0, None)))
+        whole = shift == 0 and (K if akm else M) % 4 == 0 and (K if bkm else N) % 4 == 0
+        assert list(kernels) == ["gemm_f32_kernel<dma>" if whole else "gemm_f32_kernel"]
         results.append(out)
         assert float((out.double() - want).norm() / want.norm()) < 1e-5
     assert float((results[0] - results[1]).norm() / results[1].norm()) < 1e-5
 
 
-@pytest.mark.parametrize("dtype,d,s,widths", [("bf16", 2048, 763, (5, 3)), ("fp32", 1024, 1000, (9, 7))], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("dtype,d,s,widths", [
+    ("bf16", 2048, 763, (5, 3)), ("fp32", 1024, 1000, (9, 7)),               # LayerNorm with a row per workgroup
+    ("bf16", 768, 2047, (5, 3)), ("bf16", 512, 2049, (8, 3)),                # ... per wavefront, two packs a lane and one (and b_o once with a transpose)
+    ("fp32", 512, 1025, (9, 7)), ("fp32", 256, 2049, (9, 7))], ids=["bf16", "fp32", "bf16_768", "bf16_512", "fp32_512", "fp32_256"])
 def test_bias_gradients_summed_where_their_matrices_are_made(dtype, d, s, widths):
-    """From 64 MB on (here two micro-batches per launch; one has it for du only, in bf16) the second LayerNorm's backward and the GELU' product
+    """From 64 MB on (here two micro-batches per launch; one has it for du at most, in bf16) the second LayerNorm's backward and the GELU' product
     leave the bias gradients' first passes: the same values in other chunks, so 1e-5 between the two, over a ragged last chunk; b_2
     against the column sum of the output gradient itself."""
     w = S.Workload("sums", 1, d, 16, 4 * d, s, 8, 4, dtype)
