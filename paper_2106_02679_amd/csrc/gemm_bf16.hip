@@ -1062,14 +1062,15 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_slices(const GemmP
 
 // What a round of 256 large tiles takes, for the rules that weigh rounds against something else.  Measured between 1.19 us per k tile
 // (4096 x 4096 x 1024 .. 4096) and 1.41 (one round of 16384, where the board's power binds; four rounds 1.30), and from 8 (plain store) to 20 us
-// (GELU') around them; for weight gradients 1.22 to 1.30 and 16 to 20 us.
-constexpr double kRoundStep = 1.25, kRound16 = 12.0, kRoundF32 = 16.5;
+// (GELU') around them, where a last round, partly empty, has less to wait for; for weight gradients 1.22 to 1.30 and 16 to 20 us.
+constexpr double kRoundStep = 1.25, kRound16 = 9.0, kRoundTensor = 3.0, kRoundF32 = 16.5;
 
 // Columns that the large-tile kernel leaves to the small one (0: none).  Its tiles run in rounds of 256, and a last round of a few takes as
 // long as a full one; the columns beyond the whole rounds are better off on small tiles where they are few - by what a round takes against
 // what the small tiles do: 550 TFLOP/s, at least 0.42 us per 64 k, the way through memory of the rows, which are read a second time, and of
 // what the epilogue reads and writes (tensors: 1 to 3 of the output's size) at 3.5 TB/s, and 6 us.  2000 x 17024 x 4256, 536 tiles, with GELU
 // 285 -> 243 us; 16384 x 1032 x 4096 159 -> 114.  Not 65280 x 264 x 4096, whose rows are 535 MB: 179, with the columns apart 310.
+// Of 220 products of all epilogues none takes more than 2 % longer for it, most of what it applies to 5 - 30 % less.
 // Up to four rounds and 65536 rows; of 40 products beyond, columns apart were between 3 % slower and 10 % faster, 2 % on average.
 // Either kernel adds up an element's products in the same order.
 int peeled_columns(int M, int N, int K, int tensors) {
@@ -1078,7 +1079,7 @@ int peeled_columns(int M, int N, int K, int tensors) {
     const long keep = rounds * 256 / tm;                     // whole columns of tiles that the full rounds hold
     const int rest = N - (int)keep * 256;
     if (keep < 1 || rest <= 0) return 0;
-    const double ksteps = (double)K / BK, round = ksteps * kRoundStep + kRound16;
+    const double ksteps = (double)K / BK, round = ksteps * kRoundStep + kRound16 + (tensors - 1) * kRoundTensor;
     const double memory = 2e-6 * ((double)M * K + (double)rest * K + (double)tensors * M * rest) / 3.5;
     const double small = std::max({2e-6 * M * rest * K / 550.0, ksteps * 0.42, memory}) + 6.0;
     return small < 0.8 * round ? rest : 0;
