@@ -46,26 +46,19 @@ template <class E> __device__ __forceinline__ x8<E> pack16(const f32x16 &v, int 
 constexpr int kBufRange = 0x40000000;
 constexpr int kBufPoison = 0x7FFFFF00;
 typedef __attribute__((address_space(3))) void *lds_ptr;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, kBufRange, 0x00020000);
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, int range = kBufRange) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, range, 0x00020000);
 }
-// All LDS reads issued so far have returned; the operands listed are tied to the wait so that no use of
+// All LDS reads issued so far but the newest NEWER have returned; the operands listed are tied to the wait so that no use of
 // them can be scheduled above it.
-template <class V, int N> __device__ __forceinline__ void wait_tr_reads(V (&f)[N]) {
-    static_assert(N <= 10, "operand list below");
-    if constexpr (N == 2) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]));
-    else if constexpr (N == 4) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]));
-    else if constexpr (N == 6)
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]));
-    else if constexpr (N == 7)
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]));
-    else if constexpr (N == 8)
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]));
-    else if constexpr (N == 10)
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]),
-                       "+v"(f[8]), "+v"(f[9]));
+template <int NEWER = 0, class V, int N> __device__ __forceinline__ void wait_tr_reads(V (&f)[N]) {
+    static_assert(N <= 10 && NEWER < 16, "operand list below; lgkmcnt has four bits");
+    if constexpr (N == 2) asm volatile("s_waitcnt lgkmcnt(%c2)" : "+v"(f[0]), "+v"(f[1]) : "i"(NEWER));
+    else if constexpr (N == 4) asm volatile("s_waitcnt lgkmcnt(%c4)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : "i"(NEWER));
+    else if constexpr (N == 6) asm volatile("s_waitcnt lgkmcnt(%c6)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]) : "i"(NEWER));
+    else if constexpr (N == 7) asm volatile("s_waitcnt lgkmcnt(%c7)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]) : "i"(NEWER));
+    else if constexpr (N == 8) asm volatile("s_waitcnt lgkmcnt(%c8)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]) : "i"(NEWER));
+    else if constexpr (N == 10) asm volatile("s_waitcnt lgkmcnt(%c10)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]), "+v"(f[8]), "+v"(f[9]) : "i"(NEWER));
     else static_assert(N == 2, "unsupported operand count");
 }
 // Tiles that are read both ways - rows with ds_read_b128 and transposed with ds_read_b64_tr_b16 - keep the

@@ -15,6 +15,8 @@
 //   forward      S^T = K Q^T ; P^T = softmax ; O^T += V^T P^T              streams K, V
 //   dQ kernel    S^T = K Q^T ; dP^T = V dO^T ; dS^T ; dQ^T += K^T dS^T      streams K, V
 //   dK/dV kernel S = Q K^T ; dP = dO V^T ; dV^T += dO^T P ; dK^T += Q^T dS  streams Q, dO
+#include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <type_traits>
 
@@ -64,57 +66,75 @@ template <int PITCH, class E> __device__ __forceinline__ x8<E> frag_nat_tr(const
 }
 // DMA of a ROWS x DH tile (global row pitch gp2 bytes) into LDS rows of PITCH elements.  The tile is
 // ROWS * (PITCH / 8) slots of 16 bytes, filled 64 at a time; instruction j covers slots [64 j, 64 j + 64).
-// Slots that are padding, and rows at or beyond nvalid, get the poison offset (zeros).
+// Slots that are padding get the poison offset, and rows at or beyond nvalid lie outside the buffer's range (zeros either way).
 template <int ROWS, int DH, int PITCH> struct TileDma {
     static constexpr int SLOTS = PITCH / 8;                 // per row
     static constexpr int NI = (ROWS * SLOTS + 63) / 64;     // instructions that carry data
     static constexpr int NJ = (NI + 3) / 4;                 // per wavefront (4 wavefronts): every wavefront issues NJ,
                                                             // so that "all but the newest tile" is one vmcnt value
     static constexpr int ELEMS = NJ * 4 * 512;              // LDS elements to reserve: 4 NJ instructions of 1 KB
-    int row[NJ], off[NJ];
+    int off[NJ], pitch2, row2;
     // dh <= DH: the head size in memory; columns from dh on are padding like the rest of the pitch
     __device__ __forceinline__ void init(int wave, int lane, int gp2, int dh) {
+        pitch2 = gp2;
+        row2 = dh * 2;
 #pragma unroll
         for (int i = 0; i < NJ; ++i) {
             const int slot = (i * 4 + wave) * 64 + lane, r = slot / SLOTS, pc = slot % SLOTS;
-            row[i] = (pc < dh / 8 && r < ROWS) ? r : 0x7FFFFFFF;    // padding slots never pass the row test
-            off[i] = r * gp2 + (pc << 4);
+            off[i] = pc < dh / 8 && r < ROWS ? r * gp2 + (pc << 4) : kBufPoison;
         }
     }
     // src, dst: tiles of 16-bit elements of either format
     __device__ __forceinline__ void issue(const void *src, void *dst, int nvalid, int wave) const {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src);
+        const int rows = min(nvalid, ROWS);
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src, rows > 0 ? (rows - 1) * pitch2 + row2 : 0);
 #pragma unroll
         for (int i = 0; i < NJ; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(static_cast<char *>(dst) + (i * 4 + wave) * 1024), 16,
-                                                     row[i] < nvalid ? off[i] : kBufPoison, 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(static_cast<char *>(dst) + (i * 4 + wave) * 1024), 16, off[i], 0, 0, 0);
     }
 };
 
+// S^T tiles live in ordinary registers: the exponentials read them, and the builtin's results would be in accumulation registers, a
+// move apart from any other instruction.  Two such products in a row on one tile are separated by what stands between the
+// statements; a result is read only behind at least two other matrix instructions, or the wait states below.
+template <class E> __device__ __forceinline__ void mfma_scores(x8<E> a, x8<E> b, f32x16 &c, bool first);
+#define LGA_MFMA_SCORES(E, name)                                                                                                              \
+    template <> __device__ __forceinline__ void mfma_scores<E>(x8<E> a, x8<E> b, f32x16 &c, bool first) {                                     \
+        const i32x4 ai = __builtin_bit_cast(i32x4, a), bi = __builtin_bit_cast(i32x4, b);                                                     \
+        if (first) asm volatile(name " %0, %1, %2, 0" : "=&v"(c) : "v"(ai), "v"(bi));                                                         \
+        else asm volatile(name " %0, %1, %2, %0" : "+v"(c) : "v"(ai), "v"(bi));                                                               \
+    }
+LGA_MFMA_SCORES(bf16, "v_mfma_f32_32x32x16_bf16")
+LGA_MFMA_SCORES(f16, "v_mfma_f32_32x32x16_f16")
+#undef LGA_MFMA_SCORES
+// s_waitcnt immediate: all LDS reads returned, at most n loads in flight
+constexpr int wait_loads(int n) { return 0x0070 | (n & 15) | (n >> 4 << 14); }
+
 // ============================================================================================
-// Forward.  One workgroup per (sequence, head, block of 256 queries), see block_of(); rank 0 = the last block.
+// Forward.  One workgroup per (sequence, head, block of 128 U queries), see block_of(); rank 0 = the last block.
 //
-// A wavefront owns 64 queries as two sub-blocks of 32, so every K and V operand it reads from LDS
-// feeds two MFMAs; one wavefront per SIMD, with registers for both sub-blocks' output accumulators.
-// Key tiles of 64 (K and V as stored, rows of DH) stream from global memory straight into one of two
-// LDS stages while the other is multiplied; one barrier per tile publishes it.  V^T operands come from
-// the natural V tile through the transposing LDS read.  The online softmax runs per (sub-block, 32 keys).
-template <int DH, class E>
+// A wavefront owns 32 U queries as U sub-blocks of 32, so every K and V operand it reads from LDS feeds U MFMAs.
+// Key tiles of 64 (K and V as stored, rows of DH) stream from global memory straight into one of three
+// LDS stages; one barrier per tile publishes it.  V^T operands come from the natural V tile through the
+// transposing LDS read.
+template <int DH, int U, class E>
 __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ qkv, E *__restrict__ out,
                                                        float *__restrict__ lse, AttnShape sh) {
     constexpr int KT = 64;                 // keys per streamed tile
     constexpr int NK = DH / 16, NC = DH / 32;
+    constexpr int NU = 2 * U;              // units of 32 keys x 32 queries per tile and wavefront
+    constexpr int QW = 32 * U;             // queries per wavefront
     constexpr int PK = pitch_rd<DH>(), PV = pitch_tr<DH>();    // LDS row pitches of the K and V tiles
     typedef TileDma<KT, DH, PK> DmaK;
     typedef TileDma<KT, DH, PV> DmaV;
     constexpr int STAGE = DmaK::ELEMS + DmaV::ELEMS;            // elements per stage: K tile, then V tile
-    constexpr int NSTAGE = 3;
-    constexpr int kWaitOlder = 0x0070 | (DmaK::NJ + DmaV::NJ);  // s_waitcnt lgkmcnt(0) vmcnt(loads of one tile): older tiles landed
-    static_assert(DmaK::NJ + DmaV::NJ < 16, "vmcnt immediate uses the low four bits only");
+    constexpr int NSTAGE = 3, LOADS = DmaK::NJ + DmaV::NJ;
+    // tiles requested ahead of the one that is published: with U = 2 all reads of the tile before it are done by then
+    constexpr int AHEAD = U == 2 ? 2 : 1;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     E *lds = reinterpret_cast<E *>(smem_raw);
 
-    const int qblocks = (sh.s + 255) / 256;
+    const int qblocks = (sh.s + 4 * QW - 1) / (4 * QW);
     int bh, rank;
     block_of(sh, qblocks, bh, rank);
     const int qb = qblocks - 1 - rank;
@@ -125,15 +145,15 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
     const E *seq = qkv + (size_t)b * sh.s * pitch + (size_t)h * dh;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lrow = lane & 31, half = lane >> 5;
-    const int qw0 = qb * 256 + wave * 64;          // first query of this wavefront
+    const int qw0 = (qb * 4 + wave) * QW;           // first query of this wavefront
     const bool causal = sh.causal != 0;
     // Last visible key of sub-block u's lanes = vis_u(u) + vis_lane + 4 half: the query itself, or the end of the sequence.
     const int vis_lane = (causal ? lrow : 0) - 4 * half;
     auto vis_u = [&](int u) { return causal ? qw0 + 32 * u : sh.s - 1; };
 
-    x8<E> qf[2][NK];
+    x8<E> qf[U][NK];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < U; ++u) {
         const int q = qw0 + 32 * u + lrow;
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) qf[u][ks] = frag_global(seq + (size_t)q * pitch, ks, half, q < sh.s, dh);
@@ -155,8 +175,8 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
     // units below that best score become denormal (still exact to 2^-25 of the row's largest terms).
     constexpr float kRefBias = std::is_same<E, f16>::value ? 6.f : 0.f;
     constexpr int kMaxAttempts = 6;
-    f32x16 oacc[2][NC];
-    float m_ref[2] = {-INFINITY, -INFINITY}, l_run[2];
+    f32x16 oacc[U][NC];
+    float m_ref[U], l_run[U];
     const float c2 = rsqrtf((float)dh) * kLog2e;
     // Plain (not volatile) so that the compiler keeps it an LDS access, which waits for no global load; the
     // barriers' memory clobbers make every read after them a fresh one.
@@ -168,202 +188,185 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
     DmaV dv;
     dk.init(wave, lane, (int)(pitch * 2), dh);
     dv.init(wave, lane, (int)(pitch * 2), dh);
-    auto dma_tile = [&](int k0, int stage) {
+    const int kend = causal ? min(sh.s, (qb + 1) * 4 * QW) : sh.s;  // keys needed by this block: [0, kend)
+    const int ntiles = (kend + KT - 1) / KT;
+    auto dma_tile = [&](int t, int stage) __attribute__((always_inline)) {
+        if (t >= ntiles) return;
         E *Ks = lds + stage * STAGE, *Vs = Ks + DmaK::ELEMS;
-        dk.issue(seq + (size_t)k0 * pitch + d, Ks, sh.s - k0, wave);
-        dv.issue(seq + (size_t)k0 * pitch + 2 * d, Vs, sh.s - k0, wave);
+        dk.issue(seq + (size_t)t * KT * pitch + d, Ks, sh.s - t * KT, wave);
+        dv.issue(seq + (size_t)t * KT * pitch + 2 * d, Vs, sh.s - t * KT, wave);
     };
     const int koff = lrow * PK + 8 * half;              // per-lane part of a K operand's address
     const int voff = tr_lane_off<PV>(lane);             // ... and of a V^T operand's
 
-    // ---- one key tile -------------------------------------------------------------------------
-    // Four units n = 2 kb + u (key block kb of 32, query sub-block u), each: S = NK MFMAs, the
-    // exponentials (VALU), P V = 2 NC MFMAs.  MFMAs of one unit and exponentials of another are
-    // independent, so they are issued interleaved - a few MFMAs, then a quarter of a unit's exponentials -
-    // and the matrix pipe works under the VALU instructions of the same wavefront:
-    //     slot   0      1        2          3          4       5
-    //     MFMA   S(0)   S(1)     PV(0) S(2) PV(1) S(3) PV(2)   PV(3)
-    //     VALU          exp(0)   exp(1)     exp(2)     exp(3)
-    // One set of K operand registers and one of V^T operand registers: the second key block's are read as
-    // soon as the first block's last MFMA is issued, under the other work of the slot.  The issue order is
-    // pinned (sched_barrier).  With tiles and wavefront query ranges both aligned to 64, a tile is either
-    // fully visible or the diagonal one (k0 == qw0), where masked probabilities are forced to zero.
-    x8<E> kf[NK], vf[2 * NC], pf[4][2];           // K operands and V^T operands of one key block, P operands [unit]
-    f32x16 st[4];                                  // scores per unit
-    float pr[2][8];                                // probabilities of half a unit, until they are packed
-    auto read_k = [&](const E *Ks, int kb) {
-#pragma unroll
-        for (int ks = 0; ks < NK; ++ks) kf[ks] = *reinterpret_cast<const x8<E> *>(Ks + kb * 32 * PK + 16 * ks);
+    // ---- the pipeline over units ----------------------------------------------------------------
+    // A unit is 32 keys x 32 queries, n = U kb + u of a tile: S = NK MFMAs, the exponentials (VALU), P V = 2 NC MFMAs.  A phase per unit:
+    //     MFMA   P V of the unit before it, then S of the unit behind it
+    //     VALU   its exponentials
+    // across tiles, a share of the exponentials behind every MFMA: a wavefront issues in order, and two MFMAs in a row keep the
+    // VALU waiting for the first.  One set of K and one of V^T operand registers: each is read again, for the next key
+    // block, right behind the last MFMA that uses it, so that a read is half a phase and more ahead of its use.  The issue
+    // order is pinned (sched_barrier).  Units of one tile only, groups of 2 to 4 MFMAs between groups of exponentials and scores in
+    // accumulation registers took 4590 cycles a tile of 64 queries x 64 keys x 128, of which 2048 are MFMAs; now 3700, at a lower clock: the
+    // board's power binds (8100 x 16 heads x 128: 348 -> 302 us, 1024 x 384 x 64: 114 -> 103, 2048 x 32 x 128 unmasked 106 -> 94).
+    x8<E> kf[NK], vf[2 * NC];
+    u32x4 pf[2][2];                                // P operands of a unit and of the one before it
+    f32x16 st[2];                                  // scores of a unit and of the one behind it
+    float pr[16];
+    constexpr int NM = NK + 2 * NC;                // MFMAs of a phase
+    constexpr int FIRST = NM >= 8 ? 2 : 1;         // the exponentials begin behind this many, when the scores have left the matrix pipe
+    auto read_k = [&](const E *Ks, int kb, int ks) __attribute__((always_inline)) {
+        kf[ks] = *reinterpret_cast<const x8<E> *>(Ks + kb * 32 * PK + 16 * ks);
     };
-    auto read_v = [&](const E *Vs, int kb) {
-#pragma unroll
-        for (int j2 = 0; j2 < 2; ++j2)
-#pragma unroll
-            for (int c = 0; c < NC; ++c) vf[j2 * NC + c] = frag_nat_tr<PV>(Vs, c, 2 * kb + j2);
-    };
-    auto s_group = [&](int n, int g) {             // quarter g of unit n's S MFMAs
-        const int u = n & 1;
-#pragma unroll
-        for (int ks = 0; ks < NK; ++ks) {
-            if (ks < g * NK / 4 || ks >= (g + 1) * NK / 4) continue;
-            if (ks == 0) {
-                const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                st[n] = MFMA(kf[ks], qf[u][ks], zero);
-            } else {
-                st[n] = MFMA(kf[ks], qf[u][ks], st[n]);
-            }
-        }
-    };
-    auto pv_group = [&](int n, int g) {            // quarter g of unit n's P V MFMAs
-        const int u = n & 1;
-#pragma unroll
-        for (int jc = 0; jc < 2 * NC; ++jc) {
-            if (jc < g * 2 * NC / 4 || jc >= (g + 1) * 2 * NC / 4) continue;
-            oacc[u][jc % NC] = MFMA(vf[jc], pf[n][jc / NC], oacc[u][jc % NC]);
-        }
-    };
-    // MASKED: probabilities of keys beyond the last visible one are forced to zero (the diagonal part of the
-    // sequence, or the ragged last tile of an unmasked sequence); the other copy has no test at all.
-    auto exp_group = [&](int n, int g, int k0, auto masked_c) {    // quarter g of unit n's exponentials
-        constexpr bool MASKED = decltype(masked_c)::value;
-        const int kb = n >> 1, u = n & 1;
+    auto element = [&](int n, int e, int k0, bool masked) __attribute__((always_inline)) {
+        const int u = n % U;
+        float p = __builtin_amdgcn_exp2f(fmaf(st[n & 1][e], c2, -m_ref[u]));
         // key of score register r is visible iff 8 (r / 4) + r % 4 <= qrel
-        const int qrel = vis_u(u) + vis_lane - (k0 + 32 * kb);
-#pragma unroll
-        for (int r = 4 * g; r < 4 * g + 4; ++r) {
-            float p = __builtin_amdgcn_exp2f(fmaf(st[n][r], c2, -m_ref[u]));
-            if (MASKED && 8 * (r >> 2) + (r & 3) > qrel) p = 0.f;
-            pr[n & 1][r & 7] = p;           // kept apart from the scores, which sit in accumulation registers
-            l_run[u] += p;
-        }
-        if (g & 1) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) pf[n][g >> 1][e] = (E)pr[n & 1][e];
-        }
+        if (masked && 8 * (e >> 2) + (e & 3) > vis_u(u) + vis_lane - (k0 + 32 * (n / U))) p = 0.f;
+        pr[e] = p;
     };
-    // No branch inside: with two code paths through the MFMAs the compiler merges their accumulator
-    // registers with hundreds of copies per tile.
-    auto tile = [&](int k0, int stage, auto masked_c) {
-        const E *Ks = lds + stage * STAGE + koff, *Vs = lds + stage * STAGE + DmaK::ELEMS + voff;
-        read_k(Ks, 0);
-        read_v(Vs, 0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {                  // slot 0: S(0)
-            s_group(0, g);
-            __builtin_amdgcn_sched_barrier(0);
+    auto finish = [&](int n, int e) __attribute__((always_inline)) {       // into the row's sum and, in pairs, the operand
+        l_run[n % U] += pr[e];
+        if (e & 1) {
+            typedef float f32x2 __attribute__((ext_vector_type(2)));
+            typedef E x2 __attribute__((ext_vector_type(2)));
+            const f32x2 two = {pr[e - 1], pr[e]};
+            pf[n & 1][e >> 3][(e >> 1) & 3] = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, x2));
         }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {                  // slot 1: S(1) | exp(0)
-            s_group(1, g);
-            exp_group(0, g, k0, masked_c);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        wait_tr_reads(vf);                             // issued at the start of the tile, long since returned
-        __builtin_amdgcn_sched_barrier(0);
-        read_k(Ks, 1);                                 // the K operand registers are free again: second key block
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int n = 0; n < 2; ++n) {                  // slots 2, 3: PV(n) then S(n + 2) | exp(n + 1)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                if (g < 2) {
-                    pv_group(n, 2 * g);
-                    pv_group(n, 2 * g + 1);
-                } else {
-                    s_group(n + 2, 2 * (g - 2));
-                    s_group(n + 2, 2 * (g - 2) + 1);
-                }
-                exp_group(n + 1, g, k0, masked_c);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        read_v(Vs, 1);                                 // ... and so are the V^T operand registers
-        __builtin_amdgcn_sched_barrier(0);
-        exp_group(3, 0, k0, masked_c);                 // slot 4: exp(3) | PV(2), the reads' latency under exp first
-        exp_group(3, 1, k0, masked_c);
-        wait_tr_reads(vf);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int g = 2; g < 4; ++g) {
-            pv_group(2, 2 * (g - 2));
-            pv_group(2, 2 * (g - 2) + 1);
-            exp_group(3, g, k0, masked_c);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) pv_group(3, g);    // slot 5: PV(3)
-        // overflow guard: a sum this large means that some score was far above the reference
-        if (__any(!(l_run[0] < kSumLimit) || !(l_run[1] < kSumLimit))) restart_flag[0] = 1;
     };
     // wait for this wavefront's part of the oldest tile in flight (`newer`: a younger one is in flight too),
-    // then a bare s_barrier - a __syncthreads() fence would wait for the younger tile as well.  After it the
-    // tile is published and everyone has finished the tile before it, whose stage the next loads overwrite.
-    auto publish = [&](bool newer) {
-        if (newer)
-            __builtin_amdgcn_s_waitcnt(kWaitOlder);
+    // then a bare s_barrier - a __syncthreads() fence would wait for the younger tile as well.  After it tile t is
+    // published, and everyone's reads before it have returned: tile t + AHEAD may overwrite what they read.
+    auto publish = [&](int t, int stage) __attribute__((always_inline)) {
+        if (t >= ntiles) return;
+        if (t + AHEAD - 1 < ntiles && AHEAD > 1)
+            __builtin_amdgcn_s_waitcnt(wait_loads((AHEAD - 1) * LOADS));
         else
-            __builtin_amdgcn_s_waitcnt(0x0070);
+            __builtin_amdgcn_s_waitcnt(wait_loads(0));
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
+        dma_tile(t + AHEAD, stage + AHEAD >= NSTAGE ? stage + AHEAD - NSTAGE : stage + AHEAD);
+    };
+    // Phase n of tile t, in stage `stage`.  LAST: the wavefront's last tile (masked, no scores of a tile behind it).
+    auto phase = [&](auto n_c, auto last_c, int t, int stage) __attribute__((always_inline)) {
+        constexpr int n = decltype(n_c)::value;
+        constexpr bool LAST = decltype(last_c)::value;
+        constexpr int u2 = U == 1 ? 0 : (n + 1) & 1;                    // sub-block of the units before and behind
+        constexpr bool kScores = !LAST || n + 1 < NU;                   // of the unit behind
+        constexpr bool kNextK = u2 == U - 1 && (!LAST || n + 2 < NU);   // K operands of unit n + 2 to be read
+        constexpr bool kNextV = n % U == 0;                             // V^T operands of unit n to be read
+        constexpr bool kPublish = n == NU - 2;                          // before the first reads of tile t + 1
+        constexpr int kPubAt = NK >= 8 ? 1 : 0;                         // behind this score MFMA: the V^T reads just before it return meanwhile
+        const E *Vs = lds + stage * STAGE + DmaK::ELEMS + voff;
+        const int nstage = stage == NSTAGE - 1 ? 0 : stage + 1;
+        const E *Kn = lds + (n + 2 < NU ? stage : nstage) * STAGE + koff;
+        const int k0 = t * KT;
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            if (i < 2 * NC) {
+                oacc[u2][i % NC] = MFMA(vf[i], __builtin_bit_cast(x8<E>, pf[(n + 1) & 1][i / NC]), oacc[u2][i % NC]);
+                if (kNextV) vf[i] = frag_nat_tr<PV>(Vs, i % NC, 2 * (n / U) + i / NC);
+            } else if (kScores) {
+                const int ks = i - 2 * NC;
+                mfma_scores<E>(kf[ks], qf[u2][ks], st[(n + 1) & 1], ks == 0);
+                if (kPublish && ks == kPubAt) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    publish(t + 1, nstage);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (kNextK) {
+                    constexpr int from = kPublish ? kPubAt : 0;         // reads begin behind this MFMA and end with the last one
+                    if (ks >= from) {
+#pragma unroll
+                        for (int r = (ks - from) * NK / (NK - from); r < (ks - from + 1) * NK / (NK - from); ++r) read_k(Kn, ((n + 2) / U) & 1, r);
+                    }
+                }
+            }
+            if (i >= FIRST) {
+#pragma unroll
+                for (int e = (i - FIRST) * 16 / (NM - FIRST); e < (i - FIRST + 1) * 16 / (NM - FIRST); ++e) {
+                    element(n, e, k0, LAST);
+                    if (e > 0) finish(n, e - 1);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        finish(n, 15);
+        // (K reads issued behind the V^T reads may still be under way)
+        if constexpr (kNextV) wait_tr_reads<kNextK ? NK : 0>(vf);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto tile = [&](auto last_c, int t, int stage) __attribute__((always_inline)) {
+        phase(std::integral_constant<int, 0>{}, last_c, t, stage);
+        phase(std::integral_constant<int, 1>{}, last_c, t, stage);
+        if constexpr (NU == 4) {
+            phase(std::integral_constant<int, 2>{}, last_c, t, stage);
+            phase(std::integral_constant<int, 3>{}, last_c, t, stage);
+        }
     };
 
-    const int kend = causal ? min(sh.s, qb * 256 + 256) : sh.s;      // keys needed by this block: [0, kend)
-    const int kfull = causal ? qb * 256 : sh.s / KT * KT;           // tiles before it are fully visible to every wavefront
+    // This wavefront's tiles before its last one are fully visible to it; the last one is the diagonal one, or the ragged end of the sequence.
+    const int nfull = causal ? min(qw0 / KT, ntiles - 1) : ntiles - 1;
     for (int attempt = 1;; ++attempt) {
         const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u) {
             l_run[u] = 0.f;
 #pragma unroll
             for (int c = 0; c < NC; ++c) oacc[u][c] = zero16;
         }
-        // three LDS stages: tile k0 is multiplied while tiles k0 + KT and k0 + 2 KT are in flight
-        dma_tile(0, 0);
-        if (KT < kend) dma_tile(KT, 1);
-        if (attempt == 1) {                  // uniform over the workgroup: the block below holds a barrier
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) dma_tile(i, i);
+        publish(0, 0);
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) read_k(lds + koff, 0, ks);
+        if (attempt == 1) {
             // First attempt: the scores of each query's first 32 keys fix its softmax reference (key 0 is
             // visible to every query; for the first queries of the sequence these keys are partly masked).
-            publish(KT < kend);
-            read_k(lds + koff, 0);
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                s_group(0, g);
-                s_group(1, g);
-            }
+            for (int u = 0; u < U; ++u) {
+                f32x16 first = MFMA(kf[0], qf[u][0], zero16);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
+                for (int ks = 1; ks < NK; ++ks) first = MFMA(kf[ks], qf[u][ks], first);
                 const int qrel = vis_u(u) + vis_lane;
                 float raw = -INFINITY;
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    if (8 * (r >> 2) + (r & 3) <= qrel) raw = fmaxf(raw, st[u][r]);
+                    if (8 * (r >> 2) + (r & 3) <= qrel) raw = fmaxf(raw, first[r]);
                 m_ref[u] = fmaxf(raw, __shfl_xor(raw, 32, 64)) * c2 + kRefBias;
             }
         }
-        // No early exit on the restart flag: an attempt that is going to be repeated just runs to its end
-        // (rare enough not to matter), which keeps both loops free of side exits - with those the compiler
-        // copies the whole output accumulator at every iteration.
-        int stage = 0, k0 = 0;
-        for (; k0 < kfull; k0 += KT, stage = stage == NSTAGE - 1 ? 0 : stage + 1) {      // fully visible tiles
-            publish(true);
-            dma_tile(k0 + 2 * KT, stage == 0 ? NSTAGE - 1 : stage - 1);
-            tile(k0, stage, std::false_type{});
+        // into the pipeline: unit 0's scores, a product of zeros in place of the unit before it, K operands of unit 1
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) mfma_scores<E>(kf[ks], qf[0][ks], st[0], ks == 0);
+        if constexpr (U == 1) {
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) read_k(lds + koff, 1, ks);
         }
-        for (; k0 < kend; k0 += KT, stage = stage == NSTAGE - 1 ? 0 : stage + 1) {       // the diagonal part
-            publish(k0 + KT < kend);
-            if (k0 + 2 * KT < kend) dma_tile(k0 + 2 * KT, stage == 0 ? NSTAGE - 1 : stage - 1);
-            if (!causal || k0 <= qw0) tile(k0, stage, std::true_type{});
-        }
+#pragma unroll
+        for (int i = 0; i < 2 * NC; ++i) vf[i] = __builtin_bit_cast(x8<E>, u32x4{0, 0, 0, 0});
+        pf[1][0] = pf[1][1] = u32x4{0, 0, 0, 0};
+        int stage = 0, t = 0;
+        for (; t < nfull; ++t, stage = stage == NSTAGE - 1 ? 0 : stage + 1) tile(std::false_type{}, t, stage);
+        tile(std::true_type{}, t, stage);
+#pragma unroll
+        for (int i = 0; i < 2 * NC; ++i)
+            oacc[U - 1][i % NC] = MFMA(vf[i], __builtin_bit_cast(x8<E>, pf[1][i / NC]), oacc[U - 1][i % NC]);
+        // other wavefronts' tiles behind this one's last
+        for (t += 2, stage = (stage + 2) % NSTAGE; t < ntiles; ++t, stage = stage == NSTAGE - 1 ? 0 : stage + 1) publish(t, stage);
+        // overflow guard: a sum this large means that some score was far above the reference (sums only grow, and keep what is not a number)
+        bool over = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) over = over || !(l_run[u] < kSumLimit);
+        if (__any(over)) restart_flag[0] = 1;
         __syncthreads();
         if (!restart_flag[0] || attempt == kMaxAttempts) break;
         // start over with larger references
-        __builtin_amdgcn_s_waitcnt(0x0F70);         // loads of tiles that were still in flight
         __syncthreads();
         if (threadIdx.x == 0) restart_flag[0] = 0;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u) {
             const float l_tot = l_run[u] + __shfl_xor(l_run[u], 32, 64);      // both lanes of a query see the same sum
             float raise = 0.f;                                                // a query whose sum is fine keeps its reference
             if (!(l_tot < 256.f)) raise = l_tot < 3.0e38f ? ceilf(__log2f(l_tot)) - kTargetLog2 : kRefStep;
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
         }
     }
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < U; ++u) {
         const int q = qw0 + 32 * u + lrow;
         const float l_tot = l_run[u] + __shfl_xor(l_run[u], 32, 64);
         if (q < sh.s) {
@@ -386,7 +389,7 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
                     for (int i = 0; i < 4; ++i) o[i] = (E)(oacc[u][c][4 * g + i] * inv);
                     if (c * 32 + 8 * g + 4 * half < dh) *reinterpret_cast<x4<E> *>(orow + c * 32 + 8 * g + 4 * half) = o;
                 }
-            if (half == 0) lse[((size_t)b * sh.heads + h) * sh.s + q] = m_ref[u] * kLn2 + logf(l_tot);
+            if (half == 0) lse[((size_t)b * sh.heads + h) * sh.s + q] = fmaf(m_ref[u], kLn2, logf(l_tot));
         }
     }
 }
@@ -900,7 +903,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(const E *__restric
 // Explicit instantiations: the host compiler does not always emit the launch stub of a kernel template from its
 // use in the launchers below alone.
 #define LGA_INSTANTIATE_KERNELS(DH, OCC, E)                                                                          \
-    template __global__ void attn_fwd_kernel<DH, E>(const E *, E *, float *, AttnShape);                             \
+    template __global__ void attn_fwd_kernel<DH, 1, E>(const E *, E *, float *, AttnShape);                          \
+    template __global__ void attn_fwd_kernel<DH, 2, E>(const E *, E *, float *, AttnShape);                          \
     template __global__ void attn_bwd_dq_kernel<DH, OCC, true, E>(const E *, const E *, const float *, float *, const E *, E *,  \
                                                                   AttnShape);                                        \
     template __global__ void attn_bwd_dq_kernel<DH, OCC, false, E>(const E *, const E *, const float *, float *, const E *, E *, \
@@ -933,8 +937,11 @@ template <int DH> constexpr int occ_dq() { return DH <= 128 ? 2 : 1; }     // wo
 // All three kernels use more dynamic LDS than a launch may ask for by default: raise the limit of every
 // instantiation.  Called once, outside any launch path (see attn_prepare_kernels).
 template <int DH, class E> hipError_t raise_lds_limits() {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_fwd_kernel<DH, E>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_fwd_kernel<DH, 1, E>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem_fwd<DH>());
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_fwd_kernel<DH, 2, E>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, smem_fwd<DH>());
     if (e == hipSuccess)
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_bwd_dq_kernel<DH, occ_dq<DH>(), true, E>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, smem_dq<DH>());
@@ -955,14 +962,30 @@ template <class E> hipError_t raise_lds_limits_all() {
     return e;
 }
 
+// Query sub-blocks per wavefront of the forward kernel, by what the workgroups take on 256 compute units.  One sub-block instead of two makes
+// them half as long, but reads the LDS operands for half the products: 8100 x 16 heads x 128 355 us against 302, 1024 x 384 x 64 107
+// against 103 - and few workgroups leave compute units idle behind the longest: 1024 x 48 x 64 (192 blocks of 256) 18.8 against 25.6,
+// 1000 x 56 x 152 (224) 39 against 45, 128 x 2 x 64 6.0 against 7.8.  With the causal mask a workgroup is half as long as the longest on
+// average.  (Either form adds up a row in the same order: the results are the same.)
+template <int DH> int fwd_subblocks(const AttnShape &sh) {
+    const double one = DH <= 64 ? 0.52 : 0.6;                // of what a workgroup with two takes
+    const double heads = (double)sh.n_seq * sh.heads;
+    auto time = [&](int u, double each) {
+        const double work = heads * ((sh.s + 128 * u - 1) / (128 * u)) / 256.0;
+        return each * std::max(1.0, sh.causal ? 0.5 * work : std::ceil(work));
+    };
+    return time(1, one) < time(2, 1.0) ? 1 : 2;
+}
+
 template <int DH, class E> void fwd_dh(const E *qkv, E *out, float *lse, AttnShape sh, hipStream_t s) {
-    dim3 grid((unsigned)(sh.n_seq * sh.heads) * ((sh.s + 255) / 256));
+    const int U = fwd_subblocks<DH>(sh);
+    dim3 grid((unsigned)(sh.n_seq * sh.heads) * ((sh.s + 128 * U - 1) / (128 * U)));
     char name[64];
     snprintf(name, sizeof(name), "attn_fwd_kernel<%d>", DH);
     const double pairs = (double)sh.n_seq * sh.heads * sh.s * sh.s * (sh.causal ? 0.5 : 1.0);      // visible (query, key) pairs
     const double act = (double)sh.n_seq * sh.s * sh.heads * sh.dh * 2.0;      // bytes of one [tokens, d] bf16 tensor
     ProfScope scope(name, 4.0 * pairs * sh.dh, 4.0 * act, s);
-    hipLaunchKernelGGL((attn_fwd_kernel<DH, E>), grid, dim3(256), smem_fwd<DH>(), s, qkv, out, lse, sh);
+    hipLaunchKernelGGL((U == 1 ? attn_fwd_kernel<DH, 1, E> : attn_fwd_kernel<DH, 2, E>), grid, dim3(256), smem_fwd<DH>(), s, qkv, out, lse, sh);
 }
 template <int DH, class E>
 void bwd_dh(const E *qkv, const E *out, const float *lse, float *delta, const E *dout, E *dqkv, AttnShape sh,
