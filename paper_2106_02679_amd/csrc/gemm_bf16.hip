@@ -9,10 +9,11 @@
 //   weight gradient  dW[in,out] (+)= X[t,in]^T dY[t,out]      K = tokens of the micro-batch group
 // The layer stack runs the first two with BOTH operands k-contiguous (it keeps a transposed 16-bit copy of every weight
 // matrix), the third with both as stored, [k][in] and [k][out], where it is large enough for 256 x 256 tiles, and on transposed
-// copies otherwise.  All of these are served by gemm_bf16_dma_kernel: 256 threads = 4 wavefronts (2x2) on a 256x256x64 tile,
-// v_mfma_f32_16x16x32_bf16, tiles moved global -> LDS without passing through registers.
+// copies otherwise.  All of these are served by gemm_bf16_dma_kernel: 256 threads = 4 wavefronts (2x2) on a 256x256x64 tile - or
+// 256x192, 256x128 where those fill the last round of tiles better -, v_mfma_f32_16x16x32_bf16, tiles moved global -> LDS without passing
+// through registers.
 //
-// Problems with fewer than 128 such tiles go to gemm_small.hip.
+// Most problems with fewer than 128 tiles of 256x256 go to gemm_small.hip.
 //
 // gemm_bf16_kernel is the register-staged predecessor and still serves the other operand layouts of
 // the op-level API and of the GEMM-built attention: both operands sit in LDS k-contiguous
@@ -391,12 +392,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams<E> p, int til
 // to the problems in order, each problem's slices as in a launch of its own.
 template <class E, bool TN> using DmaInput = std::conditional_t<TN, GemmGroup<E>, GemmParams<E>>;
 template <int BM, int BN, int WGM, int WGN, int EPI, class E, bool TN>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<E, TN> in, int tiles_m, int tiles_n) {
+__device__ __forceinline__ void dma_tile_product(const DmaInput<E, TN> &in, int tiles_m, int tiles_n) {
     constexpr int NW = WGM * WGN;                   // wavefronts per workgroup, WGM x WGN over the tile
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int FM = WM / 16, FN = WN / 16;       // 16 x 16 blocks of a wavefront's tile
     constexpr int NIA = BM / (8 * NW), NIB = BN / (8 * NW);     // DMA instructions per wavefront per operand tile
-    static_assert(BM == BN, "the operand ring below uses one slot size for both operands");
+    static_assert(BN <= BM && (!TN || BM == BN), "the operand ring below uses A's slot size for both operands");
     static_assert(BK == 64, "two k steps of 32 per tile");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     E *lds = reinterpret_cast<E *>(smem_raw);
@@ -475,12 +476,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
     // memory address too, so the per-lane offsets have it subtracted.  (A row is at least 128 bytes long here - the
     // launcher sends shorter leading dimensions to the other kernel - so the difference is never negative.)
     // (TN: an instruction fills two rows of 512 bytes, and the launcher sends leading dimensions below 256 elsewhere.)
-    auto dma_row = [&](int i) { return TN ? (wave * NIA + i) * 2 + (lane >> 5) : (wave * NIA + i) * 8 + (lane >> 3); };
-    static_assert(NIA == NIB && NIA % 4 == 0, "row mapping and M0 groups below");
+    auto dma_row = [&](bool is_a, int i) {
+        const int instr = wave * (is_a ? NIA : NIB) + i;
+        return TN ? instr * 2 + (lane >> 5) : instr * 8 + (lane >> 3);
+    };
     int offA[NIA], offB[NIB];
 #pragma unroll
     for (int i = 0; i < NIA; ++i) {
-        const int r = dma_row(i);
+        const int r = dma_row(true, i);
         if constexpr (TN) {
             const int chunk = (lane & 31) ^ ((r & 7) << 1);
             offA[i] = (m0 + chunk * 8 < p.M) ? r * lda2 + chunk * 16 - (i & 3) * 1024 : kBufPoison;
@@ -488,7 +491,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
     }
 #pragma unroll
     for (int i = 0; i < NIB; ++i) {
-        const int r = dma_row(i);
+        const int r = dma_row(false, i);
         if constexpr (TN) {
             const int chunk = (lane & 31) ^ ((r & 7) << 1);
             offB[i] = (n0 + chunk * 8 < p.N) ? r * ldb2 + chunk * 16 - (i & 3) * 1024 : kBufPoison;
@@ -503,8 +506,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
     // One direct-to-LDS load: instruction i of a wavefront's share of an operand tile into ring slot q.  The LDS base
     // is that of the instruction's group of four; the immediate offset (a literal, hence the switch over a value that
     // is a constant wherever this is called) places it inside the group.
-    auto lds_dma = [&](const __amdgpu_buffer_rsrc_t &r, int q, int i, int voff, int soff) {
-        E *group = slot(q) + (wave * NIA + (i & ~3)) * 8 * BK;
+    auto lds_dma = [&](bool is_a, const __amdgpu_buffer_rsrc_t &r, int q, int i, int voff, int soff) {
+        E *group = slot(q) + (wave * (is_a ? NIA : NIB) + (i & ~3)) * 8 * BK;
         switch (i & 3) {
             case 0: __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)group, 16, voff, soff, 0, 0); break;
             case 1: __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)group, 16, voff, soff, 1024, 0); break;
@@ -517,9 +520,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
         const __amdgpu_buffer_rsrc_t r = make_rsrc((is_a ? a_ptr : b_ptr) + kt * (is_a ? a_step : b_step));
         int off = is_a ? offA[i] : offB[i];
         if constexpr (TN) {
-            if (dma_row(i) >= krem) off = kBufPoison;
-        } else if (krem < BK) off |= ((((lane & 7) ^ swz16(dma_row(i))) * 8 < krem) ? 0 : kBufPoison);
-        lds_dma(r, q, i, off, 0);
+            if (dma_row(is_a, i) >= krem) off = kBufPoison;
+        } else if (krem < BK) off |= ((((lane & 7) ^ swz16(dma_row(is_a, i))) * 8 < krem) ? 0 : kBufPoison);
+        lds_dma(is_a, r, q, i, off, 0);
     };
     // MFMA operands of a whole k tile: block f of k step s (32 k each) of A and of B, 128 registers.  A tile is
     // multiplied in two halves of FM/2 A blocks against all FN B blocks, and the two products of a block - k step 0,
@@ -613,11 +616,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
         // (two calls: the host pass of the compiler does not take a conditional expression of the resource type)
         const int vo = is_a ? offA[i] : offB[i];
         if constexpr (TN) {
-            lds_dma(make_rsrc(is_a ? a_run : b_run), q, i, vo, 0);
+            lds_dma(is_a, make_rsrc(is_a ? a_run : b_run), q, i, vo, 0);
             return;
         }
-        if (is_a) lds_dma(rsA, q, i, vo, koff);
-        else lds_dma(rsB, q, i, vo, koff);
+        if (is_a) lds_dma(true, rsA, q, i, vo, koff);
+        else lds_dma(false, rsB, q, i, vo, koff);
     };
     // s_waitcnt immediates (vmcnt in bits 3:0, expcnt 6:4 left at its maximum, lgkmcnt 11:8 = 0): all LDS reads
     // returned and every load landed, or every load but the newest NIA landed.
@@ -675,7 +678,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
     // The order is pinned (sched_barrier): left to itself the compiler clumps the loads, and a wavefront that issues
     // several in a row right after the barrier, together with the three others, finds the load queue full and
     // stalls with its MFMAs behind it.
-    static_assert(NIA == 8 && NIB == 8 && FM == 8 && FN == 8, "one load per column of a half, four A blocks per half");
+    static_assert(NIA == 8 && NIB == FN && FM == 8 && FN >= 4 && FN <= 8, "a load per column of a half or more, four A blocks per half");
     // lean_c: the unrolled main loop's forms of the loads (constant slots; dkt is then the k tile's byte offset)
     auto half = [&](auto lean_c, int h, bool do_dma, bool dma_is_a, int dq, int dkt, int dkrem, bool rd_a, int ga0, bool rd_b,
                     int rqa) __attribute__((always_inline)) {
@@ -696,9 +699,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
             }
             mfma_16x16x32_acc<E>(bf[0][j], af[0][g], acc[g][j]);
             mfma_16x16x32_acc<E>(bf[1][j], af[1][g], acc[g][j]);
-            if ((pr & 3) == 0 && do_dma) {
-                if constexpr (LEAN) dma_c(dma_is_a, dq, dkt, j);
-                else dma_one(dma_is_a, dq, dkt, dkrem, j);
+            // loads evenly over the half, one per column where there are as many
+            const int nload = dma_is_a ? NIA : NIB, li = (pr * nload + 4 * FN - 1) / (4 * FN);
+            if (do_dma && li < nload && li * 4 * FN / nload == pr) {
+                if constexpr (LEAN) dma_c(dma_is_a, dq, dkt, li);
+                else dma_one(dma_is_a, dq, dkt, dkrem, li);
             }
             if (rd_a && j < 4 && ((pr & 3) == 1 || (pr & 3) == 2)) {
                 const int ia = 2 * j + (pr & 3) - 1;                    // 0 .. 7: block ga0 + ia / 2, step ia % 2
@@ -822,11 +827,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
         if (wide) {
             constexpr int SP = WN + 4;                                  // staging pitch in floats
             static_assert(NW * 16 * SP * 4 <= 5 * BM * BK * 2, "staging fits in the operand ring");
+            // A strip of 16 rows is 2 WN pieces of 8 columns, IT for a lane: piece it x 64 + lane, of row piece / PR.  With 128 columns a lane has the
+            // same 8 columns of every row it stores.
+            constexpr int PR = WN / 8, IT = 16 * PR / 64, CS = PR == 16 ? 1 : IT;
+            static_assert(16 * PR % 64 == 0, "whole pieces");
+            auto row_of = [&](int it) { return PR == 16 ? it * 4 + lq : (it * 64 + lane) / PR; };
+            auto col_of = [&](int it) { return PR == 16 ? 8 * l16 : (it * 64 + lane) % PR * 8; };
             // The residual / pre-activation values of the whole wavefront tile are requested first - FM x 4 loads of
             // 16 bytes per lane, into registers the main loop no longer needs - so that their latency is paid once,
             // under the staging of the first strip, and not once per strip.
             constexpr bool kReadsAux = EPI == EPI_BIAS_RESID || EPI == EPI_MUL_DGELU;
-            x8<E> aux8[kReadsAux ? FM : 1][kReadsAux ? 4 : 1];
+            x8<E> aux8[kReadsAux ? FM : 1][kReadsAux ? IT : 1];
             // Tiles that lie inside the matrix take a path of their own: a bounds test per row keeps the loads, arithmetic and stores of
             // different rows apart (d = 768 layer over 32768 tokens: GELU 208 -> 201 us, QKV 130 -> 126, W_o 66 -> 64; not the GELU' product, whose
             // registers a second path moves into scratch memory: 258 -> 289).
@@ -836,8 +847,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
 #pragma unroll
                     for (int i = 0; i < FM; ++i)
 #pragma unroll
-                        for (int it = 0; it < 4; ++it) {
-                            const int m = m0 + wm * WM + i * 16 + it * 4 + lq, n = n0 + wn * WN + 8 * l16;
+                        for (int it = 0; it < IT; ++it) {
+                            const int m = m0 + wm * WM + i * 16 + row_of(it), n = n0 + wn * WN + col_of(it);
                             if (decltype(inside_c)::value || (m < p.M && n < p.N)) aux8[i][it] = *reinterpret_cast<const x8<E> *>(p.aux + (size_t)m * p.ldc + n);
                         }
                 }
@@ -846,12 +857,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
             if (!inside) request_aux(std::false_type{});
             // A lane stores the same 8 columns of every row: their bias values are read once, not once per store (read
             // inside the loop below, each waits out its whole latency between the staging of two strips: 3 us per tile).
-            f32x4 bias_lo = {0.f, 0.f, 0.f, 0.f}, bias_hi = {0.f, 0.f, 0.f, 0.f};
-            if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RESID || EPI == EPI_BIAS_GELU) {
-                const int n = n0 + wn * WN + 8 * l16;
-                if (n < p.N) {
-                    bias_lo = *reinterpret_cast<const f32x4 *>(p.bias + n);
-                    bias_hi = *reinterpret_cast<const f32x4 *>(p.bias + n + 4);
+            f32x4 bias_lo[CS], bias_hi[CS];
+#pragma unroll
+            for (int it = 0; it < CS; ++it) {
+                bias_lo[it] = bias_hi[it] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RESID || EPI == EPI_BIAS_GELU) {
+                    const int n = n0 + wn * WN + col_of(it);
+                    if (n < p.N) {
+                        bias_lo[it] = *reinterpret_cast<const f32x4 *>(p.bias + n);
+                        bias_hi[it] = *reinterpret_cast<const f32x4 *>(p.bias + n + 4);
+                    }
                 }
             }
             __syncthreads();                                            // every wavefront has left the main loop
@@ -877,22 +892,28 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
 #pragma unroll
                 for (int i = 0; i < FM; ++i) {
                     asm volatile("" ::: "memory");
-                    f32x4 lo[4], hi[4];
+                    f32x4 lo[IT], hi[IT];
 #pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        lo[it] = *reinterpret_cast<const f32x4 *>(stage + (it * 4 + lq) * SP + 8 * l16);
-                        hi[it] = *reinterpret_cast<const f32x4 *>(stage + (it * 4 + lq) * SP + 8 * l16 + 4);
+                    for (int it = 0; it < IT; ++it) {
+                        lo[it] = *reinterpret_cast<const f32x4 *>(stage + row_of(it) * SP + col_of(it));
+                        hi[it] = *reinterpret_cast<const f32x4 *>(stage + row_of(it) * SP + col_of(it) + 4);
                     }
                     asm volatile("" ::: "memory");
                     if (i + 1 < FM) stage_strip(i + 1);
-                    asm volatile("" : "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[1]), "+v"(hi[1]), "+v"(lo[2]), "+v"(hi[2]), "+v"(lo[3]), "+v"(hi[3]));
+                    if constexpr (IT == 4)
+                        asm volatile("" : "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[1]), "+v"(hi[1]), "+v"(lo[2]), "+v"(hi[2]), "+v"(lo[3]), "+v"(hi[3]));
+                    else if constexpr (IT == 3)
+                        asm volatile("" : "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[1]), "+v"(hi[1]), "+v"(lo[2]), "+v"(hi[2]));
+                    else
+                        asm volatile("" : "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[IT - 1]), "+v"(hi[IT - 1]));
 #pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        const int m = m0 + wm * WM + i * 16 + it * 4 + lq, n = n0 + wn * WN + 8 * l16;
+                    for (int it = 0; it < IT; ++it) {
+                        const int m = m0 + wm * WM + i * 16 + row_of(it), n = n0 + wn * WN + col_of(it);
                         if (INSIDE || (m < p.M && n < p.N)) {
                             x8<E> o8;
-                            epilogue8<EPI, PRE, E>(p, m, n, lo[it], hi[it], aux8[kReadsAux ? i : 0][kReadsAux ? it : 0], bias_lo, bias_hi, o8);
-                            if (EPI == EPI_MUL_DGELU && p.colsum) {
+                            epilogue8<EPI, PRE, E>(p, m, n, lo[it], hi[it], aux8[kReadsAux ? i : 0][kReadsAux ? it : 0], bias_lo[it % CS],
+                                                  bias_hi[it % CS], o8);
+                            if (EPI == EPI_MUL_DGELU && PR == 16 && p.colsum) {
 #pragma unroll
                                 for (int c = 0; c < (EPI == EPI_MUL_DGELU ? 8 : 1); ++c) cols[c] += (float)o8[c];
                             }
@@ -908,7 +929,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
             };
             if constexpr (EPI != EPI_MUL_DGELU) if (inside) strips_for(std::true_type{});
             if (!inside) strips_for(std::false_type{});
-            if constexpr (EPI == EPI_MUL_DGELU) {
+            if constexpr (EPI == EPI_MUL_DGELU && PR == 16) {
                 static_assert(WM == kGemmSumRows, "a wavefront's rows are a chunk");
                 if (p.colsum && m0 + wm * WM < p.M) {                    // (uniform)
 #pragma unroll
@@ -938,18 +959,36 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<
     }
 }
 
+template <int BM, int BN, int WGM, int WGN, int EPI, class E, bool TN>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<E, TN> in, int tiles_m, int tiles_n) {
+    dma_tile_product<BM, BN, WGM, WGN, EPI, E, TN>(in, tiles_m, tiles_n);
+}
+// The same on tiles of fewer columns (see narrow_tile_width)
+template <int BN, int EPI, class E> __global__ __launch_bounds__(256) void gemm_bf16_narrow_kernel(GemmParams<E> p, int tiles_m, int tiles_n) {
+    dma_tile_product<256, BN, 2, 2, EPI, E, false>(p, tiles_m, tiles_n);
+}
+
 // Explicit instantiations: the host compiler does not always emit the launch stub of a kernel template from its use
 // in the launchers below alone.
 #define LGA_INSTANTIATE_DMA(EPI, TN)                                                                                      \
     template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, bf16, TN>(DmaInput<bf16, TN>, int, int);            \
     template __global__ void gemm_bf16_dma_kernel<256, 256, 2, 2, EPI, f16, TN>(DmaInput<f16, TN>, int, int)
-LGA_INSTANTIATE_DMA(EPI_STORE, false);
-LGA_INSTANTIATE_DMA(EPI_BIAS, false);
-LGA_INSTANTIATE_DMA(EPI_BIAS_RESID, false);
-LGA_INSTANTIATE_DMA(EPI_BIAS_GELU, false);
-LGA_INSTANTIATE_DMA(EPI_MUL_DGELU, false);
+#define LGA_INSTANTIATE_NARROW(BN, EPI)                                                      \
+    template __global__ void gemm_bf16_narrow_kernel<BN, EPI, bf16>(GemmParams<bf16>, int, int); \
+    template __global__ void gemm_bf16_narrow_kernel<BN, EPI, f16>(GemmParams<f16>, int, int)
+#define LGA_INSTANTIATE_WIDTHS(EPI)    \
+    LGA_INSTANTIATE_DMA(EPI, false);   \
+    LGA_INSTANTIATE_NARROW(192, EPI);  \
+    LGA_INSTANTIATE_NARROW(128, EPI)
+LGA_INSTANTIATE_WIDTHS(EPI_STORE);
+LGA_INSTANTIATE_WIDTHS(EPI_BIAS);
+LGA_INSTANTIATE_WIDTHS(EPI_BIAS_RESID);
+LGA_INSTANTIATE_WIDTHS(EPI_BIAS_GELU);
+LGA_INSTANTIATE_WIDTHS(EPI_MUL_DGELU);
 LGA_INSTANTIATE_DMA(EPI_ACCUM_F32, false);
 LGA_INSTANTIATE_DMA(EPI_ACCUM_F32, true);
+#undef LGA_INSTANTIATE_WIDTHS
+#undef LGA_INSTANTIATE_NARROW
 #undef LGA_INSTANTIATE_DMA
 
 // The kernel that serves a (tile size, layout, epilogue) combination and its dynamic LDS in bytes.
@@ -961,7 +1000,8 @@ template <int BM, int BN, bool A_KM, bool B_KM, int EPI, class E, bool DMA = A_K
                                         : (size_t)2 * (BM + BN) * BK * sizeof(E);    // two stages of both operands
     static constexpr bool kGroup = kDma && !A_KM;
     static auto get() -> void (*)(DmaInput<E, kGroup>, int, int) {
-        if constexpr (kDma) return gemm_bf16_dma_kernel<BM, BN, 2, 2, EPI, E, !A_KM>;
+        if constexpr (kDma && BN < BM) return gemm_bf16_narrow_kernel<BN, EPI, E>;
+        else if constexpr (kDma) return gemm_bf16_dma_kernel<BM, BN, 2, 2, EPI, E, !A_KM>;
         else return gemm_bf16_kernel<BM, BN, A_KM, B_KM, EPI, E>;
     }
     // up to 160 KB of dynamic LDS: more than a launch may ask for by default
@@ -1089,6 +1129,40 @@ template <int EPI, class E> int epilogue_tensors(const GemmParams<E> &p) {
     return 1 + (EPI == EPI_BIAS_RESID || EPI == EPI_MUL_DGELU) + (EPI == EPI_BIAS_GELU && p.out2);
 }
 
+// What a product takes in tiles of 256 x width, in us: its rounds of 256 tiles, each k tiles and a prologue and epilogue.  A k tile is the longer the more
+// compute units work - they share memory and the power that sets the clock -: the least below half a round, the most in a full one, and
+// in full rounds of the narrower tiles more with the length of the k range.
+double tiles_time(int width, long M, long N, int K, double epilogue) {
+    struct { double few, all, per_ktile, limit, fixed; } const c = width == 256   ? decltype(c){0.88, 1.25, 0.0, 1.25, 7.0}
+                                                                 : width == 192 ? decltype(c){0.68, 0.95, 0.0010, 1.17, 5.7}
+                                                                                : decltype(c){0.55, 0.66, 0.0007, 0.85, 4.5};
+    const long tiles = (M + 255) / 256 * ((N + width - 1) / width);
+    const double kt = (K + BK - 1) / BK, fixed = c.fixed + epilogue * width / 256, part = (double)(tiles % 256) / 256;
+    double us = 2.0 + (double)(tiles / 256) * (kt * std::min(c.all + c.per_ktile * kt, c.limit) + fixed);
+    if (part > 0.0) us += kt * (c.few + (c.all - c.few) * std::max(0.0, 2.0 * part - 1.0)) + fixed;
+    return us;
+}
+
+// Whether a product runs on tiles of 256 x 192 or 256 x 128 instead (0: no): the large-tile kernel with fewer columns, the same order of every sum.  Where
+// 256 x 256 tiles leave much of their last round empty, narrower ones fill more of it (us, 256 columns / these): 32768 x 768 x 768 45 / 38 with
+// 192, 2000 x 4256 x 4256 71 / 62, 4096 x 2304 x 768 20 / 17.6, 38384 x 280 x 1464 64 / 50 with 128; a full round of theirs takes longer for its
+// work, 32768 x 2048 x 2048 181 / 214.  By the times above, where they promise 3 % and no columns are left to the small kernel (16384 x 1032 x 4096,
+// 8 columns apart, 108 / 120); 128 columns up to two rounds, beyond which operands are read too often (43800 x 576 x 2864 175 / 197).
+// Fewer than 128 tiles of 256 x 256 belong to the small kernel, unless tiles of 128 columns are at least 144 and the k range 704: 6424 x 1024 x 4096
+// (208 of them) 59 / 47, 2000 x 3072 x 3072 (192) 43 / 35, 800 x 5136 x 896 (164) 16 / 13; 2048 x 2048 x 2048 (128) 24.0 / 23.7, 880 x 4168
+// x 4456 (132) 50 / 63, 2080 x 3552 x 576 (252) 13.4 / 13.8.
+// Of 690 products of all epilogues 271 take one of them: 5 % less time on average over all, the worst 3 % more (18256 x 560 x 8120).
+template <int EPI, class E> int narrow_tile_width(const GemmParams<E> &p) {
+    const long rows = (p.M + 255) / 256, big = rows * ((p.N + 255) / 256), narrow = rows * ((p.N + 127) / 128);
+    if (big < 128) return narrow >= 144 && p.K >= 704 ? 128 : 0;
+    const double epilogue = EPI == EPI_MUL_DGELU ? 8.0 : EPI == EPI_BIAS_GELU ? (p.out2 ? 5.0 : 3.0) : EPI == EPI_BIAS_RESID ? 3.0 : EPI == EPI_BIAS ? 0.5 : 0.0;
+    if (peeled_columns(p.M, p.N, p.K, epilogue_tensors<EPI>(p)) > 0) return 0;
+    const double limit = 0.97 * tiles_time(256, p.M, p.N, p.K, epilogue);
+    const double with192 = tiles_time(192, p.M, p.N, p.K, epilogue), with128 = narrow <= 512 ? tiles_time(128, p.M, p.N, p.K, epilogue) : with192;
+    if (std::min(with192, with128) >= limit) return 0;
+    return with128 < with192 ? 128 : 192;
+}
+
 template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmParams<E> &p, hipStream_t s) {
     // Large tiles when they fill the 256 CUs at least about once (the direct-to-LDS kernel is so much faster per
     // tile that a partly idle second round still wins); smaller ones otherwise.
@@ -1112,6 +1186,11 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmPa
             // tile size that pads the output less, the large one on a tie
             const double pad256 = (double)big * 65536.0, pad128 = (double)((p.M + 127) / 128) * ((p.N + 127) / 128) * 16384.0;
             large = big * p.batch >= 128 && pad256 <= 1.15 * pad128;
+        }
+        if constexpr (EPI != EPI_ACCUM_F32) {
+            const int width = p.batch > 1 || p.tri || p.colsum || short_rows ? 0 : narrow_tile_width<EPI, E>(p);
+            if (width == 192) return launch_one<256, 192, A_KM, B_KM, EPI, E>(p, s);
+            if (width == 128) return launch_one<256, 128, A_KM, B_KM, EPI, E>(p, s);
         }
         if (!large || short_rows) return launch_gemm_small<EPI, E>(p, s);
         GemmParams<E> q = p;
@@ -1365,6 +1444,10 @@ template bool launch_gemm_mfma<f16>(const GemmParams<f16> &, bool, bool, Epilogu
 namespace {
 template <bool A_KM, bool B_KM, int EPI, class E> hipError_t raise_pair() {
     hipError_t e = KernelFor<256, 256, A_KM, B_KM, EPI, E>::raise_lds_limit();
+    if constexpr (A_KM && B_KM && EPI != EPI_ACCUM_F32) {
+        if (e == hipSuccess) e = KernelFor<256, 192, A_KM, B_KM, EPI, E>::raise_lds_limit();
+        if (e == hipSuccess) e = KernelFor<256, 128, A_KM, B_KM, EPI, E>::raise_lds_limit();
+    }
     if constexpr (!(A_KM && B_KM))
         if (e == hipSuccess) e = KernelFor<128, 128, A_KM, B_KM, EPI, E>::raise_lds_limit();
     return e;
