@@ -4,8 +4,8 @@
 // What bounds it at the sizes the fp32 mode is used at (widths of 64 ... 512, a few thousand tokens) is not arithmetic
 // but the length of the serial chain over k and the number of compute units that work at all: a weight gradient has
 // 4 ... 64 output tiles and contracts over every token of the step.  So
-//  - a tile is 64 x 64, multiplied by a group of four wavefronts (one 32 x 32 quadrant each), 32 k per step, the next
-//    step's operands on their way from memory to registers while this one is multiplied, one barrier per step;
+//  - a tile is 64 x 64, multiplied by a group of four wavefronts (one 32 x 32 quadrant each) - or 32 x 64, two wavefronts, where the tiles are few -,
+//    32 k per step, the next step's operands on their way from memory while this one is multiplied, one barrier per step;
 //  - a workgroup holds KG = 1, 2 or 4 such groups, each of which takes its own part of the k range; their sums meet in
 //    LDS at the end, in group order (the result does not depend on scheduling), and every group then writes its
 //    share of the tile.  One group alone adds up the same parts in the same order, so that an activation does not depend
@@ -27,7 +27,7 @@ namespace lga {
 
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 32;
+constexpr int TN = 64, TK = 32;
 // LDS tile: [TK][PITCH], k-major.  A pitch of 66 makes all three accesses conflict-free: the operand read (lanes 0-31 one
 // row of k, lanes 32-63 the row 16 further down: 16 * 66 = 32 banks away), the transposing store of a k-contiguous
 // operand (8 k quads x 8 rows: (4 c + i) 66 + r = 8 c + r + 2 i modulo 64) and the 8-byte store of the other layout.
@@ -155,7 +155,7 @@ template <int EPI> __device__ __forceinline__ void epilogue_f32(const GemmParams
 struct Place {
     int m0, n0, kbeg, kstop;
 };
-template <int EPI, class In> __device__ __forceinline__ Place place_of(const In &in, GemmParams<float> &p, bool &vec_out) {
+template <int EPI, int TM, class In> __device__ __forceinline__ Place place_of(const In &in, GemmParams<float> &p, bool &vec_out) {
     if constexpr (std::is_same<In, GemmParams<float>>::value) {
         p = in;
         return Place{(int)blockIdx.y * TM, (int)blockIdx.x * TN, 0, p.K};
@@ -222,9 +222,10 @@ template <int EPI, int KG> struct PartSums {
 };
 
 // The sums of a wavefront's quadrant leave.  Lane: row m = l32 of it, columns n = 8 q + 4 half + (0 .. 3).
-template <int EPI, int KG>
+// W: wavefronts of a group
+template <int EPI, int KG, int W>
 __device__ __forceinline__ void finish_tile(const GemmParams<float> &p, const Place &at, const f32x16 &sum, bool vec_out, float *smem) {
-    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * W)), wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) % W);
     const int lane = threadIdx.x & 63, wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
     const int m = at.m0 + wm * 32 + l32, nq = at.n0 + wn * 32 + 4 * half;
     if constexpr (KG == 1) {
@@ -237,7 +238,7 @@ __device__ __forceinline__ void finish_tile(const GemmParams<float> &p, const Pl
         // g, g + KG, ... of all groups, neighbouring groups first
         f32x4 *red = reinterpret_cast<f32x4 *>(smem);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) red[((group * 4 + wave) * 4 + q) * 64 + lane] = f32x4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
+        for (int q = 0; q < 4; ++q) red[((group * W + wave) * 4 + q) * 64 + lane] = f32x4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
         __syncthreads();
         if (m >= p.M) return;
 #pragma unroll
@@ -246,7 +247,7 @@ __device__ __forceinline__ void finish_tile(const GemmParams<float> &p, const Pl
             if (nq + 8 * q >= p.N) continue;
             f32x4 of[KG];
 #pragma unroll
-            for (int g = 0; g < KG; ++g) of[g] = red[((g * 4 + wave) * 4 + q) * 64 + lane];
+            for (int g = 0; g < KG; ++g) of[g] = red[((g * W + wave) * 4 + q) * 64 + lane];
 #pragma unroll
             for (int i = 0; i < 4; ++i) of[0][i] = KG == 4 ? (of[0][i] + of[1][i]) + (of[2 % KG][i] + of[3 % KG][i]) : of[0][i] + of[1][i];
             epilogue_f32<EPI>(p, m, nq + 8 * q, of[0], vec_out);
@@ -259,7 +260,7 @@ __device__ __forceinline__ void finish_tile(const GemmParams<float> &p, const Pl
 template <int EPI, int KG, class In>
 __global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(In in, bool a_kc, bool b_kc, bool vec_out, int log_parts) {
     GemmParams<float> p;
-    const Place at = place_of<EPI>(in, p, vec_out);
+    const Place at = place_of<EPI, 64>(in, p, vec_out);
     extern __shared__ __attribute__((aligned(16))) float smem_f32[];
     const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(In in, bool a_kc, bo
     }
 
     sums.finish();
-    finish_tile<EPI, KG>(p, at, acc, vec_out, smem_f32);
+    finish_tile<EPI, KG, 4>(p, at, acc, vec_out, smem_f32);
 }
 
 // The same for operands whose rows are whole 16-byte pieces, in the layouts that the stack uses: tiles go from memory to LDS without passing
@@ -318,38 +319,41 @@ __global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(In in, bool a_kc, bo
 // kernel above (50 - 60 TFLOP/s): here it is one wait for loads issued NS - 1 steps ago, and a k-contiguous operand takes one 16-byte LDS
 // read for four matrix instructions.
 // In a step of 32 k, instruction j of quad q multiplies k = 8 q + j (lanes 0 - 31) and 8 q + 4 + j (lanes 32 - 63).
-// LDS, k-contiguous: 64 rows of 128 bytes, 16-byte chunk c of row r at c ^ ((r >> 1) & 7); otherwise: 32 k rows of 256 bytes, chunk c of
-// k row r at c ^ (r & 4 ? 8 : 0): the two halves of a wavefront read different banks.
-template <int EPI, int KG, int NS, bool A_KC, bool B_KC, class In>
-__global__ __launch_bounds__(256 * KG) void gemm_f32_dma_kernel(In in, bool vec_out, int log_parts) {
+// LDS, k-contiguous: rows of 128 bytes, 16-byte chunk c of row r at c ^ ((r >> 1) & 7); otherwise: 32 k rows of 256 bytes (128 for 32 columns), chunk c of
+// k row r of 256 bytes at c ^ (r & 4 ? 8 : 0): the two halves of a wavefront read different banks.
+template <int EPI, int TM, int KG, int NS, bool A_KC, bool B_KC, class In>
+__global__ __launch_bounds__(4 * TM * KG) void gemm_f32_dma_kernel(In in, bool vec_out, int log_parts) {
+    constexpr int W = TM / 16;                                   // wavefronts of a group, a quadrant of 32 x 32 each
     GemmParams<float> p;
-    const Place at = place_of<EPI>(in, p, vec_out);
+    const Place at = place_of<EPI, TM>(in, p, vec_out);
     extern __shared__ __attribute__((aligned(16))) float smem_f32[];
-    constexpr int kOperand = 64 * TK, NL = 4, kNewer = (NS - 2) * NL;      // floats of an operand's tile; loads of a wavefront per step
+    constexpr int kStage = (TM + TN) * TK, NA = TM / 8, NL = (TM + TN) / 8 / W;      // floats of a stage; A's loads; loads of a wavefront per step
+    constexpr int kNewer = (NS - 2) * NL;
     static_assert(kNewer < 64, "vmcnt has six bits");
     constexpr int kWaitOlder = 0x0070 | (kNewer & 15) | (kNewer >> 4 << 14);       // s_waitcnt lgkmcnt(0) vmcnt(kNewer)
-    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * W)), wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) % W);
     const int lane = threadIdx.x & 63, wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
     const int all = (at.kstop - at.kbeg + TK - 1) / TK, part = (all + (1 << log_parts) - 1) >> log_parts, each = (part << log_parts) / KG;
     const int steps = KG == 1 ? all : each;
     const int kg0 = at.kbeg + group * each * TK;
-    float *ring = smem_f32 + group * NS * 2 * kOperand;
+    float *ring = smem_f32 + group * NS * kStage;
 
-    // wavefronts 0, 1 load A, 2, 3 load B; load i fills 1 KB: 8 rows of a k-contiguous operand, 4 k rows of the other layout
-    const bool is_a = wave < 2, kc = is_a ? A_KC : B_KC;
-    const int ld = is_a ? p.lda : p.ldb;
-    const float *base = is_a ? (A_KC ? p.A + (size_t)at.m0 * p.lda : p.A + at.m0) : (B_KC ? p.B + (size_t)at.n0 * p.ldb : p.B + at.n0);
-    const int rows = is_a ? p.M - at.m0 : p.N - at.n0;
+    // load u = wave NL + i fills 1 KB of the stage, A's tile before B's: 8 rows of a k-contiguous operand; of the other layout 4 k rows (64 wide)
+    // or 8 (32 wide)
+    const float *base_a = A_KC ? p.A + (size_t)at.m0 * p.lda : p.A + at.m0, *base_b = B_KC ? p.B + (size_t)at.n0 * p.ldb : p.B + at.n0;
     int off[NL], kloc[NL];                                       // byte offset in the tile; first k of the piece
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-        const int u = (wave & 1) * NL + i;
-        if (kc) {
-            const int r = u * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+        const int u = wave * NL + i;
+        const bool is_a = u < NA;
+        const int v = is_a ? u : u - NA, ld = is_a ? p.lda : p.ldb, rows = is_a ? p.M - at.m0 : p.N - at.n0;
+        if (is_a ? A_KC : B_KC) {
+            const int r = v * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
             kloc[i] = 4 * c;
             off[i] = r < rows ? r * ld * 4 + c * 16 : kBufPoison;
         } else {
-            const int r = u * 4 + (lane >> 4), c = (lane & 15) ^ (r & 4 ? 8 : 0);
+            const int log_row = is_a && TM == 32 ? 3 : 4;        // pieces of a k row
+            const int r = (v << (6 - log_row)) + (lane >> log_row), c = (lane & ((1 << log_row) - 1)) ^ (log_row == 4 && (r & 4) ? 8 : 0);
             kloc[i] = r;
             off[i] = 4 * c < rows ? r * ld * 4 + c * 16 : kBufPoison;
         }
@@ -357,11 +361,17 @@ __global__ __launch_bounds__(256 * KG) void gemm_f32_dma_kernel(In in, bool vec_
     typedef __attribute__((address_space(3))) void *lds_ptr;
     auto load_step = [&](int s) __attribute__((always_inline)) {
         const int k0 = kg0 + s * TK, left = at.kstop - k0;
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(left > 0 ? base + (kc ? (size_t)k0 : (size_t)k0 * ld) : base);
-        float *stage = ring + (s % NS) * 2 * kOperand + (is_a ? 0 : kOperand) + (wave & 1) * NL * 256;
+        float *stage = ring + (s % NS) * kStage + wave * NL * 256;
+        // 64 rows: a wavefront loads one operand, A or B; 32: the first of its loads may be A's, the others B's
+        const float *one = TM == 64 && wave >= 2 ? base_b + (B_KC ? (size_t)k0 : (size_t)k0 * p.ldb) : base_a + (A_KC ? (size_t)k0 : (size_t)k0 * p.lda);
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(left > 0 ? one : base_a);
+        const __amdgpu_buffer_rsrc_t rs_b = make_rsrc(left > 0 ? base_b + (B_KC ? (size_t)k0 : (size_t)k0 * p.ldb) : base_b);
 #pragma unroll
-        for (int i = 0; i < NL; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(stage + i * 256), 16, kloc[i] < left ? off[i] : kBufPoison, 0, 0, 0);
+        for (int i = 0; i < NL; ++i) {
+            const int vo = kloc[i] < left ? off[i] : kBufPoison;
+            if (TM == 64 || wave * NL + i < NA) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(stage + i * 256), 16, vo, 0, 0, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_b, (lds_ptr)(stage + i * 256), 16, vo, 0, 0, 0);
+        }
     };
 
     PartSums<EPI, KG> sums(part);
@@ -380,14 +390,14 @@ __global__ __launch_bounds__(256 * KG) void gemm_f32_dma_kernel(In in, bool vec_
         asm volatile("" ::: "memory");
         if (s + NS - 1 < steps) load_step(s + NS - 1);
         if (kg0 + s * TK >= at.kstop) continue;                  // (a group whose share ends before the others')
-        const float *as = ring + (s % NS) * 2 * kOperand, *bs = as + kOperand;
+        const float *as = ring + (s % NS) * kStage, *bs = as + TM * TK;
         f32x4 av[4], bv[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if constexpr (A_KC) av[q] = *reinterpret_cast<const f32x4 *>(as + ra * TK + (((2 * q + half) ^ ((ra >> 1) & 7)) << 2));
             else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) av[q][j] = as[(8 * q + 4 * half + j) * 64 + (ra ^ (half << 5))];
+                for (int j = 0; j < 4; ++j) av[q][j] = as[(8 * q + 4 * half + j) * TM + (TM == 64 ? ra ^ (half << 5) : ra)];
             }
             if constexpr (B_KC) bv[q] = *reinterpret_cast<const f32x4 *>(bs + rb * TK + (((2 * q + half) ^ ((rb >> 1) & 7)) << 2));
             else {
@@ -403,13 +413,14 @@ __global__ __launch_bounds__(256 * KG) void gemm_f32_dma_kernel(In in, bool vec_
     }
     sums.finish();
     if constexpr (KG > 1) __syncthreads();                       // nobody reads the ring any more
-    finish_tile<EPI, KG>(p, at, acc, vec_out, smem_f32);
+    finish_tile<EPI, KG, W>(p, at, acc, vec_out, smem_f32);
 }
 
 constexpr int smem_bytes(int kg) { return kg * 4 * kTileFloats * (int)sizeof(float); }       // 33.8 KB per group; at least the 16 KB per group of the final sum
 
-constexpr int kDmaStages = 2;
-constexpr int dma_smem(int kg) { return kg * kDmaStages * 2 * 64 * TK * (int)sizeof(float); }       // 32 KB per group
+// Stages of tiles of TM rows: four groups' fill the LDS
+constexpr int dma_stages(int tm) { return tm == 64 ? 2 : 3; }
+constexpr int dma_smem(int tm, int kg) { return kg * dma_stages(tm) * (tm + TN) * TK * (int)sizeof(float); }       // 32 or 36 KB per group
 // The layout that the stack uses with an epilogue
 template <int EPI> constexpr bool kDmaA = EPI != EPI_ACCUM_F32;
 template <int EPI> constexpr bool kDmaB = EPI == EPI_STORE || EPI == EPI_MUL_DGELU;
@@ -427,16 +438,24 @@ template <int EPI> bool dma_takes(const GemmParams<float> &p, bool akc, bool bkc
 // Without: four where that leaves every workgroup a compute unit of its own, else two, whose 64 KB let two workgroups share one
 // (800 x 480 x 512, 104 tiles: 12.1 with four, 12.9 with two, 16.4 us with one; 3200 x 480 x 256, 400 tiles: 16.3, 14.8, 16.0;
 // 12800 x 1536 x 512, 4800 tiles: 211, 197, 222).
+template <int EPI, int TM, class In> void launch_dma_f32(const In &in, dim3 grid, int kg, int log_parts, bool vec_out, hipStream_t s) {
+    constexpr bool A = kDmaA<EPI>, B = kDmaB<EPI>;
+    constexpr int NS = dma_stages(TM);
+    if (kg == 4) hipLaunchKernelGGL((gemm_f32_dma_kernel<EPI, TM, 4, NS, A, B, In>), grid, dim3(16 * TM), dma_smem(TM, 4), s, in, vec_out, log_parts);
+    else if (kg == 2) hipLaunchKernelGGL((gemm_f32_dma_kernel<EPI, TM, 2, NS, A, B, In>), grid, dim3(8 * TM), dma_smem(TM, 2), s, in, vec_out, log_parts);
+    else hipLaunchKernelGGL((gemm_f32_dma_kernel<EPI, TM, 1, NS, A, B, In>), grid, dim3(4 * TM), dma_smem(TM, 1), s, in, vec_out, log_parts);
+}
+// Tiles of 32 rows where they leave every workgroup a compute unit of its own (work32, grid32), three stages instead of two: half the matrix
+// instructions per SIMD and a step more on its way, with the same order of every sum (us): 2048 x 256 x 1024 20.6 -> 13.7, x 256 7.8 -> 5.7,
+// 128 x 512 x 2048 36 -> 23, 256 x 192 x 64 4.7 -> 4.3.  With more of them than compute units the larger tiles' better use of what they load wins:
+// 2048 x 320 x 960 (320) 20 against 25, 8192 x 512 x 2048 142 against 175.
 template <int EPI, class In>
-void launch_tiles_f32(const In &in, dim3 grid, long work, int most, bool akc, bool bkc, bool dma, bool vec_out, hipStream_t s) {
+void launch_tiles_f32(const In &in, dim3 grid, long work, dim3 grid32, long work32, int most, bool akc, bool bkc, bool dma, bool vec_out, hipStream_t s) {
     if (dma) {
         const int kg = std::min(most, work > 256 ? 2 : 4);
         const int log_parts = (EPI == EPI_ACCUM_F32 ? kg : most) >> 1;
-        constexpr bool A = kDmaA<EPI>, B = kDmaB<EPI>;
-        if (kg == 4) hipLaunchKernelGGL((gemm_f32_dma_kernel<EPI, 4, kDmaStages, A, B, In>), grid, dim3(1024), dma_smem(4), s, in, vec_out, log_parts);
-        else if (kg == 2) hipLaunchKernelGGL((gemm_f32_dma_kernel<EPI, 2, kDmaStages, A, B, In>), grid, dim3(512), dma_smem(2), s, in, vec_out, log_parts);
-        else hipLaunchKernelGGL((gemm_f32_dma_kernel<EPI, 1, kDmaStages, A, B, In>), grid, dim3(256), dma_smem(1), s, in, vec_out, log_parts);
-        return;
+        if (work32 <= 256) return launch_dma_f32<EPI, 32>(in, grid32, kg, log_parts, vec_out, s);
+        return launch_dma_f32<EPI, 64>(in, grid, kg, log_parts, vec_out, s);
     }
     const int kg = work >= 512 ? 1 : most;
     const int log_parts = (EPI == EPI_ACCUM_F32 ? kg : most) >> 1;          // a weight gradient's k range differs with the grouping anyway
@@ -446,7 +465,7 @@ void launch_tiles_f32(const In &in, dim3 grid, long work, int most, bool akc, bo
 }
 
 template <int EPI> void launch_epi(const GemmParams<float> &p, bool akc, bool bkc, hipStream_t s) {
-    const int tm = (p.M + TM - 1) / TM, tn = (p.N + TN - 1) / TN;
+    const int tm = (p.M + 63) / 64, tn = (p.N + TN - 1) / TN;
     const long tiles = (long)tm * tn;
     auto al16 = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
     const bool vec_out = (p.ldc & 3) == 0 && (EPI == EPI_ACCUM_F32 ? al16(p.outf) : al16(p.out)) && (EPI != EPI_BIAS_GELU || al16(p.out2)) &&
@@ -456,7 +475,8 @@ template <int EPI> void launch_epi(const GemmParams<float> &p, bool akc, bool bk
     const double mn = (double)p.M * p.N;
     const bool dma = dma_takes<EPI>(p, akc, bkc);
     ProfScope scope(dma ? "gemm_f32_kernel<dma>" : "gemm_f32_kernel", 2.0 * mn * p.K, 4.0 * ((double)p.M * p.K + (double)p.K * p.N + mn), s);
-    launch_tiles_f32<EPI>(p, dim3(tn, tm), tiles, most, akc, bkc, dma, vec_out, s);
+    const int tm32 = (p.M + 31) / 32;
+    launch_tiles_f32<EPI>(p, dim3(tn, tm), tiles, dim3(tn, tm32), (long)tm32 * tn, most, akc, bkc, dma, vec_out, s);
 }
 
 template <int EPI, class In = GemmParams<float>> hipError_t raise_epi() {
@@ -467,9 +487,12 @@ template <int EPI, class In = GemmParams<float>> hipError_t raise_epi() {
     constexpr bool A = kDmaA<EPI>, B = kDmaB<EPI>;
     raise(reinterpret_cast<const void *>(gemm_f32_kernel<EPI, 4, In>), smem_bytes(4));
     raise(reinterpret_cast<const void *>(gemm_f32_kernel<EPI, 2, In>), smem_bytes(2));
-    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 4, kDmaStages, A, B, In>), dma_smem(4));
-    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 2, kDmaStages, A, B, In>), dma_smem(2));
-    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 1, kDmaStages, A, B, In>), dma_smem(1));
+    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 64, 4, dma_stages(64), A, B, In>), dma_smem(64, 4));
+    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 64, 2, dma_stages(64), A, B, In>), dma_smem(64, 2));
+    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 64, 1, dma_stages(64), A, B, In>), dma_smem(64, 1));
+    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 32, 4, dma_stages(32), A, B, In>), dma_smem(32, 4));
+    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 32, 2, dma_stages(32), A, B, In>), dma_smem(32, 2));
+    raise(reinterpret_cast<const void *>(gemm_f32_dma_kernel<EPI, 32, 1, dma_stages(32), A, B, In>), dma_smem(32, 1));
     return e;
 }
 
@@ -503,7 +526,7 @@ int gemm_f32_group_slices(const int *M, const int *N, int n, int K) {
     long tiles = 0;
     double outputs = 0.0;
     for (int i = 0; i < n; ++i) {
-        tiles += (long)((M[i] + TM - 1) / TM) * ((N[i] + TN - 1) / TN);
+        tiles += (long)((M[i] + 63) / 64) * ((N[i] + TN - 1) / TN);
         outputs += (double)M[i] * N[i];
     }
     int best = 1;
@@ -528,12 +551,13 @@ size_t gemm_f32_group_floats(const int *M, const int *N, int n, int slices) {
 void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s) {
     (void)prepare_kernels();
     int M[kGemmGroup], N[kGemmGroup];
-    long tiles = 0;
+    long tiles = 0, tiles32 = 0;
     double flops = 0.0, bytes = 0.0;
     for (int i = 0; i < n; ++i) {
         M[i] = p[i].M;
         N[i] = p[i].N;
-        tiles += (long)((M[i] + TM - 1) / TM) * ((N[i] + TN - 1) / TN);
+        tiles += (long)((M[i] + 63) / 64) * ((N[i] + TN - 1) / TN);
+        tiles32 += (long)((M[i] + 31) / 32) * ((N[i] + TN - 1) / TN);
         flops += 2.0 * M[i] * N[i] * p[i].K;
         bytes += 4.0 * ((double)M[i] * p[i].K + (double)p[i].K * N[i] + (double)M[i] * N[i]);
     }
@@ -565,7 +589,8 @@ void launch_gemm_f32_group(const GemmParams<float> *p, int n, hipStream_t s) {
     for (int i = 0; i < n; ++i) dma = dma && dma_takes<EPI_ACCUM_F32>(p[i], false, false);
     {
         ProfScope scope(dma ? "gemm_f32_kernel<dma> (grouped)" : "gemm_f32_kernel (grouped)", flops, bytes, s);
-        launch_tiles_f32<EPI_ACCUM_F32>(group, grid, tiles * sum.slices, most, false, false, dma, false, s);
+        launch_tiles_f32<EPI_ACCUM_F32>(group, grid, tiles * sum.slices, dim3((unsigned)(tiles32 * sum.slices)), tiles32 * sum.slices, most, false, false, dma,
+                                        false, s);
     }
     if (sum.slices > 1) {
         ProfScope scope("gemm_f32_reduce_kernel", (double)sum.slices * all, 4.0 * all * (sum.slices + (p[0].beta != 0.f ? 2.0 : 1.0)), s);
