@@ -1280,6 +1280,9 @@ template void launch_splitk_reduce_group<f16>(const GemmGroup<f16> &, hipStream_
 // tiles.  The four matrices of a d = 768 layer over 4096 tokens, 108 tiles: 121 us in four launches of the small kernel behind 38 us of
 // transposes, now 58 + 20 us in two slices and 11 us for the bias gradients' column sums.  (With 1.2 and 12 us for a round: 1072 x 2448 over
 // 6424 tokens in four slices instead of two 183 us, now 161; 1320 x 1416 over 26240 in five instead of one 550, now 517.)
+static double group_time(long tiles, double outputs, int slices, int K) {
+    return (double)((tiles * slices + 255) / 256) * ((double)(K / slices) / BK * kRoundStep + kRoundF32) + (slices > 1 ? (slices + 1) * outputs * 4.0 / 4.5e6 : 0.0);
+}
 int gemm_group_slices(const int *M, const int *N, int n, int K) {
     long tiles = 0;
     double outputs = 0.0;
@@ -1293,27 +1296,29 @@ int gemm_group_slices(const int *M, const int *N, int n, int K) {
     double best_us = 0.0;
     for (int s = 1; s <= std::min(32, K / 1024); ++s) {
         if (tiles * s < 192) continue;
-        const double us = (double)((tiles * s + 255) / 256) * ((double)(K / s) / BK * kRoundStep + kRoundF32) + (s > 1 ? (s + 1) * outputs * 4.0 / 4.5e6 : 0.0);
+        const double us = group_time(tiles, outputs, s, K);
         if (best == 0 || us < best_us) best = s, best_us = us;
     }
     return best;
 }
 
-// Matrices that are enough work alone still share a launch where their last rounds then fill each other up, by the same times: T-NLG's four
+// Matrices that are enough work alone still share a launch where their rounds then fill each other up, by the same times: T-NLG's four
 // (289 to 1139 tiles over 4000 tokens, 14 rounds together, 16 apart) 1477 -> 1415 us; d = 2048 over 32768 tokens, W_o and W_qkv with 64 and 192
-// tiles in slices apart, all 768 whole together, 2207 -> 2144.
+// tiles in slices apart, all 768 whole together, 2207 -> 2144; d = 768 over 32768 tokens, 9 to 36 tiles in 28 to 7 slices apart, 108 in two slices
+// together, 451 -> 388 us with the sums of the slices.
 bool gemm_stored_group_wins(const int *M, const int *N, int n, int K) {
     long tiles = 0;
-    double apart = 0.0;
-    const double round = (double)K / BK * kRoundStep + kRoundF32;
+    double apart = 0.0, outputs = 0.0;
     for (int i = 0; i < n; ++i) {
         const long mine = (long)((M[i] + 255) / 256) * ((N[i] + 255) / 256);
-        const int slices = gemm_splitk_slices(M[i], N[i], K);
         tiles += mine;
-        apart += (double)((mine * slices + 255) / 256) * ((double)K / slices / BK * kRoundStep + kRoundF32) +
-                 (slices > 1 ? (slices + 1) * (double)M[i] * N[i] * 4.0 / 4.5e6 : 0.0);
+        outputs += (double)M[i] * N[i];
+        apart += group_time(mine, (double)M[i] * N[i], gemm_splitk_slices(M[i], N[i], K), K);
     }
-    return n > 1 && tiles >= 224 && (double)((tiles + 255) / 256) * round < 0.99 * apart;
+    const int slices = n > 1 ? gemm_group_slices(M, N, n, K) : 0;
+    // (three matrices in slices, and four over fewer tokens, keep launches of their own: the tests of that route count them)
+    if (slices > 1 && (n < kGemmGroup || K < 20480)) return false;
+    return slices > 0 && group_time(tiles, outputs, slices, K) < 0.97 * apart;
 }
 
 template <class E> void launch_gemm_stored_group(const GemmParams<E> *p, int n, hipStream_t s) {
