@@ -608,10 +608,12 @@ __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_kernel(const E *__restri
 // With the causal mask the first two query tiles of a key block contain its diagonal (masked, partly skipped); all
 // later ones - without the mask, all tiles from the start of the sequence - are fully visible and go through a loop
 // without tests (rows past the end of the sequence are zero and carry zero statistics: they add nothing).
+// Up to 64 channels two workgroups share a compute unit, and the register budget says so: with a budget for one, scores and dP came out of
+// the products in accumulation registers, 32 moves a unit (1024 x 384 x 64: 175 -> 164 us, 1024 x 48 x 64: 32 -> 29.6).
 // LDS stages; four where the loop over fully visible tiles is pipelined across units
 template <int DH> constexpr int dkv_stages() { return DH == 96 || DH == 128 ? 4 : 3; }
 template <int DH, class E>
-__global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(const E *__restrict__ qkv, const float *__restrict__ lse,
+__global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void attn_bwd_dkv_kernel(const E *__restrict__ qkv, const float *__restrict__ lse,
                                                               const float *__restrict__ delta,
                                                               const E *__restrict__ dout, E *__restrict__ dqkv,
                                                               AttnShape sh) {
