@@ -70,13 +70,15 @@ __device__ __forceinline__ float sum_over_rows_of_16(float v) {
     const auto halves = __builtin_amdgcn_permlane32_swap(b, b, false, false);
     return __builtin_bit_cast(float, (uint32_t)halves[0]) + __builtin_bit_cast(float, (uint32_t)halves[1]);
 }
-__device__ __forceinline__ float wave_sum(float v) {
+// the sum of a row of 16 lanes, in each of them
+__device__ __forceinline__ float row_of_16_sum(float v) {
     v += dpp_move<0xB1>(v);                 // quad_perm 1 0 3 2
     v += dpp_move<0x4E>(v);                 // quad_perm 2 3 0 1
     v += dpp_move<0x141>(v);                // row_half_mirror: the other quad of eight lanes
     v += dpp_move<0x140>(v);                // row_mirror: the other eight of a row
-    return sum_over_rows_of_16(v);
+    return v;
 }
+__device__ __forceinline__ float wave_sum(float v) { return sum_over_rows_of_16(row_of_16_sum(v)); }
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
