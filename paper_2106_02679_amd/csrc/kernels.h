@@ -120,6 +120,18 @@ template <class E>
 void launch_adam(float *w, float *m, float *v, const float *g, E *w16, size_t n, float lr, float beta1, float beta2,
                  float eps, int step, float grad_mul, const int *skip, hipStream_t s);
 
+// The same for a layer's n parameters, with its 16-bit copies w16 and w16t (each matrix transposed, at its place); matrices in the order of their
+// places, their sizes, what lies between them and every address whole 16-byte pieces of 16-bit elements.  adam_writes_copies: whether it is the
+// faster way to both copies for a layer of these widths and so many parameters.
+bool adam_writes_copies(int d, int f, size_t n);
+struct AdamMatrix {
+    size_t at;
+    int rows, cols;
+};
+template <class E>
+void launch_adam_copies(float *w, float *m, float *v, const float *g, E *w16, E *w16t, const AdamMatrix (&matrices)[4], size_t n, float lr, float beta1,
+                        float beta2, float eps, int step, float grad_mul, const int *skip, hipStream_t s);
+
 // ---- GEMMs -------------------------------------------------------------------------------
 // C[M,N] = sum_k A(m,k) B(k,n), then the epilogue.
 //   a_kmajor: A is stored [M][lda] (k contiguous); otherwise [K][lda] (m contiguous).

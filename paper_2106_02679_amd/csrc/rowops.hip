@@ -801,6 +801,83 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ w, float 
     }
 }
 
+// The same for a whole layer with both of its 16-bit copies, as stored and each matrix transposed: what one kernel wrote a second read back from memory
+// to transpose it (d = 12288: 11.2 + 1.4 ms, now 11.5; d = 2048: 284 + 51 us, now 289; a d = 128 layer's two launches 3.3 + 4.9, now 5.5).  A workgroup has
+// a tile of 64 x 64 or 128 x 128 of a matrix, a thread a block of 4 x 4 at a time, with its sixteen loads of 16 bytes in flight; the
+// transposed tile leaves through LDS in rows of 128 or 256 bytes.  What lies between the matrices goes by 1024 elements.  For rows of whole
+// 128-byte lines in 16 bits: others are written in parts from several workgroups, d = 4256 1617 us where the two kernels take 1339 + 189.  And not for
+// layers of some million parameters, whose copies the transposing pass leaves in the caches for the products that come next: d = 768 40 us
+// against 36 + 8, but then the input gradients 29.4 us against 27.9.
+constexpr size_t kAdamSmall = (size_t)1 << 20, kAdamLarge = (size_t)1 << 24;
+struct AdamRegion {
+    size_t at;             // element in the layer's vector
+    int rows, cols;        // a matrix [rows][cols]; rows = 0: cols elements of no matrix
+};
+constexpr int kAdamRegions = 9;
+template <class E> struct AdamLayer {
+    int first[kAdamRegions];                               // (see ColsumInputs)
+    AdamRegion region[kAdamRegions];
+    float *w, *m, *v;
+    const float *g;
+    E *w16, *w16t;
+};
+
+template <int TILE, class E> __global__ __launch_bounds__(256) void adam_copies_kernel(AdamLayer<E> a, AdamConsts c, const int *__restrict__ skip) {
+    if (skip && *skip) return;          // (the copies then stay those of the weights)
+    int block = blockIdx.x;
+    const AdamRegion t = a.region[matrix_of(a.first, block)];
+    auto update = [&](const f32x4 &w, const f32x4 &m, const f32x4 &v, const f32x4 &g, size_t at) __attribute__((always_inline)) {
+        float wa[4] = {w[0], w[1], w[2], w[3]}, ma[4] = {m[0], m[1], m[2], m[3]}, va[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) adam_one(wa[k], ma[k], va[k], g[k] * c.grad_mul, c);
+        *reinterpret_cast<f32x4 *>(a.w + at) = f32x4{wa[0], wa[1], wa[2], wa[3]};
+        *reinterpret_cast<f32x4 *>(a.m + at) = f32x4{ma[0], ma[1], ma[2], ma[3]};
+        *reinterpret_cast<f32x4 *>(a.v + at) = f32x4{va[0], va[1], va[2], va[3]};
+        x4<E> o;
+        o[0] = (E)wa[0]; o[1] = (E)wa[1]; o[2] = (E)wa[2]; o[3] = (E)wa[3];
+        *reinterpret_cast<x4<E> *>(a.w16 + at) = o;
+        return o;
+    };
+    if (t.rows == 0) {
+        const int i = (block * 256 + threadIdx.x) * 4;
+        if (i >= t.cols) return;
+        const size_t at = t.at + i;
+        update(*reinterpret_cast<const f32x4 *>(a.w + at), *reinterpret_cast<const f32x4 *>(a.m + at), *reinterpret_cast<const f32x4 *>(a.v + at),
+               *reinterpret_cast<const f32x4 *>(a.g + at), at);
+        return;
+    }
+    constexpr int P = TILE + 8;                            // pitch: whole 16-byte pieces
+    __shared__ __attribute__((aligned(16))) E tile[TILE * P];           // [column][row]
+    const int across = (t.cols + TILE - 1) / TILE, r0 = block / across * TILE, c0 = block % across * TILE;
+    const int tx = threadIdx.x % (TILE / 4), ty = threadIdx.x / (TILE / 4), col = c0 + 4 * tx;
+    constexpr int STEP = 4 * 256 / (TILE / 4);             // rows that the threads cover together
+#pragma unroll 1
+    for (int r = 4 * ty; r < TILE; r += STEP) {
+        if (r0 + r >= t.rows || col >= t.cols) continue;   // (multiples of 8, both)
+        const size_t at = t.at + (size_t)(r0 + r) * t.cols + col;
+        f32x4 w[4], m[4], v[4], g[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            w[k] = *reinterpret_cast<const f32x4 *>(a.w + at + (size_t)k * t.cols);
+            m[k] = *reinterpret_cast<const f32x4 *>(a.m + at + (size_t)k * t.cols);
+            v[k] = *reinterpret_cast<const f32x4 *>(a.v + at + (size_t)k * t.cols);
+            g[k] = *reinterpret_cast<const f32x4 *>(a.g + at + (size_t)k * t.cols);
+        }
+        x4<E> o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = update(w[k], m[k], v[k], g[k], at + (size_t)k * t.cols);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<x4<E> *>(tile + (4 * tx + i) * P + r) = x4<E>{o[0][i], o[1][i], o[2][i], o[3][i]};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < TILE * TILE / 8 / 256; ++k) {
+        const int piece = k * 256 + threadIdx.x, cc = piece / (TILE / 8), rr = piece % (TILE / 8) * 8;
+        if (c0 + cc < t.cols && r0 + rr < t.rows)
+            *reinterpret_cast<x8<E> *>(a.w16t + t.at + (size_t)(c0 + cc) * t.rows + r0 + rr) = *reinterpret_cast<const x8<E> *>(tile + cc * P + rr);
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // out[c][r] = in[r][c] for 16-bit elements.  A block moves a 128 x 128 tile: each thread loads one
 // 8x8 block (16-byte row pieces, lanes along the contiguous direction), transposes it in registers,
@@ -1188,10 +1265,7 @@ void add_colsum(ColsumBatch &batch, const float *partial, int rows, int cols, fl
     finish_colsum(&batch, partial, (rows + kColsumRows - 1) / kColsumRows, cols, beta, out0, nullptr, nullptr);
 }
 
-template <class E>
-void launch_adam(float *w, float *m, float *v, const float *g, E *w16, size_t n, float lr, float beta1, float beta2,
-                 float eps, int step, float grad_mul, const int *skip, hipStream_t s) {
-    if (n == 0) return;
+static AdamConsts adam_consts(float lr, float beta1, float beta2, float eps, int step, float grad_mul) {
     AdamConsts c;
     c.beta1 = beta1;
     c.beta2 = beta2;
@@ -1202,6 +1276,13 @@ void launch_adam(float *w, float *m, float *v, const float *g, E *w16, size_t n,
     c.lr = lr;
     c.eps = eps;
     c.grad_mul = grad_mul;
+    return c;
+}
+template <class E>
+void launch_adam(float *w, float *m, float *v, const float *g, E *w16, size_t n, float lr, float beta1, float beta2,
+                 float eps, int step, float grad_mul, const int *skip, hipStream_t s) {
+    if (n == 0) return;
+    const AdamConsts c = adam_consts(lr, beta1, beta2, eps, step, grad_mul);
     ProfScope scope("adam_kernel", 12.0 * n, (w16 ? 30.0 : 28.0) * n, s);
     const bool vec = aligned16(w) && aligned16(m) && aligned16(v) && aligned16(g) &&
                      (reinterpret_cast<uintptr_t>(w16) & 7u) == 0;
@@ -1213,5 +1294,36 @@ template void launch_adam<bf16>(float *, float *, float *, const float *, bf16 *
                                 int, float, const int *, hipStream_t);
 template void launch_adam<f16>(float *, float *, float *, const float *, f16 *, size_t, float, float, float, float, int,
                                float, const int *, hipStream_t);
+
+
+bool adam_writes_copies(int d, int f, size_t n) { return d % 64 == 0 && f % 64 == 0 && (n < kAdamSmall || n >= kAdamLarge); }
+template <class E>
+void launch_adam_copies(float *w, float *m, float *v, const float *g, E *w16, E *w16t, const AdamMatrix (&matrices)[4], size_t n, float lr, float beta1,
+                        float beta2, float eps, int step, float grad_mul, const int *skip, hipStream_t s) {
+    AdamLayer<E> a{};
+    a.w = w; a.m = m; a.v = v; a.g = g; a.w16 = w16; a.w16t = w16t;
+    const int tile = n >= kAdamLarge ? 128 : 64;           // (a d = 2048 layer 289 and 301 us, a d = 128 layer 12.2 and 5.5)
+    int regions = 0, blocks = 0;
+    size_t at = 0;
+    auto add = [&](size_t from, int rows, int cols) {
+        a.first[regions] = blocks;
+        a.region[regions++] = {from, rows, cols};
+        blocks += rows > 0 ? ((rows + tile - 1) / tile) * ((cols + tile - 1) / tile) : (cols + 1023) / 1024;
+    };
+    for (const AdamMatrix &t : matrices) {
+        if (t.at > at) add(at, 0, (int)(t.at - at));
+        add(t.at, t.rows, t.cols);
+        at = t.at + (size_t)t.rows * t.cols;
+    }
+    if (n > at) add(at, 0, (int)(n - at));
+    for (int i = regions; i < kAdamRegions; ++i) a.first[i] = INT_MAX;
+    ProfScope scope("adam_kernel", 12.0 * n, 32.0 * n, s);
+    const auto kernel = tile == 64 ? adam_copies_kernel<64, E> : adam_copies_kernel<128, E>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, adam_consts(lr, beta1, beta2, eps, step, grad_mul), skip);
+}
+template void launch_adam_copies<bf16>(float *, float *, float *, const float *, bf16 *, bf16 *, const AdamMatrix (&)[4], size_t, float, float, float, float,
+                                       int, float, const int *, hipStream_t);
+template void launch_adam_copies<f16>(float *, float *, float *, const float *, f16 *, f16 *, const AdamMatrix (&)[4], size_t, float, float, float, float, int,
+                                      float, const int *, hipStream_t);
 
 }  // namespace lga

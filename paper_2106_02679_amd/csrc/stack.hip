@@ -788,13 +788,22 @@ void adam_layer(lga_stack *st, int l, const lga_adam &hp, bool async = false) {
         launch_fill_const(reinterpret_cast<float *>(flag), 1, 0.f, s);        // all bits zero
         launch_nonfinite_flag(st->grad(l), st->P, flag, s);
     }
-    if (st->cfg.dtype == LGA_FP16)
-        launch_adam<f16>(st->w(l), st->m(l), st->v(l), st->grad(l), copies ? st->w16<f16>(l) : nullptr, st->P, hp.lr,
-                         hp.beta1, hp.beta2, hp.eps, hp.step, grad_mul, flag, s);
-    else
-        launch_adam<bf16>(st->w(l), st->m(l), st->v(l), st->grad(l), copies ? st->w16<bf16>(l) : nullptr, st->P, hp.lr,
-                          hp.beta1, hp.beta2, hp.eps, hp.step, grad_mul, flag, s);
-    if (copies) refresh_transposed_weights(st, l, s);
+    const int d = st->cfg.d_model, f = st->cfg.d_ff;
+    const LayerLayout &o = st->lay;
+    const AdamMatrix matrices[4] = {{o.w_qkv, d, 3 * d}, {o.w_o, d, d}, {o.w_1, d, f}, {o.w_2, f, d}};
+    auto update = [&](auto *of_type) {
+        typedef std::remove_pointer_t<decltype(of_type)> E;
+        if (copies && adam_writes_copies(d, f, st->P)) {
+            launch_adam_copies<E>(st->w(l), st->m(l), st->v(l), st->grad(l), st->w16<E>(l), st->w16t<E>(l), matrices, st->P, hp.lr, hp.beta1, hp.beta2,
+                                  hp.eps, hp.step, grad_mul, flag, s);
+            return;
+        }
+        launch_adam<E>(st->w(l), st->m(l), st->v(l), st->grad(l), copies ? st->w16<E>(l) : nullptr, st->P, hp.lr, hp.beta1, hp.beta2, hp.eps, hp.step,
+                       grad_mul, flag, s);
+        if (copies) refresh_transposed_weights(st, l, s);
+    };
+    if (st->cfg.dtype == LGA_FP16) update((f16 *)nullptr);
+    else update((bf16 *)nullptr);
     if (async) {
         (void)hipEventRecord(st->ev_grad[st->grad_slot(l)], st->aux);
         st->grad_pending[st->grad_slot(l)] = 1;
