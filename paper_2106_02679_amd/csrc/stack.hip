@@ -1079,8 +1079,10 @@ int lga_traffic_model(const lga_config *cfg, int32_t order, uint64_t *param_byte
     const uint64_t wsz = is16 ? 2 : 4;
     // Adam: read w, m, v (12 B), write w, m, v (12 B) and the 16-bit copy; per group the GEMM families
     // read the matrices: forward all four, recompute all but W_2, input gradient all four.
-    // the 16-bit modes also write the 16-bit copy (2 B) and re-reads / writes the matrices once for the transposed copy
+    // the 16-bit modes also write the 16-bit copy (2 B) and re-reads / writes the matrices once for the transposed copy; where Adam
+    // writes both copies itself, nothing is read again
     const uint64_t copies = is16 ? 2 * P + 4 * Pm : 0;
+    const uint64_t updated = copies - (is16 && adam_writes_copies(cfg->d_model, cfg->d_ff, P) ? 2 * Pm : 0);
     const uint64_t per_group_param = wsz * (3 * Pm - df);
     // Restores of a steady-state step (param_buffers < n_layers): a layer's masters are cast again (read 4 B, write
     // 2 B per parameter, plus the transposed copy) whenever another layer has used its buffer since.  Counted by
@@ -1105,7 +1107,7 @@ int lga_traffic_model(const lga_config *cfg, int32_t order, uint64_t *param_byte
         if (order == LGA_ORDER_MICROBATCH_MAJOR) adam_copies = nbuf;
     }
     if (param_bytes)
-        *param_bytes = L * (24 * P + groups * per_group_param) + adam_copies * copies + restores * (4 * P + copies);
+        *param_bytes = L * (24 * P + groups * per_group_param) + adam_copies * updated + restores * (4 * P + copies);
     // gradient buffer: the first pass over it writes (4 B), later ones read-modify-write (8 B); Adam reads
     // (4 B).  Vectors take one pass per group; matrices one per weight-gradient GEMM, which in the layered
     // 16-bit path covers wgrad_groups groups.

@@ -329,3 +329,12 @@ def test_a_weight_gradient_over_no_tokens_is_not_divided_into_slices():
     res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
     assert res.returncode == 0, res.returncode
     assert res.stdout.split() == [str(B.LGA_ERR_HIP)] * 4
+
+
+@pytest.mark.parametrize("d,read_again", [(128, 0), (768, 2), (2048, 0), (4256, 2)])
+def test_traffic_model_counts_no_second_read_where_adam_writes_both_copies(d, read_again):
+    """Per parameter of a layer: Adam 24 B, its 16-bit copy 2, and per matrix element 2 B of the transposed copy, which a second kernel reads back at some widths."""
+    kw = dict(n_layers=1, d_model=d, n_heads=d // 8, d_ff=4 * d, seq_len=128, micro_batch=1, n_micro=1, group=1)
+    P, Pm = 12 * d * d + 13 * d, 12 * d * d
+    got = B.traffic_model(cfg(dtype=B.LGA_BF16, **kw), B.LGA_ORDER_LAYERED)[0]
+    assert got == 26 * P + (2 + read_again) * Pm + 2 * (3 * Pm - 4 * d * d)
