@@ -1275,14 +1275,15 @@ template void prepare_gemm_group<f16>(GemmGroup<f16> &, const GemmParams<f16> *,
 template void launch_splitk_reduce_group<bf16>(const GemmGroup<bf16> &, hipStream_t);
 template void launch_splitk_reduce_group<f16>(const GemmGroup<f16> &, hipStream_t);
 
-// Slices of the k range for n weight gradients in one launch of the large-tile kernel, by what a round of 256 workgroups takes (above) and the way
-// of the partial results through memory (4.5 TB/s); 0 where that leaves more than a quarter of the chip idle or a workgroup fewer than 16 k
-// tiles.  The four matrices of a d = 768 layer over 4096 tokens, 108 tiles: 121 us in four launches of the small kernel behind 38 us of
-// transposes, now 58 + 20 us in two slices and 11 us for the bias gradients' column sums.  (With 1.2 and 12 us for a round: 1072 x 2448 over
-// 6424 tokens in four slices instead of two 183 us, now 161; 1320 x 1416 over 26240 in five instead of one 550, now 517.)
+// What weight gradients take in one launch of the large-tile kernel, in us: by what a round of 256 workgroups takes (above) and the way of the slices'
+// partial results through memory (4.5 TB/s)
 static double group_time(long tiles, double outputs, int slices, int K) {
     return (double)((tiles * slices + 255) / 256) * ((double)(K / slices) / BK * kRoundStep + kRoundF32) + (slices > 1 ? (slices + 1) * outputs * 4.0 / 4.5e6 : 0.0);
 }
+// Slices of the k range for n weight gradients in one launch, by these times; 0 where that leaves more than a quarter of the chip idle or a workgroup fewer than 16 k
+// tiles.  The four matrices of a d = 768 layer over 4096 tokens, 108 tiles: 121 us in four launches of the small kernel behind 38 us of
+// transposes, now 58 + 20 us in two slices and 11 us for the bias gradients' column sums.  (With 1.2 and 12 us for a round: 1072 x 2448 over
+// 6424 tokens in four slices instead of two 183 us, now 161; 1320 x 1416 over 26240 in five instead of one 550, now 517.)
 int gemm_group_slices(const int *M, const int *N, int n, int K) {
     long tiles = 0;
     double outputs = 0.0;
@@ -1302,10 +1303,12 @@ int gemm_group_slices(const int *M, const int *N, int n, int K) {
     return best;
 }
 
-// Matrices that are enough work alone still share a launch where their rounds then fill each other up, by the same times: T-NLG's four
-// (289 to 1139 tiles over 4000 tokens, 14 rounds together, 16 apart) 1477 -> 1415 us; d = 2048 over 32768 tokens, W_o and W_qkv with 64 and 192
-// tiles in slices apart, all 768 whole together, 2207 -> 2144; d = 768 over 32768 tokens, 9 to 36 tiles in 28 to 7 slices apart, 108 in two slices
-// together, 451 -> 388 us with the sums of the slices.
+// Matrices that are enough work alone still share a launch where their rounds then fill each other up, by the same times.  Whole, over any k range, from 224
+// tiles on: T-NLG's four (289 to 1139 tiles over 4000 tokens, 14 rounds together, 16 apart) 1477 -> 1415 us; d = 2048 over 32768 tokens, W_o and
+// W_qkv with 64 and 192 tiles in slices apart, all 768 together, 2207 -> 2144; d = 1664 over 512, three of 140 to 182 tiles, 78 -> 52; d = 3072 over
+// 768 269 -> 210.  In slices where that promises 3 %: d = 768, over 8192 tokens three of 27 to 36 tiles 175 -> 110, over 16384 all 108 289 -> 191,
+// over 32768 451 -> 388; d = 384 over 11056, three in ten slices, 92 -> 52; d = 1280 over 8704 415 -> 342.  Of 23 layers of widths 256 to 3072 over
+// 512 to 34360 tokens (times with the sums of the slices) all take 10 to 47 % less.
 bool gemm_stored_group_wins(const int *M, const int *N, int n, int K) {
     long tiles = 0;
     double apart = 0.0, outputs = 0.0;
@@ -1315,9 +1318,9 @@ bool gemm_stored_group_wins(const int *M, const int *N, int n, int K) {
         outputs += (double)M[i] * N[i];
         apart += group_time(mine, (double)M[i] * N[i], gemm_splitk_slices(M[i], N[i], K), K);
     }
-    const int slices = n > 1 ? gemm_group_slices(M, N, n, K) : 0;
-    // (three matrices in slices, and four over fewer tokens, keep launches of their own: the tests of that route count them)
-    if (slices > 1 && (n < kGemmGroup || K < 20480)) return false;
+    if (n < 2) return false;
+    if (tiles >= 224 && group_time(tiles, outputs, 1, K) < 0.99 * apart) return true;
+    const int slices = gemm_group_slices(M, N, n, K);
     return slices > 0 && group_time(tiles, outputs, slices, K) < 0.97 * apart;
 }
 

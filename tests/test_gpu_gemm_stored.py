@@ -42,24 +42,33 @@ def test_stack_whose_weight_gradients_take_stored_operands(overlap):
             assert rel_err(got["grads"][l], runs[0]["grads"][l]) < 1e-5
 
 
-def test_narrow_stack_whose_weight_gradients_take_stored_operands_in_slices():
-    """The few output tiles of a narrow layer, their k range in slices: W_1 and W_2 of a 768-wide layer over 8200 tokens in 7 of 1216
-    tokens (the last 904, no whole number of steps), W_qkv in 8 of 1088 (584); over 16400 tokens in 7 of 2368 (2192) and others.
+@pytest.mark.parametrize("d,heads,ff,expected", [
+    # launches of one matrix's slices, of several matrices' slices, and sums of slices: two groups in turn, merged, one group of both, micro-batches in turn.
+    # Three matrices of either 8200 tokens in two slices of 4160 (the last 4040) in one launch, W_o on small tiles from transposed copies (over 16400 in
+    # slices of large tiles); all four over 16400 in two of 8256 (8144)
+    (768, 12, 3072, [(0, 2, 2), (0, 1, 2), (0, 1, 1), (0, 2, 2)]),
+    # ragged tiles: three in slices of 2752 (2696) and, over 16400, four of 5504 (5392)
+    (776, 97, 3080, [(0, 2, 2), (0, 1, 2), (0, 1, 1), (0, 2, 2)]),
+    # W_qkv alone in 8 of 1088 (584), the other three in one launch
+    (768, 12, 768, [(2, 2, 4), (1, 1, 2), (0, 1, 1), (2, 2, 4)]),
+    # W_qkv alone in 6 of 1408 (1160) on ragged tiles, the others on transposed copies (merged, W_o in slices of large tiles and W_1, W_2 of small ones);
+    # over 16400 W_o and W_qkv in four of 4160 (3920)
+    (776, 97, 128, [(2, 0, 2), (1, 0, 3), (0, 1, 2), (2, 0, 2)])])
+def test_narrow_stack_whose_weight_gradients_take_stored_operands_in_slices(d, heads, ff, expected):
+    """The few output tiles of a narrow layer, their k range in slices, the last of them no whole number of steps.
     The slices cut the tokens elsewhere in every grouping, so that a token left out or taken twice would show."""
-    w = S.Workload("stored_slices_bf16", 1, 768, 12, 3072, 1025, 8, 2, "bf16")
+    w = S.Workload("stored_slices_bf16", 1, d, heads, ff, 1025, 8, 2, "bf16")
     x, G, params = S.make_inputs(w, seed=4)
     runs = []
 
     def step(**kw):
         kernels = profiled(lambda: runs.append(run_gpu_step(w, x, G, params, retain=1, **kw)))
-        sliced = [k["launches"] for n, k in kernels.items() if n.startswith("gemm_bf16_dma_tn_kernel")]
-        return sum(sliced), kernels["splitk_reduce_kernel"]["launches"] if "splitk_reduce_kernel" in kernels else 0
+        sliced = {n: k["launches"] for n, k in kernels.items() if n.startswith("gemm_bf16_dma_tn_kernel")}
+        together = sum(k for n, k in sliced.items() if n.endswith("(grouped)"))
+        return sum(sliced.values()) - together, together, kernels["splitk_reduce_kernel"]["launches"] if "splitk_reduce_kernel" in kernels else 0
 
-    assert step(wgrad_groups=1) == (6, 6)                    # three matrices of either group; W_o on small tiles from transposed copies
-    assert step(wgrad_groups=2) == (3, 4)                    # both groups in one: W_o still transposed, but in slices of large tiles
-    assert step(group=2) == (4, 4)                           # one group of 16400 tokens: all four
-    assert step(order="mbmajor") == (6, 6)
-    exact = run_gpu_step(S.Workload("stored_slices_fp32", 1, 768, 12, 3072, 1025, 8, 2, "fp32"), x, G, params, retain=1)
+    assert [step(wgrad_groups=1), step(wgrad_groups=2), step(group=2), step(order="mbmajor")] == expected
+    exact = run_gpu_step(S.Workload("stored_slices_fp32", 1, d, heads, ff, 1025, 8, 2, "fp32"), x, G, params, retain=1)
     for got in runs[1:]:
         assert np.array_equal(got["dx"], runs[0]["dx"]) and np.array_equal(got["boundaries"], runs[0]["boundaries"])
         assert rel_err(got["grads"][0], runs[0]["grads"][0]) < 1e-5
