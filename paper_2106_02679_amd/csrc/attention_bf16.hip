@@ -163,8 +163,9 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
     // output accumulators are never rescaled - they live in accumulation registers that only MFMAs touch.
     // A probability far above 1 must still fit the format P is rounded to for the second product - bf16 reaches
     // as far as fp32, IEEE half ends at 65504 - and a probability is never larger than its row's running sum.  So a
-    // lane whose sum reaches kSumLimit makes the whole workgroup start over, each query with its reference raised
-    // by what its own sum asks for (to a sum of about 2^kTargetLog2), or by kRefStep if the sum overflowed fp32.
+    // lane whose sum reaches kSumLimit makes the whole workgroup start over, with its query's reference raised
+    // by what its sum asks for (to a sum of about 2^kTargetLog2), or by kRefStep if the sum overflowed fp32.  The
+    // other queries keep theirs, and come to the same sums again: a result does not depend on which queries share a workgroup.
     // On ordinary activations bf16 never restarts; half precision does when the keys beyond the first 32 score
     // some 15 (log2 units) higher, which wide layers do reach.  The number of attempts is bounded, so that scores
     // that are infinite or not numbers end in a non-finite output instead of an endless loop.
@@ -367,10 +368,8 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_kernel(const E *__restrict__ 
         if (threadIdx.x == 0) restart_flag[0] = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const float l_tot = l_run[u] + __shfl_xor(l_run[u], 32, 64);      // both lanes of a query see the same sum
-            float raise = 0.f;                                                // a query whose sum is fine keeps its reference
-            if (!(l_tot < 256.f)) raise = l_tot < 3.0e38f ? ceilf(__log2f(l_tot)) - kTargetLog2 : kRefStep;
-            m_ref[u] += raise;
+            const float other = __shfl_xor(l_run[u], 32, 64), l_tot = l_run[u] + other;      // both lanes of a query see the same sums
+            if (!(l_run[u] < kSumLimit) || !(other < kSumLimit)) m_ref[u] += l_tot < 3.0e38f ? ceilf(__log2f(l_tot)) - kTargetLog2 : kRefStep;
         }
     }
 #pragma unroll
@@ -968,7 +967,7 @@ template <class E> hipError_t raise_lds_limits_all() {
 // them half as long, but reads the LDS operands for half the products: 8100 x 16 heads x 128 355 us against 302, 1024 x 384 x 64 107
 // against 103 - and few workgroups leave compute units idle behind the longest: 1024 x 48 x 64 (192 blocks of 256) 18.8 against 25.6,
 // 1000 x 56 x 152 (224) 39 against 45, 128 x 2 x 64 6.0 against 7.8.  With the causal mask a workgroup is half as long as the longest on
-// average.  (Either form adds up a row in the same order: the results are the same.)
+// average.  (Either form adds up a row in the same order and starts over with the same references: the results are the same.)
 template <int DH> int fwd_subblocks(const AttnShape &sh) {
     const double one = DH <= 64 ? 0.52 : 0.6;                // of what a workgroup with two takes
     const double heads = (double)sh.n_seq * sh.heads;
@@ -983,7 +982,7 @@ template <int DH, class E> void fwd_dh(const E *qkv, E *out, float *lse, AttnSha
     const int U = fwd_subblocks<DH>(sh);
     dim3 grid((unsigned)(sh.n_seq * sh.heads) * ((sh.s + 128 * U - 1) / (128 * U)));
     char name[64];
-    snprintf(name, sizeof(name), "attn_fwd_kernel<%d>", DH);
+    snprintf(name, sizeof(name), "attn_fwd_kernel<%d, %d>", DH, U);
     const double pairs = (double)sh.n_seq * sh.heads * sh.s * sh.s * (sh.causal ? 0.5 : 1.0);      // visible (query, key) pairs
     const double act = (double)sh.n_seq * sh.s * sh.heads * sh.dh * 2.0;      // bytes of one [tokens, d] bf16 tensor
     ProfScope scope(name, 4.0 * pairs * sh.dh, 4.0 * act, s);
