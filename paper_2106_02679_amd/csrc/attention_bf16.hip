@@ -963,23 +963,8 @@ template <class E> hipError_t raise_lds_limits_all() {
     return e;
 }
 
-// Query sub-blocks per wavefront of the forward kernel, by what the workgroups take on 256 compute units.  One sub-block instead of two makes
-// them half as long, but reads the LDS operands for half the products: 8100 x 16 heads x 128 355 us against 302, 1024 x 384 x 64 107
-// against 103 - and few workgroups leave compute units idle behind the longest: 1024 x 48 x 64 (192 blocks of 256) 18.8 against 25.6,
-// 1000 x 56 x 152 (224) 39 against 45, 128 x 2 x 64 6.0 against 7.8.  With the causal mask a workgroup is half as long as the longest on
-// average.  (Either form adds up a row in the same order and starts over with the same references: the results are the same.)
-template <int DH> int fwd_subblocks(const AttnShape &sh) {
-    const double one = DH <= 64 ? 0.52 : 0.6;                // of what a workgroup with two takes
-    const double heads = (double)sh.n_seq * sh.heads;
-    auto time = [&](int u, double each) {
-        const double work = heads * ((sh.s + 128 * u - 1) / (128 * u)) / 256.0;
-        return each * std::max(1.0, sh.causal ? 0.5 * work : std::ceil(work));
-    };
-    return time(1, one) < time(2, 1.0) ? 1 : 2;
-}
-
 template <int DH, class E> void fwd_dh(const E *qkv, E *out, float *lse, AttnShape sh, hipStream_t s) {
-    const int U = fwd_subblocks<DH>(sh);
+    const int U = attn_fwd_subblocks(sh);
     dim3 grid((unsigned)(sh.n_seq * sh.heads) * ((sh.s + 128 * U - 1) / (128 * U)));
     char name[64];
     snprintf(name, sizeof(name), "attn_fwd_kernel<%d, %d>", DH, U);
@@ -1009,6 +994,23 @@ void bwd_dh(const E *qkv, const E *out, const float *lse, float *delta, const E 
 }
 
 }  // namespace
+
+// Query sub-blocks per wavefront of the forward kernel, by what the workgroups take on 256 compute units.  One sub-block instead of two makes
+// them half as long, but reads the LDS operands for half the products: 8100 x 16 heads x 128 355 us against 302, 1024 x 384 x 64 107
+// against 103 - and few workgroups leave compute units idle behind the longest: 1024 x 48 x 64 (192 blocks of 256) 18.8 against 25.6,
+// 1000 x 56 x 152 (224) 39 against 45, 128 x 2 x 64 6.0 against 7.8.  With the causal mask a workgroup is half as long as the longest on
+// average.  (Either form adds up a row in the same order and starts over with the same references: the results are the same.)
+// Never more of the short workgroups than a launch holds, 2^32 work items, beyond which it runs a part of them and reports nothing.
+int attn_fwd_subblocks(const AttnShape &sh) {
+    const double one = sh.dh <= 64 ? 0.52 : 0.6;             // of what a workgroup with two takes
+    const double heads = (double)sh.n_seq * sh.heads;
+    if (heads * ((sh.s + 127) / 128) * 256.0 >= 4294967296.0) return 2;
+    auto time = [&](int u, double each) {
+        const double work = heads * ((sh.s + 128 * u - 1) / (128 * u)) / 256.0;
+        return each * std::max(1.0, sh.causal ? 0.5 * work : std::ceil(work));
+    };
+    return time(1, one) < time(2, 1.0) ? 1 : 2;
+}
 
 // Head sizes 32, 64, 96, 128, 160 have kernels; any other multiple of 8 up to 160 runs in the next larger one with
 // its extra columns read as zeros and not written.

@@ -187,6 +187,7 @@ bool gemm_takes_stored_operands(int M, int N, int K);
 struct AttnShape {
     int n_seq, s, heads, dh, causal;
 };
+int attn_fwd_subblocks(const AttnShape &sh);     // of 32 queries, per wavefront of the fused forward kernel: 1 or 2
 template <class T> void launch_attn_fwd_simple(const T *qkv, T *out, float *lse, AttnShape sh, hipStream_t s);
 // dqkv: [tokens, 3 d]; delta: scratch [n_seq, heads, s] (row sums of dout * out).
 template <class T>
