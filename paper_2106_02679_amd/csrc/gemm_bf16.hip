@@ -963,7 +963,7 @@ template <int BM, int BN, int WGM, int WGN, int EPI, class E, bool TN>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(DmaInput<E, TN> in, int tiles_m, int tiles_n) {
     dma_tile_product<BM, BN, WGM, WGN, EPI, E, TN>(in, tiles_m, tiles_n);
 }
-// The same on tiles of fewer columns (see narrow_tile_width)
+// The same on tiles of fewer columns (see gemm_narrow_width)
 template <int BN, int EPI, class E> __global__ __launch_bounds__(256) void gemm_bf16_narrow_kernel(GemmParams<E> p, int tiles_m, int tiles_n) {
     dma_tile_product<256, BN, 2, 2, EPI, E, false>(p, tiles_m, tiles_n);
 }
@@ -1131,7 +1131,8 @@ template <int EPI, class E> int epilogue_tensors(const GemmParams<E> &p) {
 
 // What a product takes in tiles of 256 x width, in us: its rounds of 256 tiles, each k tiles and a prologue and epilogue.  A k tile is the longer the more
 // compute units work - they share memory and the power that sets the clock -: the least below half a round, the most in a full one, and
-// in full rounds of the narrower tiles more with the length of the k range.
+// in full rounds of the narrower tiles more with the length of the k range.  Where an epilogue moves 100 MB and more it takes longer than that
+// (32768 x 3072 x 768 with GELU' 266 us for 182, with GELU and its input stored 197 for 164): for comparing widths, not for the time itself.
 double tiles_time(int width, long M, long N, int K, double epilogue) {
     struct { double few, all, per_ktile, limit, fixed; } const c = width == 256   ? decltype(c){0.88, 1.25, 0.0, 1.25, 7.0}
                                                                  : width == 192 ? decltype(c){0.68, 0.95, 0.0010, 1.17, 5.7}
@@ -1141,26 +1142,6 @@ double tiles_time(int width, long M, long N, int K, double epilogue) {
     double us = 2.0 + (double)(tiles / 256) * (kt * std::min(c.all + c.per_ktile * kt, c.limit) + fixed);
     if (part > 0.0) us += kt * (c.few + (c.all - c.few) * std::max(0.0, 2.0 * part - 1.0)) + fixed;
     return us;
-}
-
-// Whether a product runs on tiles of 256 x 192 or 256 x 128 instead (0: no): the large-tile kernel with fewer columns, the same order of every sum.  Where
-// 256 x 256 tiles leave much of their last round empty, narrower ones fill more of it (us, 256 columns / these): 32768 x 768 x 768 45 / 38 with
-// 192, 2000 x 4256 x 4256 71 / 62, 4096 x 2304 x 768 20 / 17.6, 38384 x 280 x 1464 64 / 50 with 128; a full round of theirs takes longer for its
-// work, 32768 x 2048 x 2048 181 / 214.  By the times above, where they promise 3 % and no columns are left to the small kernel (16384 x 1032 x 4096,
-// 8 columns apart, 108 / 120); 128 columns up to two rounds, beyond which operands are read too often (43800 x 576 x 2864 175 / 197).
-// Fewer than 128 tiles of 256 x 256 belong to the small kernel, unless tiles of 128 columns are at least 144 and the k range 704: 6424 x 1024 x 4096
-// (208 of them) 59 / 47, 2000 x 3072 x 3072 (192) 43 / 35, 800 x 5136 x 896 (164) 16 / 13; 2048 x 2048 x 2048 (128) 24.0 / 23.7, 880 x 4168
-// x 4456 (132) 50 / 63, 2080 x 3552 x 576 (252) 13.4 / 13.8.
-// Of 690 products of all epilogues 271 take one of them: 5 % less time on average over all, the worst 3 % more (18256 x 560 x 8120).
-template <int EPI, class E> int narrow_tile_width(const GemmParams<E> &p) {
-    const long rows = (p.M + 255) / 256, big = rows * ((p.N + 255) / 256), narrow = rows * ((p.N + 127) / 128);
-    if (big < 128) return narrow >= 144 && p.K >= 704 ? 128 : 0;
-    const double epilogue = EPI == EPI_MUL_DGELU ? 8.0 : EPI == EPI_BIAS_GELU ? (p.out2 ? 5.0 : 3.0) : EPI == EPI_BIAS_RESID ? 3.0 : EPI == EPI_BIAS ? 0.5 : 0.0;
-    if (peeled_columns(p.M, p.N, p.K, epilogue_tensors<EPI>(p)) > 0) return 0;
-    const double limit = 0.97 * tiles_time(256, p.M, p.N, p.K, epilogue);
-    const double with192 = tiles_time(192, p.M, p.N, p.K, epilogue), with128 = narrow <= 512 ? tiles_time(128, p.M, p.N, p.K, epilogue) : with192;
-    if (std::min(with192, with128) >= limit) return 0;
-    return with128 < with192 ? 128 : 192;
 }
 
 template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmParams<E> &p, hipStream_t s) {
@@ -1188,7 +1169,7 @@ template <bool A_KM, bool B_KM, int EPI, class E> void launch_tiles(const GemmPa
             large = big * p.batch >= 128 && pad256 <= 1.15 * pad128;
         }
         if constexpr (EPI != EPI_ACCUM_F32) {
-            const int width = p.batch > 1 || p.tri || p.colsum || short_rows ? 0 : narrow_tile_width<EPI, E>(p);
+            const int width = p.batch > 1 || p.tri || p.colsum || short_rows ? 0 : gemm_narrow_width(p.M, p.N, p.K, EPI, EPI == EPI_BIAS_GELU && p.out2);
             if (width == 192) return launch_one<256, 192, A_KM, B_KM, EPI, E>(p, s);
             if (width == 128) return launch_one<256, 128, A_KM, B_KM, EPI, E>(p, s);
         }
@@ -1376,6 +1357,30 @@ template <class E> void launch_gemm_transposed_group(const GemmParams<E> *p, int
 }
 template void launch_gemm_transposed_group<bf16>(const GemmParams<bf16> *, int, hipStream_t);
 template void launch_gemm_transposed_group<f16>(const GemmParams<f16> *, int, hipStream_t);
+
+// Whether a product runs on tiles of 256 x 192 or 256 x 128 instead (0: no): the large-tile kernel with fewer columns, the same order of every sum.  Where
+// 256 x 256 tiles leave much of their last round empty, narrower ones fill more of it (us, 256 columns / these): 32768 x 768 x 768 45 / 38 with
+// 192, 2000 x 4256 x 4256 71 / 62, 4096 x 2304 x 768 20 / 17.6, 38384 x 280 x 1464 64 / 50 with 128; a full round of theirs takes longer for its
+// work, 32768 x 2048 x 2048 181 / 214.  By tiles_time, where it promises 3 % and no columns are left to the small kernel (16384 x 1032 x 4096,
+// 8 columns apart, 108 / 120); beyond four rounds 7 %, where there is less to fill than the times are off (47888 x 1544 x 5224 with GELU 808 / 882, 59824 x
+// 2168 x 200 with a residual 175 / 187); 128 columns up to two rounds, beyond which operands are read too often (43800 x 576 x 2864 175 / 197).
+// Fewer than 128 tiles of 256 x 256 belong to the small kernel, unless tiles of 128 columns are at least 144, the k range 704 and its own tiles of 128 x 128
+// more than one round: 6424 x 1024 x 4096 (208 of them) 59 / 47, 2000 x 3072 x 3072 (192) 43 / 35, 800 x 5136 x 896 (164) 16 / 13; 2048 x
+// 2048 x 2048 (128) 24.0 / 23.7, 880 x 4168 x 4456 (132) 50 / 63, 2080 x 3552 x 576 (252) 13.4 / 13.8, 808 x 4568 x 3336 (252 of the small ones) 38 / 47.
+// Of 1200 products of all epilogues 347 take one of them: 12 % less time for these on average, 4 % over all, the worst 3 % more (36880 x 2096 x 1672 with a
+// residual).  Of 1400 others 409, six of them 3 to 6 % more, most of these with an A of about the size of the last-level cache that every pass read again, which
+// the wider tiles use better: 45928 x 680 x 3128 with GELU, 10 % more on one A, 1 % on six in turn; 23056 x 728 x 6048 4 % more, 5 % less.
+int gemm_narrow_width(int M, int N, int K, int epi, bool pre) {
+    const long rows = (M + 255) / 256, big = rows * ((N + 255) / 256), narrow = rows * ((N + 127) / 128);
+    if (big < 128) return narrow >= 144 && K >= 704 && (long)((M + 127) / 128) * ((N + 127) / 128) > 256 ? 128 : 0;
+    const int tensors = 1 + (epi == EPI_BIAS_RESID || epi == EPI_MUL_DGELU) + pre;
+    if (peeled_columns(M, N, K, tensors) > 0) return 0;
+    const double epilogue = epi == EPI_MUL_DGELU ? 8.0 : epi == EPI_BIAS_GELU ? (pre ? 5.0 : 3.0) : epi == EPI_BIAS_RESID ? 3.0 : epi == EPI_BIAS ? 0.5 : 0.0;
+    const double limit = (big > 1024 ? 0.93 : 0.97) * tiles_time(256, M, N, K, epilogue);
+    const double with192 = tiles_time(192, M, N, K, epilogue), with128 = narrow <= 512 ? tiles_time(128, M, N, K, epilogue) : with192;
+    if (std::min(with192, with128) >= limit) return 0;
+    return with128 < with192 ? 128 : 192;
+}
 
 bool gemm_takes_stored_operands(int M, int N, int K) {
     if (M < 256 || N < 256) return false;

@@ -178,6 +178,9 @@ int gemm_splitk_slices(int M, int N, int K);
 // Whether a weight gradient of this size runs on the large-tile kernel, which takes both operands as stored ([K][ld], ld >= 256);
 // true for every larger K then, too.  The 16-bit kernels for smaller ones want them k-contiguous.
 bool gemm_takes_stored_operands(int M, int N, int K);
+// Columns of the 256-row tiles of a product with both operands k-contiguous and epilogue epi (pre: GELU that stores its input, too): 192, 128,
+// or 0 for 256 or the small kernel
+int gemm_narrow_width(int M, int N, int K, int epi, bool pre);
 
 // ---- causal attention --------------------------------------------------------------------
 // qkv: [tokens, 3 d] with columns [Q | K | V], head h at columns h*dh inside each third; tokens =
