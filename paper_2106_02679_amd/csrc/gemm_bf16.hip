@@ -812,6 +812,11 @@ __device__ __forceinline__ void dma_tile_product(const DmaInput<E, TN> &in, int 
     // the accumulators' last updates must have left the matrix pipe before anything else reads them (see
     // mfma_16x16x32_acc): twice the longest wait the instruction set asks for after a matrix instruction
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    // ... their spills, too: a value that leaves the registers is this statement's result, not the loop's
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j]));
 
     if constexpr (EPI != EPI_ACCUM_F32) {
         // bf16 outputs: a lane holds 4 consecutive n of 64 different (row, column group) places, so storing from
