@@ -41,7 +41,7 @@ void launch_layernorm_fwd(const T *x, const float *g, const float *b, T *y, floa
 struct ColsumJob {
     const float *partial;      // [chunks][2][cols]
     float *out0, *out1;        // out1 may be NULL
-    int chunks, cols, blocks;
+    int chunks, cols;
     float beta;
 };
 constexpr int kColsumBatch = 6;                            // four biases and two LayerNorms of a layer
@@ -92,19 +92,16 @@ template <class E>
 void launch_transpose16_colsum(const E *in, E *out, int R, int C, long ldi, long ldo, float beta, float *out0,
                                float *partial, hipStream_t s);
 
-// Up to eight matrices in one launch; those with partial != NULL (colsum_partial_floats(R, C) floats) also leave the first pass of their
+// Up to kTransposeBatch matrices in one launch; those with partial != NULL (colsum_partial_floats(R, C) floats) also leave the first pass of their
 // column sums (values of format E) there, whose second pass add_colsum adds to a batch.
 struct TransposeMatrix {
     const void *in;
     void *out;
     float *partial;
     long ldi, ldo;
-    int R, C, blocks;          // blocks: set by the launcher
+    int R, C;
 };
-struct TransposeBatch {
-    TransposeMatrix m[8];
-    int n;
-};
+constexpr int kTransposeBatch = 8;                         // the operands of a layer's four weight gradients
 template <class E> void launch_transposes(const TransposeMatrix *m, int n, hipStream_t s);
 // The second pass of first passes in chunks of 128 rows, left by a kernel that had the matrix in hand
 void add_colsum(ColsumBatch &batch, const float *partial, int rows, int cols, float beta, float *out0);

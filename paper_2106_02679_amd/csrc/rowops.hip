@@ -584,15 +584,22 @@ template <class T> struct ColsumInput {
     const T *a, *x;
     const float *mean, *rstd;
     float *partial;
-    int rows, cols, ld, blocks;
+    int rows, cols, ld;
+};
+template <class T, int N> struct ColsumInputs {
+    int first[N];                                          // see matrix_of; unused for N = 1
+    ColsumInput<T> m[N];
 };
 // first: the workgroup that matrix i begins with, INT_MAX behind the last (side by side: one scalar load finds a workgroup's matrix, where a walk
-// over the matrices waits for one after the other)
-template <class T, int N> struct ColsumInputs {
-    int first[N];
-    ColsumInput<T> m[N];
-    int n;
-};
+// over the matrices waits for one after the other).  Filled for n matrices by what each takes; returns the workgroups of all.
+template <int N, class Blocks> int first_workgroups(int (&first)[N], int n, Blocks blocks_of) {
+    int all = 0;
+    for (int i = 0; i < N; ++i) {
+        first[i] = i < n ? all : INT_MAX;
+        if (i < n) all += blocks_of(i);
+    }
+    return all;
+}
 template <int N> __device__ __forceinline__ int matrix_of(const int (&first)[N], int &block) {
     int n = 0;
 #pragma unroll
@@ -682,10 +689,9 @@ struct ColsumOne {
     ColsumJob job[1];
 };
 struct ColsumSeveral {
-    int first[8];                                          // (see ColsumInputs)
-    ColsumJob job[8];
+    int first[kColsumBatch];                               // see matrix_of
+    ColsumJob job[kColsumBatch];
 };
-static_assert(kColsumBatch <= 8, "jobs of a launch");
 
 template <int V, class Batch> __global__ __launch_bounds__(kFinalThreads) void colsum_final_kernel(Batch batch) {
     constexpr bool ONE = std::is_same<Batch, ColsumOne>::value;
@@ -815,7 +821,7 @@ struct AdamRegion {
 };
 constexpr int kAdamRegions = 9;
 template <class E> struct AdamLayer {
-    int first[kAdamRegions];                               // (see ColsumInputs)
+    int first[kAdamRegions];                               // see matrix_of
     AdamRegion region[kAdamRegions];
     float *w, *m, *v;
     const float *g;
@@ -885,13 +891,13 @@ template <int TILE, class E> __global__ __launch_bounds__(256) void adam_copies_
 constexpr int kTrTile = 128;
 constexpr int kTrPitch = kTrTile + 8;     // elements; keeps 16-byte alignment and skews the banks
 
-// One launch moves up to eight matrices (the operands of a layer's weight gradients; its four weight matrices): launched one by
+// One launch moves up to kTransposeBatch matrices (the operands of a layer's weight gradients; its four weight matrices): launched one by
 // one, a narrow layer's each take their 4 us.  With partial given the block also adds up its 128 rows of every column it moves
 // (as values of format E, in fp32) and writes them to partial[row chunk][0][c] - the first pass of the column sums
 // (colsum_partial_kernel's layout, same 128-row chunks), so that the bias gradient costs no pass of its own over a matrix that is being transposed anyway.
 struct TransposeSeveral {
-    int first[8];                                          // (see ColsumInputs)
-    TransposeMatrix m[8];
+    int first[kTransposeBatch];                            // see matrix_of
+    TransposeMatrix m[kTransposeBatch];
 };
 struct TransposeOne {
     TransposeMatrix m[1];
@@ -1046,29 +1052,23 @@ size_t layernorm_bwd_partial_floats(int rows, int d) {
 
 void launch_colsum_batch(const ColsumBatch &batch, hipStream_t s, bool timed) {
     if (batch.n == 0) return;
-    int blocks = 0;
     double bytes = 0.0;
-    for (int i = 0; i < batch.n; ++i) {
-        blocks += batch.job[i].blocks;
-        bytes += (batch.job[i].out1 ? 8.0 : 4.0) * batch.job[i].chunks * batch.job[i].cols;
-    }
+    for (int i = 0; i < batch.n; ++i) bytes += (batch.job[i].out1 ? 8.0 : 4.0) * batch.job[i].chunks * batch.job[i].cols;
     ProfScope scope("colsum_final_kernel", 0.25 * bytes, bytes, s, timed);
     bool vec = true;
     for (int i = 0; i < batch.n; ++i) vec &= batch.job[i].cols % 4 == 0;
     int longest = 0;
     for (int i = 0; i < batch.n; ++i) longest = std::max(longest, batch.job[i].chunks);
     vec = vec && (batch.n > 1 || longest > kFewChunks);
-    const dim3 grid((unsigned)blocks), block(kFinalThreads);
+    ColsumSeveral all{};
+    const dim3 grid((unsigned)first_workgroups(all.first, batch.n, [&](int i) { return (batch.job[i].cols + kFinalCols - 1) / kFinalCols; }));
+    const dim3 block(kFinalThreads);
     if (batch.n == 1) {
         const ColsumOne one{{batch.job[0]}};
         if (vec) hipLaunchKernelGGL((colsum_final_kernel<4, ColsumOne>), grid, block, 0, s, one);
         else hipLaunchKernelGGL((colsum_final_kernel<1, ColsumOne>), grid, block, 0, s, one);
     } else {
-        ColsumSeveral all{};
-        for (int i = 0, first = 0; i < 8; ++i) {
-            all.first[i] = i < batch.n ? first : INT_MAX;
-            if (i < batch.n) first += batch.job[i].blocks, all.job[i] = batch.job[i];
-        }
+        std::copy(batch.job, batch.job + batch.n, all.job);
         if (vec) hipLaunchKernelGGL((colsum_final_kernel<4, ColsumSeveral>), grid, block, 0, s, all);
         else hipLaunchKernelGGL((colsum_final_kernel<1, ColsumSeveral>), grid, block, 0, s, all);
     }
@@ -1077,7 +1077,7 @@ void launch_colsum_batch(const ColsumBatch &batch, hipStream_t s, bool timed) {
 // The second pass of one sum: with the caller's others, or at once.
 static void finish_colsum(ColsumBatch *batch, const float *partial, int chunks, int cols, float beta, float *out0, float *out1, hipStream_t s,
                           bool timed = true) {
-    const ColsumJob job{partial, out0, out1, chunks, cols, (cols + kFinalCols - 1) / kFinalCols, beta};
+    const ColsumJob job{partial, out0, out1, chunks, cols, beta};
     if (batch) {
         batch->job[batch->n++] = job;
         return;
@@ -1172,23 +1172,22 @@ template <class T> void launch_colsums(const ColsumMatrix<T> *m, int n, float be
         xhat |= m[i].out1 != nullptr;
         elems += (double)m[i].rows * m[i].cols;
     }
-    int blocks = 0;
-    for (int i = 0; i < 4; ++i) in.first[i] = INT_MAX;
-    for (int i = 0; i < n; ++i) {
-        const int chunks = (m[i].rows + kColsumRows - 1) / kColsumRows, width = 32 * (vec ? VMAX : 1);
-        const int mine = chunks * ((m[i].cols + width - 1) / width);
-        if (mine > 0) in.first[in.n] = blocks, in.m[in.n++] = {m[i].a, m[i].x, m[i].mean, m[i].rstd, m[i].partial, m[i].rows, m[i].cols, m[i].ld, mine};
-        blocks += mine;
-    }
+    int taken = 0;
+    for (int i = 0; i < n; ++i)
+        if (m[i].rows > 0 && m[i].cols > 0) in.m[taken++] = {m[i].a, m[i].x, m[i].mean, m[i].rstd, m[i].partial, m[i].rows, m[i].cols, m[i].ld};
+    const int width = 32 * (vec ? VMAX : 1);
+    const int blocks = first_workgroups(in.first, taken, [&](int i) {
+        return (in.m[i].rows + kColsumRows - 1) / kColsumRows * ((in.m[i].cols + width - 1) / width);
+    });
     if (blocks > 0) {
         ProfScope scope(xhat ? "colsum_partial_kernel(with xhat)" : "colsum_partial_kernel", (xhat ? 4.0 : 1.0) * elems,
                         (xhat ? 2.0 : 1.0) * sizeof(T) * elems, s, timed);
-        const int across = (in.m[0].cols + 32 * (vec ? VMAX : 1) - 1) / (32 * (vec ? VMAX : 1));
+        const int across = (in.m[0].cols + width - 1) / width;
         auto launch = [&](auto v_c, auto xhat_c) {
             constexpr int V = decltype(v_c)::value;
             constexpr bool XHAT = decltype(xhat_c)::value;
-            if (in.n == 1 && blocks / across <= 65535) {
-                const ColsumInputs<T, 1> one{{0}, {in.m[0]}, 1};
+            if (taken == 1 && blocks / across <= 65535) {
+                const ColsumInputs<T, 1> one{{0}, {in.m[0]}};
                 hipLaunchKernelGGL((colsum_partial_kernel<T, V, XHAT, 1>), dim3(across, blocks / across), dim3(256), 0, s, one);
             } else {
                 hipLaunchKernelGGL((colsum_partial_kernel<T, V, XHAT, 4>), dim3((unsigned)blocks), dim3(256), 0, s, in);
@@ -1214,30 +1213,24 @@ LGA_COLSUM(f16);
 #undef LGA_COLSUM
 
 template <class E> void launch_transposes(const TransposeMatrix *m, int n, hipStream_t s) {
-    TransposeBatch batch{};
-    int blocks = 0;
+    TransposeSeveral all{};
+    int taken = 0;
     double elems = 0.0;
     bool sums = false;
     for (int i = 0; i < n; ++i) {
         if (m[i].R == 0 || m[i].C == 0) continue;
-        batch.m[batch.n] = m[i];
-        batch.m[batch.n].blocks = ((m[i].C + kTrTile - 1) / kTrTile) * ((m[i].R + kTrTile - 1) / kTrTile);
-        blocks += batch.m[batch.n++].blocks;
+        all.m[taken++] = m[i];
         elems += (double)m[i].R * m[i].C;
         sums |= m[i].partial != nullptr;
     }
+    const int blocks = first_workgroups(all.first, taken, [&](int i) { return ((all.m[i].C + kTrTile - 1) / kTrTile) * ((all.m[i].R + kTrTile - 1) / kTrTile); });
     if (blocks == 0) return;
     ProfScope scope(sums ? "transpose16_kernel(with column sums)" : "transpose16_kernel", sums ? elems : 0.0, 4.0 * elems, s);
-    const int across = (batch.m[0].C + kTrTile - 1) / kTrTile;
-    if (batch.n == 1 && blocks / across <= 65535) {
-        const TransposeOne one{{batch.m[0]}};
+    const int across = (all.m[0].C + kTrTile - 1) / kTrTile;
+    if (taken == 1 && blocks / across <= 65535) {
+        const TransposeOne one{{all.m[0]}};
         hipLaunchKernelGGL((transpose16_kernel<E, TransposeOne>), dim3(across, blocks / across), dim3(256), 0, s, one);
     } else {
-        TransposeSeveral all{};
-        for (int i = 0, first = 0; i < 8; ++i) {
-            all.first[i] = i < batch.n ? first : INT_MAX;
-            if (i < batch.n) first += batch.m[i].blocks, all.m[i] = batch.m[i];
-        }
         hipLaunchKernelGGL((transpose16_kernel<E, TransposeSeveral>), dim3((unsigned)blocks), dim3(256), 0, s, all);
     }
 }
@@ -1245,7 +1238,7 @@ template void launch_transposes<bf16>(const TransposeMatrix *, int, hipStream_t)
 template void launch_transposes<f16>(const TransposeMatrix *, int, hipStream_t);
 
 void launch_transpose16(const void *in, void *out, int R, int C, long ldi, long ldo, hipStream_t s) {
-    const TransposeMatrix m{in, out, nullptr, ldi, ldo, R, C, 0};
+    const TransposeMatrix m{in, out, nullptr, ldi, ldo, R, C};
     launch_transposes<bf16>(&m, 1, s);
 }
 
@@ -1253,7 +1246,7 @@ template <class E>
 void launch_transpose16_colsum(const E *in, E *out, int R, int C, long ldi, long ldo, float beta, float *out0,
                                float *partial, hipStream_t s) {
     if (C == 0) return;
-    const TransposeMatrix m{in, out, partial, ldi, ldo, R, C, 0};
+    const TransposeMatrix m{in, out, partial, ldi, ldo, R, C};
     launch_transposes<E>(&m, 1, s);
     finish_colsum(nullptr, partial, (R + kTrTile - 1) / kTrTile, C, beta, out0, nullptr, s);
 }
@@ -1303,20 +1296,19 @@ void launch_adam_copies(float *w, float *m, float *v, const float *g, E *w16, E 
     AdamLayer<E> a{};
     a.w = w; a.m = m; a.v = v; a.g = g; a.w16 = w16; a.w16t = w16t;
     const int tile = n >= kAdamLarge ? 128 : 64;           // (a d = 2048 layer 289 and 301 us, a d = 128 layer 12.2 and 5.5)
-    int regions = 0, blocks = 0;
+    int regions = 0;
     size_t at = 0;
-    auto add = [&](size_t from, int rows, int cols) {
-        a.first[regions] = blocks;
-        a.region[regions++] = {from, rows, cols};
-        blocks += rows > 0 ? ((rows + tile - 1) / tile) * ((cols + tile - 1) / tile) : (cols + 1023) / 1024;
-    };
+    auto add = [&](size_t from, int rows, int cols) { a.region[regions++] = {from, rows, cols}; };
     for (const AdamMatrix &t : matrices) {
         if (t.at > at) add(at, 0, (int)(t.at - at));
         add(t.at, t.rows, t.cols);
         at = t.at + (size_t)t.rows * t.cols;
     }
     if (n > at) add(at, 0, (int)(n - at));
-    for (int i = regions; i < kAdamRegions; ++i) a.first[i] = INT_MAX;
+    const int blocks = first_workgroups(a.first, regions, [&](int i) {
+        const int rows = a.region[i].rows, cols = a.region[i].cols;
+        return rows > 0 ? ((rows + tile - 1) / tile) * ((cols + tile - 1) / tile) : (cols + 1023) / 1024;
+    });
     ProfScope scope("adam_kernel", 12.0 * n, 32.0 * n, s);
     const auto kernel = tile == 64 ? adam_copies_kernel<64, E> : adam_copies_kernel<128, E>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, adam_consts(lr, beta1, beta2, eps, step, grad_mul), skip);

@@ -369,10 +369,10 @@ void refresh_transposed_weights(lga_stack *st, int l, hipStream_t s) {
     const LayerLayout &o = st->lay;
     const uint16_t *w = st->w16(l);
     uint16_t *wt = st->w16t(l);
-    const TransposeMatrix m[4] = {{w + o.w_qkv, wt + o.w_qkv, nullptr, 3 * d, d, d, 3 * d, 0},
-                                  {w + o.w_o, wt + o.w_o, nullptr, d, d, d, d, 0},
-                                  {w + o.w_1, wt + o.w_1, nullptr, f, d, d, f, 0},
-                                  {w + o.w_2, wt + o.w_2, nullptr, d, f, f, d, 0}};
+    const TransposeMatrix m[4] = {{w + o.w_qkv, wt + o.w_qkv, nullptr, 3 * d, d, d, 3 * d},
+                                  {w + o.w_o, wt + o.w_o, nullptr, d, d, d, d},
+                                  {w + o.w_1, wt + o.w_1, nullptr, f, d, d, f},
+                                  {w + o.w_2, wt + o.w_2, nullptr, d, f, f, d}};
     launch_transposes<bf16>(m, 4, s);
 }
 
@@ -682,7 +682,7 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
     const bool dgelu_adds = !std::is_same<T, float>::value && p.stored[1] && sizeof(T) * t * f >= kCached && gemm_dgelu_adds_columns(t, f, d);
     // The weight gradients that are not enough work alone wait, with their transposes, until all operands are there.
     GemmParams<T> together[4], moved[4];                     // on operands as stored, on transposed copies
-    TransposeMatrix moves[8];
+    TransposeMatrix moves[kTransposeBatch];
     int n_together = 0, n_moved = 0, n_moves = 0;
 
     // gW[in, out] (+)= X[t, in]^T dY[t, out], contracted over tokens.  The 16-bit modes' large-tile kernel takes both operands as they
@@ -713,8 +713,8 @@ template <class T> void layer_backward(lga_stack *st, int l, const T *x_in, cons
                 const int ldk = (int)p.ldk;
                 T *xT = st->at<T>(p.xT[which]), *dyT = st->at<T>(p.dyT[which]);
                 // the bias gradient is the column sum of dY: taken from the tiles as they are transposed
-                moves[n_moves++] = {X, xT + (size_t)gs.slot * t, nullptr, ldx, ldk, t, in, 0};
-                moves[n_moves++] = {dY, dyT + (size_t)gs.slot * t, partial, ldy, ldk, t, out, 0};
+                moves[n_moves++] = {X, xT + (size_t)gs.slot * t, nullptr, ldx, ldk, t, in};
+                moves[n_moves++] = {dY, dyT + (size_t)gs.slot * t, partial, ldy, ldk, t, out};
                 add_colsum(sums, partial, t, out, beta, gbuf + b_off);
                 g.A = xT; g.lda = ldk; g.B = dyT; g.ldb = ldk;
                 moved[n_moved++] = g;
