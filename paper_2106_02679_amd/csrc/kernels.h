@@ -119,8 +119,8 @@ void launch_adam(float *w, float *m, float *v, const float *g, E *w16, size_t n,
 
 // The same for a layer's n parameters, with its 16-bit copies w16 and w16t (each matrix transposed, at its place); matrices in the order of their
 // places, their sizes, what lies between them and every address whole 16-byte pieces of 16-bit elements.  adam_writes_copies: whether it is the
-// faster way to both copies for a layer of these widths and so many parameters.
-bool adam_writes_copies(int d, int f, size_t n);
+// faster way to both copies for one of `layers` layers of these widths and n parameters each.
+bool adam_writes_copies(int d, int f, size_t n, int layers);
 struct AdamMatrix {
     size_t at;
     int rows, cols;

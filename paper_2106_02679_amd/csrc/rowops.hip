@@ -813,8 +813,12 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ w, float 
 // transposed tile leaves through LDS in rows of 128 or 256 bytes.  What lies between the matrices goes by 1024 elements.  For rows of whole
 // 128-byte lines in 16 bits: others are written in parts from several workgroups, d = 4256 1617 us where the two kernels take 1339 + 189.  And not for
 // layers of some million parameters, whose copies the transposing pass leaves in the caches for the products that come next: d = 768 40 us
-// against 36 + 8, but then the input gradients 29.4 us against 27.9.
-constexpr size_t kAdamSmall = (size_t)1 << 20, kAdamLarge = (size_t)1 << 24;
+// against 36 + 8, but then the input gradients 29.4 us against 27.9.  Of whole steps (us, two kernels / this one): below 2^20 parameters always 1 to 3 % less (1, 2 and
+// 4 layers of 64 to 256, 4 of 192 435 / 423); from 2^20 to 2^24 3 % less to 1 % more, left to two kernels (4 layers of 768 over 4096 tokens 2115 / 2098, 2 of 896 in
+// micro-batch order over 16384 5187 / 5237); above 8 % less to 1 % more for several layers (6 of 1280 4348 / 4320, 2 of 4096 over 512 5534 / 5222, 2 of
+// 1216 832 / 837).  A layer alone, whose copies the very next pass reads, gains from 2^25 on only (512 tokens: 1216 395 / 411, 1536 553 / 580, 1664
+// 608 / 611, 1728 663 / 658, 2048 862 / 845; d_ff = d = 3072 931 / 944, over 128 727 / 701).
+constexpr size_t kAdamSmall = (size_t)1 << 20, kAdamLarge = (size_t)1 << 24, kAdamLargeAlone = (size_t)1 << 25;
 struct AdamRegion {
     size_t at;             // element in the layer's vector
     int rows, cols;        // a matrix [rows][cols]; rows = 0: cols elements of no matrix
@@ -1289,7 +1293,9 @@ template void launch_adam<f16>(float *, float *, float *, const float *, f16 *, 
                                float, const int *, hipStream_t);
 
 
-bool adam_writes_copies(int d, int f, size_t n) { return d % 64 == 0 && f % 64 == 0 && (n < kAdamSmall || n >= kAdamLarge); }
+bool adam_writes_copies(int d, int f, size_t n, int layers) {
+    return d % 64 == 0 && f % 64 == 0 && (n < kAdamSmall || n >= (layers > 1 ? kAdamLarge : kAdamLargeAlone));
+}
 template <class E>
 void launch_adam_copies(float *w, float *m, float *v, const float *g, E *w16, E *w16t, const AdamMatrix (&matrices)[4], size_t n, float lr, float beta1,
                         float beta2, float eps, int step, float grad_mul, const int *skip, hipStream_t s) {

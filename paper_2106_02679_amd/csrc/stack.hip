@@ -793,7 +793,7 @@ void adam_layer(lga_stack *st, int l, const lga_adam &hp, bool async = false) {
     const AdamMatrix matrices[4] = {{o.w_qkv, d, 3 * d}, {o.w_o, d, d}, {o.w_1, d, f}, {o.w_2, f, d}};
     auto update = [&](auto *of_type) {
         typedef std::remove_pointer_t<decltype(of_type)> E;
-        if (copies && adam_writes_copies(d, f, st->P)) {
+        if (copies && adam_writes_copies(d, f, st->P, st->cfg.n_layers)) {
             launch_adam_copies<E>(st->w(l), st->m(l), st->v(l), st->grad(l), st->w16<E>(l), st->w16t<E>(l), matrices, st->P, hp.lr, hp.beta1, hp.beta2,
                                   hp.eps, hp.step, grad_mul, flag, s);
             return;
@@ -1082,7 +1082,7 @@ int lga_traffic_model(const lga_config *cfg, int32_t order, uint64_t *param_byte
     // the 16-bit modes also write the 16-bit copy (2 B) and re-reads / writes the matrices once for the transposed copy; where Adam
     // writes both copies itself, nothing is read again
     const uint64_t copies = is16 ? 2 * P + 4 * Pm : 0;
-    const uint64_t updated = copies - (is16 && adam_writes_copies(cfg->d_model, cfg->d_ff, P) ? 2 * Pm : 0);
+    const uint64_t updated = copies - (is16 && adam_writes_copies(cfg->d_model, cfg->d_ff, P, cfg->n_layers) ? 2 * Pm : 0);
     const uint64_t per_group_param = wsz * (3 * Pm - df);
     // Restores of a steady-state step (param_buffers < n_layers): a layer's masters are cast again (read 4 B, write
     // 2 B per parameter, plus the transposed copy) whenever another layer has used its buffer since.  Counted by

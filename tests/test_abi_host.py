@@ -338,3 +338,12 @@ def test_traffic_model_counts_no_second_read_where_adam_writes_both_copies(d, re
     P, Pm = 12 * d * d + 13 * d, 12 * d * d
     got = B.traffic_model(cfg(dtype=B.LGA_BF16, **kw), B.LGA_ORDER_LAYERED)[0]
     assert got == 26 * P + (2 + read_again) * Pm + 2 * (3 * Pm - 4 * d * d)
+
+
+@pytest.mark.parametrize("d,layers,read_again", [(1152, 1, 2), (1216, 1, 2), (1216, 2, 0), (1536, 1, 2), (1536, 4, 0), (1664, 1, 2), (1728, 1, 0), (1152, 2, 2), (256, 1, 0)])
+def test_a_layer_alone_takes_two_kernels_up_to_more_parameters(d, layers, read_again):
+    """A layer alone of 2^24 to 2^25 parameters, whose copies are the next thing to be read, was slower with one kernel (1536 over 512 tokens 553 -> 580 us)."""
+    kw = dict(n_layers=layers, d_model=d, n_heads=d // 8, d_ff=4 * d, seq_len=128, micro_batch=1, n_micro=1, group=1)
+    P, Pm = 12 * d * d + 13 * d, 12 * d * d
+    got = B.traffic_model(cfg(dtype=B.LGA_BF16, **kw), B.LGA_ORDER_LAYERED)[0]
+    assert got == layers * (26 * P + (2 + read_again) * Pm + 2 * (3 * Pm - 4 * d * d))

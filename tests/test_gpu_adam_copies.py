@@ -13,9 +13,10 @@ TYPE = {BF16: torch.bfloat16, F16: torch.float16}
 
 
 @pytest.mark.parametrize("dt", [BF16, F16])
-@pytest.mark.parametrize("d,heads,ff", [(64, 2, 64), (64, 1, 192), (192, 3, 320), (136, 17, 264), (320, 5, 1280), (1216, 19, 4864)])
-def test_the_next_pass_uses_the_updated_weights(d, heads, ff, dt):
-    layers, n_micro, s = 2, 2, 24
+@pytest.mark.parametrize("d,heads,ff,layers", [(64, 2, 64, 2), (64, 1, 192, 2), (192, 3, 320, 2), (136, 17, 264, 2), (320, 5, 1280, 2), (1216, 19, 4864, 2),
+                                               (192, 3, 320, 1), (1216, 19, 4864, 1), (1728, 27, 6912, 1)])
+def test_the_next_pass_uses_the_updated_weights(d, heads, ff, layers, dt):
+    n_micro, s = 2, 24
     cfg = B.make_config(layers, d, heads, ff, s, 1, n_micro, dt, group=2, retain_grads=1)
     rng = np.random.default_rng(d + ff)
     params = (rng.standard_normal(layers * B.params_per_layer(cfg)) * 0.05).astype(np.float32)
