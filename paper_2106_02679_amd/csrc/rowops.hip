@@ -608,7 +608,17 @@ template <int N> __device__ __forceinline__ int matrix_of(const int (&first)[N],
     return n;
 }
 
-template <class T, int V, bool WITH_XHAT, int N>
+// Whether a thread requests its sixteen rows of a whole chunk before it adds the first (in a loop, some wait out the latency of those before).  Up to 32 MB, what the
+// L2 caches hold, the latencies are what the pass takes: the four biases of a layer of width 64 over 256 tokens in fp32 6.6 -> 3.0 us, of width 256 over
+// 2048 7.7 -> 4.8, 28620 x 512 in 16 bits 10.2 -> 7.3.  Beyond, so many loads at once are in each other's way: in fp32 22522 x 676 15.2 -> 18.6, 44272 x 304
+// 13.5 -> 15.8, 6637 x 6624 28.1 -> 30.4, of 45 sums 2 % more on average; in 16 bits up to 72 MB 2033 x 10216 12.5 -> 14.5, 29951 x 840 14.4 -> 16.4, of 10
+// 2 % more; but above that 2 % less on average of 22, 32768 x 768 + 2304 29 -> 24.
+template <class T> bool colsum_loads_ahead(double elems) {
+    const double mb = sizeof(T) * elems / 1048576.0;
+    return mb <= 32.0 || (sizeof(T) == 2 && mb > 72.0);
+}
+
+template <class T, int V, bool WITH_XHAT, bool AHEAD, int N>
 __global__ __launch_bounds__(256) void colsum_partial_kernel(ColsumInputs<T, N> in) {
     constexpr bool ONE = N == 1;
     __shared__ float red[2][8][32 * V + 1];
@@ -639,10 +649,7 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(ColsumInputs<T, N> 
         }
     };
     if (c0 < cols) {
-        if (!WITH_XHAT && r1 == r0 + kColsumRows) {
-            // A whole chunk: a thread's sixteen rows are requested before the first is added (in a loop, some wait out the latency of those before:
-            // the four biases of a layer of width 64 over 256 tokens in fp32 6.6 -> 3.0 us, of width 256 over 2048 7.7 -> 4.8, 29 -> 24 over
-            // 32768 x 768 + 2304 in 16 bits).
+        if (AHEAD && r1 == r0 + kColsumRows) {
             float av[kColsumRows / 8][V];
 #pragma unroll
             for (int k = 0; k < kColsumRows / 8; ++k) load_pack<T, V>(a + (size_t)(r0 + ty + 8 * k) * ld + c0, av[k]);
@@ -1187,22 +1194,25 @@ template <class T> void launch_colsums(const ColsumMatrix<T> *m, int n, float be
         ProfScope scope(xhat ? "colsum_partial_kernel(with xhat)" : "colsum_partial_kernel", (xhat ? 4.0 : 1.0) * elems,
                         (xhat ? 2.0 : 1.0) * sizeof(T) * elems, s, timed);
         const int across = (in.m[0].cols + width - 1) / width;
-        auto launch = [&](auto v_c, auto xhat_c) {
+        auto launch = [&](auto v_c, auto xhat_c, auto ahead_c) {
             constexpr int V = decltype(v_c)::value;
-            constexpr bool XHAT = decltype(xhat_c)::value;
+            constexpr bool XHAT = decltype(xhat_c)::value, AHEAD = decltype(ahead_c)::value;
             if (taken == 1 && blocks / across <= 65535) {
                 const ColsumInputs<T, 1> one{{0}, {in.m[0]}};
-                hipLaunchKernelGGL((colsum_partial_kernel<T, V, XHAT, 1>), dim3(across, blocks / across), dim3(256), 0, s, one);
+                hipLaunchKernelGGL((colsum_partial_kernel<T, V, XHAT, AHEAD, 1>), dim3(across, blocks / across), dim3(256), 0, s, one);
             } else {
-                hipLaunchKernelGGL((colsum_partial_kernel<T, V, XHAT, 4>), dim3((unsigned)blocks), dim3(256), 0, s, in);
+                hipLaunchKernelGGL((colsum_partial_kernel<T, V, XHAT, AHEAD, 4>), dim3((unsigned)blocks), dim3(256), 0, s, in);
             }
         };
         typedef std::integral_constant<int, VMAX> Wide;
         typedef std::integral_constant<int, 1> Narrow;
-        if (vec && xhat) launch(Wide{}, std::true_type{});
-        else if (vec) launch(Wide{}, std::false_type{});
-        else if (xhat) launch(Narrow{}, std::true_type{});
-        else launch(Narrow{}, std::false_type{});
+        const bool ahead = colsum_loads_ahead<T>(elems);
+        if (vec && xhat) launch(Wide{}, std::true_type{}, std::false_type{});
+        else if (vec && ahead) launch(Wide{}, std::false_type{}, std::true_type{});
+        else if (vec) launch(Wide{}, std::false_type{}, std::false_type{});
+        else if (xhat) launch(Narrow{}, std::true_type{}, std::false_type{});
+        else if (ahead) launch(Narrow{}, std::false_type{}, std::true_type{});
+        else launch(Narrow{}, std::false_type{}, std::false_type{});
     }
     for (int i = 0; i < n; ++i)
         finish_colsum(batch, m[i].partial, m[i].rows > 0 ? (m[i].rows + kColsumRows - 1) / kColsumRows : 0, m[i].cols, beta, m[i].out0, m[i].out1, s, timed);
