@@ -1000,11 +1000,16 @@ void bwd_dh(const E *qkv, const E *out, const float *lse, float *delta, const E 
 // against 103 - and few workgroups leave compute units idle behind the longest: 1024 x 48 x 64 (192 blocks of 256) 18.8 against 25.6,
 // 1000 x 56 x 152 (224) 39 against 45, 128 x 2 x 64 6.0 against 7.8.  With the causal mask a workgroup is half as long as the longest on
 // average.  (Either form adds up a row in the same order and starts over with the same references: the results are the same.)
+// Nor where a sequence of 129 to 256 queries is one workgroup, and would be two in more than a round: the second is short and takes its fixed part all the
+// same (12 x 137 x 12 x 112 causal 14.9 with one sub-block, 12.4 with two; 6 x 132 x 24 x 128 15.0, 12.7; 4 x 153 x 88 x 48 unmasked 16.6, 14.2; 13 of 14
+// such shapes 2 to 37 % more, one 1 % less); but with the mask and up to 64 channels, where several share a compute unit, 210 x 162 x 48 8.3
+// against 10.7, 216 x 319 x 32 8.8 against 11.9.
 // Never more of the short workgroups than a launch holds, 2^32 work items, beyond which it runs a part of them and reports nothing.
 int attn_fwd_subblocks(const AttnShape &sh) {
     const double one = sh.dh <= 64 ? 0.52 : 0.6;             // of what a workgroup with two takes
     const double heads = (double)sh.n_seq * sh.heads;
     if (heads * ((sh.s + 127) / 128) * 256.0 >= 4294967296.0) return 2;
+    if (sh.s > 128 && sh.s <= 256 && heads > 128.0 && (sh.dh > 64 || !sh.causal)) return 2;
     auto time = [&](int u, double each) {
         const double work = heads * ((sh.s + 128 * u - 1) / (128 * u)) / 256.0;
         return each * std::max(1.0, sh.causal ? 0.5 * work : std::ceil(work));

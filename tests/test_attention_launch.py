@@ -29,6 +29,9 @@ def test_a_launch_has_fewer_than_two_to_the_32_work_items(s, dh, causal):
 
 @pytest.mark.parametrize("n_seq,s,heads,dh,causal,u", [
     (4, 1024, 12, 64, 1, 1), (32, 1024, 12, 64, 1, 2), (1, 1000, 28, 152, 1, 1), (2, 1000, 28, 152, 1, 1), (4, 1000, 28, 152, 1, 2),
-    (1, 8100, 16, 128, 1, 2), (8, 1024, 32, 128, 0, 2), (1, 128, 2, 64, 1, 1)])
+    (1, 8100, 16, 128, 1, 2), (8, 1024, 32, 128, 0, 2), (1, 128, 2, 64, 1, 1),
+    # one workgroup of 256 queries a sequence: two short ones only in one round, or where several share a compute unit
+    (12, 137, 12, 112, 1, 2), (6, 132, 24, 128, 1, 2), (4, 153, 88, 48, 0, 2), (3, 236, 57, 96, 1, 2), (1, 129, 129, 72, 0, 2), (1, 256, 129, 72, 0, 2),
+    (1, 137, 128, 112, 1, 1), (1, 137, 128, 48, 0, 1), (6, 210, 27, 48, 1, 1), (11, 216, 29, 32, 1, 1), (1, 128, 129, 112, 1, 1), (1, 257, 70, 112, 1, 1)])
 def test_few_workgroups_are_short_ones(n_seq, s, heads, dh, causal, u):
     assert subblocks(n_seq, s, heads, dh, causal) == u
